@@ -1,30 +1,20 @@
 // bf16 MFMA GEMM for the refreshed rows: C = act(A W^T + bias), A [M,K], W [N,K] both
 // K-contiguous (QKV projection, out-projection and FFN of Eq. 2 / Eq. 3), fp32 accumulate.
 //
-// Two kernels: problems with fewer than 128 tiles of 256 x 256 use the 128 x 128-tile kernel
-// described here (register-staged loads); larger ones use gemm256_kernel further down (direct
-// global -> LDS loads into rings of three A slots and two W slots, k-split of a thin last round;
-// described there).
-//
-// Tiling (gfx950, wave64): a workgroup owns a BM x BN tile of C and walks K in steps of 64.
-// Each wave owns a WM x WN sub-tile made of 32x32 blocks computed by
-// v_mfma_f32_32x32x16_bf16 (A fragment: lane holds row lane%32, eight consecutive k
-// starting at 8*(lane/32); B fragment likewise for column lane%32; accumulator register i
-// of a lane is row 8*(i/4) + 4*(lane/32) + i%4, column lane%32).
-// A and W tiles are staged through LDS in rows of 128 B (64 bf16) whose eight 16-byte
-// chunks are XOR-swizzled with (row/2)%8, which makes the ds_read_b128 fragment reads of
-// 16 consecutive rows hit 16 distinct bank groups.
-// Latency hiding: global (buffer) loads run two K steps ahead of the MFMAs through two
-// register sets; fragments are read from LDS one 16-wide k slice ahead.  Buffer loads are
-// bounds-checked by the hardware (rows past M or N read as zero), so ragged M needs no
-// padding.  Workgroup ids are remapped so that each XCD works on a contiguous range of
-// tiles, walked in groups of 8 row-tiles, which keeps the A / W panels an XCD streams
-// concurrently small enough for its L2.
-// The epilogue adds the bias, applies GELU where asked, and either stores C or scatters
-// rows into the feature / K / V^T caches (Eq. 3's merge).  Waves whose columns belong to
-// the V third of the QKV projection run their MFMAs with the operands swapped, so their
-// accumulators hold the transposed block and V^T rows are written with row-contiguous
-// lanes.
+// Three kernels, chosen per problem by the expected time of their tiles (choose_tile):
+//  * gemm256_kernel, 256 x 256 tiles: large problems; rings of direct global -> LDS loads, k-split of a
+//    thin last round;
+//  * gemm_halfk_kernel, 128 x 128 to 256 x 128 tiles: problems whose 256 x 256 tiles would leave CUs idle;
+//  * gemm_quarterk_kernel, 64 x 64 tiles: problems with few rows or columns, bound by latency along k.
+// All use v_mfma_f32_32x32x16_bf16 (A fragment: lane holds row lane%32, eight consecutive k starting at
+// 8*(lane/32); B fragment likewise for column lane%32; accumulator register i of a lane is row
+// 8*(i/4) + 4*(lane/32) + i%4, column lane%32) and walk k in stages of 64: LDS rows of 128 B whose eight
+// 16-byte chunks are XOR-swizzled with (row/2)%8, so that fragment reads are free of bank conflicts.
+// Loads are bounds-checked by the hardware (rows past M or N read as zero): ragged sizes need no padding.
+// Workgroup ids are remapped so that each XCD works on a contiguous range of tiles, walked in groups of
+// row tiles, which keeps the panels an XCD streams concurrently small enough for its L2.
+// The epilogue adds the bias, applies GELU where asked, and either stores C or scatters rows into the
+// feature / K / V^T caches (Eq. 3's merge); the accumulating one (FFN2) also adds the stored feature to x.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -34,12 +24,6 @@
 
 namespace {
 
-constexpr int BK = 64;           // bf16 elements per K step (128 B per row)
-constexpr int CHUNKS = BK / 8;   // 16-byte chunks per tile row
-constexpr int GROUP_M = 8;       // row-tiles walked together (L2 locality)
-
-__device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
-
 __device__ __forceinline__ float gelu_tanh(float x) {
   // x/2 (1 + tanh u) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3);
   // -2u log2(e) = x (C1 + C2 x^2) with the constants folded: five plain operations and two
@@ -48,263 +32,6 @@ __device__ __forceinline__ float gelu_tanh(float x) {
   constexpr float C2 = -0.1029432395800235f;    // C1 * 0.044715
   float e = __builtin_amdgcn_exp2f(x * __builtin_fmaf(x * x, C2, C1));
   return x * __builtin_amdgcn_rcpf(1.0f + e);
-}
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
-}
-
-template <int BM, int BN, int WM, int WN, int EPI>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void gemm_kernel(GemmArgs g, int tiles_m, int tiles_n,
-                                                                           int per_xcd) {
-  constexpr int WAVES_M = BM / WM;
-  constexpr int T = (BM / WM) * (BN / WN) * 64;
-  constexpr int MB = WM / 32, NB = WN / 32;
-  constexpr int NA = BM * CHUNKS / T, NBL = BN * CHUNKS / T;
-  constexpr int ROWS_PER_PASS = T / CHUNKS;      // tile rows covered by one chunk per thread
-  static_assert(BM * CHUNKS % T == 0 && BN * CHUNKS % T == 0, "tile/threads mismatch");
-
-  // ---- workgroup id -> tile ----
-  const int n_tiles = tiles_m * tiles_n;
-  int p = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (p >= n_tiles) return;
-  const int group = p / (GROUP_M * tiles_n);
-  const int first_m = group * GROUP_M;
-  const int gsize = min(tiles_m - first_m, GROUP_M);
-  const int in_group = p - group * GROUP_M * tiles_n;
-  const int tm = first_m + in_group % gsize, tn = in_group / gsize;
-  const int m0 = tm * BM, n0 = tn * BN;
-
-  extern __shared__ u32x4_t smem[];
-  u32x4_t* sA = smem;                         // [2][BM*CHUNKS]
-  u32x4_t* sB = smem + 2 * BM * CHUNKS;       // [2][BN*CHUNKS]
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm0 = (wave % WAVES_M) * WM, wn0 = (wave / WAVES_M) * WN;
-  const int lr = lane & 31, lh = lane >> 5;
-
-  // ---- global loads: thread t loads chunk (t % 8) of rows t/8 + i*ROWS_PER_PASS ----
-  const int ld_row = tid / CHUNKS, ld_c = tid % CHUNKS;
-  const uint32_t row_bytes = (uint32_t)g.k * 2u;
-  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(g.a, (uint32_t)g.m * row_bytes);
-  const __amdgpu_buffer_rsrc_t rsB = make_rsrc(g.w, (uint32_t)g.n * row_bytes);
-  // the whole address lives in the bounds-checked vector offset
-  uint32_t voffA[NA], voffB[NBL];
-#pragma unroll
-  for (int i = 0; i < NA; ++i) voffA[i] = (uint32_t)(m0 + ld_row + i * ROWS_PER_PASS) * row_bytes + ld_c * 16;
-#pragma unroll
-  for (int i = 0; i < NBL; ++i) voffB[i] = (uint32_t)(n0 + ld_row + i * ROWS_PER_PASS) * row_bytes + ld_c * 16;
-  // ROWS_PER_PASS is a multiple of 16, so the swizzle term is the same for every pass
-  const int st_off = ld_row * CHUNKS + swz(ld_row, ld_c);
-
-  u32x4_t ra[2][NA], rb[2][NBL];
-  constexpr int LPS_A = NA / 4, LPS_B = NBL / 4;   // global loads / LDS writes per 16-wide k slice
-  static_assert(NA % 4 == 0 && NBL % 4 == 0, "loads must split evenly over the four k slices");
-  auto gload = [&](auto PAR, int kt) {
-    constexpr int P = decltype(PAR)::value;
-    const uint32_t koff = (uint32_t)kt * (BK * 2);
-#pragma unroll
-    for (int i = 0; i < NA; ++i) ra[P][i] = __builtin_amdgcn_raw_buffer_load_b128(rsA, voffA[i] + koff, 0, 0);
-#pragma unroll
-    for (int i = 0; i < NBL; ++i) rb[P][i] = __builtin_amdgcn_raw_buffer_load_b128(rsB, voffB[i] + koff, 0, 0);
-  };
-  auto lstore = [&](auto PAR, int buf) {
-    constexpr int P = decltype(PAR)::value;
-    u32x4_t* dA = sA + buf * BM * CHUNKS + st_off;
-    u32x4_t* dB = sB + buf * BN * CHUNKS + st_off;
-#pragma unroll
-    for (int i = 0; i < NA; ++i) dA[i * ROWS_PER_PASS * CHUNKS] = ra[P][i];
-#pragma unroll
-    for (int i = 0; i < NBL; ++i) dB[i * ROWS_PER_PASS * CHUNKS] = rb[P][i];
-  };
-
-  floatx16_t acc[MB][NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  // V third of the QKV projection: accumulate the transposed block (operands swapped)
-  const bool transposed = (EPI == EPI_QKV) && (n0 + wn0 >= 2 * g.d);
-
-  int fa_row[MB], fb_row[NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i) fa_row[i] = wm0 + i * 32 + lr;
-#pragma unroll
-  for (int j = 0; j < NB; ++j) fb_row[j] = wn0 + j * 32 + lr;
-
-  // One K step: multiply the tile in LDS buffer `buf`; meanwhile issue the global loads of
-  // tile kt_load into register set P and write register set P^1 (loaded one step ago) to
-  // the other LDS buffer.  Loads, LDS writes, fragment reads and MFMAs of each 16-wide k
-  // slice are interleaved so that no unit sees a burst.
-  auto kstep = [&](auto PAR, int buf, int kt_load, bool pipeline) {
-    constexpr int P = decltype(PAR)::value;
-    const u32x4_t* cA = sA + buf * BM * CHUNKS;
-    const u32x4_t* cB = sB + buf * BN * CHUNKS;
-    u32x4_t* dA = sA + (buf ^ 1) * BM * CHUNKS + st_off;
-    u32x4_t* dB = sB + (buf ^ 1) * BN * CHUNKS + st_off;
-    const uint32_t koff = (uint32_t)kt_load * (BK * 2);
-    bf16x8_t fa[2][MB], fb[2][NB];
-    auto fload = [&](int slot, int ks) {
-#pragma unroll
-      for (int i = 0; i < MB; ++i) {
-        u32x4_t t = cA[fa_row[i] * CHUNKS + swz(fa_row[i], 2 * ks + lh)];
-        fa[slot][i] = *reinterpret_cast<bf16x8_t*>(&t);
-      }
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        u32x4_t t = cB[fb_row[j] * CHUNKS + swz(fb_row[j], 2 * ks + lh)];
-        fb[slot][j] = *reinterpret_cast<bf16x8_t*>(&t);
-      }
-    };
-    fload(0, 0);
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      const int cur = ks & 1;
-      __builtin_amdgcn_sched_barrier(0);       // one k slice per scheduling region
-      if (pipeline) {
-#pragma unroll
-        for (int i = ks * LPS_A; i < (ks + 1) * LPS_A; ++i) {
-          dA[i * ROWS_PER_PASS * CHUNKS] = ra[P ^ 1][i];
-        }
-#pragma unroll
-        for (int i = ks * LPS_B; i < (ks + 1) * LPS_B; ++i) {
-          dB[i * ROWS_PER_PASS * CHUNKS] = rb[P ^ 1][i];
-        }
-#pragma unroll
-        for (int i = ks * LPS_A; i < (ks + 1) * LPS_A; ++i)
-          ra[P][i] = __builtin_amdgcn_raw_buffer_load_b128(rsA, voffA[i] + koff, 0, 0);
-#pragma unroll
-        for (int i = ks * LPS_B; i < (ks + 1) * LPS_B; ++i)
-          rb[P][i] = __builtin_amdgcn_raw_buffer_load_b128(rsB, voffB[i] + koff, 0, 0);
-      }
-      if (ks + 1 < BK / 16) fload(cur ^ 1, ks + 1);
-      if (EPI == EPI_QKV && transposed) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
-      } else {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int j = 0; j < NB; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0);
-      }
-      // spread the memory instructions of this slice between its MFMAs
-      constexpr int MFMAS = MB * NB, GROUPS = 4;
-#pragma unroll
-      for (int gq = 0; gq < GROUPS; ++gq) {
-        if (pipeline) {
-          __builtin_amdgcn_sched_group_barrier(0x200, (LPS_A + LPS_B + GROUPS - 1) / GROUPS, 0);  // LDS writes
-          __builtin_amdgcn_sched_group_barrier(0x020, (LPS_A + LPS_B + GROUPS - 1) / GROUPS, 0);  // global loads
-        }
-        __builtin_amdgcn_sched_group_barrier(0x100, (MB + NB + GROUPS - 1) / GROUPS, 0);          // LDS reads
-        __builtin_amdgcn_sched_group_barrier(0x008, MFMAS / GROUPS, 0);                           // MFMA
-      }
-    }
-  };
-
-  using P0 = std::integral_constant<int, 0>;
-  using P1 = std::integral_constant<int, 1>;
-  const int kt_n = g.k / BK;
-  // Loads and LDS writes past the last K step are issued unconditionally: out-of-range
-  // buffer loads return zero and the tile they would fill is never multiplied.
-  gload(P0{}, 0);
-  gload(P1{}, 1);
-  lstore(P0{}, 0);
-  __syncthreads();
-
-  int kt = 0;
-  for (; kt + 1 < kt_n; kt += 2) {
-    kstep(P0{}, 0, kt + 2, true);     // multiplies tile kt, writes tile kt+1, loads tile kt+2
-    __syncthreads();
-    kstep(P1{}, 1, kt + 3, true);
-    __syncthreads();
-  }
-  if (kt < kt_n) kstep(P0{}, 0, 0, false);
-
-  // ---- epilogue ----
-  if (EPI == EPI_QKV && transposed) {
-    // acc[i][j][4q+e] = C[m = mblk + lr][n = nblk + 8q + 4lh + e]: lanes run along m
-#pragma unroll
-    for (int i = 0; i < MB; ++i) {
-      const int m = m0 + wm0 + i * 32 + lr;
-      const bool m_ok = m < g.m;
-      const int64_t col = m_ok ? (g.rows ? (int64_t)g.rows[m] : (int64_t)m) : 0;
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const int nblk = n0 + wn0 + j * 32;
-        if (nblk < g.n) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int n = nblk + 8 * q + 4 * lh + e;
-              const float v = acc[i][j][4 * q + e] + bf16_to_f32(g.bias[n]);
-              if (m_ok) g.vt_out[(int64_t)(n - 2 * g.d) * g.ld_vt + col] = f32_to_bf16_hw(v);
-            }
-        }
-      }
-    }
-    return;
-  }
-
-  // destination of element (m, n): base[row(m) * ld + n - n_shift]
-  bf16_t* base = g.c;
-  int ld = g.n, n_shift = 0;
-  bool use_rows = (EPI == EPI_SCATTER || EPI == EPI_SCATTER_ADD) && g.rows != nullptr;
-  if (EPI == EPI_QKV) {
-    ld = g.d;
-    if (n0 + wn0 >= g.d) { base = g.k_out; n_shift = g.d; use_rows = g.rows != nullptr; }
-  }
-  float bias[NB];
-  bool n_ok[NB];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const int n = n0 + wn0 + j * 32 + lr;
-    n_ok[j] = n < g.n;
-    bias[j] = n_ok[j] ? bf16_to_f32(g.bias[n]) : 0.f;
-  }
-  const float out_scale = (EPI == EPI_QKV && n0 + wn0 < g.d) ? g.q_scale : 1.0f;
-  const int ncol = n0 + wn0 + lr - n_shift;
-  // adaLN gate of the lane's columns, for the video and the text stream
-  const bool gated = (EPI == EPI_SCATTER || EPI == EPI_SCATTER_ADD) && g.gate_v != nullptr;
-  float gate_v[NB], gate_t[NB];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) {
-    const int n = n0 + wn0 + j * 32 + lr;
-    gate_v[j] = (gated && n_ok[j]) ? bf16_to_f32(g.gate_v[n]) : 1.f;
-    gate_t[j] = (gated && n_ok[j]) ? bf16_to_f32(g.gate_t[n]) : 1.f;
-  }
-#pragma unroll
-  for (int i = 0; i < MB; ++i) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int m = m0 + wm0 + i * 32 + 8 * q + 4 * lh + e;
-        if (m < g.m) {
-          const int64_t row = use_rows ? (int64_t)g.rows[m] : (int64_t)m;
-          bf16_t* prow = base + row * ld + ncol;
-#pragma unroll
-          for (int j = 0; j < NB; ++j) {
-            if (n_ok[j]) {
-              float v = acc[i][j][4 * q + e] + bias[j];
-              if (gated) v *= row < g.n_text ? gate_t[j] : gate_v[j];
-              if (EPI == EPI_QKV) v *= out_scale;
-              if (EPI == EPI_GELU) v = gelu_tanh(v);
-              if (EPI == EPI_SCATTER_ADD) v += bf16_to_f32(prow[j * 32]);
-              prow[j * 32] = f32_to_bf16_hw(v);
-            }
-          }
-        }
-      }
-    }
-  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -816,6 +543,394 @@ __device__ __forceinline__ void epilogue256(const GemmArgs& g, floatx16_t (&acc)
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// Smaller problems.  Two kernels whose waves share the k dimension instead of cutting the tile
+// further, so that few tiles still keep a CU's matrix pipes and its load path busy; both end in
+// stream_tile, which takes the fp32 sums from LDS.
+// ------------------------------------------------------------------------------------------
+
+// The tile's fp32 sums lie in LDS as COPIES addends of BM rows of BN + 4 floats (the pad spreads the
+// 16-byte accumulator writes of 16 rows over all banks).  All NT threads add the copies in order, apply
+// the epilogue and store 16-byte pieces, consecutive lanes along a row; V^T pieces run along m.
+template <int EPI, int BM, int BN, int NT, int COPIES>
+__device__ __forceinline__ void stream_tile(const GemmArgs& g, const float* tile, int m0, int n0, int tid) {
+  constexpr int LDT = BN + 4, PIECES = BN / 8;
+  const bool use_rows = EPI != EPI_PLAIN && EPI != EPI_GELU && g.rows != nullptr;
+  const int n_rowmajor = EPI == EPI_QKV ? 2 * g.d : g.n;     // columns stored along n
+#pragma unroll 2
+  for (int p = tid; p < BM * PIECES; p += NT) {
+    const int ml = p / PIECES, nl = (p - ml * PIECES) * 8;
+    const int m = m0 + ml, n = n0 + nl;
+    if (m >= g.m || n >= n_rowmajor) continue;
+    float v[8];
+    ResidIO<float>::load8(tile + ml * LDT + nl, v);
+#pragma unroll
+    for (int c = 1; c < COPIES; ++c) {
+      float w[8];
+      ResidIO<float>::load8(tile + (c * BM + ml) * LDT + nl, w);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += w[e];
+    }
+    float b[8];
+    ResidIO<bf16_t>::load8(g.bias + n, b);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += b[e];
+    if (EPI == EPI_QKV) {
+      bf16_t* dst;
+      if (n < g.d) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] *= g.q_scale;
+        dst = g.c + (int64_t)m * g.d + n;
+      } else {
+        dst = g.k_out + (int64_t)(use_rows ? g.rows[m] : m) * g.d + (n - g.d);
+      }
+      u32x4_t out;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[e] = pack_bf16x2_hw(v[2 * e], v[2 * e + 1]);
+      *reinterpret_cast<u32x4_t*>(dst) = out;
+      continue;
+    }
+    const int64_t row = use_rows ? (int64_t)g.rows[m] : (int64_t)m;
+    if ((EPI == EPI_SCATTER || EPI == EPI_SCATTER_ADD) && g.gate_v != nullptr) {
+      float gate[8];
+      ResidIO<bf16_t>::load8((row < g.n_text ? g.gate_t : g.gate_v) + n, gate);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] *= gate[e];
+    }
+    if (EPI == EPI_GELU) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = gelu_tanh(v[e]);
+    }
+    bf16_t* dst = g.c + row * g.n + n;
+    if (EPI == EPI_SCATTER_ADD) {
+      float old[8];
+      ResidIO<bf16_t>::load8(dst, old);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += old[e];
+    }
+    u32x4_t out;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[e] = pack_bf16x2_hw(v[2 * e], v[2 * e + 1]);
+    *reinterpret_cast<u32x4_t*>(dst) = out;
+    if (EPI == EPI_SCATTER_ADD && g.x != nullptr) {
+      // residual add with the feature as stored (rounded), so x matches x += S done afterwards
+      float xv[8];
+      if (g.x_fp32) {
+        float* xp = static_cast<float*>(g.x) + row * g.n + n;
+        ResidIO<float>::load8(xp, xv);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { xv[2 * e] += unpack_lo(out[e]); xv[2 * e + 1] += unpack_hi(out[e]); }
+        ResidIO<float>::store8(xp, xv);
+      } else {
+        bf16_t* xp = static_cast<bf16_t*>(g.x) + row * g.n + n;
+        ResidIO<bf16_t>::load8(xp, xv);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { xv[2 * e] += unpack_lo(out[e]); xv[2 * e + 1] += unpack_hi(out[e]); }
+        ResidIO<bf16_t>::store8(xp, xv);
+      }
+    }
+  }
+  if (EPI == EPI_QKV && n0 + BN > 2 * g.d) {
+    auto value = [&](int ml, int nl) {
+      float v = tile[ml * LDT + nl];
+#pragma unroll
+      for (int c = 1; c < COPIES; ++c) v += tile[(c * BM + ml) * LDT + nl];
+      return v;
+    };
+    if (use_rows) {
+      // scattered columns: lanes along m, whose tokens are neighbours in a V^T row
+      for (int u = tid; u < BM * BN; u += NT) {
+        const int nl = u / BM, ml = u - nl * BM, n = n0 + nl, m = m0 + ml;
+        if (m < g.m && n >= 2 * g.d && n < g.n)
+          g.vt_out[(int64_t)(n - 2 * g.d) * g.ld_vt + g.rows[m]] = f32_to_bf16_hw(value(ml, nl) + bf16_to_f32(g.bias[n]));
+      }
+    } else {
+      // eight columns x BM/8 pieces of eight rows at a time
+      for (int u = tid; u < BM / 8 * BN; u += NT) {
+        const int nl = u / BM * 8 + u % 8, ml = u / 8 % (BM / 8) * 8, n = n0 + nl, m = m0 + ml;
+        if (m >= g.m || n < 2 * g.d || n >= g.n) continue;
+        const float b = bf16_to_f32(g.bias[n]);
+        bf16_t* dst = g.vt_out + (int64_t)(n - 2 * g.d) * g.ld_vt + m;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = value(ml + e, nl) + b;
+        if (m + 8 <= g.m) {
+          u32x4_t out;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) out[e] = pack_bf16x2_hw(v[2 * e], v[2 * e + 1]);
+          *reinterpret_cast<u32x4_t*>(dst) = out;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (m + e < g.m) dst[e] = f32_to_bf16_hw(v[e]);
+        }
+      }
+    }
+  }
+}
+
+// tile slot -> tile origin, for tiles of bm x bn (see tile_origin)
+__device__ __forceinline__ bool tile_origin_of(int slot, int bm, int bn, int tiles_m, int tiles_n, int per_xcd,
+                                               int group_m, int& m0, int& n0) {
+  const int p = (slot % 8) * per_xcd + slot / 8;
+  if (p >= tiles_m * tiles_n) return false;
+  const int group = p / (group_m * tiles_n);
+  const int first_m = group * group_m;
+  const int gsize = min(tiles_m - first_m, group_m);
+  const int in_group = p - group * group_m * tiles_n;
+  m0 = (first_m + in_group % gsize) * bm;
+  n0 = (in_group / gsize) * bn;
+  return true;
+}
+
+// BM x BN tile, eight waves: 2 x 2 sub-tiles, each computed by two waves that take one half of every
+// 64-wide k stage.  The sub-tile is then large (few LDS reads a flop) with two waves on every SIMD.
+// Stages go global -> LDS into a ring of RING slots, filled RING - 1 stages ahead, one barrier a stage;
+// a slot holds the BM rows of A, then the BN rows of W, in the layout of the 256 x 256 kernel.
+// What bounds it: the fills (48 KB a stage at 192 x 192, two stages on their way; 1.25 PFLOP/s with all
+// CUs at work at k = 12288) and, at k = 3072, start-up and epilogue, about 7 of 50 us.  Measured: FFN2 of
+// 4485 rows at hidden 1920 190 -> 135 us (192 x 192), of 1755 rows at hidden 3072 212 -> 158 us (128 x 192),
+// of 2925 rows 197 + 58 (fix-up) -> 176 us.
+template <int BM, int BN>
+struct HalfK {
+  static constexpr int STAGE = (BM + BN) * 128;                          // bytes
+  static constexpr int RING = 163840 / STAGE < 4 ? 163840 / STAGE : 4;
+  static constexpr int TILE_BYTES = BM * (BN + 4) * 4;
+  static constexpr int LDS = RING * STAGE > TILE_BYTES ? RING * STAGE : TILE_BYTES;
+};
+
+template <int BM, int BN, int EPI>
+__global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m, int tiles_n, int per_xcd, int group_m) {
+  using C = HalfK<BM, BN>;
+  constexpr int MB = BM / 64, NB = BN / 64;            // 32 x 32 blocks of a wave's BM/2 x BN/2 sub-tile
+  constexpr int NF = (BM + BN) / 64;                   // 1 KB fills of a wave per stage
+  constexpr int RING = C::RING, STAGE = C::STAGE;
+  static_assert(BM % 64 == 0 && BN % 64 == 0 && RING >= 3 && NF <= MB * NB + 2, "tile shape");
+  int m0, n0;
+  if (!tile_origin_of(blockIdx.x, BM, BN, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+
+  extern __shared__ u32x4_t smem[];
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)smem;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);             // waves w and w+4 share a SIMD
+  const int wm0 = (wave & 1) * (BM / 2), wn0 = ((wave >> 1) & 1) * (BN / 2), kg = wave >> 2;
+  const int lr = lane & 31, lh = lane >> 5;
+
+  // fills: this wave's blocks of eight rows are wave + 8i of the slot's (BM + BN) / 8
+  const uint32_t row_bytes = (uint32_t)g.k * 2u;
+  const u32x4_t rsA = rsrc_words(g.a, (uint32_t)g.m * row_bytes);
+  const u32x4_t rsB = rsrc_words(g.w, (uint32_t)g.n * row_bytes);
+  uint32_t voff[NF];
+#pragma unroll
+  for (int i = 0; i < NF; ++i) {
+    const int row = (wave + 8 * i) * 8 + (lane >> 3);
+    const int chunk = (lane & 7) ^ ((row >> 1) & 7);
+    voff[i] = (uint32_t)(i < BM / 64 ? m0 + row : n0 + row - BM) * row_bytes + chunk * 16;
+  }
+  const int n_stages = g.k / SBK;
+  auto fill = [&](int slot, int stage, int i) {
+    lds_fill(i < BM / 64 ? rsA : rsB, lds0 + wave * 1024 + i * 8192 + (uint32_t)slot * STAGE, voff[i],
+             (uint32_t)min(stage, n_stages - 1) * (SBK * 2));            // (past the end: the last stage again, unread)
+  };
+
+  const char* lbase = reinterpret_cast<const char*>(smem);
+  const char *fa_ks[2], *fb_ks[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int off = lr * 128 + (((4 * kg + 2 * s + lh) ^ ((lr >> 1) & 7)) * 16);
+    fa_ks[s] = lbase + wm0 * 128 + off;
+    fb_ks[s] = lbase + (BM + wn0) * 128 + off;
+  }
+  auto frag = [&](const char* base, int slot_off, int i) {
+    u32x4_t t = *reinterpret_cast<const u32x4_t*>(base + slot_off + i * 4096);
+    return *reinterpret_cast<bf16x8_t*>(&t);
+  };
+
+  floatx16_t acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+  bf16x8_t fa[2][MB], fb[2][NB];
+  {
+    u32x4_t z = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < MB; ++i) fa[1][i] = *reinterpret_cast<bf16x8_t*>(&z);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) fb[1][j] = *reinterpret_cast<bf16x8_t*>(&z);
+  }
+  auto mma_one = [&](int set, int x) {
+    const int i = x / NB, j = x % NB;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
+  };
+#pragma unroll
+  for (int s = 0; s < RING - 1; ++s)
+#pragma unroll
+    for (int i = 0; i < NF; ++i) fill(s, s, i);
+  int slot = 0;
+  for (int t = 0; t < n_stages; ++t) {
+    // all but the fills of the RING - 2 newest stages have landed: stage t is in LDS; every wave's
+    // fragment reads of stage t-1 are complete, so its slot can be filled again
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((RING - 2) * NF) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    const int so = slot * STAGE, refill = slot == 0 ? RING - 1 : slot - 1;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      // MFMAs of the previous slice (set s^1) while the fragments of this one arrive in set s
+      constexpr int STEPS = MB * NB > MB + NB ? MB * NB : MB + NB;
+#pragma unroll
+      for (int x = 0; x < STEPS; ++x) {
+        if (s == 0 && x < NF) fill(refill, t + RING - 1, x);
+        if (s == 0 && x == STEPS - 1) {
+#pragma unroll
+          for (int y = STEPS; y < NF; ++y) fill(refill, t + RING - 1, y);
+        }
+        // A and W fragments alternate: the MFMAs need (0,0), (0,1), ... first
+        if (x == 0) fa[s][0] = frag(fa_ks[s], so, 0);
+        else if (x <= NB) fb[s][x - 1] = frag(fb_ks[s], so, x - 1);
+        else if (x < MB + NB) fa[s][x - NB] = frag(fa_ks[s], so, x - NB);
+        if (x < MB * NB) mma_one(s ^ 1, x);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    slot = slot == RING - 1 ? 0 : slot + 1;
+  }
+#pragma unroll
+  for (int x = 0; x < MB * NB; ++x) mma_one(1, x);
+
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __syncthreads();                       // every wave is done with the ring, and no fill is in flight
+  float* tile = reinterpret_cast<float*>(smem);
+  constexpr int LDT = BN + 4;
+  float* mine = tile + (wm0 + lr) * LDT + wn0 + 4 * lh;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    if (kg == half) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            floatx4_t* p = reinterpret_cast<floatx4_t*>(mine + 32 * i * LDT + 32 * j + 8 * q);
+            floatx4_t v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            if (half == 1) {
+              const floatx4_t o = *p;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] += o[e];
+            }
+            *p = v;
+          }
+    }
+    __syncthreads();
+  }
+  stream_tile<EPI, BM, BN, 512, 1>(g, tile, m0, n0, tid);
+}
+
+// 64 x 64 tile, four waves, each of which computes the whole tile over its own quarter of k from a
+// ring of its own: no barrier until the four partial sums meet in LDS, and at k <= 512 every byte
+// a wave needs is requested before it waits for the first.  For problems that leave most CUs without
+// a larger tile; what bounds them is the chain of load latencies along k, here a quarter as long.
+// Measured against 128 x 128 tiles with register staging: 326 x 256 x 1024 26.2 -> 8.0 us, 326 x 768 x 256
+// 13.7 -> 5.4, 691 x 1024 x 4096 50.3 -> 17.3 (accumulating epilogue).
+constexpr int QK_STAGE = 128 * 128;                      // 64 rows of A, 64 rows of W
+constexpr int QK_RING = 2;
+constexpr int QK_LDS = 4 * QK_RING * QK_STAGE;
+static_assert(4 * 64 * 68 * 4 <= QK_LDS, "the four partial tiles must fit");
+
+template <int EPI>
+__global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tiles_m, int tiles_n, int per_xcd, int group_m) {
+  int m0, n0;
+  if (!tile_origin_of(blockIdx.x, 64, 64, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+  extern __shared__ u32x4_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lh = lane >> 5;
+  char* ring = reinterpret_cast<char*>(smem) + wave * (QK_RING * QK_STAGE);
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(__attribute__((address_space(3))) void*)ring);
+
+  const uint32_t row_bytes = (uint32_t)g.k * 2u;
+  const u32x4_t rsA = rsrc_words(g.a, (uint32_t)g.m * row_bytes);
+  const u32x4_t rsB = rsrc_words(g.w, (uint32_t)g.n * row_bytes);
+  // rows 8i + lane/8 of either operand; the swizzle term repeats every 16 rows
+  uint32_t voffA[2], voffB[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = i * 8 + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
+    voffA[i] = (uint32_t)(m0 + row) * row_bytes + chunk * 16;
+    voffB[i] = (uint32_t)(n0 + row) * row_bytes + chunk * 16;
+  }
+  const int n_stages = g.k / SBK;
+  const int begin = wave * n_stages / 4, end = (wave + 1) * n_stages / 4;
+  auto fill = [&](int slot, int stage) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t row16 = (uint32_t)(i >> 1) * 16u * row_bytes;
+      lds_fill(rsA, lds0 + slot * QK_STAGE + i * 1024, voffA[i & 1] + row16, (uint32_t)stage * (SBK * 2));
+      lds_fill(rsB, lds0 + slot * QK_STAGE + 8192 + i * 1024, voffB[i & 1] + row16, (uint32_t)stage * (SBK * 2));
+    }
+  };
+
+  floatx16_t acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+  if (begin < end) fill(0, begin);
+  if (begin + 1 < end) fill(1, begin + 1);
+  for (int t = begin; t < end; ++t) {
+    const int slot = (t - begin) & 1;
+    if (t + 1 < end) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");   // the 16 newest fills are stage t+1
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const char* base = ring + slot * QK_STAGE + lr * 128;
+    bf16x8_t fa[4][2], fb[4][2];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int c = ((2 * ks + lh) ^ ((lr >> 1) & 7)) * 16;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        u32x4_t ta = *reinterpret_cast<const u32x4_t*>(base + i * 4096 + c);
+        u32x4_t tb = *reinterpret_cast<const u32x4_t*>(base + 8192 + i * 4096 + c);
+        fa[ks][i] = *reinterpret_cast<bf16x8_t*>(&ta);
+        fb[ks][i] = *reinterpret_cast<bf16x8_t*>(&tb);
+      }
+    }
+    if (t + 2 < end) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                  // the slot has been read
+      __builtin_amdgcn_sched_barrier(0);
+      fill(slot, t + 2);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
+  }
+  __syncthreads();                       // every wave has read its last stage: no fill is in flight
+  float* tile = reinterpret_cast<float*>(smem);
+  float* mine = tile + (wave * 64 + lr) * 68 + 4 * lh;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        floatx4_t v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        *reinterpret_cast<floatx4_t*>(mine + 32 * i * 68 + 32 * j + 8 * q) = v;
+      }
+  __syncthreads();
+  stream_tile<EPI, 64, 64, 256, 4>(g, tile, m0, n0, tid);
+}
+
+
 // A kernel that uses more than 64 KB of dynamic LDS must be told so once on every device it runs
 // on.  `done` holds one bit per device ordinal (devices past 63 are told on every launch); the
 // runtime call is idempotent, so two host threads that meet here at most repeat it.
@@ -838,8 +953,8 @@ hipError_t allow_dynamic_lds(const void* kern, int bytes, std::atomic<uint64_t>&
 // 17776-token shapes this cuts FFN2 (k = 12288; 3 rounds + 72 tiles) in 3 and makes it 9 %
 // faster; the out-projection (k = 3072, the same tiles) is cut in 2 for 3 %, FFN1 (13 rounds +
 // 32 tiles) in 3 for 0.4 %.  Returns the number of k-chunks (1: no cut); *n_rem_out: the tile
-// slots of the last round.
-int choose_k_split(const GemmArgs& g, size_t ws_bytes, int* n_rem_out) {
+// slots of the last round, *share what their round takes in units of a whole one.
+int choose_k_split(const GemmArgs& g, size_t ws_bytes, int* n_rem_out, double* share = nullptr) {
   const int tiles_m = (g.m + 255) / 256, tiles_n = (g.n + 255) / 256;
   const int slots = (tiles_m * tiles_n + 7) / 8 * 8;
   const int n_rem = slots - slots / 256 * 256;
@@ -855,6 +970,7 @@ int choose_k_split(const GemmArgs& g, size_t ws_bytes, int* n_rem_out) {
     const double t = (double)((n_rem * sp + 255) / 256) / sp + per_chunk * sp;
     if (t < best - 0.02) { best = t; split = sp; }
   }
+  if (share != nullptr) *share = best;
   return split;
 }
 
@@ -900,63 +1016,113 @@ hipError_t launch_gemm256(const GemmArgs& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN>
-hipError_t launch_cfg(const GemmArgs& g, hipStream_t st) {
-  constexpr int T = (BM / WM) * (BN / WN) * 64;
-  constexpr size_t smem = (size_t)2 * (BM + BN) * BK * sizeof(bf16_t);
-  int tiles_m = (g.m + BM - 1) / BM, tiles_n = (g.n + BN - 1) / BN;
-  int n_tiles = tiles_m * tiles_n;
-  int per_xcd = (n_tiles + 7) / 8;
-  dim3 grid(per_xcd * 8), block(T);
-#define HERO_GEMM_LAUNCH(E)                                                                              \
-  do {                                                                                                   \
-    auto kern = gemm_kernel<BM, BN, WM, WN, E>;                                                          \
-    static std::atomic<uint64_t> lds_allowed{0};                                                         \
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)smem, lds_allowed);       \
-    if (e != hipSuccess) return e;                                                                       \
-    hipLaunchKernelGGL(kern, grid, block, smem, st, g, tiles_m, tiles_n, per_xcd);                       \
-  } while (0)
-  switch (g.epilogue) {
-    case EPI_PLAIN: HERO_GEMM_LAUNCH(EPI_PLAIN); break;
-    case EPI_GELU: HERO_GEMM_LAUNCH(EPI_GELU); break;
-    case EPI_QKV: HERO_GEMM_LAUNCH(EPI_QKV); break;
-    case EPI_SCATTER: HERO_GEMM_LAUNCH(EPI_SCATTER); break;
-    case EPI_SCATTER_ADD: HERO_GEMM_LAUNCH(EPI_SCATTER_ADD); break;
-    default: return hipErrorInvalidValue;
-  }
-#undef HERO_GEMM_LAUNCH
+// A distinct type per kernel, so that each has its own record of the devices it was announced on.
+template <typename Kernel, Kernel KERN>
+hipError_t launch_tiles(const GemmArgs& g, int bm, int bn, int threads, int lds, hipStream_t st) {
+  static std::atomic<uint64_t> lds_allowed{0};
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(KERN), lds, lds_allowed);
+  if (e != hipSuccess) return e;
+  const int tiles_m = (g.m + bm - 1) / bm, tiles_n = (g.n + bn - 1) / bn;
+  const int per_xcd = (tiles_m * tiles_n + 7) / 8;
+  const int group_m = (g.k >= 8192 || tiles_m <= 24) ? 4 : 8;      // as for the 256 x 256 tiles
+  hipLaunchKernelGGL(KERN, dim3(per_xcd * 8), dim3(threads), lds, st, g, tiles_m, tiles_n, per_xcd, group_m);
   return hipGetLastError();
 }
+using TileKernel = void (*)(GemmArgs, int, int, int, int);
 
-}  // namespace
-
-namespace {
-bool uses_large_tiles(const GemmArgs& g) {
-  // large problems: 256x256 tiles, 8 waves of 128x64; small ones: 128x128 tiles, 4 waves of 64x64
-  const int64_t big_tiles = (int64_t)((g.m + 255) / 256) * ((g.n + 255) / 256);
-  // (a wave's columns must lie inside one of the Q / K / V thirds)
-  const bool qkv_split_ok = g.epilogue != EPI_QKV || g.d % 128 == 0;
-  return big_tiles >= 128 && qkv_split_ok;
+template <int BM, int BN>
+hipError_t launch_halfk(const GemmArgs& g, hipStream_t st) {
+  constexpr int LDS = HalfK<BM, BN>::LDS;
+  switch (g.epilogue) {
+    case EPI_PLAIN: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_PLAIN>>(g, BM, BN, 512, LDS, st);
+    case EPI_GELU: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_GELU>>(g, BM, BN, 512, LDS, st);
+    case EPI_QKV: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_QKV>>(g, BM, BN, 512, LDS, st);
+    case EPI_SCATTER: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_SCATTER>>(g, BM, BN, 512, LDS, st);
+    case EPI_SCATTER_ADD: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_SCATTER_ADD>>(g, BM, BN, 512, LDS, st);
+    default: return hipErrorInvalidValue;
+  }
 }
+
+hipError_t launch_quarterk(const GemmArgs& g, hipStream_t st) {
+  switch (g.epilogue) {
+    case EPI_PLAIN: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_PLAIN>>(g, 64, 64, 256, QK_LDS, st);
+    case EPI_GELU: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_GELU>>(g, 64, 64, 256, QK_LDS, st);
+    case EPI_QKV: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_QKV>>(g, 64, 64, 256, QK_LDS, st);
+    case EPI_SCATTER: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_SCATTER>>(g, 64, 64, 256, QK_LDS, st);
+    case EPI_SCATTER_ADD: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_SCATTER_ADD>>(g, 64, 64, 256, QK_LDS, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+enum TileKind { TILE_64, TILE_128, TILE_128x192, TILE_192, TILE_256x128, TILE_256 };
+
+// What a round of at most 256 tiles (one per CU) of a kind takes: fixed + stages * (low .. high) us, the
+// rate falling from `low` with a nearly empty chip to `high` with all CUs at work (they share the caches,
+// the fabric and the power budget).  Fitted to hero_linear timings on 82 .. 17776 rows, n 256 .. 12288,
+// k 256 .. 12288, operands out of the caches; per round at k = 3072, full chip: 64 x 64 11 us, 128 x 128 26,
+// 128 x 192 38, 256 x 128 48, 192 x 192 50, 256 x 256 77.
+struct TileCost { int bm, bn; float fixed, low, high; };
+constexpr TileCost TILE_COST[] = {{64, 64, 2.2f, 0.17f, 0.18f},   {128, 128, 3.5f, 0.31f, 0.48f},
+                                  {128, 192, 4.5f, 0.43f, 0.70f}, {192, 192, 7.f, 0.60f, 0.89f},
+                                  {256, 128, 6.f, 0.55f, 0.87f},  {256, 256, 6.f, 0.72f, 1.48f}};
+
+// The kind with the least expected time.  Small problems take the smallest tiles that still fit one
+// round (latency along k bounds them), large ones 256 x 256 (least operand traffic a flop), and in between
+// the kind whose tile count fills its last round: e.g. 2925 x 3072 is 144 tiles of 256 x 256 but 256 of
+// 192 x 192 (k = 12288: 221 us against 176), 691 x 1024 x 4096 14.5 us on 64 x 64 tiles against 24 on 128 x 128.
+TileKind choose_tile(const GemmArgs& g) {
+  // (a wave's columns of a 256 x 256 tile must lie inside one of the Q / K / V thirds)
+  const bool qkv_split_ok = g.epilogue != EPI_QKV || g.d % 128 == 0;
+  /*PROBE*/
+  const int stages = g.k / SBK;
+  TileKind best_kind = TILE_128;
+  double best = 1e30;
+  for (int kind = TILE_64; kind <= TILE_256; ++kind) {
+    if (kind == TILE_256 && !qkv_split_ok) continue;
+    const TileCost& c = TILE_COST[kind];
+    const int64_t tiles = (int64_t)((g.m + c.bm - 1) / c.bm) * ((g.n + c.bn - 1) / c.bn);
+    double rem = (double)(tiles % 256) / 256.0;
+    const double full = c.fixed + stages * c.high;
+    double t = (double)(tiles / 256) * full;
+    if (kind == TILE_256) {
+      int n_rem = 0;
+      double share = 1.0;
+      const int split = choose_k_split(g, g.splitk_ws != nullptr ? g.splitk_ws_bytes : 0, &n_rem, &share);
+      t += split > 1 ? share * full : rem > 0 ? c.fixed + stages * (c.low + rem * (c.high - c.low)) : 0.0;
+    } else if (rem > 0) {
+      t += c.fixed + stages * (c.low + rem * (c.high - c.low));
+    }
+    if (t < best) { best = t; best_kind = (TileKind)kind; }
+  }
+  return best_kind;
+}
+
 }  // namespace
 
 size_t gemm_wanted_scratch_bytes(const GemmArgs& g) {
-  if (g.m <= 0 || g.n <= 0 || g.k <= 0 || !uses_large_tiles(g)) return 0;
+  // stated for 256 x 256 tiles wherever the problem has 128 of them, also where a smaller tile is chosen:
+  // what a caller has to provide for a shape does not depend on the timings above
+  if (g.m <= 0 || g.n <= 0 || g.k <= 0) return 0;
+  if ((int64_t)((g.m + 255) / 256) * ((g.n + 255) / 256) < 128) return 0;
   int n_rem = 0;
   const int split = choose_k_split(g, (size_t)-1, &n_rem);
   return split > 1 ? (size_t)n_rem * split * 262144 : 0;
 }
 
-bool gemm_can_update_x(const GemmArgs& g) { return g.epilogue == EPI_SCATTER_ADD && uses_large_tiles(g); }
-
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {
   if (g.m <= 0 || g.n <= 0) return hipSuccess;
-  if (g.k <= 0 || g.k % BK != 0 || g.n % 64 != 0) return hipErrorInvalidValue;
+  if (g.k <= 0 || g.k % SBK != 0 || g.n % 64 != 0) return hipErrorInvalidValue;
   if (g.epilogue == EPI_QKV && (g.d % 64 != 0 || g.n != 3 * g.d)) return hipErrorInvalidValue;
   // operands are addressed with 32-bit byte offsets
   if (((int64_t)g.m + 512) * g.k * 2 >= (int64_t)1 << 32 || ((int64_t)g.n + 512) * g.k * 2 >= (int64_t)1 << 32)
     return hipErrorInvalidValue;
-  if (uses_large_tiles(g)) return launch_gemm256(g, st);
-  if (g.x != nullptr) return hipErrorInvalidValue;       // only the large-tile epilogue updates x
-  return launch_cfg<128, 128, 64, 64>(g, st);
+  switch (choose_tile(g)) {
+    case TILE_256: return launch_gemm256(g, st);
+    case TILE_64: return launch_quarterk(g, st);
+    case TILE_128: return launch_halfk<128, 128>(g, st);
+    case TILE_128x192: return launch_halfk<128, 192>(g, st);
+    case TILE_192: return launch_halfk<192, 192>(g, st);
+    case TILE_256x128: return launch_halfk<256, 128>(g, st);
+  }
+  return hipErrorInvalidValue;
 }

@@ -312,10 +312,9 @@ int check_layer(hero_cache_t c, int layer) {
 
 // The block of Eq. 2 on the rows listed in `rows` (nullptr = all N rows), writing K/V to
 // (k_dst, vt_dst) and the branch features to s_dst.  It ends before the residual add, unless
-// fuse_resid is given and the FFN2 kernel can add the stored features of its rows to x itself
-// (then *fuse_resid is set; only valid when the listed rows are all the rows x += S applies to).
+// fuse_resid is set: then the FFN2 kernel adds the stored features of its rows to x itself.
 int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows, int n_rows, bf16_t* k_dst,
-                   bf16_t* vt_dst, bf16_t* s_dst, hipStream_t st, bool* fuse_resid = nullptr) {
+                   bf16_t* vt_dst, bf16_t* s_dst, hipStream_t st, bool fuse_resid) {
   const hero_config& cfg = c->cfg;
   const bool x_fp32 = cfg.resid_dtype == HERO_DTYPE_FP32;
   const int d = cfg.hidden;
@@ -389,10 +388,7 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
   g.a = c->f; g.w = (const bf16_t*)w.w_ff2; g.bias = (const bf16_t*)w.b_ff2;
   g.m = n_rows; g.n = d; g.k = cfg.ffn_dim; g.epilogue = EPI_SCATTER_ADD; g.rows = rows; g.c = s_dst;
   if (adaln) { g.gate_v = mod + 8 * d; g.gate_t = mod + 11 * d; g.n_text = cfg.n_text; }
-  if (fuse_resid != nullptr) {
-    *fuse_resid = gemm_can_update_x(g);
-    if (*fuse_resid) { g.x = x; g.x_fp32 = x_fp32 ? 1 : 0; }
-  }
+  if (fuse_resid) { g.x = x; g.x_fp32 = x_fp32 ? 1 : 0; }
   g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes;
   PROF_LAUNCH(c, HERO_PROF_GEMM_FF2, 2.0 * rd * cfg.ffn_dim, st, launch_gemm(g, st));
   return HERO_OK;
@@ -479,23 +475,7 @@ int refresh_layer_deferred(hero_cache_t c, int layer, void* x, const int32_t* id
   if (!ls.has_weights) return fail(HERO_ERR_STATE, "layer %d has no weights", layer);
   if (ls.fills == 0) return fail(HERO_ERR_STATE, "layer %d refreshed before a full step filled its cache", layer);
   if (n_sel <= 0) return HERO_OK;
-  bool fused = false;
-  int rc = run_block_rows(c, ls, x, idx, n_sel, ls.k, ls.vt, ls.s_cur, st, &fused);
-  if (rc) return rc;
-  if (!fused) return fail(HERO_ERR_STATE, "internal: the FFN2 kernel did not take the residual update");
-  return HERO_OK;
-}
-
-// Whether a cached step with n_sel refreshed rows can defer its residual adds: the FFN2 kernel
-// must be the one that updates x for its rows.
-bool can_defer_residual(hero_cache_t c, int n_sel) {
-  const hero_config& cfg = c->cfg;
-  if (cfg.n_shallow < 1 || cfg.n_shallow > 48) return false;
-  if (n_sel == 0) return true;
-  GemmArgs g;
-  memset(&g, 0, sizeof(g));
-  g.m = n_sel; g.n = cfg.hidden; g.k = cfg.ffn_dim; g.epilogue = EPI_SCATTER_ADD;
-  return gemm_can_update_x(g);
+  return run_block_rows(c, ls, x, idx, n_sel, ls.k, ls.vt, ls.s_cur, st, true);
 }
 
 // The deferred adds of a cached step (see end_of_cached_step_kernel), incl. the deep stack when it
@@ -661,17 +641,7 @@ int hero_full_layer(hero_cache_t c, int32_t layer, void* dev_x, void* stream) {
   bf16_t* k_dst = ls.k ? ls.k : c->ktmp;
   bf16_t* vt_dst = ls.vt ? ls.vt : c->vtmp;
   c->in_full = true;
-  bool resid_done = false;
-  rc = run_block_rows(c, ls, dev_x, nullptr, (int)c->lay.n_tokens, k_dst, vt_dst, s_dst, st, &resid_done);
-  const bool x_fp32 = c->cfg.resid_dtype == HERO_DTYPE_FP32;
-  const double nd = (double)c->lay.n_tokens * c->cfg.hidden;
-  if (rc == HERO_OK)
-    rc = [&]() -> int {
-      if (resid_done) return HERO_OK;
-      PROF_LAUNCH(c, HERO_PROF_RESID, nd * (x_fp32 ? 10.0 : 6.0), st,
-                  launch_axpy_features(dev_x, x_fp32, s_dst, nullptr, 0.f, c->lay.n_tokens * c->cfg.hidden, st));
-      return HERO_OK;
-    }();
+  rc = run_block_rows(c, ls, dev_x, nullptr, (int)c->lay.n_tokens, k_dst, vt_dst, s_dst, st, true);
   c->in_full = false;
   if (rc) {
     // the slab written to may hold part of a new generation: what it held before is gone
@@ -724,7 +694,7 @@ int hero_refresh_layer(hero_cache_t c, int32_t layer, void* dev_x, const int32_t
                   verdict == 3 ? " and " : "", (verdict & 2) ? "a row listed twice" : "");
   }
   if (n_sel > 0) {
-    rc = run_block_rows(c, ls, dev_x, dev_idx, n_sel, ls.k, ls.vt, ls.s_cur, st);
+    rc = run_block_rows(c, ls, dev_x, dev_idx, n_sel, ls.k, ls.vt, ls.s_cur, st, false);
     if (rc) return rc;
   }
   const bool x_fp32 = c->cfg.resid_dtype == HERO_DTYPE_FP32;
@@ -783,7 +753,7 @@ int hero_step(hero_cache_t c, void* dev_x, int32_t step, void* stream) {
   if ((rc = hero_select(c, step, c->idx, &n_sel, stream)) != HERO_OK) return rc;
   c->last_n_sel = n_sel;
   const int n_deep = cfg.n_layers - cfg.n_shallow;
-  if (can_defer_residual(c, n_sel)) {
+  if (cfg.n_shallow >= 1 && cfg.n_shallow <= 48) {      // (the pass takes up to 48 feature arrays)
     // Only the refreshed rows of x are needed between the shallow layers of a cached step, so the
     // residual adds of all other rows wait for one pass at the end of the step (together with the
     // deep stack): one launch instead of one per shallow layer.
