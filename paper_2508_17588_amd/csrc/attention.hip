@@ -18,7 +18,7 @@
 // eight k-slots a lane feeds to one PV MFMA are eight consecutive keys, which makes the V^T
 // fragment a single 16-byte LDS read.
 //
-// Two code paths share that layout:
+// Two code paths share that layout (a third, for few query blocks and head_dim 32, is described with its kernel):
 //
 //  * head_dim 64, the production path: a software pipeline over 32-key blocks in which the
 //    QK^T MFMAs of block b+1, the exponentials of block b and the PV MFMAs of block b-1 are
@@ -37,10 +37,11 @@
 //    go to a caller-provided workspace (they simply add, there being no reference point), and a
 //    fix-up kernel adds them, makes the row-sum check on the totals and finishes the block.
 //
-//  * the general path (head_dim 32, and the fallback of the production path): classic online
+//  * the general path (the fallback of both kernels): classic online
 //    softmax with a running maximum that is only raised when some query exceeds it by more
 //    than 2^8, one 64-key tile at a time, register-staged double-buffered LDS.
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "hero_device.h"
@@ -262,18 +263,6 @@ __device__ __forceinline__ void attention_general(const AttnArgs& a, int head, i
         }
     }
   }
-}
-
-template <int HD, int NW>
-__global__ __launch_bounds__(NW * 64, 2) void attention_general_kernel(AttnArgs a, int n_qblocks, int n_blocks,
-                                                                       int per_xcd) {
-  // each XCD (consecutive workgroup ids round-robin over 8 XCDs) gets a contiguous range of heads
-  int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (logical >= n_blocks) return;
-  const int head = logical / n_qblocks, qb = logical % n_qblocks;
-  __shared__ u32x4_t sK[2 * BKV * HD / 8];
-  __shared__ u32x4_t sV[2 * HD * BKV / 8];
-  attention_general<HD, NW>(a, head, qb * (NW * 64) + (threadIdx.x >> 6) * 64, a.q_scale, sK, sV);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -714,42 +703,322 @@ __device__ __forceinline__ void attention_finish(const AttnArgs& a, int head, in
   }
 }
 
-template <int HD, int NW>
-hipError_t launch_cfg(const AttnArgs& a, hipStream_t st) {
-  int n_qblocks = (a.r + NW * 64 - 1) / (NW * 64);
-  int n_blocks = n_qblocks * a.n_heads;
-  int per_xcd = (n_blocks + 7) / 8;
-  if (HD == 64) {
-    // The chip runs 512 of these workgroups at a time (two per CU).  The n_rem blocks of the last
-    // round are cut into s key ranges so that the round takes ceil(n_rem*s/512)/s of a block's
-    // time (plus about two key tiles of pipeline fill per range); s minimises that.
-    KeySplit ks;
-    const int slots = per_xcd * 8;
-    ks.full_items = slots / 512 * 512;
-    ks.split = 1;
-    ks.ws = a.split_ws;
-    const int n_rem = slots - ks.full_items;
-    const int key_tiles = a.n_keys / BKV;
-    if (a.split_ws != nullptr && n_rem > 0) {
-      const int s_max = (int)std::min<size_t>((size_t)std::min(key_tiles / 16, 16),
-                                              a.split_ws_bytes / ((size_t)n_rem * PART_FLOATS * sizeof(float)));
-      double best = 1.0;
-      for (int sp = 2; sp <= s_max; ++sp) {
-        const double t = (double)((n_rem * sp + 511) / 512) / sp * (1.0 + 2.0 * sp / key_tiles) + 0.004 * sp;
-        if (t < best - 0.02) { best = t; ks.split = sp; }
-      }
+// ------------------------------------------------------------------------------------------
+// few query blocks, and head_dim 32: 64 queries per workgroup, four waves that share the keys
+// ------------------------------------------------------------------------------------------
+// Each wave walks a quarter of the 64-key tiles for the same 64 queries, from K and V^T tiles of its own
+// in LDS (no barrier in the loop); the reference-free form of the exponentials makes the unnormalised
+// outputs and row sums of the waves simply add, in LDS, at the end.  The next K tile is fetched while
+// the exponentials and PV of this one run, the next V^T tile during the following QK^T.
+// Against 256 queries per workgroup this has 4 x the workgroups and a quarter of the serial chain.
+// What bounds it: a tile's chain of QK^T, exponentials and PV inside one wave (1.2 us with one workgroup on
+// a CU); eight waves a workgroup gain nothing.  Measured against the kernel above: 326 queries and keys x 4 heads
+// 14.3 -> 8.7 us, 691 x 2032 x 16 34.1 -> 15.7, 2032 x 2032 x 16 34.7 -> 24.8; head_dim 32, against the running
+// maximum: 2032 x 2032 x 8 36.8 -> 11.8, 8000 x 8000 x 16 213 -> 192.  The scale is applied to the fp32 scores.
+constexpr int SHARE_WAVES = 4;
+template <int HD>
+struct ShareKeys {
+  static constexpr int QUADS = HD / 32 * 2 * 4;              // float4 accumulator pieces per lane
+  static constexpr int TILE_CHUNKS = BKV * HD / 8;           // 16-byte chunks of a K or V^T tile
+  u32x4_t tiles[SHARE_WAVES][2][TILE_CHUNKS];                         // [wave][K, V^T]; afterwards the partial outputs
+  float sums[SHARE_WAVES][2][64];
+  static_assert(QUADS * 64 == 2 * TILE_CHUNKS, "the partial outputs take the place of the tiles");
+};
+template <int HD> using share_keys_lds = __attribute__((address_space(3))) ShareKeys<HD>;
+
+// One pass over the keys for queries q0 .. q0+63: leaves the waves' partial outputs in LDS ([wave][quad][lane],
+// quad = (cb*2 + ig)*4 + q) and returns whether some row sum is outside the range of the reference-free form.
+template <int HD, bool SCALED>
+__device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int q0, share_keys_lds<HD>* ldsp, float (&l)[2]) {
+  ShareKeys<HD>& lds = *(ShareKeys<HD>*)ldsp;
+  constexpr int KCH = HD / 8, VCH = BKV / 8;       // 16-byte chunks per K / V^T tile row
+  constexpr int KS = HD / 16, CB = HD / 32;
+  constexpr int NF = HD / 8;                       // 1 KB fills per tile, K and V^T each
+  constexpr int KROWS = 512 / HD;                  // K rows per fill (V^T: 8)
+  constexpr int KPER = 16 / KROWS;                 // fills after which the swizzle repeats (V^T: 2)
+  constexpr int QUADS = ShareKeys<HD>::QUADS;
+  const int d = a.n_heads * HD;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lh = lane >> 5;
+  // fills: lane l of K fill i takes row KROWS*i + l/KCH, chunk slot l%KCH; of V^T fill i row 8i + l/8, slot l%8
+  const u32x4_t rsK = make_rsrc_words(a.k + head * HD, (uint32_t)((int64_t)a.n_keys * d * 2 - head * HD * 2));
+  const u32x4_t rsV = make_rsrc_words(a.vt + (int64_t)head * HD * a.ld_vt, (uint32_t)(((int64_t)d - head * HD) * a.ld_vt * 2));
+  const uint32_t k_row_bytes = (uint32_t)d * 2, v_row_bytes = (uint32_t)a.ld_vt * 2;
+  uint32_t k_voff[KPER], v_voff[2];
+#pragma unroll
+  for (int i = 0; i < KPER; ++i) {
+    const int row = i * KROWS + lane / KCH;
+    k_voff[i] = (uint32_t)row * k_row_bytes + ((lane % KCH) ^ ((row >> 1) & (KCH - 1))) * 16;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = i * 8 + lane / VCH;
+    v_voff[i] = (uint32_t)row * v_row_bytes + ((lane % VCH) ^ ((row >> 1) & (VCH - 1))) * 16;
+  }
+  const uint32_t lds_k = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr_t)&ldsp->tiles[wave][0][0]);
+  const uint32_t lds_v = lds_k + ShareKeys<HD>::TILE_CHUNKS * 16;
+  auto fill_k = [&](int tile) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+      direct_lds_load(rsK, lds_k + i * 1024, k_voff[i % KPER] + ((uint32_t)tile * BKV + i / KPER * 16) * k_row_bytes);
+  };
+  auto fill_v = [&](int tile) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+      direct_lds_load(rsV, lds_v + i * 1024, v_voff[i % 2] + (uint32_t)(i / 2 * 16) * v_row_bytes + (uint32_t)tile * (BKV * 2));
+  };
+
+  const int n_tiles = (a.n_keys + BKV - 1) / BKV;
+  const int t_begin = wave * n_tiles / SHARE_WAVES, t_end = (wave + 1) * n_tiles / SHARE_WAVES;
+  const int kperm = (lr & ~12) | ((lr & 4) << 1) | ((lr & 8) >> 1);   // K row read as MFMA row lr
+
+  if (t_begin < t_end) { fill_k(t_begin); fill_v(t_begin); }
+  bf16x8_t qf[2][KS];
+#pragma unroll
+  for (int ig = 0; ig < 2; ++ig) {
+    const u32x4_t* qp = reinterpret_cast<const u32x4_t*>(a.q + (int64_t)min(q0 + ig * 32 + lr, a.r - 1) * d + head * HD);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      u32x4_t t = qp[2 * s + lh];
+      qf[ig][s] = *reinterpret_cast<bf16x8_t*>(&t);
     }
-    if (ks.split == 1) ks.full_items = slots;
-    const int n_split = slots - ks.full_items;
-    hipLaunchKernelGGL((attention_hd64_kernel<NW>), dim3(ks.full_items + n_split * ks.split), dim3(NW * 64), 0, st, a,
-                       n_qblocks, n_blocks, per_xcd, ks);
-    if (n_split > 0)
-      hipLaunchKernelGGL((attention_hd64_fixup_kernel<NW>), dim3(n_split), dim3(NW * 64), 0, st, a, n_qblocks,
-                         n_blocks, per_xcd, ks);
-  } else
-    hipLaunchKernelGGL((attention_general_kernel<HD, NW>), dim3(per_xcd * 8), dim3(NW * 64), 0, st, a, n_qblocks,
-                       n_blocks, per_xcd);
+  }
+  floatx16_t o[CB][2];
+  float la[2] = {0.f, 0.f}, lb[2] = {0.f, 0.f};
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int ig = 0; ig < 2; ++ig)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[cb][ig][e] = 0.f;
+
+  for (int tile = t_begin; tile < t_end; ++tile) {
+    const bool more = tile + 1 < t_end;
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NF) : "memory");        // all but the V^T fills: K is in LDS
+    bf16x8_t kf[2][KS];
+#pragma unroll
+    for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int row = jb * 32 + kperm;
+        u32x4_t t = lds.tiles[wave][0][row * KCH + ((2 * ks + lh) ^ ((row >> 1) & (KCH - 1)))];
+        kf[jb][ks] = *reinterpret_cast<bf16x8_t*>(&t);
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");               // read: the next K tile may land
+    __builtin_amdgcn_sched_barrier(0);
+    if (more) fill_k(tile + 1);
+    bf16x8_t pf[2][2][2];          // [jb][ig][t]
+#pragma unroll
+    for (int jb = 0; jb < 2; ++jb) {
+      floatx16_t s[2];
+#pragma unroll
+      for (int ig = 0; ig < 2; ++ig)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[ig][e] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int ig = 0; ig < 2; ++ig) s[ig] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[jb][ks], qf[ig][ks], s[ig], 0, 0, 0);
+      if ((tile + 1) * BKV > a.n_keys) {                             // the ragged last tile
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int j = tile * BKV + jb * 32 + 16 * (g >> 1) + 8 * lh + 4 * (g & 1) + e;
+            if (j >= a.n_keys) { s[0][4 * g + e] = -INFINITY; s[1][4 * g + e] = -INFINITY; }
+          }
+      }
+#pragma unroll
+      for (int ig = 0; ig < 2; ++ig)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          uint32_t pk[4];
+#pragma unroll
+          for (int e2 = 0; e2 < 4; ++e2) {
+            const float s0 = s[ig][8 * h + 2 * e2], s1 = s[ig][8 * h + 2 * e2 + 1];
+            const float x0 = __builtin_amdgcn_exp2f(SCALED ? s0 * a.q_scale : s0);
+            const float x1 = __builtin_amdgcn_exp2f(SCALED ? s1 * a.q_scale : s1);
+            la[ig] += x0;
+            lb[ig] += x1;
+            pk[e2] = pack_bf16x2_hw(x0, x1);
+          }
+          u32x4_t t = {pk[0], pk[1], pk[2], pk[3]};
+          pf[jb][ig][h] = *reinterpret_cast<bf16x8_t*>(&t);
+        }
+    }
+    if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NF) : "memory");   // all but the next K tile: V^T is in LDS
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bf16x8_t vf[CB][4];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int row = cb * 32 + lr;
+        u32x4_t t = lds.tiles[wave][1][row * VCH + ((2 * x + lh) ^ ((row >> 1) & (VCH - 1)))];
+        vf[cb][x] = *reinterpret_cast<bf16x8_t*>(&t);
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (more) fill_v(tile + 1);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int ig = 0; ig < 2; ++ig)
+          o[cb][ig] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[cb][x], pf[x >> 1][ig][x & 1], o[cb][ig], 0, 0, 0);
+  }
+
+  // the four partial results meet in LDS: [wave][quad][lane], quad = (cb*2 + ig)*4 + q
+  __syncthreads();
+  floatx4_t* part = reinterpret_cast<floatx4_t*>(&lds.tiles[0][0][0]);
+#pragma unroll
+  for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+    for (int ig = 0; ig < 2; ++ig)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        floatx4_t v = {o[cb][ig][4 * q], o[cb][ig][4 * q + 1], o[cb][ig][4 * q + 2], o[cb][ig][4 * q + 3]};
+        part[(wave * QUADS + (cb * 2 + ig) * 4 + q) * 64 + lane] = v;
+      }
+#pragma unroll
+  for (int ig = 0; ig < 2; ++ig) lds.sums[wave][ig][lane] = la[ig] + lb[ig];
+  __syncthreads();
+#pragma unroll
+  for (int ig = 0; ig < 2; ++ig) {
+    l[ig] = 0.f;
+#pragma unroll
+    for (int w = 0; w < SHARE_WAVES; ++w) l[ig] += lds.sums[w][ig][lane];
+    l[ig] += __shfl_xor(l[ig], 32, 64);            // the two key halves of the query
+  }
+  const int bad = !(l[0] >= 0x1p-80f && l[0] <= 0x1p80f) | !(l[1] >= 0x1p-80f && l[1] <= 0x1p80f);
+  return __syncthreads_or(bad) != 0;
+}
+
+// Some row sum of the workgroup's 64 queries is out of range: they are recomputed with the running maximum
+// (stored by the first wave only: the others carry no valid query).  The fallback counter counts blocks of 256
+// queries, so the workgroup then runs the pass of the block's earlier 64s to see whether one of them counts.
+// Out of line: inlined, it makes the kernel park registers around its loop.
+template <int HD, bool SCALED>
+__device__ __attribute__((noinline)) void share_keys_fallback(AttnArgs a, int head, int qb, share_keys_lds<HD>* lds) {
+  u32x4_t* sk = (u32x4_t*)&lds->tiles[0][0][0];
+  attention_general<HD, SHARE_WAVES>(a, head, threadIdx.x < 64 ? qb * 64 : a.r, a.q_scale, sk, sk + 2 * BKV * HD / 8);
+  if (HD != 64 || a.fallback_count == nullptr) return;        // (head_dim 32 has no count: it never had one)
+  for (int b = qb & ~3; b < qb; ++b) {
+    __syncthreads();
+    float l[2];
+    if (share_keys_pass<HD, SCALED>(a, head, b * 64, lds, l)) return;
+  }
+  if (threadIdx.x == 0) atomicAdd(a.fallback_count, 1u);
+}
+
+template <int HD, bool SCALED>
+__global__ __launch_bounds__(SHARE_WAVES * 64, 2) void attention_share_keys_kernel(AttnArgs a, int n_qblocks, int n_blocks, int per_xcd) {
+  constexpr int QUADS = ShareKeys<HD>::QUADS;
+  extern __shared__ u32x4_t smem[];
+  const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (logical >= n_blocks) return;
+  const int head = logical / n_qblocks, qb = logical % n_qblocks, q0 = qb * 64;
+  auto* lds = (share_keys_lds<HD>*)(lds_ptr_t)smem;
+  float l[2];
+  if (share_keys_pass<HD, SCALED>(a, head, q0, lds, l)) {
+    share_keys_fallback<HD, SCALED>(a, head, qb, lds);
+    return;
+  }
+  const int d = a.n_heads * HD;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 31, lh = lane >> 5;
+  const floatx4_t* part = reinterpret_cast<const floatx4_t*>(smem);
+  // each wave adds up and stores its share of the quads: lane owns query lr of group ig, channels 8q + 4lh .. +3
+#pragma unroll
+  for (int i = 0; i < QUADS / SHARE_WAVES; ++i) {
+    const int quad = wave * (QUADS / SHARE_WAVES) + i, q = quad & 3, ig = (quad >> 2) & 1, cb = quad >> 3;
+    floatx4_t v = part[quad * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < SHARE_WAVES; ++w) {
+      const floatx4_t t = part[(w * QUADS + quad) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += t[e];
+    }
+    const float inv = 1.0f / (ig ? l[1] : l[0]);
+    const int qrow = q0 + ig * 32 + lr;
+    if (qrow < a.r) {
+      u32x2_t pk = {pack_bf16x2_hw(v[0] * inv, v[1] * inv), pack_bf16x2_hw(v[2] * inv, v[3] * inv)};
+      *reinterpret_cast<u32x2_t*>(a.o + (int64_t)qrow * d + head * HD + cb * 32 + 8 * q + 4 * lh) = pk;
+    }
+  }
+}
+
+template <int HD, bool SCALED>
+hipError_t launch_share_keys(const AttnArgs& a, hipStream_t st) {
+  static std::atomic<uint64_t> lds_allowed{0};
+  auto kern = attention_share_keys_kernel<HD, SCALED>;
+  constexpr int LDS = (int)sizeof(ShareKeys<HD>);
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), LDS, lds_allowed);
+  if (e != hipSuccess) return e;
+  const int n_q64 = (a.r + 63) / 64, n_blocks = n_q64 * a.n_heads, per_xcd = (n_blocks + 7) / 8;
+  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(SHARE_WAVES * 64), LDS, st, a, n_q64, n_blocks, per_xcd);
   return hipGetLastError();
+}
+
+// The chip runs 512 of the 256-query workgroups at a time (two per CU).  The n_rem blocks of the last
+// round are cut into s key ranges so that the round takes ceil(n_rem*s/512)/s of a block's
+// time (plus about two key tiles of pipeline fill per range); s minimises that.
+KeySplit choose_key_split(const AttnArgs& a, int slots) {
+  KeySplit ks;
+  ks.full_items = slots / 512 * 512;
+  ks.split = 1;
+  ks.ws = a.split_ws;
+  const int n_rem = slots - ks.full_items;
+  const int key_tiles = a.n_keys / BKV;
+  if (a.split_ws != nullptr && n_rem > 0) {
+    const int s_max = (int)std::min<size_t>((size_t)std::min(key_tiles / 16, 16),
+                                            a.split_ws_bytes / ((size_t)n_rem * PART_FLOATS * sizeof(float)));
+    double best = 1.0;
+    for (int sp = 2; sp <= s_max; ++sp) {
+      const double t = (double)((n_rem * sp + 511) / 512) / sp * (1.0 + 2.0 * sp / key_tiles) + 0.004 * sp;
+      if (t < best - 0.02) { best = t; ks.split = sp; }
+    }
+  }
+  if (ks.split == 1) ks.full_items = slots;
+  return ks;
+}
+
+hipError_t launch_hd64(const AttnArgs& a, hipStream_t st) {
+  constexpr int NW = 4;
+  const int n_qblocks = (a.r + NW * 64 - 1) / (NW * 64);
+  const int n_blocks = n_qblocks * a.n_heads;
+  const int per_xcd = (n_blocks + 7) / 8;
+  const int slots = per_xcd * 8;
+  const KeySplit ks = choose_key_split(a, slots);
+  const int n_split = slots - ks.full_items;
+  hipLaunchKernelGGL((attention_hd64_kernel<NW>), dim3(ks.full_items + n_split * ks.split), dim3(NW * 64), 0, st, a,
+                     n_qblocks, n_blocks, per_xcd, ks);
+  if (n_split > 0)
+    hipLaunchKernelGGL((attention_hd64_fixup_kernel<NW>), dim3(n_split), dim3(NW * 64), 0, st, a, n_qblocks,
+                       n_blocks, per_xcd, ks);
+  return hipGetLastError();
+}
+
+// Whether sharing the keys is the faster way at head_dim 64: expected times in us, fitted to 82 .. 2800
+// queries x 326 .. 12000 keys x 2 .. 48 heads.  A key tile takes a CU 0.95 us for one block of 256 queries and
+// 1.72 for two; 64 queries' quarter of the tiles 1.2 us each for one workgroup on a CU, 2.1 for two (2.35 when
+// every CU has two).  Both ways measured: 326 x 326 x 4 heads 14.3 us against 8.7, 2032 x 2032 x 16
+// 34.7 against 24.8, 1000 x 4000 x 48 63.8 against 62.9, 3000 x 12000 x 6 (cut into key ranges) 69 against 98.
+bool sharing_keys_is_faster(const AttnArgs& a) {
+  /*PROBE*/
+  const double tiles = (double)((a.n_keys + BKV - 1) / BKV);
+  const int64_t n_q64 = (int64_t)((a.r + 63) / 64) * a.n_heads;
+  const int64_t rem = n_q64 % 512;
+  const double share = tiles / 4 * (2.35 * (double)(n_q64 / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 1.2 : 2.1));
+  const int64_t slots = ((int64_t)((a.r + 255) / 256) * a.n_heads + 7) / 8 * 8;
+  const KeySplit ks = choose_key_split(a, (int)slots);
+  const int64_t last = slots % 512 * ks.split;         // work items of the last round
+  double whole = 1.72 * tiles * (double)(slots / 512);
+  if (last > 0) whole += tiles / ks.split * (double)((last + 511) / 512) * (last <= 256 ? 0.95 : 1.72);
+  if (ks.split > 1) whole += 5.0 + 0.02 * (double)last;
+  return share < whole;
 }
 
 }  // namespace
@@ -761,7 +1030,9 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
   if (((int64_t)a.n_keys + 4 * BKV) * a.n_heads * a.head_dim * 2 >= ((int64_t)1 << 32) ||
       (int64_t)a.n_heads * a.head_dim * a.ld_vt * 2 >= ((int64_t)1 << 32))
     return hipErrorInvalidValue;
-  if (a.head_dim == 64) return launch_cfg<64, 4>(a, st);
-  if (a.head_dim == 32) return launch_cfg<32, 4>(a, st);
-  return hipErrorInvalidValue;
+  const bool scaled = a.q_scale != 1.0f;
+  if (a.head_dim == 32) return scaled ? launch_share_keys<32, true>(a, st) : launch_share_keys<32, false>(a, st);
+  if (a.head_dim != 64) return hipErrorInvalidValue;
+  if (sharing_keys_is_faster(a)) return scaled ? launch_share_keys<64, true>(a, st) : launch_share_keys<64, false>(a, st);
+  return launch_hd64(a, st);
 }

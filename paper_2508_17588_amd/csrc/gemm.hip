@@ -931,20 +931,6 @@ __global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tile
 }
 
 
-// A kernel that uses more than 64 KB of dynamic LDS must be told so once on every device it runs
-// on.  `done` holds one bit per device ordinal (devices past 63 are told on every launch); the
-// runtime call is idempotent, so two host threads that meet here at most repeat it.
-hipError_t allow_dynamic_lds(const void* kern, int bytes, std::atomic<uint64_t>& done) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const uint64_t bit = dev < 64 ? 1ull << dev : 0;
-  if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
-  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
-  return e;
-}
-
 // The chip runs 256 workgroups at a time, so the last round of tiles may leave most of it
 // idle.  Cutting those n_rem tiles into s k-chunks makes the round take ceil(n_rem*s/256)/s of
 // a tile's time, and costs a fix-up pass that moves n_rem*s blocks of 256 KB twice (about

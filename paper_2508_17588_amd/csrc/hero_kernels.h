@@ -2,8 +2,23 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
 
 typedef uint16_t bf16_t;
+
+// A kernel that uses more than 64 KB of dynamic LDS must be told so once on every device it runs
+// on.  `done` holds one bit per device ordinal (devices past 63 are told on every launch); the
+// runtime call is idempotent, so two host threads that meet here at most repeat it.
+inline hipError_t allow_dynamic_lds(const void* kern, int bytes, std::atomic<uint64_t>& done) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? 1ull << dev : 0;
+  if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+  return e;
+}
 
 // Patch grid of Eq. 4 and the closed-form output offsets of the selection list.
 // n_take[class]: tokens taken per patch; class = 2*(clipped bottom row) + (clipped right column).
