@@ -1007,7 +1007,6 @@ hipError_t launch_hd64(const AttnArgs& a, hipStream_t st) {
 // every CU has two).  Both ways measured: 326 x 326 x 4 heads 14.3 us against 8.7, 2032 x 2032 x 16
 // 34.7 against 24.8, 1000 x 4000 x 48 63.8 against 62.9, 3000 x 12000 x 6 (cut into key ranges) 69 against 98.
 bool sharing_keys_is_faster(const AttnArgs& a) {
-  /*PROBE*/
   const double tiles = (double)((a.n_keys + BKV - 1) / BKV);
   const int64_t n_q64 = (int64_t)((a.r + 63) / 64) * a.n_heads;
   const int64_t rem = n_q64 % 512;

@@ -616,28 +616,47 @@ hipError_t launch_second_diff_stats(const bf16_t* f_prev, const bf16_t* f_cur, c
 // ---------------------------------------------------------------------------------
 // q / k post-processing of the modulated block: LayerNorm over each head's channels (eps 1e-6,
 // one gain / bias vector of head_dim elements shared by the heads), then 3-D rotary positions on
-// video rows, then (q only) the softmax scale.  In place, one wave per row: a lane holds 8
-// consecutive channels = 4 rotation pairs, a head spans head_dim / 8 neighbouring lanes.
+// video rows, then (q only) the softmax scale.  In place, one wave per q row and one per k row: a lane
+// holds 8 consecutive channels = 4 rotation pairs, a head spans head_dim / 8 neighbouring lanes.  A lane's
+// pieces, 512 channels apart, lie at the same place of their heads, so that its gains, biases and angles
+// are fetched once a row; three pieces are on their way at a time.
+// Bound by memory (8 d bytes a row), by latency on few rows.  Against one wave for q and k together, parameters
+// fetched anew for each piece: 17776 x 3072 107 -> 72 us (6.1 TB/s), 8775 listed rows x 3072 68 -> 41 (5.3 TB/s),
+// 2032 x 1024 7.8 -> 6.6, 691 listed rows x 1024 6.8 -> 5.5.
 // ---------------------------------------------------------------------------------
 template <int HD>
 __global__ __launch_bounds__(256) void qk_post_kernel(QkPostArgs a) {
+  constexpr int BATCH = 3;
   const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), r = unit >> 1;
   if (r >= a.n_rows) return;
+  const bool is_q = (unit & 1) == 0;
   const int64_t src = a.rows ? (int64_t)a.rows[r] : (int64_t)r;
-  const bool rotate = a.rope != nullptr && src >= a.n_text;
-  const float2* table = rotate ? a.rope + (src - a.n_text) * (HD / 2) : nullptr;
+  bf16_t* __restrict__ row = is_q ? a.q + (int64_t)r * a.d : a.k + src * a.d;
+  const bf16_t* gain = is_q ? a.qn_g : a.kn_g;
+  const bf16_t* bias = is_q ? a.qn_b : a.kn_b;
+  const float scale = is_q ? a.q_scale : 1.0f;
   const int n_chunks = a.d >> 3;
+  const int ch = (lane * 8) % HD;                     // first channel of this lane inside its heads: 512 % HD == 0
+  const bool rotate = a.rope != nullptr && src >= a.n_text;
+  float g8[8], b8[8];
+  if (gain != nullptr) {
+    ResidIO<bf16_t>::load8(gain + ch, g8);
+    ResidIO<bf16_t>::load8(bias + ch, b8);
+  }
+  float cs[8];                                        // (cos, sin) of the lane's four pairs
+  if (rotate) ResidIO<float>::load8(reinterpret_cast<const float*>(a.rope + (src - a.n_text) * (HD / 2) + ch / 2), cs);
+  for (int c0 = lane; c0 < n_chunks; c0 += BATCH * 64) {
+    u32x4_t in[BATCH];
 #pragma unroll
-  for (int which = 0; which < 2; ++which) {
-    bf16_t* row = which == 0 ? a.q + (int64_t)r * a.d : a.k + src * a.d;
-    const bf16_t* gain = which == 0 ? a.qn_g : a.kn_g;
-    const bf16_t* bias = which == 0 ? a.qn_b : a.kn_b;
-    const float scale = which == 0 ? a.q_scale : 1.0f;
-    for (int c = lane; c < n_chunks; c += 64) {      // whole heads stay inside one pass: 512 % HD == 0
+    for (int b = 0; b < BATCH; ++b)
+      if (c0 + b * 64 < n_chunks) in[b] = *reinterpret_cast<const u32x4_t*>(row + (c0 + b * 64) * 8);
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b) {
+      if (c0 + b * 64 >= n_chunks) break;             // (whole heads: n_chunks is a multiple of HD / 8)
       float v[8];
-      ResidIO<bf16_t>::load8(row + c * 8, v);
-      const int ch = (c * 8) % HD;                    // first channel of this lane inside its head
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { v[2 * j] = unpack_lo(in[b][j]); v[2 * j + 1] = unpack_hi(in[b][j]); }
       if (gain != nullptr) {
         float s = 0.f;
 #pragma unroll
@@ -651,24 +670,20 @@ __global__ __launch_bounds__(256) void qk_post_kernel(QkPostArgs a) {
 #pragma unroll
         for (int o = 1; o < HD / 8; o <<= 1) sq += __shfl_xor(sq, o, 64);
         const float rstd = rsqrtf(sq * (1.0f / HD) + 1e-6f);
-        float g8[8], b8[8];
-        ResidIO<bf16_t>::load8(gain + ch, g8);
-        ResidIO<bf16_t>::load8(bias + ch, b8);
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = (v[j] - mean) * rstd * g8[j] + b8[j];
       }
       if (rotate) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-          const float2 cs = table[ch / 2 + p];
           const float x0 = v[2 * p], x1 = v[2 * p + 1];
-          v[2 * p] = x0 * cs.x - x1 * cs.y;
-          v[2 * p + 1] = x0 * cs.y + x1 * cs.x;
+          v[2 * p] = x0 * cs[2 * p] - x1 * cs[2 * p + 1];
+          v[2 * p + 1] = x0 * cs[2 * p + 1] + x1 * cs[2 * p];
         }
       }
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] *= scale;
-      ResidIO<bf16_t>::store8(row + c * 8, v);
+      ResidIO<bf16_t>::store8(row + (c0 + b * 64) * 8, v);
     }
   }
 }
@@ -676,7 +691,7 @@ __global__ __launch_bounds__(256) void qk_post_kernel(QkPostArgs a) {
 hipError_t launch_qk_post(const QkPostArgs& a, hipStream_t st) {
   if (a.n_rows <= 0) return hipSuccess;
   if (a.d % a.head_dim != 0 || (a.head_dim != 32 && a.head_dim != 64)) return hipErrorInvalidValue;
-  dim3 grid((a.n_rows + 3) / 4), block(256);
+  dim3 grid((a.n_rows + 1) / 2), block(256);
   if (a.head_dim == 64) hipLaunchKernelGGL(qk_post_kernel<64>, grid, block, 0, st, a);
   else hipLaunchKernelGGL(qk_post_kernel<32>, grid, block, 0, st, a);
   return hipGetLastError();
