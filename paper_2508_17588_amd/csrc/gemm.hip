@@ -6,6 +6,7 @@
 //    thin last round;
 //  * gemm_halfk_kernel, 128 x 128 to 256 x 128 tiles: problems whose 256 x 256 tiles would leave CUs idle;
 //  * gemm_quarterk_kernel, 64 x 64 tiles: problems with few rows or columns, bound by latency along k.
+// A fourth, gemm_ln_kernel, normalises the rows itself (narrow models).
 // All use v_mfma_f32_32x32x16_bf16 (A fragment: lane holds row lane%32, eight consecutive k starting at
 // 8*(lane/32); B fragment likewise for column lane%32; accumulator register i of a lane is row
 // 8*(i/4) + 4*(lane/32) + i%4, column lane%32) and walk k in stages of 64: LDS rows of 128 B whose eight
@@ -930,6 +931,151 @@ __global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tile
   stream_tile<EPI, 64, 64, 256, 4>(g, tile, m0, n0, tid);
 }
 
+// LayerNorm and the 64 x 64 tile in one kernel, for models of at most 256 channels: the whole k extent of both
+// operands lies in LDS, W arriving by direct loads while the waves normalise their 64 / WAVES rows each (LPR
+// lanes a row, eight elements a lane) and round them to bf16 as the stand-alone LayerNorm does.
+// What bounds it: the latency of the row loads and of the two reductions (a wave's rows are reduced side by
+// side, step by step), then of the short walk along k.  326 rows, 256 channels: 3.4 (LayerNorm) + 5.8 us (QKV) in two
+// launches; the interval of the 42-layer model of that size 2430 -> 2215 us, of the 128-channel model 203 -> 171.
+template <int EPI, typename XT, int LPR, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void gemm_ln_kernel(GemmArgs g, LnInput ln, int tiles_m, int tiles_n, int per_xcd, int group_m) {
+  int m0, n0;
+  if (!tile_origin_of(blockIdx.x, 64, 64, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+  extern __shared__ u32x4_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lh = lane >> 5;
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)smem;
+  const int n_stages = g.k / SBK;                      // 64 k elements of 64 rows: 8 KB, swizzled as everywhere here
+  char* lds_a = reinterpret_cast<char*>(smem);
+  const int w_off = n_stages * 8192;
+
+  // W: blocks of eight rows of one stage, in turn to the waves
+  const uint32_t row_bytes = (uint32_t)g.k * 2u;
+  const u32x4_t rsB = rsrc_words(g.w, (uint32_t)g.n * row_bytes);
+  for (int i = wave; i < n_stages * 8; i += WAVES) {
+    const int row = (i & 7) * 8 + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
+    lds_fill(rsB, lds0 + w_off + i * 1024, (uint32_t)(n0 + row) * row_bytes + chunk * 16, (uint32_t)(i >> 3) * (SBK * 2));
+  }
+
+  // A: rows of the residual stream (plus the branch feature), normalised
+  constexpr int ROWS = 64 / WAVES, PER_PASS = 64 / LPR, BATCH = ROWS / PER_PASS;     // rows of a wave, of a pass; passes
+  static_assert(BATCH >= 1 && BATCH * PER_PASS == ROWS, "whole passes");
+  const int c = lane % LPR;                            // this lane's 8-element piece of a row
+  const bool in_row = c * 8 < g.k;
+  float gain[8], bias[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) gain[e] = bias[e] = 0.f;
+  if (in_row) {
+    ResidIO<bf16_t>::load8(ln.gain + c * 8, gain);
+    ResidIO<bf16_t>::load8(ln.bias + c * 8, bias);
+  }
+  // (bf16 pairs: shift and scale of the video stream, then of the text stream)
+  u32x4_t mod[4];
+  const bool modulated = ln.mod.scale_v != nullptr;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    mod[i] = u32x4_t{0u, 0u, 0u, 0u};
+    const bf16_t* p = i == 0 ? ln.mod.shift_v : i == 1 ? ln.mod.scale_v : i == 2 ? ln.mod.shift_t : ln.mod.scale_t;
+    if (modulated && in_row) mod[i] = *reinterpret_cast<const u32x4_t*>(p + c * 8);
+  }
+  const float inv_k = 1.0f / (float)g.k;
+  int src[BATCH];
+  float v[BATCH][8], sum[BATCH], sq[BATCH];
+#pragma unroll
+  for (int p = 0; p < BATCH; ++p) {
+    const int m = min(m0 + wave * ROWS + p * PER_PASS + lane / LPR, g.m - 1);   // (rows past m: not stored)
+    src[p] = ln.rows ? ln.rows[m] : m;
+  }
+#pragma unroll
+  for (int p = 0; p < BATCH; ++p) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[p][e] = 0.f;
+    if (in_row) ResidIO<XT>::load8(static_cast<const XT*>(ln.x) + (int64_t)src[p] * g.k + c * 8, v[p]);
+  }
+  if (ln.add != nullptr && in_row) {
+#pragma unroll
+    for (int p = 0; p < BATCH; ++p) {
+      float a8[8];
+      ResidIO<bf16_t>::load8(ln.add + (int64_t)src[p] * g.k + c * 8, a8);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[p][e] += a8[e];
+    }
+  }
+  // the reductions of the batch go step by step together, so that the latency of one hides the others'
+#pragma unroll
+  for (int p = 0; p < BATCH; ++p) {
+    sum[p] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum[p] += v[p][e];
+  }
+#pragma unroll
+  for (int o = LPR / 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int p = 0; p < BATCH; ++p) sum[p] += __shfl_xor(sum[p], o, 64);
+#pragma unroll
+  for (int p = 0; p < BATCH; ++p) {
+    sq[p] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      v[p][e] -= sum[p] * inv_k;
+      sq[p] += in_row ? v[p][e] * v[p][e] : 0.f;
+    }
+  }
+#pragma unroll
+  for (int o = LPR / 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int p = 0; p < BATCH; ++p) sq[p] += __shfl_xor(sq[p], o, 64);
+  if (in_row) {
+#pragma unroll
+    for (int p = 0; p < BATCH; ++p) {
+      const float rstd = rsqrtf(sq[p] * inv_k + ln.eps);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[p][e] = v[p][e] * rstd * gain[e] + bias[e];
+      if (modulated) {
+        const bool text = src[p] < ln.mod.n_text;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t sh = text ? mod[2][e] : mod[0][e], sc = text ? mod[3][e] : mod[1][e];
+          v[p][2 * e] = v[p][2 * e] * (1.0f + unpack_lo(sc)) + unpack_lo(sh);
+          v[p][2 * e + 1] = v[p][2 * e + 1] * (1.0f + unpack_hi(sc)) + unpack_hi(sh);
+        }
+      }
+      u32x4_t out;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[e] = pack_bf16x2_hw(v[p][2 * e], v[p][2 * e + 1]);
+      const int row = wave * ROWS + p * PER_PASS + lane / LPR;
+      *reinterpret_cast<u32x4_t*>(lds_a + (c >> 3) * 8192 + row * 128 + ((c & 7) ^ ((row >> 1) & 7)) * 16) = out;
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's part of W is in LDS
+  __syncthreads();
+
+  // 2 x 2 sub-tiles, each computed by KG waves that share the slices of 16 along k
+  constexpr int KG = WAVES / 4;
+  const int wm0 = (wave & 1) * 32, wn0 = ((wave >> 1) & 1) * 32, kg = wave >> 2, n_slices = g.k / 16;
+  floatx16_t acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  const char* fa = lds_a + (wm0 + lr) * 128;
+  const char* fb = lds_a + w_off + (wn0 + lr) * 128;
+  for (int t = kg * n_slices / KG; t < (kg + 1) * n_slices / KG; ++t) {
+    const int off = (t >> 2) * 8192 + ((2 * (t & 3) + lh) ^ ((lr >> 1) & 7)) * 16;
+    u32x4_t ta = *reinterpret_cast<const u32x4_t*>(fa + off);
+    u32x4_t tb = *reinterpret_cast<const u32x4_t*>(fb + off);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<bf16x8_t*>(&tb), *reinterpret_cast<bf16x8_t*>(&ta), acc, 0, 0, 0);
+  }
+  __syncthreads();                                     // the sums take the operands' place
+  float* tile = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    floatx4_t v = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    *reinterpret_cast<floatx4_t*>(tile + (kg * 64 + wm0 + lr) * 68 + wn0 + 8 * q + 4 * lh) = v;
+  }
+  __syncthreads();
+  stream_tile<EPI, 64, 64, WAVES * 64, KG>(g, tile, m0, n0, tid);
+}
+
 
 // The chip runs 256 workgroups at a time, so the last round of tiles may leave most of it
 // idle.  Cutting those n_rem tiles into s k-chunks makes the round take ceil(n_rem*s/256)/s of
@@ -1040,6 +1186,30 @@ hipError_t launch_quarterk(const GemmArgs& g, hipStream_t st) {
   }
 }
 
+template <int EPI, typename XT, int LPR, int WAVES>
+hipError_t launch_ln_tiles(const GemmArgs& g, const LnInput& ln, hipStream_t st) {
+  static std::atomic<uint64_t> lds_allowed{0};
+  auto kern = gemm_ln_kernel<EPI, XT, LPR, WAVES>;
+  constexpr int OPERANDS = LPR * 8 * 256, SUMS = WAVES / 4 * 64 * 68 * 4;         // k <= LPR * 8 of both operands
+  constexpr int LDS = OPERANDS > SUMS ? OPERANDS : SUMS;
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), LDS, lds_allowed);
+  if (e != hipSuccess) return e;
+  const int tiles_m = (g.m + 63) / 64, tiles_n = (g.n + 63) / 64;
+  const int per_xcd = (tiles_m * tiles_n + 7) / 8;
+  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(WAVES * 64), LDS, st, g, ln, tiles_m, tiles_n, per_xcd, 4);
+  return hipGetLastError();
+}
+
+template <int EPI, typename XT>
+hipError_t launch_ln_epilogue(const GemmArgs& g, const LnInput& ln, hipStream_t st) {
+  // up to 128 channels eight waves have little to normalise (16 waves measure the same); of 256 channels 16 waves
+  // take a lone workgroup of a CU sooner to its end, and two workgroups of eight a CU that has several:
+  // interval of 10 layers, 326 rows 753 against 771 us, 2042 rows 1058 against 1034
+  const int64_t tiles = (int64_t)((g.m + 63) / 64) * ((g.n + 63) / 64);
+  if (g.k <= 128) return launch_ln_tiles<EPI, XT, 16, 8>(g, ln, st);
+  return tiles <= 256 ? launch_ln_tiles<EPI, XT, 32, 16>(g, ln, st) : launch_ln_tiles<EPI, XT, 32, 8>(g, ln, st);
+}
+
 enum TileKind { TILE_64, TILE_128, TILE_128x192, TILE_192, TILE_256x128, TILE_256 };
 
 // What a round of at most 256 tiles (one per CU) of a kind takes: fixed + stages * (low .. high) us, the
@@ -1059,7 +1229,6 @@ constexpr TileCost TILE_COST[] = {{64, 64, 2.2f, 0.17f, 0.18f},   {128, 128, 3.5
 TileKind choose_tile(const GemmArgs& g) {
   // (a wave's columns of a 256 x 256 tile must lie inside one of the Q / K / V thirds)
   const bool qkv_split_ok = g.epilogue != EPI_QKV || g.d % 128 == 0;
-  /*PROBE*/
   const int stages = g.k / SBK;
   TileKind best_kind = TILE_128;
   double best = 1e30;
@@ -1111,4 +1280,22 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {
     case TILE_256x128: return launch_halfk<256, 128>(g, st);
   }
   return hipErrorInvalidValue;
+}
+
+// Every column tile normalises its rows again, so the line lies where that costs more than a launch and a pass
+// over memory in between.  Intervals of six layers, two kernels against one: 128 channels 558 -> 477 us at 90 rows,
+// 2557 -> 2363 at 17450; 256 channels 599 -> 539 at 90, 911 -> 828 at 2042, 1803 -> 1789 at 8218 (2064 tiles),
+// but 4315 -> 4479 at 17450; 320 channels 635 -> 624 at 90 and 951 -> 1006 at 2042.
+bool gemm_takes_ln(const GemmArgs& g) {
+  if (g.epilogue != EPI_QKV && g.epilogue != EPI_GELU) return false;
+  const int64_t tiles = (int64_t)((g.m + 63) / 64) * ((g.n + 63) / 64);
+  return g.k <= 128 || (g.k <= 256 && tiles <= 2048);
+}
+
+hipError_t launch_gemm_ln(const GemmArgs& g, const LnInput& ln, hipStream_t st) {
+  if (g.m <= 0 || g.n <= 0) return hipSuccess;
+  if (!gemm_takes_ln(g) || g.k <= 0 || g.k % SBK != 0 || g.n % 64 != 0) return hipErrorInvalidValue;
+  if (g.epilogue == EPI_QKV && (g.d % 64 != 0 || g.n != 3 * g.d)) return hipErrorInvalidValue;
+  if (g.epilogue == EPI_QKV) return ln.x_fp32 ? launch_ln_epilogue<EPI_QKV, float>(g, ln, st) : launch_ln_epilogue<EPI_QKV, bf16_t>(g, ln, st);
+  return ln.x_fp32 ? launch_ln_epilogue<EPI_GELU, float>(g, ln, st) : launch_ln_epilogue<EPI_GELU, bf16_t>(g, ln, st);
 }

@@ -333,9 +333,6 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
     m2.shift_v = mod + 6 * d; m2.scale_v = mod + 7 * d; m2.shift_t = mod + 9 * d; m2.scale_t = mod + 10 * d;
     m1.n_text = m2.n_text = cfg.n_text;
   }
-  PROF_LAUNCH(c, HERO_PROF_LN, rd * (xsz + 2.0), st,
-              launch_gather_ln(x, x_fp32, nullptr, rows, n_rows, d, (const bf16_t*)w.ln1_g,
-                               (const bf16_t*)w.ln1_b, cfg.ln_eps, c->a, st, m1));
   GemmArgs g;
   memset(&g, 0, sizeof(g));
   g.a = c->a; g.w = (const bf16_t*)w.w_qkv; g.bias = (const bf16_t*)w.b_qkv;
@@ -346,7 +343,15 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
   const float softmax_scale = 1.4426950408889634f / sqrtf((float)cfg.head_dim);
   g.q_scale = qk_post ? 1.0f : softmax_scale;
   g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes;
-  PROF_LAUNCH(c, HERO_PROF_GEMM_QKV, 6.0 * rd * d, st, launch_gemm(g, st));
+  if (gemm_takes_ln(g)) {
+    const LnInput ln = {x, x_fp32, nullptr, rows, (const bf16_t*)w.ln1_g, (const bf16_t*)w.ln1_b, cfg.ln_eps, m1};
+    PROF_LAUNCH(c, HERO_PROF_GEMM_QKV, 6.0 * rd * d, st, launch_gemm_ln(g, ln, st));
+  } else {
+    PROF_LAUNCH(c, HERO_PROF_LN, rd * (xsz + 2.0), st,
+                launch_gather_ln(x, x_fp32, nullptr, rows, n_rows, d, (const bf16_t*)w.ln1_g,
+                                 (const bf16_t*)w.ln1_b, cfg.ln_eps, c->a, st, m1));
+    PROF_LAUNCH(c, HERO_PROF_GEMM_QKV, 6.0 * rd * d, st, launch_gemm(g, st));
+  }
   if (qk_post) {
     QkPostArgs qa;
     memset(&qa, 0, sizeof(qa));
@@ -375,14 +380,19 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
   g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes;
   PROF_LAUNCH(c, HERO_PROF_GEMM_O, 2.0 * rd * d, st, launch_gemm(g, st));
 
-  PROF_LAUNCH(c, HERO_PROF_LN, rd * (xsz + 4.0), st,
-              launch_gather_ln(x, x_fp32, s_dst, rows, n_rows, d, (const bf16_t*)w.ln2_g,
-                               (const bf16_t*)w.ln2_b, cfg.ln_eps, c->a, st, m2));
   memset(&g, 0, sizeof(g));
   g.a = c->a; g.w = (const bf16_t*)w.w_ff1; g.bias = (const bf16_t*)w.b_ff1;
   g.m = n_rows; g.n = cfg.ffn_dim; g.k = d; g.epilogue = EPI_GELU; g.c = c->f;
   g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes;
-  PROF_LAUNCH(c, HERO_PROF_GEMM_FF1, 2.0 * rd * cfg.ffn_dim, st, launch_gemm(g, st));
+  if (gemm_takes_ln(g)) {
+    const LnInput ln = {x, x_fp32, s_dst, rows, (const bf16_t*)w.ln2_g, (const bf16_t*)w.ln2_b, cfg.ln_eps, m2};
+    PROF_LAUNCH(c, HERO_PROF_GEMM_FF1, 2.0 * rd * cfg.ffn_dim, st, launch_gemm_ln(g, ln, st));
+  } else {
+    PROF_LAUNCH(c, HERO_PROF_LN, rd * (xsz + 4.0), st,
+                launch_gather_ln(x, x_fp32, s_dst, rows, n_rows, d, (const bf16_t*)w.ln2_g,
+                                 (const bf16_t*)w.ln2_b, cfg.ln_eps, c->a, st, m2));
+    PROF_LAUNCH(c, HERO_PROF_GEMM_FF1, 2.0 * rd * cfg.ffn_dim, st, launch_gemm(g, st));
+  }
 
   memset(&g, 0, sizeof(g));
   g.a = c->f; g.w = (const bf16_t*)w.w_ff2; g.bias = (const bf16_t*)w.b_ff2;

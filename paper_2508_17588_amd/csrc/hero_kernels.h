@@ -117,6 +117,21 @@ struct GemmArgs {
 };
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t st);
+
+// The rows a GEMM normalises by itself instead of reading them from `a`: LayerNorm of x[row] (+ add[row]) over
+// the k channels, as launch_gather_ln computes it.
+struct LnInput {
+  const void* x;
+  bool x_fp32;
+  const bf16_t* add;          // nullptr: none
+  const int32_t* rows;        // nullptr: row m
+  const bf16_t *gain, *bias;
+  float eps;
+  LnMod mod;
+};
+// whether one kernel takes LayerNorm and this (QKV or GELU) GEMM faster than two
+bool gemm_takes_ln(const GemmArgs& g);
+hipError_t launch_gemm_ln(const GemmArgs& g, const LnInput& ln, hipStream_t st);
 // bytes of scratch launch_gemm would use for this problem if it had all it wanted (0: the problem is not cut along k)
 size_t gemm_wanted_scratch_bytes(const GemmArgs& g);
 
