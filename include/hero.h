@@ -265,7 +265,8 @@ int hero_linear_scratch(const void* dev_a, const void* dev_w, const void* dev_bi
  * in which some row sum leaves that range recomputes its 256 queries with the running-maximum form
  * (the result is the plain definition's either way; the cost of such a block roughly triples).
  * With scores of a few units, as LayerNorm-ed activations give, that never happens; it takes
- * |q.k| / sqrt(head_dim) beyond about 50. */
+ * |q.k| / sqrt(head_dim) beyond about 50.  head_dim 32 refers its exponentials to a maximum and has
+ * no such way out: the counter stays as it is. */
 int hero_attention_counted(const void* dev_q, const void* dev_k, const void* dev_vt, int64_t ld_vt,
                            void* dev_o, int32_t r, int32_t n_keys, int32_t n_heads, int32_t head_dim,
                            void* dev_scratch, size_t scratch_bytes, uint32_t* dev_fallbacks, void* stream);

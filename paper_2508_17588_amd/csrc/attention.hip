@@ -37,7 +37,7 @@
 //    go to a caller-provided workspace (they simply add, there being no reference point), and a
 //    fix-up kernel adds them, makes the row-sum check on the totals and finishes the block.
 //
-//  * the general path (the fallback of both kernels): classic online
+//  * the general path (the fallback at head_dim 64): classic online
 //    softmax with a running maximum that is only raised when some query exceeds it by more
 //    than 2^8, one 64-key tile at a time, register-staged double-buffered LDS.
 #include <algorithm>
@@ -707,14 +707,15 @@ __device__ __forceinline__ void attention_finish(const AttnArgs& a, int head, in
 // few query blocks, and head_dim 32: 64 queries per workgroup, four waves that share the keys
 // ------------------------------------------------------------------------------------------
 // Each wave walks a quarter of the 64-key tiles for the same 64 queries, from K and V^T tiles of its own
-// in LDS (no barrier in the loop); the reference-free form of the exponentials makes the unnormalised
-// outputs and row sums of the waves simply add, in LDS, at the end.  The next K tile is fetched while
+// in LDS (no barrier in the loop); the unnormalised outputs and row sums of the waves add up in LDS at the end,
+// as they are or, at head_dim 32, brought to one reference point first.  The next K tile is fetched while
 // the exponentials and PV of this one run, the next V^T tile during the following QK^T.
 // Against 256 queries per workgroup this has 4 x the workgroups and a quarter of the serial chain.
 // What bounds it: a tile's chain of QK^T, exponentials and PV inside one wave (1.2 us with one workgroup on
 // a CU); eight waves a workgroup gain nothing.  Measured against the kernel above: 326 queries and keys x 4 heads
 // 14.3 -> 8.7 us, 691 x 2032 x 16 34.1 -> 15.7, 2032 x 2032 x 16 34.7 -> 24.8; head_dim 32, against the running
-// maximum: 2032 x 2032 x 8 36.8 -> 11.8, 8000 x 8000 x 16 213 -> 192.  The scale is applied to the fp32 scores.
+// maximum with 256 queries a workgroup: 2032 x 2032 x 8 38.0 -> 13.6, 8000 x 8000 x 16 271 -> 247, 17776 x 17776 x 16
+// 1193 -> 1020.  The scale is applied to the fp32 scores.
 constexpr int SHARE_WAVES = 4;
 template <int HD>
 struct ShareKeys {
@@ -722,13 +723,25 @@ struct ShareKeys {
   static constexpr int TILE_CHUNKS = BKV * HD / 8;           // 16-byte chunks of a K or V^T tile
   u32x4_t tiles[SHARE_WAVES][2][TILE_CHUNKS];                         // [wave][K, V^T]; afterwards the partial outputs
   float sums[SHARE_WAVES][2][64];
+  float refs[SHARE_WAVES][2][64];                            // the waves' reference points (KEYS_RUNNING)
   static_assert(QUADS * 64 == 2 * TILE_CHUNKS, "the partial outputs take the place of the tiles");
 };
 template <int HD> using share_keys_lds = __attribute__((address_space(3))) ShareKeys<HD>;
 
+// What the exponentials of a pass refer to:
+//  KEYS_FREE     nothing: exact while every row sum stays within [2^-80, 2^80];
+//  KEYS_RUNNING  a reference point per query and wave: the maximum of the wave's first tile, raised to the maximum so
+//                far when the row sum passes 2^26 (or is no number; at most 2^24 keys of probability 1 stay below).
+//                It bounds the unnormalised values whatever the scores, without a maximum per tile; the waves'
+//                outputs and sums are brought to the largest of their reference points before they are added.
+// head_dim 32 takes KEYS_RUNNING: 2 - 7 % slower on ordinary scores than KEYS_FREE (13.6 against 12.8 us at
+// 2032 x 2032 x 8), but without a second pass where scores spread (standard deviation 17 in log2 units: 15.6 us against
+// 51.8, and 1080 against 4850 at 17776 x 17776 x 16) and finite for whatever values the running maximum handles.
+enum ShareMode { KEYS_FREE, KEYS_RUNNING };
+
 // One pass over the keys for queries q0 .. q0+63: leaves the waves' partial outputs in LDS ([wave][quad][lane],
 // quad = (cb*2 + ig)*4 + q) and returns whether some row sum is outside the range of the reference-free form.
-template <int HD, bool SCALED>
+template <int HD, bool SCALED, ShareMode MODE>
 __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int q0, share_keys_lds<HD>* ldsp, float (&l)[2]) {
   ShareKeys<HD>& lds = *(ShareKeys<HD>*)ldsp;
   constexpr int KCH = HD / 8, VCH = BKV / 8;       // 16-byte chunks per K / V^T tile row
@@ -786,6 +799,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   }
   floatx16_t o[CB][2];
   float la[2] = {0.f, 0.f}, lb[2] = {0.f, 0.f};
+  float ref[2] = {0.f, 0.f};
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
@@ -793,7 +807,8 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[cb][ig][e] = 0.f;
 
-  for (int tile = t_begin; tile < t_end; ++tile) {
+  auto step = [&](int tile, auto first) {
+    constexpr bool FIRST = decltype(first)::value;                   // of the wave's tiles (KEYS_RUNNING)
     const bool more = tile + 1 < t_end;
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NF) : "memory");        // all but the V^T fills: K is in LDS
     bf16x8_t kf[2][KS];
@@ -809,13 +824,12 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
     __builtin_amdgcn_sched_barrier(0);
     if (more) fill_k(tile + 1);
     bf16x8_t pf[2][2][2];          // [jb][ig][t]
-#pragma unroll
-    for (int jb = 0; jb < 2; ++jb) {
-      floatx16_t s[2];
+    // scores of 32 keys; accumulators start at -reference where Q carries the scale
+    auto scores = [&](int jb, floatx16_t (&s)[2]) {
 #pragma unroll
       for (int ig = 0; ig < 2; ++ig)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) s[ig][e] = 0.f;
+        for (int e = 0; e < 16; ++e) s[ig][e] = MODE == KEYS_RUNNING && !SCALED ? -ref[ig] : 0.f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -829,6 +843,9 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
             if (j >= a.n_keys) { s[0][4 * g + e] = -INFINITY; s[1][4 * g + e] = -INFINITY; }
           }
       }
+    };
+    // probabilities of 32 keys, packed; their sums are added to sa, sb
+    auto probabilities = [&](int jb, const floatx16_t (&s)[2], float (&sa)[2], float (&sb)[2], auto exponent) {
 #pragma unroll
       for (int ig = 0; ig < 2; ++ig)
 #pragma unroll
@@ -836,16 +853,63 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
           uint32_t pk[4];
 #pragma unroll
           for (int e2 = 0; e2 < 4; ++e2) {
-            const float s0 = s[ig][8 * h + 2 * e2], s1 = s[ig][8 * h + 2 * e2 + 1];
-            const float x0 = __builtin_amdgcn_exp2f(SCALED ? s0 * a.q_scale : s0);
-            const float x1 = __builtin_amdgcn_exp2f(SCALED ? s1 * a.q_scale : s1);
-            la[ig] += x0;
-            lb[ig] += x1;
+            const float x0 = __builtin_amdgcn_exp2f(exponent(s[ig][8 * h + 2 * e2], ig));
+            const float x1 = __builtin_amdgcn_exp2f(exponent(s[ig][8 * h + 2 * e2 + 1], ig));
+            sa[ig] += x0;
+            sb[ig] += x1;
             pk[e2] = pack_bf16x2_hw(x0, x1);
           }
           u32x4_t t = {pk[0], pk[1], pk[2], pk[3]};
           pf[jb][ig][h] = *reinterpret_cast<bf16x8_t*>(&t);
         }
+    };
+    if constexpr (MODE == KEYS_FREE) {
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb) {
+        floatx16_t s[2];
+        scores(jb, s);
+        probabilities(jb, s, la, lb, [&](float v, int) { return SCALED ? v * a.q_scale : v; });
+      }
+    } else {
+      floatx16_t s[2][2];
+      float na[2] = {la[0], la[1]}, nb[2] = {lb[0], lb[1]};          // the sums with this tile's
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb) {
+        scores(jb, s[jb]);
+        if (!FIRST) probabilities(jb, s[jb], na, nb, [&](float v, int ig) { return SCALED ? __builtin_fmaf(v, a.q_scale, -ref[ig]) : v; });
+      }
+      if (FIRST || __builtin_amdgcn_ballot_w64(!(na[0] + nb[0] + na[1] + nb[1] <= 0x1p26f)) != 0) {
+        float shift[2];                                              // what the scores have yet to lose
+#pragma unroll
+        for (int ig = 0; ig < 2; ++ig) {
+          float mx = s[0][ig][0];
+#pragma unroll
+          for (int e = 1; e < 32; ++e) mx = fmaxf(mx, s[e >> 4][ig][e & 15]);
+          auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+          mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));   // both halves of the query's keys
+          const float cand = SCALED ? mx * a.q_scale : mx + ref[ig];
+          float raised;
+          if (FIRST) {
+            raised = cand > -0x1p126f ? cand : 0.f;                  // (a tile of scores of -inf has no say)
+          } else {
+            raised = fmaxf(cand, ref[ig]);
+            const float alpha = __builtin_amdgcn_exp2f(ref[ig] - raised);
+            na[ig] = la[ig] * alpha;
+            nb[ig] = lb[ig] * alpha;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) o[cb][ig][e] *= alpha;
+          }
+          shift[ig] = SCALED ? raised : raised - ref[ig];
+          ref[ig] = raised;
+        }
+#pragma unroll
+        for (int jb = 0; jb < 2; ++jb)
+          probabilities(jb, s[jb], na, nb, [&](float v, int ig) { return SCALED ? __builtin_fmaf(v, a.q_scale, -shift[ig]) : v - shift[ig]; });
+      }
+#pragma unroll
+      for (int ig = 0; ig < 2; ++ig) { la[ig] = na[ig]; lb[ig] = nb[ig]; }
     }
     if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NF) : "memory");   // all but the next K tile: V^T is in LDS
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -868,10 +932,35 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
 #pragma unroll
         for (int ig = 0; ig < 2; ++ig)
           o[cb][ig] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[cb][x], pf[x >> 1][ig][x & 1], o[cb][ig], 0, 0, 0);
+  };
+  if constexpr (MODE == KEYS_FREE) {
+    for (int tile = t_begin; tile < t_end; ++tile) step(tile, std::false_type{});
+  } else {
+    if (t_begin < t_end) step(t_begin, std::true_type{});
+    for (int tile = t_begin + 1; tile < t_end; ++tile) step(tile, std::false_type{});
   }
 
   // the four partial results meet in LDS: [wave][quad][lane], quad = (cb*2 + ig)*4 + q
+  if constexpr (MODE == KEYS_RUNNING) {
+#pragma unroll
+    for (int ig = 0; ig < 2; ++ig) lds.refs[wave][ig][lane] = t_begin < t_end ? ref[ig] : -INFINITY;
+  }
   __syncthreads();
+  if constexpr (MODE == KEYS_RUNNING) {
+#pragma unroll
+    for (int ig = 0; ig < 2; ++ig) {
+      float top = lds.refs[0][ig][lane];
+#pragma unroll
+      for (int w = 1; w < SHARE_WAVES; ++w) top = fmaxf(top, lds.refs[w][ig][lane]);
+      const float f = t_begin < t_end ? __builtin_amdgcn_exp2f(ref[ig] - top) : 0.f;
+      la[ig] *= f;
+      lb[ig] *= f;
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[cb][ig][e] *= f;
+    }
+  }
   floatx4_t* part = reinterpret_cast<floatx4_t*>(&lds.tiles[0][0][0]);
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
@@ -892,6 +981,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
     for (int w = 0; w < SHARE_WAVES; ++w) l[ig] += lds.sums[w][ig][lane];
     l[ig] += __shfl_xor(l[ig], 32, 64);            // the two key halves of the query
   }
+  if (MODE == KEYS_RUNNING) return false;
   const int bad = !(l[0] >= 0x1p-80f && l[0] <= 0x1p80f) | !(l[1] >= 0x1p-80f && l[1] <= 0x1p80f);
   return __syncthreads_or(bad) != 0;
 }
@@ -900,20 +990,20 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
 // (stored by the first wave only: the others carry no valid query).  The fallback counter counts blocks of 256
 // queries, so the workgroup then runs the pass of the block's earlier 64s to see whether one of them counts.
 // Out of line: inlined, it makes the kernel park registers around its loop.
-template <int HD, bool SCALED>
+template <int HD, bool SCALED, ShareMode MODE>
 __device__ __attribute__((noinline)) void share_keys_fallback(AttnArgs a, int head, int qb, share_keys_lds<HD>* lds) {
   u32x4_t* sk = (u32x4_t*)&lds->tiles[0][0][0];
   attention_general<HD, SHARE_WAVES>(a, head, threadIdx.x < 64 ? qb * 64 : a.r, a.q_scale, sk, sk + 2 * BKV * HD / 8);
-  if (HD != 64 || a.fallback_count == nullptr) return;        // (head_dim 32 has no count: it never had one)
+  if (a.fallback_count == nullptr) return;
   for (int b = qb & ~3; b < qb; ++b) {
     __syncthreads();
     float l[2];
-    if (share_keys_pass<HD, SCALED>(a, head, b * 64, lds, l)) return;
+    if (share_keys_pass<HD, SCALED, MODE>(a, head, b * 64, lds, l)) return;
   }
   if (threadIdx.x == 0) atomicAdd(a.fallback_count, 1u);
 }
 
-template <int HD, bool SCALED>
+template <int HD, bool SCALED, ShareMode MODE>
 __global__ __launch_bounds__(SHARE_WAVES * 64, 2) void attention_share_keys_kernel(AttnArgs a, int n_qblocks, int n_blocks, int per_xcd) {
   constexpr int QUADS = ShareKeys<HD>::QUADS;
   extern __shared__ u32x4_t smem[];
@@ -922,8 +1012,8 @@ __global__ __launch_bounds__(SHARE_WAVES * 64, 2) void attention_share_keys_kern
   const int head = logical / n_qblocks, qb = logical % n_qblocks, q0 = qb * 64;
   auto* lds = (share_keys_lds<HD>*)(lds_ptr_t)smem;
   float l[2];
-  if (share_keys_pass<HD, SCALED>(a, head, q0, lds, l)) {
-    share_keys_fallback<HD, SCALED>(a, head, qb, lds);
+  if (share_keys_pass<HD, SCALED, MODE>(a, head, q0, lds, l)) {
+    share_keys_fallback<HD, SCALED, MODE>(a, head, qb, lds);
     return;
   }
   const int d = a.n_heads * HD;
@@ -950,10 +1040,10 @@ __global__ __launch_bounds__(SHARE_WAVES * 64, 2) void attention_share_keys_kern
   }
 }
 
-template <int HD, bool SCALED>
+template <int HD, bool SCALED, ShareMode MODE>
 hipError_t launch_share_keys(const AttnArgs& a, hipStream_t st) {
   static std::atomic<uint64_t> lds_allowed{0};
-  auto kern = attention_share_keys_kernel<HD, SCALED>;
+  auto kern = attention_share_keys_kernel<HD, SCALED, MODE>;
   constexpr int LDS = (int)sizeof(ShareKeys<HD>);
   hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), LDS, lds_allowed);
   if (e != hipSuccess) return e;
@@ -1030,8 +1120,9 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
       (int64_t)a.n_heads * a.head_dim * a.ld_vt * 2 >= ((int64_t)1 << 32))
     return hipErrorInvalidValue;
   const bool scaled = a.q_scale != 1.0f;
-  if (a.head_dim == 32) return scaled ? launch_share_keys<32, true>(a, st) : launch_share_keys<32, false>(a, st);
+  if (a.head_dim == 32)
+    return scaled ? launch_share_keys<32, true, KEYS_RUNNING>(a, st) : launch_share_keys<32, false, KEYS_RUNNING>(a, st);
   if (a.head_dim != 64) return hipErrorInvalidValue;
-  if (sharing_keys_is_faster(a)) return scaled ? launch_share_keys<64, true>(a, st) : launch_share_keys<64, false>(a, st);
+  if (sharing_keys_is_faster(a)) return scaled ? launch_share_keys<64, true, KEYS_FREE>(a, st) : launch_share_keys<64, false, KEYS_FREE>(a, st);
   return launch_hd64(a, st);
 }

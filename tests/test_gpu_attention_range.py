@@ -1,0 +1,96 @@
+"""Attention on scores and values far from ordinary: scores that rise, fall or spread over hundreds of powers of two
+along the keys, and (32-channel heads) values whose products with unnormalised probabilities leave the fp32 range.
+Against float64 on the operands the kernel reads."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2508_17588_amd import binding as B
+from workloads import get_config, round_to_bf16
+from hero_testlib import to_dev_bf16, to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+
+def rnd(seed, *shape):
+    return round_to_bf16(np.random.default_rng(seed).standard_normal(shape, dtype=np.float32))
+
+
+def check(got, q, k, v, scale_log2, hd, what):
+    """Per head softmax2(scale_log2 q.k) v.  Each probability is rounded to bf16 (8 significant bits: off by at most
+    2^-8 of itself) and carries the fp32 error of its exponent, a few units of 2^-23 of the largest score (counted as
+    eight); the result is rounded to bf16."""
+    assert np.isfinite(got).all(), f"{what}: {int((~np.isfinite(got)).sum())} values are not finite"
+    for h in range(q.shape[1] // hd):
+        c = slice(h * hd, (h + 1) * hd)
+        s = q[:, c] @ k[:, c].T * scale_log2
+        p = np.exp2(s - s.max(1, keepdims=True))
+        p /= p.sum(1, keepdims=True)
+        want = p @ v[:, c]
+        bound = 2.0 ** -8 * np.abs(want) + (2.0 ** -8 + 2.0 ** -20 * np.abs(s).max()) * (p @ np.abs(v[:, c]))
+        err = np.abs(got[:, c] - want)
+        assert (err <= 1.01 * bound).all(), f"{what} head {h}: {(err / bound).max():.2f} of the bound"
+
+
+def operands(scores, r, n_keys, heads, hd):
+    q, k, v = rnd(1, r, heads * hd), rnd(2, n_keys, heads * hd), rnd(3, n_keys, heads * hd)
+    per_unit = np.log2(np.e) / np.sqrt(hd)              # log2 units of score for each unit of q.k
+    along = np.arange(n_keys, dtype=np.float32)[:, None] / max(1, n_keys - 1) * 16
+    if scores in ("up", "down"):                        # all scores near +-69
+        k[:, ::hd], q[:, ::hd] = 16.0, round_to_bf16(np.float32(69 / 16 / per_unit * (1 if scores == "up" else -1)))
+    elif scores == "rise":                              # from 0 to 300
+        k[:, ::hd], q[:, ::hd] = round_to_bf16(along), round_to_bf16(np.float32(300 / 16 / per_unit))
+    elif scores == "fall":
+        k[:, ::hd], q[:, ::hd] = round_to_bf16(along[::-1].copy()), round_to_bf16(np.float32(300 / 16 / per_unit))
+    else:
+        q = round_to_bf16(q * 24)
+    return q, k, v
+
+
+@pytest.mark.parametrize("r,n_keys,heads", [(1, 1, 2), (65, 65, 2), (129, 257, 2), (300, 2033, 2)])
+@pytest.mark.parametrize("scores,v_exp,hd", [
+    ("up", 60, 32), ("down", -60, 32), ("up", 0, 64), ("down", 0, 64),
+    ("rise", 0, 32), ("fall", 0, 32), ("spread", 0, 32), ("rise", 0, 64), ("fall", 0, 64), ("spread", 0, 64),
+])
+def test_attention_of_unusual_scores(scores, v_exp, hd, r, n_keys, heads):
+    print(f"[case] r={r} n_keys={n_keys} hd={hd} scores {scores}, values x 2^{v_exp}", flush=True)
+    q, k, v = operands(scores, r, n_keys, heads, hd)
+    v = np.ldexp(v, v_exp).astype(np.float32)
+    vt = np.zeros((heads * hd, (n_keys + 63) // 64 * 64), np.float32)
+    vt[:, :n_keys] = v.T
+    o = torch.full((r + 1, heads * hd), 3.0, dtype=torch.bfloat16, device="cuda")
+    B.hero_attention(to_dev_bf16(q), to_dev_bf16(k), to_dev_bf16(vt), o, n_keys, heads, hd)
+    torch.cuda.synchronize()
+    check(to_host_f64(o[:r]), q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), np.log2(np.e) / np.sqrt(hd),
+          hd, scores)
+    assert float((o[r:] - 3.0).abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("q_size", [0.5, 40.0, 600.0])
+@pytest.mark.parametrize("hd,heads,height,width", [(32, 4, 5, 7), (32, 2, 17, 19), (64, 2, 5, 7), (64, 1, 17, 19)])
+def test_layer_attention_of_unusual_scores(hd, heads, height, width, q_size):
+    """A layer whose queries are the bias of their projection (so the softmax scale is folded into known values),
+    whose out-projection is the identity and whose FFN is zero: its feature is the attention output, compared
+    with float64 on the K and V it cached."""
+    d = heads * hd
+    cfg = get_config("tiny", n_layers=1, n_shallow=1, hidden=d, n_heads=heads, head_dim=hd, ffn_dim=2 * d, frames=1,
+                     height=height, width=width, n_text=3)
+    print(f"[case] {cfg.n_tokens} rows, {heads} heads of {hd}, queries of size {q_size}", flush=True)
+    bias = rnd(4, d) * np.float32(q_size / np.sqrt(hd))
+    w = {"ln1_g": np.ones(d), "ln2_g": np.ones(d), "w_o": np.eye(d), "w_ff1": np.zeros((2 * d, d)), "b_ff1": np.zeros(2 * d),
+         "w_ff2": np.zeros((d, 2 * d)), **{n: np.zeros(d) for n in ("ln1_b", "ln2_b", "b_o", "b_ff2")},
+         "w_qkv": np.concatenate([np.zeros((d, d)), rnd(5, 2 * d, d) / np.sqrt(d)]),
+         "b_qkv": np.concatenate([bias, np.zeros(2 * d)])}
+    w = {n: round_to_bf16(t.astype(np.float32)) for n, t in w.items()}
+    cache = B.HeroCache(B.make_config(cfg))
+    cache.hero_set_layer_weights(0, {n: to_dev_bf16(t) for n, t in w.items()})
+    x = to_dev_bf16(rnd(6, cfg.n_tokens, d)).float()
+    cache.hero_full_layer(0, x)
+    torch.cuda.synchronize()
+    k = to_host_f64(cache.hero_cache_view(0, B.VIEW_K))
+    v = to_host_f64(cache.hero_cache_view(0, B.VIEW_VT)[:, :cfg.n_tokens]).T
+    scale = np.float32(1.4426950408889634) / np.sqrt(np.float32(hd))
+    q = round_to_bf16(w["b_qkv"][:d] * scale).astype(np.float64)
+    got = to_host_f64(cache.hero_cache_view(0, B.VIEW_S_CUR))
+    check(got, np.broadcast_to(q, got.shape), k, v, 1.0, hd, f"queries of size {q_size}")
+    cache.close()
