@@ -37,7 +37,7 @@
 //    go to a caller-provided workspace (they simply add, there being no reference point), and a
 //    fix-up kernel adds them, makes the row-sum check on the totals and finishes the block.
 //
-//  * the general path (the fallback at head_dim 64): classic online
+//  * the general path (the fallback of the production path): classic online
 //    softmax with a running maximum that is only raised when some query exceeds it by more
 //    than 2^8, one 64-key tile at a time, register-staged double-buffered LDS.
 #include <algorithm>
@@ -737,7 +737,8 @@ template <int HD> using share_keys_lds = __attribute__((address_space(3))) Share
 // head_dim 32 takes KEYS_RUNNING: 2 - 7 % slower on ordinary scores than KEYS_FREE (13.6 against 12.8 us at
 // 2032 x 2032 x 8), but without a second pass where scores spread (standard deviation 17 in log2 units: 15.6 us against
 // 51.8, and 1080 against 4850 at 17776 x 17776 x 16) and finite for whatever values the running maximum handles.
-enum ShareMode { KEYS_FREE, KEYS_RUNNING };
+//  KEYS_SUMS     as KEYS_FREE, but the row sums only, to see whether they are in range.
+enum ShareMode { KEYS_FREE, KEYS_RUNNING, KEYS_SUMS };
 
 // One pass over the keys for queries q0 .. q0+63: leaves the waves' partial outputs in LDS ([wave][quad][lane],
 // quad = (cb*2 + ig)*4 + q) and returns whether some row sum is outside the range of the reference-free form.
@@ -786,7 +787,8 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   const int t_begin = wave * n_tiles / SHARE_WAVES, t_end = (wave + 1) * n_tiles / SHARE_WAVES;
   const int kperm = (lr & ~12) | ((lr & 4) << 1) | ((lr & 8) >> 1);   // K row read as MFMA row lr
 
-  if (t_begin < t_end) { fill_k(t_begin); fill_v(t_begin); }
+  if (t_begin < t_end) fill_k(t_begin);
+  if (MODE != KEYS_SUMS && t_begin < t_end) fill_v(t_begin);
   bf16x8_t qf[2][KS];
 #pragma unroll
   for (int ig = 0; ig < 2; ++ig) {
@@ -810,7 +812,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   auto step = [&](int tile, auto first) {
     constexpr bool FIRST = decltype(first)::value;                   // of the wave's tiles (KEYS_RUNNING)
     const bool more = tile + 1 < t_end;
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NF) : "memory");        // all but the V^T fills: K is in LDS
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MODE == KEYS_SUMS ? 0 : NF) : "memory");    // all but the V^T fills: K is in LDS
     bf16x8_t kf[2][KS];
 #pragma unroll
     for (int jb = 0; jb < 2; ++jb)
@@ -863,7 +865,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
           pf[jb][ig][h] = *reinterpret_cast<bf16x8_t*>(&t);
         }
     };
-    if constexpr (MODE == KEYS_FREE) {
+    if constexpr (MODE != KEYS_RUNNING) {
 #pragma unroll
       for (int jb = 0; jb < 2; ++jb) {
         floatx16_t s[2];
@@ -911,6 +913,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
 #pragma unroll
       for (int ig = 0; ig < 2; ++ig) { la[ig] = na[ig]; lb[ig] = nb[ig]; }
     }
+    if constexpr (MODE == KEYS_SUMS) return;
     if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NF) : "memory");   // all but the next K tile: V^T is in LDS
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     bf16x8_t vf[CB][4];
@@ -933,7 +936,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
         for (int ig = 0; ig < 2; ++ig)
           o[cb][ig] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[cb][x], pf[x >> 1][ig][x & 1], o[cb][ig], 0, 0, 0);
   };
-  if constexpr (MODE == KEYS_FREE) {
+  if constexpr (MODE != KEYS_RUNNING) {
     for (int tile = t_begin; tile < t_end; ++tile) step(tile, std::false_type{});
   } else {
     if (t_begin < t_end) step(t_begin, std::true_type{});
@@ -963,7 +966,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   }
   floatx4_t* part = reinterpret_cast<floatx4_t*>(&lds.tiles[0][0][0]);
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb)
+  for (int cb = 0; cb < (MODE == KEYS_SUMS ? 0 : CB); ++cb)
 #pragma unroll
     for (int ig = 0; ig < 2; ++ig)
 #pragma unroll
@@ -986,41 +989,15 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   return __syncthreads_or(bad) != 0;
 }
 
-// Some row sum of the workgroup's 64 queries is out of range: they are recomputed with the running maximum
-// (stored by the first wave only: the others carry no valid query).  The fallback counter counts blocks of 256
-// queries, so the workgroup then runs the pass of the block's earlier 64s to see whether one of them counts.
-// Out of line: inlined, it makes the kernel park registers around its loop.
-template <int HD, bool SCALED, ShareMode MODE>
-__device__ __attribute__((noinline)) void share_keys_fallback(AttnArgs a, int head, int qb, share_keys_lds<HD>* lds) {
-  u32x4_t* sk = (u32x4_t*)&lds->tiles[0][0][0];
-  attention_general<HD, SHARE_WAVES>(a, head, threadIdx.x < 64 ? qb * 64 : a.r, a.q_scale, sk, sk + 2 * BKV * HD / 8);
-  if (a.fallback_count == nullptr) return;
-  for (int b = qb & ~3; b < qb; ++b) {
-    __syncthreads();
-    float l[2];
-    if (share_keys_pass<HD, SCALED, MODE>(a, head, b * 64, lds, l)) return;
-  }
-  if (threadIdx.x == 0) atomicAdd(a.fallback_count, 1u);
-}
-
-template <int HD, bool SCALED, ShareMode MODE>
-__global__ __launch_bounds__(SHARE_WAVES * 64, 2) void attention_share_keys_kernel(AttnArgs a, int n_qblocks, int n_blocks, int per_xcd) {
+// Adds up the waves' partial outputs of queries q0 .. q0+63 and stores them: each wave its share of the quads; lane owns
+// query lr of group ig, channels 8q + 4lh .. +3.
+template <int HD>
+__device__ __forceinline__ void share_keys_store(const AttnArgs& a, int head, int q0, share_keys_lds<HD>* ldsp, float l0, float l1) {
   constexpr int QUADS = ShareKeys<HD>::QUADS;
-  extern __shared__ u32x4_t smem[];
-  const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (logical >= n_blocks) return;
-  const int head = logical / n_qblocks, qb = logical % n_qblocks, q0 = qb * 64;
-  auto* lds = (share_keys_lds<HD>*)(lds_ptr_t)smem;
-  float l[2];
-  if (share_keys_pass<HD, SCALED, MODE>(a, head, q0, lds, l)) {
-    share_keys_fallback<HD, SCALED, MODE>(a, head, qb, lds);
-    return;
-  }
   const int d = a.n_heads * HD;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 31, lh = lane >> 5;
-  const floatx4_t* part = reinterpret_cast<const floatx4_t*>(smem);
-  // each wave adds up and stores its share of the quads: lane owns query lr of group ig, channels 8q + 4lh .. +3
+  const floatx4_t* part = reinterpret_cast<const floatx4_t*>(&((ShareKeys<HD>*)ldsp)->tiles[0][0][0]);
 #pragma unroll
   for (int i = 0; i < QUADS / SHARE_WAVES; ++i) {
     const int quad = wave * (QUADS / SHARE_WAVES) + i, q = quad & 3, ig = (quad >> 2) & 1, cb = quad >> 3;
@@ -1031,13 +1008,50 @@ __global__ __launch_bounds__(SHARE_WAVES * 64, 2) void attention_share_keys_kern
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] += t[e];
     }
-    const float inv = 1.0f / (ig ? l[1] : l[0]);
+    const float inv = 1.0f / (ig ? l1 : l0);
     const int qrow = q0 + ig * 32 + lr;
     if (qrow < a.r) {
       u32x2_t pk = {pack_bf16x2_hw(v[0] * inv, v[1] * inv), pack_bf16x2_hw(v[2] * inv, v[3] * inv)};
       *reinterpret_cast<u32x2_t*>(a.o + (int64_t)qrow * d + head * HD + cb * 32 + 8 * q + 4 * lh) = pk;
     }
   }
+}
+
+// Some row sum of the workgroup's 64 queries is out of range: a second pass gives them reference points.  The
+// fallback counter counts blocks of 256 queries, so the workgroup then looks at the row sums of the block's earlier
+// 64s, as far as one that counts.  Out of line: inlined, it makes the kernel park registers around its loop.
+// Kernel times with scores of standard deviation 1.44 / 35 in log2 units (35: every block falls back), one wave of four
+// with queries of its own in the running-maximum form before: 326 x 326 x 4 heads 7.8 / 29.3 -> 20.0 us,
+// 2032 x 2032 x 16 25.4 / 137.9 -> 82.3; with some 64s of most blocks in range (17): 166.7 -> 100.6.
+template <int HD, bool SCALED>
+__device__ __attribute__((noinline)) void share_keys_fallback(AttnArgs a, int head, int qb, share_keys_lds<HD>* lds) {
+  float l[2];
+  share_keys_pass<HD, SCALED, KEYS_RUNNING>(a, head, qb * 64, lds, l);
+  share_keys_store<HD>(a, head, qb * 64, lds, l[0], l[1]);
+  if (a.fallback_count == nullptr) return;
+  for (int b = qb & ~3; b < qb; ++b) {
+    __syncthreads();
+    if (share_keys_pass<HD, SCALED, KEYS_SUMS>(a, head, b * 64, lds, l)) return;
+  }
+  if (threadIdx.x == 0) atomicAdd(a.fallback_count, 1u);
+}
+
+template <int HD, bool SCALED, ShareMode MODE>
+__global__ __launch_bounds__(SHARE_WAVES * 64, 2) void attention_share_keys_kernel(AttnArgs a, int n_qblocks, int n_blocks, int per_xcd) {
+  extern __shared__ u32x4_t smem[];
+  const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (logical >= n_blocks) return;
+  const int head = logical / n_qblocks, qb = logical % n_qblocks;
+  auto* lds = (share_keys_lds<HD>*)(lds_ptr_t)smem;
+  float l[2];
+  const bool bad = share_keys_pass<HD, SCALED, MODE>(a, head, qb * 64, lds, l);
+  if constexpr (MODE == KEYS_FREE) {
+    if (bad) {
+      share_keys_fallback<HD, SCALED>(a, head, qb, lds);
+      return;
+    }
+  }
+  share_keys_store<HD>(a, head, qb * 64, lds, l[0], l[1]);
 }
 
 template <int HD, bool SCALED, ShareMode MODE>

@@ -94,3 +94,32 @@ def test_layer_attention_of_unusual_scores(hd, heads, height, width, q_size):
     got = to_host_f64(cache.hero_cache_view(0, B.VIEW_S_CUR))
     check(got, np.broadcast_to(q, got.shape), k, v, 1.0, hd, f"queries of size {q_size}")
     cache.close()
+
+
+@pytest.mark.parametrize("hd,heads,passes", [(64, 16, 4.0), (32, 8, 2.0)])
+def test_price_of_spread_scores(hd, heads, passes):
+    """Scores of standard deviation 35 in log2 units.  head_dim 64: the pass that finds its row sums out of range, one
+    that gives them reference points, and at most one look at other row sums; head_dim 32: one pass that raises its
+    reference points (measured 3.2 and 1.3 passes)."""
+    n = 2032
+    print(f"[case] {n} queries and keys, {heads} heads of {hd}", flush=True)
+    d, gen = heads * hd, torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    q, k, v = (torch.randn(n, d, generator=gen, device="cuda") for _ in range(3))
+    k, vt = k.to(torch.bfloat16), torch.zeros(d, (n + 63) // 64 * 64, dtype=torch.bfloat16, device="cuda")
+    vt[:, :n] = v.T.to(torch.bfloat16)
+    o = torch.empty(n, d, dtype=torch.bfloat16, device="cuda")
+    count = torch.zeros(1, dtype=torch.int32, device="cuda")
+    times = {1: [], 24: []}
+    for _ in range(7):
+        for size in times:
+            qs = (q * size).to(torch.bfloat16)
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            B.hero_attention(qs, k, vt, o, n, heads, hd, None, count)
+            begin.record()
+            for _ in range(20):
+                B.hero_attention(qs, k, vt, o, n, heads, hd, None, count)
+            end.record()
+            torch.cuda.synchronize()
+            times[size].append(begin.elapsed_time(end))
+    assert np.median(times[24]) <= passes * np.median(times[1]), times
