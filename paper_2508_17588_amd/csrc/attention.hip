@@ -714,7 +714,7 @@ __device__ __forceinline__ void attention_finish(const AttnArgs& a, int head, in
 // What bounds it: a tile's chain of QK^T, exponentials and PV inside one wave (1.2 us with one workgroup on
 // a CU); eight waves a workgroup gain nothing.  Measured against the kernel above: 326 queries and keys x 4 heads
 // 14.3 -> 8.7 us, 691 x 2032 x 16 34.1 -> 15.7, 2032 x 2032 x 16 34.7 -> 24.8; head_dim 32, against the running
-// maximum with 256 queries a workgroup: 2032 x 2032 x 8 38.0 -> 13.6, 8000 x 8000 x 16 271 -> 247, 17776 x 17776 x 16
+// maximum with 256 queries a workgroup: 2032 x 2032 x 8 38.0 -> 13.5, 8000 x 8000 x 16 271 -> 247, 17776 x 17776 x 16
 // 1193 -> 1020.  The scale is applied to the fp32 scores.
 constexpr int SHARE_WAVES = 4;
 template <int HD>
@@ -734,10 +734,10 @@ template <int HD> using share_keys_lds = __attribute__((address_space(3))) Share
 //                far when the row sum passes 2^26 (or is no number; at most 2^24 keys of probability 1 stay below).
 //                It bounds the unnormalised values whatever the scores, without a maximum per tile; the waves'
 //                outputs and sums are brought to the largest of their reference points before they are added.
-// head_dim 32 takes KEYS_RUNNING: 2 - 7 % slower on ordinary scores than KEYS_FREE (13.6 against 12.8 us at
-// 2032 x 2032 x 8), but without a second pass where scores spread (standard deviation 17 in log2 units: 15.6 us against
-// 51.8, and 1080 against 4850 at 17776 x 17776 x 16) and finite for whatever values the running maximum handles.
 //  KEYS_SUMS     as KEYS_FREE, but the row sums only, to see whether they are in range.
+// head_dim 32 takes KEYS_RUNNING: 4 - 6 % slower on ordinary scores of many keys than KEYS_FREE (13.5 against 13.0 us at
+// 2032 x 2032 x 8), but without a second pass where scores spread (standard deviation 17 in log2 units: 15.6 us against
+// 51.8, and 1080 against 4850 at 17776 x 17776 x 16) and finite for values up to 2^100.
 enum ShareMode { KEYS_FREE, KEYS_RUNNING, KEYS_SUMS };
 
 // One pass over the keys for queries q0 .. q0+63: leaves the waves' partial outputs in LDS ([wave][quad][lane],
@@ -880,7 +880,8 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
         scores(jb, s[jb]);
         if (!FIRST) probabilities(jb, s[jb], na, nb, [&](float v, int ig) { return SCALED ? __builtin_fmaf(v, a.q_scale, -ref[ig]) : v; });
       }
-      if (FIRST || __builtin_amdgcn_ballot_w64(!(na[0] + nb[0] + na[1] + nb[1] <= 0x1p26f)) != 0) {
+      const bool beyond = !(na[0] + nb[0] + na[1] + nb[1] <= 0x1p26f);
+      if (FIRST || __builtin_expect(__builtin_amdgcn_ballot_w64(beyond) != 0, 0)) {
         float shift[2];                                              // what the scores have yet to lose
 #pragma unroll
         for (int ig = 0; ig < 2; ++ig) {
