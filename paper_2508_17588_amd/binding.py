@@ -33,6 +33,7 @@ WEIGHT_FIELDS = ("ln1_g", "ln1_b", "w_qkv", "b_qkv", "w_o", "b_o",
                  "ln2_g", "ln2_b", "w_ff1", "b_ff1", "w_ff2", "b_ff2")
 EXTRA_WEIGHT_FIELDS = ("q_norm_g", "q_norm_b", "k_norm_g", "k_norm_b", "mod")
 BLOCK_ADALN, BLOCK_QKNORM, BLOCK_ROPE = 1, 2, 4
+ROUTE_PLAIN, ROUTE_GELU, ROUTE_QKV, ROUTE_OUT, ROUTE_FFN2 = range(5)
 CACHE_KV_ALL_LAYERS, CACHE_PREV_ALL_LAYERS = 1, 2
 DEBUG_CHECK_IDX = 1
 
@@ -43,6 +44,7 @@ EXPORTS = (
     "hero_cache_view", "hero_cache_state", "hero_profile_begin", "hero_profile_begin_kinds", "hero_profile_end", "hero_gather_ln", "hero_linear", "hero_linear_scratch", "hero_linear_static",
     "hero_attention", "hero_attention_scratch", "hero_attention_counted",
     "hero_axpy_features", "hero_second_diff_stats", "hero_stability_scores",
+    "hero_linear_route", "hero_attention_route",
 )
 
 
@@ -109,6 +111,8 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
         "hero_axpy_features": [P, I, P, P, c_float, c_int64, P],
         "hero_second_diff_stats": [P, P, P, c_int64, P, ctypes.c_size_t, P, I, P],
         "hero_stability_scores": [POINTER(ctypes.c_double), I, POINTER(ctypes.c_double)],
+        "hero_linear_route": [I, I, I, I, I, ctypes.c_size_t, POINTER(I), POINTER(I), POINTER(I)],
+        "hero_attention_route": [I, I, I, I, ctypes.c_size_t, POINTER(I), POINTER(I)],
     }
     for name, argtypes in sig.items():
         fn = getattr(lib, name)
@@ -372,6 +376,20 @@ def hero_attention(q, k, vt, o, n_keys: int, n_heads: int, head_dim: int, scratc
         return
     _check(load_library().hero_attention(_ptr(q), _ptr(k), _ptr(vt), vt.shape[1], _ptr(o), r, n_keys,
                                          n_heads, head_dim, _stream()))
+
+
+def hero_linear_route(m: int, n: int, k: int, what: int = ROUTE_PLAIN, listed: bool = False, scratch_bytes: int = 0):
+    """(tile rows, tile columns, chunks along k of the last round's tiles) of a GEMM; host only."""
+    out = [c_int32() for _ in range(3)]
+    _check(load_library().hero_linear_route(m, n, k, what, int(listed), scratch_bytes, *(byref(v) for v in out)))
+    return tuple(v.value for v in out)
+
+
+def hero_attention_route(r: int, n_keys: int, n_heads: int, head_dim: int, scratch_bytes: int = 0):
+    """(queries per workgroup, key ranges of the last round's blocks) of an attention; host only."""
+    out = [c_int32() for _ in range(2)]
+    _check(load_library().hero_attention_route(r, n_keys, n_heads, head_dim, scratch_bytes, *(byref(v) for v in out)))
+    return tuple(v.value for v in out)
 
 
 def hero_axpy_features(x, s_cur, s_prev, alpha: float):

@@ -1127,6 +1127,12 @@ bool sharing_keys_is_faster(const AttnArgs& a) {
 
 }  // namespace
 
+void attention_route(const AttnArgs& a, int* queries, int* key_ranges) {
+  const bool share = a.head_dim == 32 || sharing_keys_is_faster(a);
+  *queries = share ? 64 : 256;
+  *key_ranges = share ? 1 : choose_key_split(a, ((a.r + 255) / 256 * a.n_heads + 7) / 8 * 8).split;
+}
+
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
   if (a.r <= 0 || a.n_keys <= 0) return hipSuccess;
   if (a.ld_vt % 64 != 0 || a.ld_vt < a.n_keys) return hipErrorInvalidValue;

@@ -1282,6 +1282,14 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
+void gemm_route(const GemmArgs& g, int* tile_m, int* tile_n, int* k_chunks) {
+  const TileKind kind = choose_tile(g);
+  *tile_m = TILE_COST[kind].bm;
+  *tile_n = TILE_COST[kind].bn;
+  int n_rem;
+  *k_chunks = kind == TILE_256 ? choose_k_split(g, g.splitk_ws != nullptr ? g.splitk_ws_bytes : 0, &n_rem) : 1;
+}
+
 // Every column tile normalises its rows again, so the line lies where that costs more than a launch and a pass
 // over memory in between.  Intervals of six layers, two kernels against one: 128 channels 558 -> 477 us at 90 rows,
 // 2557 -> 2363 at 17450; 256 channels 599 -> 539 at 90, 911 -> 828 at 2042, 1803 -> 1789 at 8218 (2064 tiles),

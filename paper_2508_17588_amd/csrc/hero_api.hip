@@ -918,6 +918,42 @@ int hero_linear_static(const void* dev_a, const void* dev_w, const void* dev_bia
   return hero_linear_scratch(dev_a, dev_w, dev_bias, dev_c, m, n, k, act, ws, STATIC_SCRATCH_BYTES, stream);
 }
 
+// (the routes only ask whether there is scratch and how much: any address stands for it)
+int hero_linear_route(int32_t m, int32_t n, int32_t k, int32_t what, int32_t listed, size_t scratch_bytes, int32_t* tile_m,
+                      int32_t* tile_n, int32_t* k_chunks) {
+  if (!tile_m || !tile_n || !k_chunks) return fail(HERO_ERR_INVALID_ARG, "output pointer is null");
+  if (m <= 0 || n <= 0 || k <= 0) return fail(HERO_ERR_INVALID_ARG, "bad sizes");
+  if (what < HERO_ROUTE_PLAIN || what > HERO_ROUTE_FFN2) return fail(HERO_ERR_INVALID_ARG, "unknown GEMM %d", what);
+  if (k % 64 != 0 || n % 64 != 0 || (what == HERO_ROUTE_QKV && n % 192 != 0))
+    return fail(HERO_ERR_SHAPE, "k and n must be multiples of 64 (QKV: n of 192)");
+  if (!gemm_offsets_fit(m, n, k)) return fail(HERO_ERR_SHAPE, "beyond the 32-bit operand offsets");
+  static const int32_t any_row = 0;
+  GemmArgs g;
+  memset(&g, 0, sizeof(g));
+  g.m = m; g.n = n; g.k = k; g.d = n / 3;
+  g.epilogue = what == HERO_ROUTE_PLAIN ? EPI_PLAIN : what == HERO_ROUTE_GELU ? EPI_GELU : what == HERO_ROUTE_QKV ? EPI_QKV
+               : what == HERO_ROUTE_OUT ? EPI_SCATTER : EPI_SCATTER_ADD;
+  if (listed) g.rows = &any_row;
+  if (scratch_bytes > 0) { g.splitk_ws = reinterpret_cast<float*>(&g); g.splitk_ws_bytes = scratch_bytes; }
+  gemm_route(g, tile_m, tile_n, k_chunks);
+  return HERO_OK;
+}
+
+int hero_attention_route(int32_t r, int32_t n_keys, int32_t n_heads, int32_t head_dim, size_t scratch_bytes, int32_t* queries,
+                         int32_t* key_ranges) {
+  if (!queries || !key_ranges) return fail(HERO_ERR_INVALID_ARG, "output pointer is null");
+  if (r < 1 || n_keys < 1 || n_heads < 1) return fail(HERO_ERR_INVALID_ARG, "bad sizes");
+  if (head_dim != 32 && head_dim != 64) return fail(HERO_ERR_SHAPE, "head_dim must be 32 or 64");
+  if (!attention_offsets_fit(n_keys, (int64_t)n_heads * head_dim, ((int64_t)n_keys + 63) / 64 * 64))
+    return fail(HERO_ERR_SHAPE, "beyond the 32-bit operand offsets");
+  AttnArgs a;
+  memset(&a, 0, sizeof(a));
+  a.r = r; a.n_keys = n_keys; a.n_heads = n_heads; a.head_dim = head_dim;
+  if (scratch_bytes > 0) { a.split_ws = reinterpret_cast<float*>(&a); a.split_ws_bytes = scratch_bytes; }
+  attention_route(a, queries, key_ranges);
+  return HERO_OK;
+}
+
 int hero_attention_counted(const void* dev_q, const void* dev_k, const void* dev_vt, int64_t ld_vt, void* dev_o,
                            int32_t r, int32_t n_keys, int32_t n_heads, int32_t head_dim, void* dev_scratch,
                            size_t scratch_bytes, uint32_t* dev_fallbacks, void* stream) {

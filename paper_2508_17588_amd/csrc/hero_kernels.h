@@ -117,6 +117,8 @@ struct GemmArgs {
 };
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t st);
+// the tile launch_gemm takes for this problem, and the chunks along k of the last round's tiles (1: not cut)
+void gemm_route(const GemmArgs& g, int* tile_m, int* tile_n, int* k_chunks);
 
 // The rows a GEMM normalises by itself instead of reading them from `a`: LayerNorm of x[row] (+ add[row]) over
 // the k channels, as launch_gather_ln computes it.
@@ -150,3 +152,5 @@ struct AttnArgs {
 };
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st);
+// queries per workgroup of the kernel launch_attention takes, and the key ranges of the last round's blocks (1: not cut)
+void attention_route(const AttnArgs& a, int* queries, int* key_ranges);

@@ -1,0 +1,45 @@
+"""Which kernel a problem goes to (host only)."""
+import pytest
+
+from paper_2508_17588_amd import binding as B
+
+MIB = 1 << 20
+TILES = {(64, 64), (128, 128), (128, 192), (192, 192), (256, 128), (256, 256)}
+
+
+@pytest.mark.parametrize("what", [B.ROUTE_PLAIN, B.ROUTE_GELU, B.ROUTE_QKV, B.ROUTE_OUT, B.ROUTE_FFN2])
+@pytest.mark.parametrize("listed", [False, True])
+def test_linear_routes_over_the_range(what, listed):
+    seen = set()
+    for hidden in (64, 192, 448, 1024, 1920, 3072, 8192):
+        for m in (1, 63, 65, 300, 691, 1755, 2925, 4485, 17776):
+            n = 3 * hidden if what == B.ROUTE_QKV else hidden
+            for scratch in (0, MIB, 128 * MIB):
+                tm, tn, chunks = B.hero_linear_route(m, n, hidden, what, listed, scratch)
+                assert (tm, tn) in TILES and 1 <= chunks <= 8
+                # only 256 x 256 tiles are cut, only with scratch that holds a block of every chunk, never a QKV projection
+                assert chunks == 1 or ((tm, tn) == (256, 256) and scratch >= chunks * 256 * 256 * 4 and what != B.ROUTE_QKV)
+                # a wave's columns of a 256 x 256 tile lie inside one of Q, K and V
+                assert what != B.ROUTE_QKV or hidden % 128 == 0 or (tm, tn) != (256, 256)
+                seen.add((tm, tn))
+    assert len(seen) >= 4
+
+
+def test_attention_routes_over_the_range():
+    for r in (1, 65, 300, 1755, 4485, 17776):
+        for n_keys in (1, 90, 2032, 17776):
+            for heads in (1, 4, 16, 48):
+                assert B.hero_attention_route(r, n_keys, heads, 32, 128 * MIB) == (64, 1)
+                queries, ranges = B.hero_attention_route(r, n_keys, heads, 64, 128 * MIB)
+                assert queries in (64, 256) and 1 <= ranges <= 16 and (queries == 256 or ranges == 1)
+                assert B.hero_attention_route(r, n_keys, heads, 64, 0)[1] == 1
+    assert B.hero_attention_route(4485, 17776, 48, 64, 128 * MIB) == (256, 4)
+
+
+def test_routes_refuse_what_the_calls_refuse():
+    for args in ((0, 64, 64), (1, 64, 65), (1, 65, 64), (1, 64, 64, 5), (1, 128, 64, B.ROUTE_QKV), (699_051, 256, 3072)):
+        with pytest.raises(B.HeroError):
+            B.hero_linear_route(*args)
+    for args in ((1, 1, 1, 48), (1, 0, 1, 64), (1, 699_100, 48, 64)):
+        with pytest.raises(B.HeroError):
+            B.hero_attention_route(*args)
