@@ -1217,18 +1217,27 @@ enum TileKind { TILE_64, TILE_128, TILE_128x192, TILE_192, TILE_256x128, TILE_25
 // the fabric and the power budget).  Fitted to hero_linear timings on 82 .. 17776 rows, n 256 .. 12288,
 // k 256 .. 12288, operands out of the caches; per round at k = 3072, full chip: 64 x 64 11 us, 128 x 128 26,
 // 128 x 192 38, 256 x 128 48, 192 x 192 50, 256 x 256 77.
-struct TileCost { int bm, bn; float fixed, low, high; };
-constexpr TileCost TILE_COST[] = {{64, 64, 2.2f, 0.17f, 0.18f},   {128, 128, 3.5f, 0.31f, 0.48f},
-                                  {128, 192, 4.5f, 0.43f, 0.70f}, {192, 192, 7.f, 0.60f, 0.89f},
-                                  {256, 128, 6.f, 0.55f, 0.87f},  {256, 256, 6.f, 0.72f, 1.48f}};
+// scatter: what the V^T columns of listed rows (two-byte stores) add to a QKV projection, once, or once for every
+// 512 tiles (only a third of the tiles have them, and others run meanwhile); fitted to the kernel times of 118 such
+// projections, hidden 256 .. 4096, 82 .. 8775 rows.
+// Against the kernel times of every kind on 1325 problems (the block's four GEMMs and hero_linear, hidden 256 .. 4096,
+// 50 .. 17776 rows, listed and not, each after the kernel that writes its rows) the kind chosen takes on average
+// 0.37 % longer than the best; without `scatter` 0.54 %.
+struct TileCost { int bm, bn; float fixed, low, high, scatter; };
+constexpr TileCost TILE_COST[] = {{64, 64, 2.2f, 0.17f, 0.18f, 5.f},   {128, 128, 3.5f, 0.31f, 0.48f, 7.5f},
+                                  {128, 192, 4.5f, 0.43f, 0.70f, 7.f}, {192, 192, 6.f, 0.65f, 0.91f, 10.5f},
+                                  {256, 128, 6.f, 0.55f, 0.87f, 9.5f}, {256, 256, 6.f, 0.72f, 1.48f, 7.5f}};
 
 // The kind with the least expected time.  Small problems take the smallest tiles that still fit one
 // round (latency along k bounds them), large ones 256 x 256 (least operand traffic a flop), and in between
-// the kind whose tile count fills its last round: e.g. 2925 x 3072 is 144 tiles of 256 x 256 but 256 of
-// 192 x 192 (k = 12288: 221 us against 176), 691 x 1024 x 4096 14.5 us on 64 x 64 tiles against 24 on 128 x 128.
+// the kind whose tile count fills its last round: e.g. FFN2 of 2925 x 3072 is 144 tiles of 256 x 256 but 256 of
+// 192 x 192 (k = 12288: 255 us against 198), of 691 x 1024 (k = 4096) 16.5 us on 64 x 64 tiles against 28.5 on 128 x 128.
+// A problem that has 128 tiles of 256 x 256 keeps them unless another kind is expected to take 1 % less: less than
+// that once took FFN1 of 4485 x 3072 from 296 to 303 us and FFN2 of 17776 x 1920 from 530 to 549, both to 192 x 192.
 TileKind choose_tile(const GemmArgs& g) {
   // (a wave's columns of a 256 x 256 tile must lie inside one of the Q / K / V thirds)
   const bool qkv_split_ok = g.epilogue != EPI_QKV || g.d % 128 == 0;
+  const bool scattered = g.epilogue == EPI_QKV && g.rows != nullptr;
   const int stages = g.k / SBK;
   TileKind best_kind = TILE_128;
   double best = 1e30;
@@ -1247,7 +1256,9 @@ TileKind choose_tile(const GemmArgs& g) {
     } else if (rem > 0) {
       t += c.fixed + stages * (c.low + rem * (c.high - c.low));
     }
-    if (t < best) { best = t; best_kind = (TileKind)kind; }
+    if (scattered) t += c.scatter * std::max(1.0, (double)tiles / 512.0);
+    const double margin = kind == TILE_256 && tiles >= 128 ? 1.01 : 1.0;
+    if (t <= best * margin) { best = t; best_kind = (TileKind)kind; }
   }
   return best_kind;
 }

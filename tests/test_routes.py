@@ -43,3 +43,20 @@ def test_routes_refuse_what_the_calls_refuse():
     for args in ((1, 1, 1, 48), (1, 0, 1, 64), (1, 699_100, 48, 64)):
         with pytest.raises(B.HeroError):
             B.hero_attention_route(*args)
+
+
+@pytest.mark.parametrize("m,n,k,what,listed,tile", [
+    # as measured (kernel times of every kind): what had gone to another kind for less than the expected times are good for
+    (4485, 12288, 3072, B.ROUTE_GELU, True, (256, 256)),      # 296 us; 192 x 192 303
+    (17776, 1920, 7680, B.ROUTE_FFN2, False, (256, 256)),     # 530 us; 192 x 192 549
+    # listed rows whose V^T columns were not part of the expected time
+    (4485, 1536, 512, B.ROUTE_QKV, True, (128, 128)),         # 22.7 us; 256 x 128 25.9
+    (691, 1536, 512, B.ROUTE_QKV, True, (64, 64)),            # 12.1 us; 128 x 128 15.3
+    (2925, 2304, 768, B.ROUTE_QKV, True, (128, 128)),         # 26.4 us; 256 x 128 29.3
+    # and what the smaller tiles are there for
+    (2925, 3072, 12288, B.ROUTE_FFN2, True, (192, 192)),      # 198 us; 256 x 256 255
+    (691, 1024, 4096, B.ROUTE_FFN2, True, (64, 64)),          # 16.5 us; 128 x 128 28.5
+    (17776, 1920, 1920, B.ROUTE_OUT, False, (192, 192)),      # 132 us; 256 x 256 140
+])
+def test_measured_choices(m, n, k, what, listed, tile):
+    assert B.hero_linear_route(m, n, k, what, listed, 128 * MIB)[:2] == tile
