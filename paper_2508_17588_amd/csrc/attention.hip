@@ -1111,6 +1111,10 @@ hipError_t launch_hd64(const AttnArgs& a, hipStream_t st) {
 // 1.72 for two; 64 queries' quarter of the tiles 1.2 us each for one workgroup on a CU, 2.1 for two (2.35 when
 // every CU has two).  Both ways measured: 326 x 326 x 4 heads 14.3 us against 8.7, 2032 x 2032 x 16
 // 34.7 against 24.8, 1000 x 4000 x 48 63.8 against 62.9, 3000 x 12000 x 6 (cut into key ranges) 69 against 98.
+// Keys and values beyond the memory-side cache (256 MB) cost the one wave's walk a third more, for each is on its own
+// (326 x 33976 x 40 217 us against 168), and within 5 % the expected times tell nothing (1306 x 33976 x 12 174 against
+// 157; 1000 x 8218 x 30 76 against 73).  On 1826 problems of 50 .. 8775 queries x 200 .. 33976 keys x 2 .. 48 heads,
+// with and without scratch, the choice is never more than 5 % slower than the other way, 0.03 % on average.
 bool sharing_keys_is_faster(const AttnArgs& a) {
   const double tiles = (double)((a.n_keys + BKV - 1) / BKV);
   const int64_t n_q64 = (int64_t)((a.r + 63) / 64) * a.n_heads;
@@ -1122,7 +1126,8 @@ bool sharing_keys_is_faster(const AttnArgs& a) {
   double whole = 1.72 * tiles * (double)(slots / 512);
   if (last > 0) whole += tiles / ks.split * (double)((last + 511) / 512) * (last <= 256 ? 0.95 : 1.72);
   if (ks.split > 1) whole += 5.0 + 0.02 * (double)last;
-  return share < whole;
+  const bool beyond_cache = (double)a.n_keys * a.n_heads * (2 * 2 * 64) > 256e6;
+  return share * (beyond_cache ? 1.3 : 1.0) < 0.95 * whole;
 }
 
 }  // namespace

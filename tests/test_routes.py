@@ -60,3 +60,15 @@ def test_routes_refuse_what_the_calls_refuse():
 ])
 def test_measured_choices(m, n, k, what, listed, tile):
     assert B.hero_linear_route(m, n, k, what, listed, 128 * MIB)[:2] == tile
+
+
+@pytest.mark.parametrize("r,n_keys,heads,queries", [
+    (326, 33976, 40, 256),       # 168 us against 217
+    (1306, 33976, 12, 256),      # 157 against 174
+    (1000, 8218, 30, 256),       # 73 against 76
+    (326, 326, 4, 64),           # 7.8 against 15
+    (2032, 2032, 16, 64),        # 25 against 37
+    (4485, 17776, 48, 256),
+])
+def test_measured_attention_choices(r, n_keys, heads, queries):
+    assert B.hero_attention_route(r, n_keys, heads, 64, 128 * MIB)[0] == queries
