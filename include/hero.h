@@ -305,15 +305,15 @@ int hero_attention_scratch(const void* dev_q, const void* dev_k, const void* dev
 
 /* Which kernel a problem goes to (host only, nothing is launched; for tests and tools: the choice is a matter of
  * expected time and may change with the library).
- * hero_linear_route: the tile of the GEMM for `what` of a layer (HERO_ROUTE_*; PLAIN and GELU are hero_linear's act
- * 0 and 1; QKV: n = 3 * hidden), on listed rows or not, with scratch_bytes of scratch; *k_chunks: the number of
- * chunks along k of the tiles of the last round (1: not cut).  Layers of at most 256 channels may normalise their
- * rows inside the QKV and FFN1 kernels instead, on 64 x 64 tiles.
+ * hero_linear_route: the tile of a GEMM (HERO_ROUTE_*: hero_linear with act 0 and 1, then the four of a layer; QKV:
+ * n = 3 * hidden), on listed rows or not, with scratch_bytes of scratch; *k_chunks: the number of chunks along k of
+ * the tiles of the last round (1: not cut); *normalises: 1 where a layer's QKV or FFN1 kernel normalises its rows
+ * itself (models of at most 256 channels).
  * hero_attention_route: queries per workgroup (64: the workgroup's waves share the keys, 256: each wave has
  * queries of its own) and *key_ranges, the number of key ranges of the blocks of the last round. */
-enum { HERO_ROUTE_PLAIN = 0, HERO_ROUTE_GELU = 1, HERO_ROUTE_QKV = 2, HERO_ROUTE_OUT = 3, HERO_ROUTE_FFN2 = 4 };
+enum { HERO_ROUTE_PLAIN = 0, HERO_ROUTE_GELU = 1, HERO_ROUTE_QKV = 2, HERO_ROUTE_OUT = 3, HERO_ROUTE_FFN1 = 4, HERO_ROUTE_FFN2 = 5 };
 int hero_linear_route(int32_t m, int32_t n, int32_t k, int32_t what, int32_t listed, size_t scratch_bytes,
-                      int32_t* tile_m, int32_t* tile_n, int32_t* k_chunks);
+                      int32_t* tile_m, int32_t* tile_n, int32_t* k_chunks, int32_t* normalises);
 int hero_attention_route(int32_t r, int32_t n_keys, int32_t n_heads, int32_t head_dim, size_t scratch_bytes,
                          int32_t* queries, int32_t* key_ranges);
 

@@ -33,7 +33,7 @@ WEIGHT_FIELDS = ("ln1_g", "ln1_b", "w_qkv", "b_qkv", "w_o", "b_o",
                  "ln2_g", "ln2_b", "w_ff1", "b_ff1", "w_ff2", "b_ff2")
 EXTRA_WEIGHT_FIELDS = ("q_norm_g", "q_norm_b", "k_norm_g", "k_norm_b", "mod")
 BLOCK_ADALN, BLOCK_QKNORM, BLOCK_ROPE = 1, 2, 4
-ROUTE_PLAIN, ROUTE_GELU, ROUTE_QKV, ROUTE_OUT, ROUTE_FFN2 = range(5)
+ROUTE_PLAIN, ROUTE_GELU, ROUTE_QKV, ROUTE_OUT, ROUTE_FFN1, ROUTE_FFN2 = range(6)
 CACHE_KV_ALL_LAYERS, CACHE_PREV_ALL_LAYERS = 1, 2
 DEBUG_CHECK_IDX = 1
 
@@ -111,7 +111,7 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
         "hero_axpy_features": [P, I, P, P, c_float, c_int64, P],
         "hero_second_diff_stats": [P, P, P, c_int64, P, ctypes.c_size_t, P, I, P],
         "hero_stability_scores": [POINTER(ctypes.c_double), I, POINTER(ctypes.c_double)],
-        "hero_linear_route": [I, I, I, I, I, ctypes.c_size_t, POINTER(I), POINTER(I), POINTER(I)],
+        "hero_linear_route": [I, I, I, I, I, ctypes.c_size_t, POINTER(I), POINTER(I), POINTER(I), POINTER(I)],
         "hero_attention_route": [I, I, I, I, ctypes.c_size_t, POINTER(I), POINTER(I)],
     }
     for name, argtypes in sig.items():
@@ -379,8 +379,9 @@ def hero_attention(q, k, vt, o, n_keys: int, n_heads: int, head_dim: int, scratc
 
 
 def hero_linear_route(m: int, n: int, k: int, what: int = ROUTE_PLAIN, listed: bool = False, scratch_bytes: int = 0):
-    """(tile rows, tile columns, chunks along k of the last round's tiles) of a GEMM; host only."""
-    out = [c_int32() for _ in range(3)]
+    """(tile rows, tile columns, chunks along k of the last round's tiles, whether it normalises its rows) of a GEMM;
+    host only."""
+    out = [c_int32() for _ in range(4)]
     _check(load_library().hero_linear_route(m, n, k, what, int(listed), scratch_bytes, *(byref(v) for v in out)))
     return tuple(v.value for v in out)
 

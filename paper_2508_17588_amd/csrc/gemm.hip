@@ -1301,14 +1301,16 @@ void gemm_route(const GemmArgs& g, int* tile_m, int* tile_n, int* k_chunks) {
   *k_chunks = kind == TILE_256 ? choose_k_split(g, g.splitk_ws != nullptr ? g.splitk_ws_bytes : 0, &n_rem) : 1;
 }
 
-// Every column tile normalises its rows again, so the line lies where that costs more than a launch and a pass
-// over memory in between.  Intervals of six layers, two kernels against one: 128 channels 558 -> 477 us at 90 rows,
-// 2557 -> 2363 at 17450; 256 channels 599 -> 539 at 90, 911 -> 828 at 2042, 1803 -> 1789 at 8218 (2064 tiles),
-// but 4315 -> 4479 at 17450; 320 channels 635 -> 624 at 90 and 951 -> 1006 at 2042.
+// Every column tile normalises its rows again, so the line lies where the chip's rounds of tiles cost more in that way
+// than a launch and a pass over the rows in between.  Four layers, two kernels against one: 128 channels, FFN 512,
+// 17576 rows 807 -> 771 us (2200 tiles), FFN 2048, 2050 rows 216 -> 197 (1056 tiles), but 8126 rows 376 -> 394 (4064)
+// and FFN 8192, 17576 rows 1576 -> 1889 (35200); 192 channels, FFN 1536, 1306 rows 186 -> 169 (504), 2050 rows 214 -> 215
+// (792); 256 channels, FFN 1024, 1306 rows 182 -> 167 (336), 8126 rows 515 -> 549 (2032); from 320 channels on it loses.
 bool gemm_takes_ln(const GemmArgs& g) {
   if (g.epilogue != EPI_QKV && g.epilogue != EPI_GELU) return false;
   const int64_t tiles = (int64_t)((g.m + 63) / 64) * ((g.n + 63) / 64);
-  return g.k <= 128 || (g.k <= 256 && tiles <= 2048);
+  if (g.k <= 128) return tiles <= 1300 + g.m / (g.k <= 64 ? 6 : 4);
+  return g.k <= 256 && tiles <= (g.k <= 192 ? 600 : 500) + g.m / 30;
 }
 
 hipError_t launch_gemm_ln(const GemmArgs& g, const LnInput& ln, hipStream_t st) {

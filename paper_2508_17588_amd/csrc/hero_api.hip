@@ -920,8 +920,8 @@ int hero_linear_static(const void* dev_a, const void* dev_w, const void* dev_bia
 
 // (the routes only ask whether there is scratch and how much: any address stands for it)
 int hero_linear_route(int32_t m, int32_t n, int32_t k, int32_t what, int32_t listed, size_t scratch_bytes, int32_t* tile_m,
-                      int32_t* tile_n, int32_t* k_chunks) {
-  if (!tile_m || !tile_n || !k_chunks) return fail(HERO_ERR_INVALID_ARG, "output pointer is null");
+                      int32_t* tile_n, int32_t* k_chunks, int32_t* normalises) {
+  if (!tile_m || !tile_n || !k_chunks || !normalises) return fail(HERO_ERR_INVALID_ARG, "output pointer is null");
   if (m <= 0 || n <= 0 || k <= 0) return fail(HERO_ERR_INVALID_ARG, "bad sizes");
   if (what < HERO_ROUTE_PLAIN || what > HERO_ROUTE_FFN2) return fail(HERO_ERR_INVALID_ARG, "unknown GEMM %d", what);
   if (k % 64 != 0 || n % 64 != 0 || (what == HERO_ROUTE_QKV && n % 192 != 0))
@@ -931,11 +931,13 @@ int hero_linear_route(int32_t m, int32_t n, int32_t k, int32_t what, int32_t lis
   GemmArgs g;
   memset(&g, 0, sizeof(g));
   g.m = m; g.n = n; g.k = k; g.d = n / 3;
-  g.epilogue = what == HERO_ROUTE_PLAIN ? EPI_PLAIN : what == HERO_ROUTE_GELU ? EPI_GELU : what == HERO_ROUTE_QKV ? EPI_QKV
-               : what == HERO_ROUTE_OUT ? EPI_SCATTER : EPI_SCATTER_ADD;
+  static const int epilogue[] = {EPI_PLAIN, EPI_GELU, EPI_QKV, EPI_SCATTER, EPI_GELU, EPI_SCATTER_ADD};
+  g.epilogue = epilogue[what];
   if (listed) g.rows = &any_row;
   if (scratch_bytes > 0) { g.splitk_ws = reinterpret_cast<float*>(&g); g.splitk_ws_bytes = scratch_bytes; }
-  gemm_route(g, tile_m, tile_n, k_chunks);
+  *normalises = (what == HERO_ROUTE_QKV || what == HERO_ROUTE_FFN1) && gemm_takes_ln(g) ? 1 : 0;
+  if (*normalises) { *tile_m = *tile_n = 64; *k_chunks = 1; }
+  else gemm_route(g, tile_m, tile_n, k_chunks);
   return HERO_OK;
 }
 

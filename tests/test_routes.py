@@ -7,7 +7,7 @@ MIB = 1 << 20
 TILES = {(64, 64), (128, 128), (128, 192), (192, 192), (256, 128), (256, 256)}
 
 
-@pytest.mark.parametrize("what", [B.ROUTE_PLAIN, B.ROUTE_GELU, B.ROUTE_QKV, B.ROUTE_OUT, B.ROUTE_FFN2])
+@pytest.mark.parametrize("what", [B.ROUTE_PLAIN, B.ROUTE_GELU, B.ROUTE_QKV, B.ROUTE_OUT, B.ROUTE_FFN1, B.ROUTE_FFN2])
 @pytest.mark.parametrize("listed", [False, True])
 def test_linear_routes_over_the_range(what, listed):
     seen = set()
@@ -15,12 +15,13 @@ def test_linear_routes_over_the_range(what, listed):
         for m in (1, 63, 65, 300, 691, 1755, 2925, 4485, 17776):
             n = 3 * hidden if what == B.ROUTE_QKV else hidden
             for scratch in (0, MIB, 128 * MIB):
-                tm, tn, chunks = B.hero_linear_route(m, n, hidden, what, listed, scratch)
+                tm, tn, chunks, normalises = B.hero_linear_route(m, n, hidden, what, listed, scratch)
                 assert (tm, tn) in TILES and 1 <= chunks <= 8
                 # only 256 x 256 tiles are cut, only with scratch that holds a block of every chunk, never a QKV projection
                 assert chunks == 1 or ((tm, tn) == (256, 256) and scratch >= chunks * 256 * 256 * 4 and what != B.ROUTE_QKV)
                 # a wave's columns of a 256 x 256 tile lie inside one of Q, K and V
                 assert what != B.ROUTE_QKV or hidden % 128 == 0 or (tm, tn) != (256, 256)
+                assert not normalises or (hidden <= 256 and what in (B.ROUTE_QKV, B.ROUTE_FFN1) and (tm, tn) == (64, 64))
                 seen.add((tm, tn))
     assert len(seen) >= 4
 
@@ -37,7 +38,7 @@ def test_attention_routes_over_the_range():
 
 
 def test_routes_refuse_what_the_calls_refuse():
-    for args in ((0, 64, 64), (1, 64, 65), (1, 65, 64), (1, 64, 64, 5), (1, 128, 64, B.ROUTE_QKV), (699_051, 256, 3072)):
+    for args in ((0, 64, 64), (1, 64, 65), (1, 65, 64), (1, 64, 64, 6), (1, 128, 64, B.ROUTE_QKV), (699_051, 256, 3072)):
         with pytest.raises(B.HeroError):
             B.hero_linear_route(*args)
     for args in ((1, 1, 1, 48), (1, 0, 1, 64), (1, 699_100, 48, 64)):
@@ -47,7 +48,7 @@ def test_routes_refuse_what_the_calls_refuse():
 
 @pytest.mark.parametrize("m,n,k,what,listed,tile", [
     # as measured (kernel times of every kind): what had gone to another kind for less than the expected times are good for
-    (4485, 12288, 3072, B.ROUTE_GELU, True, (256, 256)),      # 296 us; 192 x 192 303
+    (4485, 12288, 3072, B.ROUTE_FFN1, True, (256, 256)),      # 296 us; 192 x 192 303
     (17776, 1920, 7680, B.ROUTE_FFN2, False, (256, 256)),     # 530 us; 192 x 192 549
     # listed rows whose V^T columns were not part of the expected time
     (4485, 1536, 512, B.ROUTE_QKV, True, (128, 128)),         # 22.7 us; 256 x 128 25.9
@@ -60,6 +61,22 @@ def test_routes_refuse_what_the_calls_refuse():
 ])
 def test_measured_choices(m, n, k, what, listed, tile):
     assert B.hero_linear_route(m, n, k, what, listed, 128 * MIB)[:2] == tile
+
+
+@pytest.mark.parametrize("m,hidden,ffn,qkv,ffn1", [
+    # four layers, us, with FFN1 normalising or not as noted
+    (326, 128, 512, True, True),
+    (17576, 64, 4096, True, False),          # 769; normalising 927
+    (17576, 128, 512, True, True),           # 771; apart 807
+    (17576, 128, 8192, True, False),         # 1546; normalising 1889
+    (8126, 256, 1024, False, False),         # 510; both normalising 549
+    (1306, 256, 4096, True, False),          # 214; normalising 244
+    (1306, 256, 1024, True, True),           # 165; apart 182
+    (90, 320, 1280, False, False),
+])
+def test_measured_choices_of_narrow_models(m, hidden, ffn, qkv, ffn1):
+    assert bool(B.hero_linear_route(m, 3 * hidden, hidden, B.ROUTE_QKV)[3]) == qkv
+    assert bool(B.hero_linear_route(m, ffn, hidden, B.ROUTE_FFN1)[3]) == ffn1
 
 
 @pytest.mark.parametrize("r,n_keys,heads,queries", [
