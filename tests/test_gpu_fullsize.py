@@ -5,8 +5,7 @@ The float64 oracle cannot run a whole 17 776-token block in seconds, so after a 
 computes what is cheap in full (K and V of every row: one GEMM) and the features on sampled
 rows; after a refresh it computes EVERY refreshed row (the rows the method recomputes), and
 sampled non-refreshed and text rows.  Selection indices and ages are compared in full, bit for
-bit.  One test runs hero_step itself, at a size where it takes its deferred-residual path,
-against the oracle's step.
+bit.  One test runs hero_step itself, with its deferred residual adds, against the oracle's step.
 """
 import numpy as np
 import pytest
@@ -44,8 +43,8 @@ def sample_rows(cfg, idx, rng, n_each=20):
 
 def run_block(base_name, sweeps, block_flags=0, every_row=("10", "25", "50", "paper"), via_step=False):
     """One block at full size: fill, select, refresh -- through the per-layer entry points, or with
-    via_step through hero_step itself (steps 0 and 1 of a one-layer model with M = 2; at these sizes
-    the cached step takes hero_step's deferred-residual path: refreshed rows of x updated by the
+    via_step through hero_step itself (steps 0 and 1 of a one-layer model with M = 2; the cached
+    step's residual adds are deferred: refreshed rows of x updated by the
     FFN2 kernel, all other rows by the end-of-step pass).  K and V are compared on every element.  The
     features S and the increment of x are compared on sampled rows after the fill and, after the
     refresh, on EVERY refreshed row for the sweeps named in every_row (else on sampled rows),
@@ -226,8 +225,7 @@ def test_cvx5b_long_video_refresh_and_extrapolation():
 
 @pytest.mark.parametrize("resid_fp32", [True, False])
 def test_hero_step_with_deferred_residual_adds_against_the_oracle_step(resid_fp32):
-    """hero_step on a problem large enough for its deferred-residual path (the FFN2 problem of a
-    cached step has 9 x 16 = 144 tiles of 256 x 256, so the FFN2 kernel updates the refreshed rows
+    """hero_step on a wide problem (the FFN2 kernel of a cached step updates the refreshed rows
     of x and one pass at the end of the step adds the cached features of all other rows and the
     deep stack), against Alg. 1 as the oracle runs it, layer by layer with a residual add per
     layer: four steps (full, cached, full, cached; M = 2), two shallow and two deep layers, hidden
@@ -295,7 +293,7 @@ def test_hero_step_with_deferred_residual_adds_against_the_oracle_step(resid_fp3
 
 @pytest.mark.parametrize("n_layers,n_shallow", [(4, 2), (3, 2), (2, 2)])
 def test_cached_step_with_deferred_residual_adds_matches_the_per_layer_calls(n_layers, n_shallow):
-    """At this size hero_step defers the residual adds of a cached step: refreshed rows are updated
+    """hero_step defers the residual adds of a cached step: refreshed rows are updated
     by the FFN2 kernel layer by layer, all other rows once at the end of the step together with the
     deep stack.  It must agree, up to the order of fp32 additions, with the per-layer entry points
     (each of which is checked against the oracle elsewhere), and leave the same caches."""

@@ -98,8 +98,7 @@ def test_gather_ln(hidden, x_dtype):
 @pytest.mark.parametrize("m,n,k,act", [
     (1, 128, 64, 0), (300, 384, 128, 0), (64, 128, 512, 1), (257, 512, 128, 1),
     (1000, 1920, 256, 0), (3000, 3072, 256, 0), (3001, 3072 + 64, 192, 1), (4485, 5760, 128, 0),
-    # large-tile kernel with 1, 5 and 7 stages of 64 (its stage loop is unrolled six times, the
-    # activation ring is three slots deep)
+    # 1, 5 and 7 stages of 64
     (4096, 2048, 64, 0), (3000, 3072, 320, 1), (3000, 3072, 448, 0),
 ])
 def test_linear(m, n, k, act):
@@ -118,15 +117,15 @@ def test_linear(m, n, k, act):
 
 
 @pytest.mark.parametrize("m,n,k,act,scratch_mib", [
-    (2040, 4096, 4096, 0, 64),       # 128 tiles, all cut in two
-    (2700, 6144, 6144, 1, 64),       # 264 tiles: 256 whole, 8 cut in six
-    (2700, 6144, 6144, 0, 5),        # scratch for two chunks per tile only
-    (2700, 6144, 6144, 0, 1),        # scratch too small to cut anything
-    (2700, 6144, 1024, 0, 64),       # k too short to cut
-    (4000, 3072, 3072, 0, 64),       # 192 tiles: the round is too full to cut
+    (2700, 6144, 6144, 1, 64),       # 264 tiles of 256 x 256: 256 whole, 8 cut in six
+    # scratch that is left alone: tiles of another kind, or a round too full to cut
+    (2040, 4096, 4096, 0, 64), (2700, 6144, 6144, 0, 5), (2700, 6144, 6144, 0, 1), (2700, 6144, 1024, 0, 64),
+    (4000, 3072, 3072, 0, 64),
 ])
-def test_linear_with_k_split(m, n, k, act, scratch_mib):
-    say(f"linear (k-split) m={m} n={n} k={k} act={act} scratch={scratch_mib} MiB")
+def test_linear_with_scratch(m, n, k, act, scratch_mib):
+    say(f"linear m={m} n={n} k={k} act={act} scratch={scratch_mib} MiB")
+    cut = B.hero_linear_route(m, n, k, B.ROUTE_GELU if act else B.ROUTE_PLAIN, False, scratch_mib << 20)[2] > 1
+    assert cut == (act == 1)
     a = rnd(13, m, k)
     w = rnd(14, n, k, scale=1.0 / np.sqrt(k))
     b = rnd(15, n, scale=0.5)
@@ -137,17 +136,17 @@ def test_linear_with_k_split(m, n, k, act, scratch_mib):
     want = O.linear(a.astype(np.float64), w.astype(np.float64), b.astype(np.float64))
     if act:
         want = O.gelu_tanh(want)
-    assert_close(to_host_f64(c[:m]), want, "linear with k-split")
+    assert_close(to_host_f64(c[:m]), want, "linear with scratch")
     assert float((c[m:] - 7.0).abs().max()) == 0.0
 
 
 def _random_linear_shapes():
-    """Seeded shapes around the kernels' tile edges: both kernels, ragged m, every n and k granule."""
+    """Seeded shapes around the kernels' tile edges: ragged m, every n and k granule."""
     g = np.random.default_rng(2024)
     shapes = []
-    for _ in range(10):         # small-tile kernel
+    for _ in range(10):         # few tiles
         shapes.append((int(g.integers(1, 1500)), 64 * int(g.integers(1, 20)), 64 * int(g.integers(1, 12))))
-    for _ in range(8):          # at least 128 tiles of 256 x 256: large-tile kernel, 1 to 3 rounds
+    for _ in range(8):          # at least 128 tiles of 256 x 256, 1 to 3 rounds
         tm, tn = int(g.integers(8, 30)), int(g.integers(8, 24))
         tn = max(tn, -(-128 // tm))
         shapes.append((256 * tm - int(g.integers(0, 255)), 256 * tn - 64 * int(g.integers(0, 4)), 64 * int(g.integers(1, 40))))
@@ -206,25 +205,49 @@ def vt_padded(v, ld):
     (1, 1, 1, 64, "plain"), (5, 11, 2, 64, "plain"), (64, 64, 1, 64, "plain"), (300, 1000, 3, 64, "plain"),
     (257, 129, 2, 32, "plain"), (70, 272, 4, 32, "plain"), (130, 777, 2, 64, "peaky"),
     (130, 777, 2, 64, "outlier"), (513, 2048, 1, 64, "plain"),
-    # scores far outside the fp32 exponent range of a reference-free exp2: the head_dim-64 kernel
-    # must notice and recompute with the running-maximum form (huge: overflow, allneg: every
+    # scores far outside the fp32 exponent range of a reference-free exp2: at head_dim 64 the kernel
+    # must notice and run a second pass (huge: overflow, allneg: every
     # probability underflows, onequery: a single query of the workgroup is affected)
     (130, 777, 2, 64, "huge"), (130, 777, 2, 64, "allneg"), (300, 200, 1, 64, "onequery"),
     (70, 272, 4, 32, "huge"),
 ])
 def test_attention(r, n_keys, heads, hd, case):
+    assert B.hero_attention_route(r, n_keys, heads, hd) == (64, 1)
     run_attention(r, n_keys, heads, hd, case, scratch_mib=0)
 
 
-# query blocks cut along the keys (their partial sums pass through scratch): every block is cut here
-# because the grid is far smaller than the chip; n_keys = 4133 has 64 whole key tiles and a ragged
-# tail, so ranges of 16 tiles; 3000 keys: ranges of 23 / 23 tiles; 1 MiB of scratch: fewer ranges
+# The kernel of the large problems, 256 queries to a workgroup: ragged last query block and key tile, fewer keys than
+# its pipeline is deep, and all its ways out (a block that leaves the range recomputes with the running maximum)
+@pytest.mark.parametrize("r,n_keys,heads,case", [
+    (2000, 130, 32, "plain"), (4000, 97, 16, "plain"), (2000, 520, 32, "plain"), (2000, 130, 32, "peaky"),
+    (2000, 130, 32, "outlier"), (2000, 130, 32, "huge"), (2000, 130, 32, "allneg"), (2000, 130, 32, "onequery"),
+])
+def test_attention_of_256_queries_a_workgroup(r, n_keys, heads, case):
+    assert B.hero_attention_route(r, n_keys, heads, 64) == (256, 1)
+    run_attention(r, n_keys, heads, 64, case, scratch_mib=0)
+
+
+# Its query blocks cut along the keys (their partial sums pass through scratch, and the fix-up kernel has ways out of its
+# own): every block is cut here because the grid is far smaller than the chip.  8200 keys are 128 whole key tiles and a
+# ragged tail; with less scratch there are fewer ranges
+@pytest.mark.parametrize("r,n_keys,heads,case,scratch_mib,ranges", [
+    (600, 8200, 4, "plain", 64, 8), (600, 8200, 4, "peaky", 64, 8), (600, 8200, 4, "huge", 64, 8),
+    (600, 8200, 4, "allneg", 64, 8), (600, 8200, 4, "onequery", 64, 8), (257, 6000, 2, "plain", 64, 5),
+    (600, 8200, 4, "plain", 5, 4), (600, 16400, 4, "plain", 64, 11),
+])
+def test_attention_of_cut_query_blocks(r, n_keys, heads, case, scratch_mib, ranges):
+    assert B.hero_attention_route(r, n_keys, heads, 64, scratch_mib << 20) == (256, ranges)
+    run_attention(r, n_keys, heads, 64, case, scratch_mib)
+
+
+# scratch that the kernel of few query blocks leaves alone
 @pytest.mark.parametrize("r,n_keys,heads,hd,case,scratch_mib", [
     (600, 4133, 4, 64, "plain", 64), (600, 4133, 4, 64, "peaky", 64), (600, 4133, 4, 64, "huge", 64),
     (600, 4133, 4, 64, "allneg", 64), (600, 4133, 4, 64, "onequery", 64), (257, 3000, 2, 64, "plain", 64),
     (600, 4133, 4, 64, "plain", 3), (600, 4133, 4, 64, "plain", 1), (300, 2048, 3, 32, "plain", 64),
 ])
-def test_attention_with_key_split(r, n_keys, heads, hd, case, scratch_mib):
+def test_attention_with_scratch(r, n_keys, heads, hd, case, scratch_mib):
+    assert B.hero_attention_route(r, n_keys, heads, hd, scratch_mib << 20) == (64, 1)
     run_attention(r, n_keys, heads, hd, case, scratch_mib)
 
 

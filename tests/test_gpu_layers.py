@@ -513,10 +513,9 @@ def test_stability_scores_from_a_runs_own_caches():
     cache.close()
 
 
-def test_full_layer_with_out_projection_and_ffn2_cut_along_k():
-    """hidden = ffn = 4096 and exactly 2048 tokens: 128 tiles of 256 x 256 in the out-projection and
-    in FFN2, each cut into two k-chunks (scatter and accumulate epilogues through the fix-up kernel,
-    FFN2 also updating x), checked on every element."""
+def test_full_layer_of_a_wide_block_on_every_element():
+    """hidden = ffn = 4096 and exactly 2048 tokens (256 x 128 tiles in the out-projection and in FFN2), checked on
+    every element against the oracle."""
     cfg = get_config("tiny", n_layers=1, n_shallow=1, hidden=4096, n_heads=64, head_dim=64, ffn_dim=4096,
                      frames=2, height=30, width=34, n_text=8)
     assert cfg.n_tokens == 2048
@@ -537,9 +536,9 @@ def test_full_layer_with_out_projection_and_ffn2_cut_along_k():
         ref[stored] = (k,) + bo.rows(x64, rows, k, v)
     torch.cuda.synchronize()
     (k, ga, gf, s_want), (k16, _, _, s_ideal) = ref[False], ref[True]
-    assert_close(to_host_f64(cache.hero_cache_view(0, B.VIEW_S_CUR)), s_want, "k-split layer: S", stored_parts=[ga], emul=s_ideal)
-    assert_close(to_host_f64(xd) - x64, s_want, "k-split layer: x increment", stored_parts=[ga], emul=s_ideal)
-    assert_close(to_host_f64(cache.hero_cache_view(0, B.VIEW_K)), k, "k-split layer: K", emul=k16)
+    assert_close(to_host_f64(cache.hero_cache_view(0, B.VIEW_S_CUR)), s_want, "wide layer: S", stored_parts=[ga], emul=s_ideal)
+    assert_close(to_host_f64(xd) - x64, s_want, "wide layer: x increment", stored_parts=[ga], emul=s_ideal)
+    assert_close(to_host_f64(cache.hero_cache_view(0, B.VIEW_K)), k, "wide layer: K", emul=k16)
     cache.close()
 
 

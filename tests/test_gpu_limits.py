@@ -38,13 +38,14 @@ def rows_f64(t, rows):
 
 
 @pytest.mark.parametrize("m,n,k,kernel", [
-    # (m + 512) * k * 2 = 4 291 657 728 < 2^32: 2727 row tiles of the 256 x 256 kernel
-    (698_000, 256, 3072, "large-tile"),
-    # 118 tiles of 256 x 256 is below the large-tile threshold: the 128 x 128 kernel, 1099 k steps
-    (30_000, 128, 70_336, "small-tile"),
+    # (m + 512) * k * 2 = 4 291 657 728 < 2^32: 2727 row tiles
+    (698_000, 256, 3072, (256, 256)),
+    # 235 row tiles, 1099 stages
+    (30_000, 128, 70_336, (128, 128)),
 ])
 def test_linear_near_offset_limit(m, n, k, kernel):
-    say(f"linear near the 32-bit offset limit ({kernel}) m={m} n={n} k={k}")
+    say(f"linear near the 32-bit offset limit {kernel} m={m} n={n} k={k}")
+    assert B.hero_linear_route(m, n, k)[:2] == kernel
     assert (m + 512) * k * 2 < 2 ** 32
     a = dev_randn_bf16(40, m, k)
     w = dev_randn_bf16(41, n, k, scale=1.0 / np.sqrt(k))
@@ -73,11 +74,12 @@ def test_linear_beyond_offset_limit_is_an_error():
     assert float((c - 7.0).abs().max()) == 0.0                  # nothing ran
 
 
-@pytest.mark.parametrize("scratch_mib", [0, 64])
-def test_attention_near_offset_limit(scratch_mib):
-    """698 500 keys of 48 heads x 64: K and V^T are 4.29 GB each; with scratch the query blocks are cut
-    into key ranges, whose first keys then sit anywhere in that span."""
-    r, n_keys, heads, hd = 300, 698_500, 48, 64
+@pytest.mark.parametrize("r,scratch_mib,route", [(300, 0, (64, 1)), (300, 64, (256, 5)), (1000, 0, (256, 1))])
+def test_attention_near_offset_limit(r, scratch_mib, route):
+    """698 500 keys of 48 heads x 64: K and V^T are 4.29 GB each, for waves that share the keys and for workgroups of
+    256 queries; with scratch the query blocks are cut into key ranges, whose first keys then sit anywhere in that span."""
+    n_keys, heads, hd = 698_500, 48, 64
+    assert B.hero_attention_route(r, n_keys, heads, hd, scratch_mib << 20) == route
     d = heads * hd
     ld = (n_keys + 63) // 64 * 64
     say(f"attention near the 32-bit offset limit r={r} n_keys={n_keys} heads={heads} scratch={scratch_mib} MiB")

@@ -2,8 +2,8 @@
 width past that: one block in full and refreshed, against the same block in float64 torch."""
 import pytest
 
-import test_gpu_gemm_tiles as tiles
-from workloads import BLOCK_ADALN
+from torch_block import run_block
+from workloads import BLOCK_ADALN, get_config
 
 pytestmark = pytest.mark.gpu
 
@@ -18,4 +18,6 @@ pytestmark = pytest.mark.gpu
     (5, 2, 10, 15, 26),       # 320 channels: LayerNorm by itself
 ])
 def test_block_of_a_narrow_model(heads, frames, height, width, n_text, flags, fp32):
-    tiles.test_block_with_every_tile_kind(heads, frames, height, width, n_text, flags, fp32)
+    d = heads * 64
+    run_block(get_config("tiny", n_layers=1, n_shallow=1, hidden=d, n_heads=heads, head_dim=64, ffn_dim=4 * d, frames=frames,
+                         height=height, width=width, n_text=n_text, block_flags=flags, resid_fp32=fp32))

@@ -9,7 +9,7 @@ from oracle import hero_oracle as O
 from paper_2508_17588_amd import binding as B
 from workloads import BLOCK_QKNORM, BLOCK_ROPE, get_config
 from hero_testlib import to_host_f64
-from test_gpu_gemm_tiles import weights
+from torch_block import weights
 
 pytestmark = pytest.mark.gpu
 
@@ -24,13 +24,13 @@ def test_keys_are_the_plain_keys_post_processed(heads, head_dim, flags):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(5)
     plain, post = get_config("tiny", block_flags=0, **base), get_config("tiny", block_flags=flags, **base)
-    w = weights(plain, gen)
+    w = weights(plain, gen, most=1600)
     if flags & BLOCK_QKNORM:
         for n in ("q_norm", "k_norm"):
             w[n + "_g"] = (torch.randn(head_dim, generator=gen, device="cuda") * 0.1 + 1).to(torch.bfloat16)
             w[n + "_b"] = (torch.randn(head_dim, generator=gen, device="cuda") * 0.1).to(torch.bfloat16)
     caches = [B.HeroCache(B.make_config(c)) for c in (plain, post)]
-    names = set(weights(plain, gen))
+    names = set(weights(plain, gen, most=1600))
     caches[0].hero_set_layer_weights(0, {n: t for n, t in w.items() if n in names})
     caches[1].hero_set_layer_weights(0, w)
     n, idx = plain.n_tokens, torch.zeros(plain.n_tokens, dtype=torch.int32, device="cuda")

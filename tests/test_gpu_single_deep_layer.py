@@ -5,7 +5,7 @@ import torch
 
 from paper_2508_17588_amd import binding as B
 from workloads import get_config
-from test_gpu_gemm_tiles import weights
+from torch_block import weights
 
 pytestmark = pytest.mark.gpu
 

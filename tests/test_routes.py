@@ -2,6 +2,7 @@
 import pytest
 
 from paper_2508_17588_amd import binding as B
+from torch_block import BLOCKS, block_config
 
 MIB = 1 << 20
 TILES = {(64, 64), (128, 128), (128, 192), (192, 192), (256, 128), (256, 256)}
@@ -89,3 +90,23 @@ def test_measured_choices_of_narrow_models(m, hidden, ffn, qkv, ffn1):
 ])
 def test_measured_attention_choices(r, n_keys, heads, queries):
     assert B.hero_attention_route(r, n_keys, heads, 64, 128 * MIB)[0] == queries
+
+
+def test_the_blocks_that_the_gemm_tests_run_take_every_kernel():
+    seen = set()
+    for shape in BLOCKS:
+        cfg = block_config(*shape)
+        d, f = cfg.hidden, cfg.ffn_dim
+        scratch = 128 * MIB if cfg.n_tokens >= 2048 else 0            # what a handle has
+        for listed, m in ((False, cfg.n_tokens), (True, B.hero_num_selected(B.make_config(cfg)))):
+            for what, n, k in ((B.ROUTE_QKV, 3 * d, d), (B.ROUTE_OUT, d, d), (B.ROUTE_FFN1, f, d), (B.ROUTE_FFN2, d, f)):
+                tm, tn, chunks, normalises = B.hero_linear_route(m, n, k, what, listed, scratch)
+                seen.add((what, listed, "normalises" if normalises else (tm, tn)))
+                if chunks > 1:
+                    seen.add((what, listed, "cut"))
+    for listed in (False, True):
+        for what in (B.ROUTE_QKV, B.ROUTE_OUT, B.ROUTE_FFN1, B.ROUTE_FFN2):
+            for tile in TILES:
+                assert (what, listed, tile) in seen, (what, listed, tile)
+            assert (what, listed, "normalises") in seen or what in (B.ROUTE_OUT, B.ROUTE_FFN2)
+            assert (what, listed, "cut") in seen or what == B.ROUTE_QKV

@@ -48,9 +48,10 @@ def run_pair(m, n, k, act, seed):
 
 def test_static_scratch_gemm_matches_the_caller_scratch_gemm_on_two_calls_in_a_row():
     # 296 tiles of 256 x 256: one round of 256 plus 40 tiles cut into 3 k-chunks (30 MiB of partial sums),
-    # then 272 tiles: 16 cut in 2 (8 MiB), then a problem too small to be cut at all
-    for (m, n, k, act, seed) in ((9472, 2048, 3072, 1, 100), (4300, 4096, 2048, 0, 200), (300, 256, 128, 1, 300)):
+    # then 286 tiles: 30 (in 32 slots) cut in 2 (16 MiB), then a problem too small to be cut at all
+    for (m, n, k, act, seed, chunks) in ((9472, 2048, 3072, 1, 100, 3), (2726, 6592, 2048, 0, 200, 2), (300, 256, 128, 1, 300, 1)):
         say(f"hero_linear_static m={m} n={n} k={k} act={act}")
+        assert B.hero_linear_route(m, n, k, B.ROUTE_GELU if act else B.ROUTE_PLAIN, False, STATIC_BYTES)[2] == chunks
         c_static, c_scratch, want, probe = run_pair(m, n, k, act, seed)
         assert torch.equal(c_static, c_scratch), "static and caller scratch differ"      # same cut, same order of additions
         assert float((c_static[m:] - 7.0).abs().max()) == 0.0                         # rows past M untouched
