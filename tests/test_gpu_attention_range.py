@@ -67,8 +67,11 @@ def test_attention_of_unusual_scores(scores, v_exp, hd, r, n_keys, heads):
 
 
 @pytest.mark.parametrize("q_size", [0.5, 40.0, 600.0])
-@pytest.mark.parametrize("hd,heads,height,width", [(32, 4, 5, 7), (32, 2, 17, 19), (64, 2, 5, 7), (64, 1, 17, 19)])
-def test_layer_attention_of_unusual_scores(hd, heads, height, width, q_size):
+@pytest.mark.parametrize("hd,heads,height,width,route", [
+    (32, 4, 5, 7, (64, 1)), (32, 2, 17, 19, (64, 1)), (64, 2, 5, 7, (64, 1)), (64, 1, 17, 19, (64, 1)),
+    (64, 40, 26, 50, (256, 1)), (64, 48, 50, 52, (256, 2)),
+])
+def test_layer_attention_of_unusual_scores(hd, heads, height, width, route, q_size):
     """A layer whose queries are the bias of their projection (so the softmax scale is folded into known values),
     whose out-projection is the identity and whose FFN is zero: its feature is the attention output, compared
     with float64 on the K and V it cached."""
@@ -76,6 +79,7 @@ def test_layer_attention_of_unusual_scores(hd, heads, height, width, q_size):
     cfg = get_config("tiny", n_layers=1, n_shallow=1, hidden=d, n_heads=heads, head_dim=hd, ffn_dim=2 * d, frames=1,
                      height=height, width=width, n_text=3)
     print(f"[case] {cfg.n_tokens} rows, {heads} heads of {hd}, queries of size {q_size}", flush=True)
+    assert B.hero_attention_route(cfg.n_tokens, cfg.n_tokens, heads, hd, 128 << 20 if cfg.n_tokens >= 2048 else 0) == route
     bias = rnd(4, d) * np.float32(q_size / np.sqrt(hd))
     w = {"ln1_g": np.ones(d), "ln2_g": np.ones(d), "w_o": np.eye(d), "w_ff1": np.zeros((2 * d, d)), "b_ff1": np.zeros(2 * d),
          "w_ff2": np.zeros((d, 2 * d)), **{n: np.zeros(d) for n in ("ln1_b", "ln2_b", "b_o", "b_ff2")},
@@ -92,7 +96,7 @@ def test_layer_attention_of_unusual_scores(hd, heads, height, width, q_size):
     scale = np.float32(1.4426950408889634) / np.sqrt(np.float32(hd))
     q = round_to_bf16(w["b_qkv"][:d] * scale).astype(np.float64)
     got = to_host_f64(cache.hero_cache_view(0, B.VIEW_S_CUR))
-    check(got, np.broadcast_to(q, got.shape), k, v, 1.0, hd, f"queries of size {q_size}")
+    check(got, q[None], k, v, 1.0, hd, f"queries of size {q_size}")         # (every row has the same query)
     cache.close()
 
 
