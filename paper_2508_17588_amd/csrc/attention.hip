@@ -273,24 +273,6 @@ constexpr int TILE = 512;   // 16-byte chunks per 64-key K or V^T tile at head_d
 template <int I> using IC = std::integral_constant<int, I>;
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
-// buffer resource words: base address, no stride, byte count, raw 32-bit data format
-__device__ __forceinline__ u32x4_t make_rsrc_words(const void* p, uint32_t bytes) {
-  const uint64_t addr = (uint64_t)p;
-  u32x4_t r = {(uint32_t)addr, (uint32_t)(addr >> 32) & 0xffffu, bytes, 0x00020000u};
-  r[0] = __builtin_amdgcn_readfirstlane(r[0]); r[1] = __builtin_amdgcn_readfirstlane(r[1]);
-  r[2] = __builtin_amdgcn_readfirstlane(r[2]); r[3] = __builtin_amdgcn_readfirstlane(r[3]);
-  return r;
-}
-
-// 16 bytes per lane from a buffer straight into LDS at lds_base + 16*lane; bytes past the end
-// of the buffer arrive as zero.  The compiler's own builtin for this instruction makes every
-// later LDS read wait for the load, so it is issued by hand and waited for explicitly with
-// vmcnt(0) before the barrier that publishes the tile.  Nothing else in this kernel uses m0.
-__device__ __forceinline__ void direct_lds_load(u32x4_t rsrc, uint32_t lds_base, uint32_t voffset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(lds_base), "v"(voffset), "s"(rsrc) : "memory");
-}
-
 // Split of the last, partly filled round of workgroups along the keys.  Block slots
 // 0 .. full_items-1 are whole work items; every later slot is cut into `split` key ranges whose
 // unnormalised outputs and row sums (the reference-free form needs no common maximum, so they
@@ -369,8 +351,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_hd64_kernel(AttnArgs a, 
   //      chunk slot l%8, which holds the row's logical chunk (l%8) ^ ((row>>1)&7) ----
   const uint32_t k_bytes = (uint32_t)((int64_t)n_keys * d * 2 - head * HD * 2);
   const uint32_t v_bytes = (uint32_t)(((int64_t)d - head * HD) * a.ld_vt * 2 - (int64_t)t_begin * BKV * 2);
-  const u32x4_t rsK = make_rsrc_words(kbase + head * HD, k_bytes);
-  const u32x4_t rsV = make_rsrc_words(vtbase + (int64_t)head * HD * a.ld_vt, v_bytes);
+  const u32x4_t rsK = rsrc_words(kbase + head * HD, k_bytes);
+  const u32x4_t rsV = rsrc_words(vtbase + (int64_t)head * HD * a.ld_vt, v_bytes);
   // LDS byte address of this wave's first 1 KB slot in buffer 0 (wave-uniform)
   const uint32_t lds_k0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr_t)&sK[0][64 * wave]);
   const uint32_t lds_v0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr_t)&sV[0][64 * wave]);
@@ -386,12 +368,12 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_hd64_kernel(AttnArgs a, 
   auto gload_k = [&](int tile, int buf) {
 #pragma unroll
     for (int i = 0; i < NL; ++i)
-      direct_lds_load(rsK, lds_k0 + (uint32_t)(buf * TILE + 64 * NW * i) * 16, k_voff[i] + (uint32_t)tile * k_tile_bytes);
+      lds_fill(rsK, lds_k0 + (uint32_t)(buf * TILE + 64 * NW * i) * 16, k_voff[i] + (uint32_t)tile * k_tile_bytes);
   };
   auto gload_v = [&](int tile, int buf) {
 #pragma unroll
     for (int i = 0; i < NL; ++i)
-      direct_lds_load(rsV, lds_v0 + (uint32_t)(buf * TILE + 64 * NW * i) * 16, v_voff[i] + (uint32_t)tile * v_tile_bytes);
+      lds_fill(rsV, lds_v0 + (uint32_t)(buf * TILE + 64 * NW * i) * 16, v_voff[i] + (uint32_t)tile * v_tile_bytes);
   };
 
   // ---- fragment read offsets (chunks) ----
@@ -756,8 +738,8 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lh = lane >> 5;
   // fills: lane l of K fill i takes row KROWS*i + l/KCH, chunk slot l%KCH; of V^T fill i row 8i + l/8, slot l%8
-  const u32x4_t rsK = make_rsrc_words(a.k + head * HD, (uint32_t)((int64_t)a.n_keys * d * 2 - head * HD * 2));
-  const u32x4_t rsV = make_rsrc_words(a.vt + (int64_t)head * HD * a.ld_vt, (uint32_t)(((int64_t)d - head * HD) * a.ld_vt * 2));
+  const u32x4_t rsK = rsrc_words(a.k + head * HD, (uint32_t)((int64_t)a.n_keys * d * 2 - head * HD * 2));
+  const u32x4_t rsV = rsrc_words(a.vt + (int64_t)head * HD * a.ld_vt, (uint32_t)(((int64_t)d - head * HD) * a.ld_vt * 2));
   const uint32_t k_row_bytes = (uint32_t)d * 2, v_row_bytes = (uint32_t)a.ld_vt * 2;
   uint32_t k_voff[KPER], v_voff[2];
 #pragma unroll
@@ -775,12 +757,12 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   auto fill_k = [&](int tile) {
 #pragma unroll
     for (int i = 0; i < NF; ++i)
-      direct_lds_load(rsK, lds_k + i * 1024, k_voff[i % KPER] + ((uint32_t)tile * BKV + i / KPER * 16) * k_row_bytes);
+      lds_fill(rsK, lds_k + i * 1024, k_voff[i % KPER] + ((uint32_t)tile * BKV + i / KPER * 16) * k_row_bytes);
   };
   auto fill_v = [&](int tile) {
 #pragma unroll
     for (int i = 0; i < NF; ++i)
-      direct_lds_load(rsV, lds_v + i * 1024, v_voff[i % 2] + (uint32_t)(i / 2 * 16) * v_row_bytes + (uint32_t)tile * (BKV * 2));
+      lds_fill(rsV, lds_v + i * 1024, v_voff[i % 2] + (uint32_t)(i / 2 * 16) * v_row_bytes + (uint32_t)tile * (BKV * 2));
   };
 
   const int n_tiles = (a.n_keys + BKV - 1) / BKV;

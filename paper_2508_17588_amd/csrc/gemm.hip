@@ -82,32 +82,6 @@ constexpr int RING_BYTES = (RING_A + RING_B) * STAGE_BYTES;   // 160 KB
 constexpr int GEMM256_LDS = 8 * STAGE_REGION > RING_BYTES ? 8 * STAGE_REGION : RING_BYTES;
 static_assert(64 * CST32 <= STAGE_REGION && 64 * CSTT <= STAGE_REGION, "half-tile / transposed tile must fit the staging region");
 
-// buffer resource words: base address, no stride, byte count, raw 32-bit data format
-__device__ __forceinline__ u32x4_t rsrc_words(const void* p, uint32_t bytes) {
-  const uint64_t addr = (uint64_t)p;
-  u32x4_t r = {(uint32_t)addr, (uint32_t)(addr >> 32) & 0xffffu, bytes, 0x00020000u};
-  r[0] = __builtin_amdgcn_readfirstlane(r[0]); r[1] = __builtin_amdgcn_readfirstlane(r[1]);
-  r[2] = __builtin_amdgcn_readfirstlane(r[2]); r[3] = __builtin_amdgcn_readfirstlane(r[3]);
-  return r;
-}
-
-// 16 bytes per lane from a buffer straight into LDS at lds_addr + 16*lane.  The bounds check
-// covers voffset only (rows past the end arrive as zero); soffset carries the k advance.  Issued
-// by hand so that the compiler does not make later LDS reads wait for it: completion is awaited
-// explicitly with vmcnt before the stage's barrier.  Nothing else in the kernel uses m0.
-__device__ __forceinline__ void lds_fill(u32x4_t rsrc, uint32_t lds_addr, uint32_t voffset, uint32_t soffset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset) : "memory");
-}
-
-// keeps a wave-uniform value in a scalar register and stops the compiler from hoisting the
-// comparisons made with it out of the loop (hoisted, they come back as lane masks that need
-// VALU instructions at every use)
-__device__ __forceinline__ int opaque(int v) {
-  asm volatile("" : "+s"(v));
-  return v;
-}
-
 // Split of the last, partly filled wave of tiles along k.  Tile slots 0 .. full_items-1 are
 // whole work items; every later slot is cut into `split` k-chunks whose fp32 partial sums go to a
 // workspace (one 256 KB block per chunk, in accumulator order: [i][j][quad][thread] float4) and
@@ -118,18 +92,18 @@ struct SplitK {
   float* ws;
 };
 
-// tile slot -> tile origin (each XCD owns a contiguous range of tiles, walked in groups of
+// tile slot -> origin of its bm x bn tile (each XCD owns a contiguous range of tiles, walked in groups of
 // group_m row tiles); false for the empty slots that pad the range to a multiple of 8
-__device__ __forceinline__ bool tile_origin(int slot, int tiles_m, int tiles_n, int per_xcd, int group_m,
-                                            int& m0, int& n0) {
+__device__ __forceinline__ bool tile_origin(int slot, int bm, int bn, int tiles_m, int tiles_n, int per_xcd,
+                                            int group_m, int& m0, int& n0) {
   const int p = (slot % 8) * per_xcd + slot / 8;
   if (p >= tiles_m * tiles_n) return false;
   const int group = p / (group_m * tiles_n);
   const int first_m = group * group_m;
   const int gsize = min(tiles_m - first_m, group_m);
   const int in_group = p - group * group_m * tiles_n;
-  m0 = (first_m + in_group % gsize) * 256;
-  n0 = (in_group / gsize) * 256;
+  m0 = (first_m + in_group % gsize) * bm;
+  n0 = (in_group / gsize) * bn;
   return true;
 }
 
@@ -149,7 +123,7 @@ __global__ __launch_bounds__(512) void gemm256_kernel(GemmArgs g, int tiles_m, i
     n_chunks = sk.split;
   }
   int m0, n0;
-  if (!tile_origin(slot, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+  if (!tile_origin(slot, 256, 256, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
 
   extern __shared__ u32x4_t smem[];
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)smem;
@@ -313,7 +287,7 @@ __global__ __launch_bounds__(64) void gemm256_fixup_kernel(GemmArgs g, int tiles
                                                            int group_m, SplitK sk) {
   const int tile = blockIdx.x >> 3, wave = blockIdx.x & 7;
   int m0, n0;
-  if (!tile_origin(sk.full_items + tile, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+  if (!tile_origin(sk.full_items + tile, 256, 256, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
   extern __shared__ u32x4_t smem[];
   const int lane = threadIdx.x;
   floatx16_t acc[4][2];
@@ -670,20 +644,6 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& g, const float* tile
   }
 }
 
-// tile slot -> tile origin, for tiles of bm x bn (see tile_origin)
-__device__ __forceinline__ bool tile_origin_of(int slot, int bm, int bn, int tiles_m, int tiles_n, int per_xcd,
-                                               int group_m, int& m0, int& n0) {
-  const int p = (slot % 8) * per_xcd + slot / 8;
-  if (p >= tiles_m * tiles_n) return false;
-  const int group = p / (group_m * tiles_n);
-  const int first_m = group * group_m;
-  const int gsize = min(tiles_m - first_m, group_m);
-  const int in_group = p - group * group_m * tiles_n;
-  m0 = (first_m + in_group % gsize) * bm;
-  n0 = (in_group / gsize) * bn;
-  return true;
-}
-
 // BM x BN tile, eight waves: 2 x 2 sub-tiles, each computed by two waves that take one half of every
 // 64-wide k stage.  The sub-tile is then large (few LDS reads a flop) with two waves on every SIMD.
 // Stages go global -> LDS into a ring of RING slots, filled RING - 1 stages ahead, one barrier a stage;
@@ -708,7 +668,7 @@ __global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m
   constexpr int RING = C::RING, STAGE = C::STAGE;
   static_assert(BM % 64 == 0 && BN % 64 == 0 && RING >= 3 && NF <= MB * NB + 2, "tile shape");
   int m0, n0;
-  if (!tile_origin_of(blockIdx.x, BM, BN, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+  if (!tile_origin(blockIdx.x, BM, BN, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
 
   extern __shared__ u32x4_t smem[];
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)smem;
@@ -845,7 +805,7 @@ static_assert(4 * 64 * 68 * 4 <= QK_LDS, "the four partial tiles must fit");
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tiles_m, int tiles_n, int per_xcd, int group_m) {
   int m0, n0;
-  if (!tile_origin_of(blockIdx.x, 64, 64, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+  if (!tile_origin(blockIdx.x, 64, 64, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
   extern __shared__ u32x4_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -940,7 +900,7 @@ __global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tile
 template <int EPI, typename XT, int LPR, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void gemm_ln_kernel(GemmArgs g, LnInput ln, int tiles_m, int tiles_n, int per_xcd, int group_m) {
   int m0, n0;
-  if (!tile_origin_of(blockIdx.x, 64, 64, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+  if (!tile_origin(blockIdx.x, 64, 64, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
   extern __shared__ u32x4_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

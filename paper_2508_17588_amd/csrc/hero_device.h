@@ -78,3 +78,25 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
+
+// buffer resource words: base address, no stride, byte count, raw 32-bit data format
+__device__ __forceinline__ u32x4_t rsrc_words(const void* p, uint32_t bytes) {
+  const uint64_t addr = (uint64_t)p;
+  u32x4_t r = {(uint32_t)addr, (uint32_t)(addr >> 32) & 0xffffu, bytes, 0x00020000u};
+  r[0] = __builtin_amdgcn_readfirstlane(r[0]); r[1] = __builtin_amdgcn_readfirstlane(r[1]);
+  r[2] = __builtin_amdgcn_readfirstlane(r[2]); r[3] = __builtin_amdgcn_readfirstlane(r[3]);
+  return r;
+}
+
+// 16 bytes per lane from a buffer straight into LDS at lds_addr + 16*lane; bytes past the end of the buffer arrive
+// as zero.  The bounds check covers voffset only; soffset carries an advance that stays inside a row.  Issued by hand,
+// because the compiler's own builtin makes every later LDS read wait for it: completion is awaited explicitly with
+// vmcnt.  Nothing else in the kernels that use it uses m0.
+__device__ __forceinline__ void lds_fill(u32x4_t rsrc, uint32_t lds_addr, uint32_t voffset, uint32_t soffset) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset) : "memory");
+}
+__device__ __forceinline__ void lds_fill(u32x4_t rsrc, uint32_t lds_addr, uint32_t voffset) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               :: "s"(lds_addr), "v"(voffset), "s"(rsrc) : "memory");
+}
