@@ -181,16 +181,17 @@ int hero_extrapolate_layer(hero_cache_t c, int32_t layer, void* dev_x, int32_t k
  * hero_full_layer, then ages = 0), otherwise select once and run
  * refresh (l < K) / extrapolate (l >= K) with k = step - last full step.
  * On a cached step the deep layers only add their extrapolated features to x
- * (Eq. 5, Alg. 1), so with two or more deep layers hero_step applies them in one
- * pass: it keeps T = sum over deep layers of S (fp32, one array per full-step
+ * (Eq. 5, Alg. 1), so hero_step applies them in one pass: with two or more deep
+ * layers it keeps T = sum over deep layers of S (fp32, one array per full-step
  * generation, summed once after each full step) and adds
  * (1 + k/M) T_t - (k/M) T_{t+M}.  The result equals calling
  * hero_extrapolate_layer for every deep layer up to fp32 summation order.
  * Likewise, between the shallow layers of a cached step only the refreshed rows
- * of x are read, so at large shapes hero_step updates those rows layer by layer
- * and adds the shallow layers' cached features to all other rows once, in the
- * same final pass; x equals the result of the per-layer calls up to fp32
- * summation order and the caches are identical.
+ * of x are read, so with 1 to 48 shallow layers hero_step updates those rows layer
+ * by layer and adds the shallow layers' cached features to all other rows once, in
+ * the same final pass; x equals the result of the per-layer calls up to fp32
+ * summation order (a bf16 stream is rounded once there instead of once per layer)
+ * and the caches are identical.
  * The call enqueues kernels only (no memsets, copies or synchronisation), so once every kernel has
  * run eagerly it may be recorded under stream capture; the step number and k are launch scalars and
  * the schedule state advances at record time, so a graph holds one position of the schedule. */
@@ -216,10 +217,13 @@ int hero_cache_state(hero_cache_t c, int32_t* n_full, int32_t* last_full_step);
  * Slot = kind for launches made by hero_full_layer, kind + HERO_PROF_KINDS otherwise.
  * HERO_PROF_EXTRAP covers both the per-layer update and hero_step's one-pass update of the
  * whole deep stack; HERO_PROF_DEEPSUM is the once-per-generation summation behind the latter.
- * A full layer of a large problem adds its features to x inside the FFN2 kernel: it then has
- * no HERO_PROF_RESID launch and the time is part of HERO_PROF_GEMM_FF2.  A cached hero_step of a
- * large problem does the same for the refreshed rows and adds the features of all other rows,
- * of all shallow layers, in its one pass at the end of the step (HERO_PROF_EXTRAP).
+ * A full layer adds its features to x inside the FFN2 kernel: it has no HERO_PROF_RESID launch
+ * and the time is part of HERO_PROF_GEMM_FF2.  A cached hero_step (1 to 48 shallow layers) does
+ * the same for the refreshed rows and adds the features of all other rows, of all shallow
+ * layers, in its one pass at the end of the step (HERO_PROF_EXTRAP).
+ * Where a model of at most 256 channels normalises its rows inside the QKV or FFN1 kernel (see
+ * hero_linear_route), there is no HERO_PROF_LN launch for them and the time is part of
+ * HERO_PROF_GEMM_QKV or HERO_PROF_GEMM_FF1.
  * The three output arrays have 2 * HERO_PROF_KINDS entries (any may be NULL). */
 enum {
   HERO_PROF_SELECT = 0, HERO_PROF_LN = 1, HERO_PROF_GEMM_QKV = 2, HERO_PROF_ATTN = 3,

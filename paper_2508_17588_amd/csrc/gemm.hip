@@ -648,10 +648,10 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& g, const float* tile
 // 64-wide k stage.  The sub-tile is then large (few LDS reads a flop) with two waves on every SIMD.
 // Stages go global -> LDS into a ring of RING slots, filled RING - 1 stages ahead, one barrier a stage;
 // a slot holds the BM rows of A, then the BN rows of W, in the layout of the 256 x 256 kernel.
-// What bounds it: the fills (48 KB a stage at 192 x 192, two stages on their way; 1.25 PFLOP/s with all
-// CUs at work at k = 12288) and, at k = 3072, start-up and epilogue, about 7 of 50 us.  Measured: FFN2 of
-// 4485 rows at hidden 1920 190 -> 135 us (192 x 192), of 1755 rows at hidden 3072 212 -> 158 us (128 x 192),
-// of 2925 rows 197 + 58 (fix-up) -> 176 us.
+// What bounds it: the fills (48 KB a stage at 192 x 192, two stages on their way; 1.13 PFLOP/s with all
+// CUs at work at k = 12288) and, at k = 3072, start-up and epilogue, about 7 of 50 us.  Kernel times of FFN2 after
+// the kernel that writes its rows, against 256 x 256 or the earlier 128 x 128 tiles: 4485 rows at hidden 1920
+// 174 -> 124 us (192 x 192), 1755 rows at hidden 3072 202 -> 153 (128 x 192), 2925 rows 241, fix-up included, -> 194.
 template <int BM, int BN>
 struct HalfK {
   static constexpr int STAGE = (BM + BN) * 128;                          // bytes
@@ -795,8 +795,8 @@ __global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m
 // ring of its own: no barrier until the four partial sums meet in LDS, and at k <= 512 every byte
 // a wave needs is requested before it waits for the first.  For problems that leave most CUs without
 // a larger tile; what bounds them is the chain of load latencies along k, here a quarter as long.
-// Measured against 128 x 128 tiles with register staging: 326 x 256 x 1024 26.2 -> 8.0 us, 326 x 768 x 256
-// 13.7 -> 5.4, 691 x 1024 x 4096 50.3 -> 17.3 (accumulating epilogue).
+// Kernel times against 128 x 128 tiles with register staging: FFN2 of 326 rows at hidden 256 30.4 -> 7.4 us, of 691
+// rows at hidden 1024 50.3 -> 16.2; QKV of 326 listed rows at hidden 256 14.8 -> 6.9.
 constexpr int QK_STAGE = 128 * 128;                      // 64 rows of A, 64 rows of W
 constexpr int QK_RING = 2;
 constexpr int QK_LDS = 4 * QK_RING * QK_STAGE;
@@ -896,7 +896,7 @@ __global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tile
 // lanes a row, eight elements a lane) and round them to bf16 as the stand-alone LayerNorm does.
 // What bounds it: the latency of the row loads and of the two reductions (a wave's rows are reduced side by
 // side, step by step), then of the short walk along k.  326 rows, 256 channels: 3.4 (LayerNorm) + 5.8 us (QKV) in two
-// launches; the interval of the 42-layer model of that size 2430 -> 2215 us, of the 128-channel model 203 -> 171.
+// launches, 6.9 in one; the interval of the 42-layer model of that size 2430 -> 2215 us, of the 128-channel model 203 -> 171.
 template <int EPI, typename XT, int LPR, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void gemm_ln_kernel(GemmArgs g, LnInput ln, int tiles_m, int tiles_n, int per_xcd, int group_m) {
   int m0, n0;
@@ -1191,7 +1191,7 @@ constexpr TileCost TILE_COST[] = {{64, 64, 2.2f, 0.17f, 0.18f, 5.f},   {128, 128
 // The kind with the least expected time.  Small problems take the smallest tiles that still fit one
 // round (latency along k bounds them), large ones 256 x 256 (least operand traffic a flop), and in between
 // the kind whose tile count fills its last round: e.g. FFN2 of 2925 x 3072 is 144 tiles of 256 x 256 but 256 of
-// 192 x 192 (k = 12288: 255 us against 198), of 691 x 1024 (k = 4096) 16.5 us on 64 x 64 tiles against 28.5 on 128 x 128.
+// 192 x 192 (241 us against 194), of 691 x 1024 (k = 4096) 16.2 us on 64 x 64 tiles against 28.3 on 128 x 128.
 // A problem that has 128 tiles of 256 x 256 keeps them unless another kind is expected to take 1 % less: less than
 // that once took FFN1 of 4485 x 3072 from 296 to 303 us and FFN2 of 17776 x 1920 from 530 to 549, both to 192 x 192.
 TileKind choose_tile(const GemmArgs& g) {
