@@ -254,8 +254,9 @@ int hero_linear(const void* dev_a, const void* dev_w, const void* dev_bias, void
                 int32_t m, int32_t n, int32_t k, int32_t act, void* stream);
 
 /* The same product, computed the way the layer entry points compute theirs: with device scratch
- * (caller-owned, 16-byte aligned, any size; 64 MiB lets every problem use it) the tiles of the
- * last, partly filled round of workgroups are cut along K, their fp32 partial sums pass through
+ * (caller-owned, 16-byte aligned, any size; 64 MiB lets every problem use it) a problem that goes
+ * to the largest tiles (hero_linear_route) may have those of the last, partly filled round of
+ * workgroups cut along K; their fp32 partial sums pass through
  * the scratch and a second kernel adds them up and applies bias and activation.  The result
  * differs from hero_linear's only by the order of the fp32 additions.  Calls that share a
  * scratch buffer must not overlap. */
@@ -266,8 +267,9 @@ int hero_linear_scratch(const void* dev_a, const void* dev_w, const void* dev_bi
 /* The same, and *dev_fallbacks (device uint32, optional) += the number of workgroups (256 queries of
  * one head) that took the slower way out.  head_dim 64 evaluates softmax as 2^(q.k log2(e)/sqrt(head_dim))
  * without a running maximum, which is exact while every row sum stays within [2^-80, 2^80]; a workgroup
- * in which some row sum leaves that range recomputes its 256 queries with the running-maximum form
- * (the result is the plain definition's either way; the cost of such a block roughly triples).
+ * in which some row sum leaves that range recomputes its queries relative to a maximum (the result is the
+ * plain definition's either way; the cost of such a block roughly triples).  Where a workgroup has 64
+ * queries (hero_attention_route), a block of 256 counts once, however many of its four leave the range.
  * With scores of a few units, as LayerNorm-ed activations give, that never happens; it takes
  * |q.k| / sqrt(head_dim) beyond about 50.  head_dim 32 refers its exponentials to a maximum and has
  * no such way out: the counter stays as it is. */
@@ -299,7 +301,8 @@ int hero_attention(const void* dev_q, const void* dev_k, const void* dev_vt, int
 
 /* The same attention, computed the way the layer entry points compute theirs: with device scratch
  * (caller-owned, 16-byte aligned; 128 MiB lets every problem use it) the query blocks of the last,
- * partly filled round of workgroups are cut along the keys (head_dim 64 only); their unnormalised
+ * partly filled round of workgroups are cut along the keys (head_dim 64 and 256 queries a workgroup only,
+ * see hero_attention_route); their unnormalised
  * partial outputs and row sums pass through the scratch and a second kernel adds them up,
  * normalises and stores.  The result differs from hero_attention's only by the order of the fp32
  * additions.  Calls that share a scratch buffer must not overlap. */
