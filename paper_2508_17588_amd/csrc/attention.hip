@@ -696,8 +696,8 @@ __device__ __forceinline__ void attention_finish(const AttnArgs& a, int head, in
 // What bounds it: a tile's chain of QK^T, exponentials and PV inside one wave (1.2 us with one workgroup on
 // a CU); eight waves a workgroup gain nothing.  Measured against the kernel above: 326 queries and keys x 4 heads
 // 14.3 -> 8.7 us, 691 x 2032 x 16 34.1 -> 15.7, 2032 x 2032 x 16 34.7 -> 24.8; head_dim 32, against the running
-// maximum with 256 queries a workgroup: 2032 x 2032 x 8 38.0 -> 13.5, 8000 x 8000 x 16 271 -> 247, 17776 x 17776 x 16
-// 1193 -> 1020.  The scale is applied to the fp32 scores.
+// maximum with 256 queries a workgroup: 2032 x 2032 x 8 38.0 -> 13.8, 8000 x 8000 x 16 258 -> 227, 17776 x 17776 x 16
+// 1164 -> 989.  The scale is applied to the fp32 scores.
 constexpr int SHARE_WAVES = 4;
 template <int HD>
 struct ShareKeys {
@@ -705,7 +705,7 @@ struct ShareKeys {
   static constexpr int TILE_CHUNKS = BKV * HD / 8;           // 16-byte chunks of a K or V^T tile
   u32x4_t tiles[SHARE_WAVES][2][TILE_CHUNKS];                         // [wave][K, V^T]; afterwards the partial outputs
   float sums[SHARE_WAVES][2][64];
-  float refs[SHARE_WAVES][2][64];                            // the waves' reference points (KEYS_RUNNING)
+  float refs[SHARE_WAVES][2][64];                            // the waves' reference points (KEYS_RUNNING, KEYS_LAZY)
   static_assert(QUADS * 64 == 2 * TILE_CHUNKS, "the partial outputs take the place of the tiles");
 };
 template <int HD> using share_keys_lds = __attribute__((address_space(3))) ShareKeys<HD>;
@@ -716,14 +716,18 @@ template <int HD> using share_keys_lds = __attribute__((address_space(3))) Share
 //                far when the row sum passes 2^26 (or is no number; at most 2^24 keys of probability 1 stay below).
 //                It bounds the unnormalised values whatever the scores, without a maximum per tile; the waves'
 //                outputs and sums are brought to the largest of their reference points before they are added.
+//  KEYS_LAZY     reference points too, but looked at only after a tile has been added, so that its exponentials run
+//                beside its PV: 0 while the first tile's maximum is within 2^+-24, raised by the row sum itself when
+//                that passes 2^26.  A sum beyond 2^120 or an output that is not finite asks for a KEYS_RUNNING pass.
 //  KEYS_SUMS     as KEYS_FREE, but the row sums only, to see whether they are in range.
-// head_dim 32 takes KEYS_RUNNING: 4 - 6 % slower on ordinary scores of many keys than KEYS_FREE (13.5 against 13.0 us at
-// 2032 x 2032 x 8), but without a second pass where scores spread (standard deviation 17 in log2 units: 15.6 us against
-// 51.8, and 1080 against 4850 at 17776 x 17776 x 16) and finite for values up to 2^100.
-enum ShareMode { KEYS_FREE, KEYS_RUNNING, KEYS_SUMS };
+// head_dim 32 takes KEYS_LAZY, as it took a running maximum before: 1 - 2 % slower on ordinary scores of many keys than
+// KEYS_FREE (KEYS_RUNNING 3 - 4 %: 8776 x 8776 x 12 189, 191 and 198 us), but with one pass where
+// scores spread (standard deviation 17 in log2 units: 2032 x 2032 x 8 13.0 us, KEYS_FREE with its second pass 51.7;
+// 17776 x 17776 x 16 1006 and 4710) and finite wherever the running maximum is.
+enum ShareMode { KEYS_FREE, KEYS_RUNNING, KEYS_LAZY, KEYS_SUMS };
 
 // One pass over the keys for queries q0 .. q0+63: leaves the waves' partial outputs in LDS ([wave][quad][lane],
-// quad = (cb*2 + ig)*4 + q) and returns whether some row sum is outside the range of the reference-free form.
+// quad = (cb*2 + ig)*4 + q) and returns whether another pass is needed (KEYS_FREE, KEYS_SUMS: some row sum is out of range).
 template <int HD, bool SCALED, ShareMode MODE>
 __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int q0, share_keys_lds<HD>* ldsp, float (&l)[2]) {
   ShareKeys<HD>& lds = *(ShareKeys<HD>*)ldsp;
@@ -733,6 +737,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   constexpr int KROWS = 512 / HD;                  // K rows per fill (V^T: 8)
   constexpr int KPER = 16 / KROWS;                 // fills after which the swizzle repeats (V^T: 2)
   constexpr int QUADS = ShareKeys<HD>::QUADS;
+  constexpr bool REFERRED = MODE == KEYS_RUNNING || MODE == KEYS_LAZY;
   const int d = a.n_heads * HD;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -784,6 +789,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   floatx16_t o[CB][2];
   float la[2] = {0.f, 0.f}, lb[2] = {0.f, 0.f};
   float ref[2] = {0.f, 0.f};
+  bool jumped = false, shifted = false;            // KEYS_LAZY: sums beyond repair (per lane); some reference point is not 0
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
@@ -791,8 +797,10 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[cb][ig][e] = 0.f;
 
-  auto step = [&](int tile, auto first) {
-    constexpr bool FIRST = decltype(first)::value;                   // of the wave's tiles (KEYS_RUNNING)
+  enum Tile { FIRST_TILE, PLAIN, SHIFTED };                           // PLAIN: no query has a reference point but 0
+  auto step = [&](int tile, auto kind) {
+    constexpr int KIND = decltype(kind)::value;
+    constexpr bool FIRST = KIND == FIRST_TILE;
     const bool more = tile + 1 < t_end;
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MODE == KEYS_SUMS ? 0 : NF) : "memory");    // all but the V^T fills: K is in LDS
     bf16x8_t kf[2][KS];
@@ -813,7 +821,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
 #pragma unroll
       for (int ig = 0; ig < 2; ++ig)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) s[ig][e] = MODE == KEYS_RUNNING && !SCALED ? -ref[ig] : 0.f;
+        for (int e = 0; e < 16; ++e) s[ig][e] = KIND == SHIFTED && !SCALED ? -ref[ig] : 0.f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
@@ -847,12 +855,14 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
           pf[jb][ig][h] = *reinterpret_cast<bf16x8_t*>(&t);
         }
     };
-    if constexpr (MODE != KEYS_RUNNING) {
+    if constexpr (!FIRST && MODE != KEYS_RUNNING) {
 #pragma unroll
       for (int jb = 0; jb < 2; ++jb) {
         floatx16_t s[2];
         scores(jb, s);
-        probabilities(jb, s, la, lb, [&](float v, int) { return SCALED ? v * a.q_scale : v; });
+        probabilities(jb, s, la, lb, [&](float v, int ig) {
+          return !SCALED ? v : KIND == SHIFTED ? __builtin_fmaf(v, a.q_scale, -ref[ig]) : v * a.q_scale;
+        });
       }
     } else {
       floatx16_t s[2][2];
@@ -876,6 +886,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
           float raised;
           if (FIRST) {
             raised = cand > -0x1p126f ? cand : 0.f;                  // (a tile of scores of -inf has no say)
+            if (MODE == KEYS_LAZY && fabsf(raised) < 24.f) raised = 0.f;
           } else {
             raised = fmaxf(cand, ref[ig]);
             const float alpha = __builtin_amdgcn_exp2f(ref[ig] - raised);
@@ -918,21 +929,63 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
 #pragma unroll
         for (int ig = 0; ig < 2; ++ig)
           o[cb][ig] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[cb][x], pf[x >> 1][ig][x & 1], o[cb][ig], 0, 0, 0);
+    if constexpr (MODE == KEYS_LAZY && !FIRST) {
+      const float sum = la[0] + lb[0] + la[1] + lb[1];
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(sum <= 0x1p26f)) != 0, 0)) {
+        jumped |= !(sum <= 0x1p120f);
+        shifted = true;
+#pragma unroll
+        for (int ig = 0; ig < 2; ++ig) {
+          const float mine = la[ig] + lb[ig];
+          auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mine), __float_as_uint(mine), false, false);
+          const float most = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));     // both halves of the query's keys
+          const float shift = most > 1.0f ? __builtin_amdgcn_logf(most) : 0.f;
+          const float alpha = __builtin_amdgcn_exp2f(-shift);
+          ref[ig] += shift;
+          la[ig] *= alpha;
+          lb[ig] *= alpha;
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[cb][ig][e] *= alpha;
+        }
+      }
+    }
   };
-  if constexpr (MODE != KEYS_RUNNING) {
-    for (int tile = t_begin; tile < t_end; ++tile) step(tile, std::false_type{});
+  using First = std::integral_constant<int, FIRST_TILE>;
+  using Plain = std::integral_constant<int, PLAIN>;
+  using Shifted = std::integral_constant<int, SHIFTED>;
+  int tile = t_begin;
+  if constexpr (REFERRED) {
+    if (tile < t_end) step(tile++, First{});
+  }
+  if constexpr (MODE == KEYS_LAZY) {
+    shifted = __builtin_amdgcn_ballot_w64(ref[0] != 0.f || ref[1] != 0.f) != 0;
+    for (; tile < t_end && !shifted; ++tile) step(tile, Plain{});
+  }
+  if constexpr (REFERRED) {
+    for (; tile < t_end; ++tile) step(tile, Shifted{});
   } else {
-    if (t_begin < t_end) step(t_begin, std::true_type{});
-    for (int tile = t_begin + 1; tile < t_end; ++tile) step(tile, std::false_type{});
+    for (; tile < t_end; ++tile) step(tile, Plain{});
   }
 
+  if constexpr (MODE == KEYS_LAZY) {
+    float z = 0.f;                                                   // no longer 0 if some output is not finite
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int ig = 0; ig < 2; ++ig)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) z = __builtin_fmaf(o[cb][ig][e], 0.f, z);
+    jumped |= z != 0.f;
+  }
   // the four partial results meet in LDS: [wave][quad][lane], quad = (cb*2 + ig)*4 + q
-  if constexpr (MODE == KEYS_RUNNING) {
+  if constexpr (REFERRED) {
 #pragma unroll
     for (int ig = 0; ig < 2; ++ig) lds.refs[wave][ig][lane] = t_begin < t_end ? ref[ig] : -INFINITY;
   }
   __syncthreads();
-  if constexpr (MODE == KEYS_RUNNING) {
+  if constexpr (REFERRED) {
 #pragma unroll
     for (int ig = 0; ig < 2; ++ig) {
       float top = lds.refs[0][ig][lane];
@@ -968,6 +1021,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
     l[ig] += __shfl_xor(l[ig], 32, 64);            // the two key halves of the query
   }
   if (MODE == KEYS_RUNNING) return false;
+  if (MODE == KEYS_LAZY) return __syncthreads_or(jumped) != 0;
   const int bad = !(l[0] >= 0x1p-80f && l[0] <= 0x1p80f) | !(l[1] >= 0x1p-80f && l[1] <= 0x1p80f);
   return __syncthreads_or(bad) != 0;
 }
@@ -1000,7 +1054,7 @@ __device__ __forceinline__ void share_keys_store(const AttnArgs& a, int head, in
   }
 }
 
-// Some row sum of the workgroup's 64 queries is out of range: a second pass gives them reference points.  The
+// A pass over the workgroup's 64 queries does not hold: a second one gives them reference points.  The
 // fallback counter counts blocks of 256 queries, so the workgroup then looks at the row sums of the block's earlier
 // 64s, as far as one that counts.  Out of line: inlined, it makes the kernel park registers around its loop.
 // Kernel times with scores of standard deviation 1.44 / 35 in log2 units (35: every block falls back), one wave of four
@@ -1011,7 +1065,7 @@ __device__ __attribute__((noinline)) void share_keys_fallback(AttnArgs a, int he
   float l[2];
   share_keys_pass<HD, SCALED, KEYS_RUNNING>(a, head, qb * 64, lds, l);
   share_keys_store<HD>(a, head, qb * 64, lds, l[0], l[1]);
-  if (a.fallback_count == nullptr) return;
+  if (HD == 32 || a.fallback_count == nullptr) return;        // (head_dim 32 keeps no count)
   for (int b = qb & ~3; b < qb; ++b) {
     __syncthreads();
     if (share_keys_pass<HD, SCALED, KEYS_SUMS>(a, head, b * 64, lds, l)) return;
@@ -1028,7 +1082,7 @@ __global__ __launch_bounds__(SHARE_WAVES * 64, 2) void attention_share_keys_kern
   auto* lds = (share_keys_lds<HD>*)(lds_ptr_t)smem;
   float l[2];
   const bool bad = share_keys_pass<HD, SCALED, MODE>(a, head, qb * 64, lds, l);
-  if constexpr (MODE == KEYS_FREE) {
+  if constexpr (MODE != KEYS_RUNNING) {
     if (bad) {
       share_keys_fallback<HD, SCALED>(a, head, qb, lds);
       return;
@@ -1129,7 +1183,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     return hipErrorInvalidValue;
   const bool scaled = a.q_scale != 1.0f;
   if (a.head_dim == 32)
-    return scaled ? launch_share_keys<32, true, KEYS_RUNNING>(a, st) : launch_share_keys<32, false, KEYS_RUNNING>(a, st);
+    return scaled ? launch_share_keys<32, true, KEYS_LAZY>(a, st) : launch_share_keys<32, false, KEYS_LAZY>(a, st);
   if (a.head_dim != 64) return hipErrorInvalidValue;
   if (sharing_keys_is_faster(a)) return scaled ? launch_share_keys<64, true, KEYS_FREE>(a, st) : launch_share_keys<64, false, KEYS_FREE>(a, st);
   return launch_hd64(a, st);

@@ -42,6 +42,9 @@ def operands(scores, r, n_keys, heads, hd):
         k[:, ::hd], q[:, ::hd] = round_to_bf16(along), round_to_bf16(np.float32(300 / 16 / per_unit))
     elif scores == "fall":
         k[:, ::hd], q[:, ::hd] = round_to_bf16(along[::-1].copy()), round_to_bf16(np.float32(300 / 16 / per_unit))
+    elif scores == "spike":                             # around 0, but 200 for three of the last keys
+        k[:, ::hd], q[:, ::hd] = 0.0, round_to_bf16(np.float32(200 / 16 / per_unit))
+        k[max(0, n_keys - 9)::4, ::hd] = 16.0
     else:
         q = round_to_bf16(q * 24)
     return q, k, v
@@ -50,7 +53,8 @@ def operands(scores, r, n_keys, heads, hd):
 @pytest.mark.parametrize("r,n_keys,heads", [(1, 1, 2), (65, 65, 2), (129, 257, 2), (300, 2033, 2)])
 @pytest.mark.parametrize("scores,v_exp,hd", [
     ("up", 60, 32), ("down", -60, 32), ("up", 0, 64), ("down", 0, 64),
-    ("rise", 0, 32), ("fall", 0, 32), ("spread", 0, 32), ("rise", 0, 64), ("fall", 0, 64), ("spread", 0, 64),
+    ("rise", 0, 32), ("fall", 0, 32), ("spread", 0, 32), ("spike", 0, 32), ("spike", 60, 32),
+    ("rise", 0, 64), ("fall", 0, 64), ("spread", 0, 64), ("spike", 0, 64),
 ])
 def test_attention_of_unusual_scores(scores, v_exp, hd, r, n_keys, heads):
     print(f"[case] r={r} n_keys={n_keys} hd={hd} scores {scores}, values x 2^{v_exp}", flush=True)
@@ -100,11 +104,11 @@ def test_layer_attention_of_unusual_scores(hd, heads, height, width, route, q_si
     cache.close()
 
 
-@pytest.mark.parametrize("hd,heads,passes", [(64, 16, 4.0), (32, 8, 2.0)])
+@pytest.mark.parametrize("hd,heads,passes", [(64, 16, 4.0), (32, 8, 2.6)])
 def test_price_of_spread_scores(hd, heads, passes):
     """Scores of standard deviation 35 in log2 units.  head_dim 64: the pass that finds its row sums out of range, one
-    that gives them reference points, and at most one look at other row sums; head_dim 32: one pass that raises its
-    reference points (measured 3.2 and 1.3 passes)."""
+    that gives them reference points, and at most one look at other row sums (measured 3.2 passes); head_dim 32: a pass,
+    and where a sum jumps out of range a second one, which takes 1.3 (measured 1.9; 2.3 if every workgroup needs it)."""
     n = 2032
     print(f"[case] {n} queries and keys, {heads} heads of {hd}", flush=True)
     d, gen = heads * hd, torch.Generator(device="cuda")
