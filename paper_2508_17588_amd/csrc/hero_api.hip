@@ -742,7 +742,7 @@ int hero_extrapolate_layer(hero_cache_t c, int32_t layer, void* dev_x, int32_t k
   const double bytes = (double)c->lay.n_tokens * c->cfg.hidden * ((x_fp32 ? 8.0 : 4.0) + (prev ? 4.0 : 2.0));
   PROF_LAUNCH(c, HERO_PROF_EXTRAP, bytes, (hipStream_t)stream,
               launch_axpy_features(dev_x, x_fp32, ls.s_cur, prev, alpha, c->lay.n_tokens * c->cfg.hidden,
-                                   (hipStream_t)stream));
+                                   (hipStream_t)stream, layer % 2 == 0));
   return HERO_OK;
 }
 

@@ -62,8 +62,9 @@ struct QkPostArgs {
 };
 hipError_t launch_qk_post(const QkPostArgs& a, hipStream_t st);
 hipError_t launch_rope_table(float2* table, int frames, int height, int width, int head_dim, hipStream_t st);
+// from_end: the arrays are walked from their last element to their first
 hipError_t launch_axpy_features(void* x, bool x_fp32, const bf16_t* s_cur, const bf16_t* s_prev, float alpha,
-                                int64_t n_elems, hipStream_t st);
+                                int64_t n_elems, hipStream_t st, bool from_end = false);
 
 // Deep-stack collapse: t = (accumulate ? t : 0) + sum of up to 48 bf16 feature arrays (fp32 result),
 // and x += t_cur + (t_cur - t_prev) * alpha (t_prev may be null: x += t_cur).
