@@ -223,7 +223,8 @@ int hero_cache_state(hero_cache_t c, int32_t* n_full, int32_t* last_full_step);
  * layers, in its one pass at the end of the step (HERO_PROF_EXTRAP).
  * Where a model of at most 256 channels normalises its rows inside the QKV or FFN1 kernel (see
  * hero_linear_route), there is no HERO_PROF_LN launch for them and the time is part of
- * HERO_PROF_GEMM_QKV or HERO_PROF_GEMM_FF1.
+ * HERO_PROF_GEMM_QKV or HERO_PROF_GEMM_FF1.  Where one kernel takes such a model's rows from the attention output to
+ * the residual add, its launch and work (out-projection, FFN1, FFN2) are one HERO_PROF_GEMM_FF2 entry.
  * The three output arrays have 2 * HERO_PROF_KINDS entries (any may be NULL). */
 enum {
   HERO_PROF_SELECT = 0, HERO_PROF_LN = 1, HERO_PROF_GEMM_QKV = 2, HERO_PROF_ATTN = 3,

@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libhero.so")
-SOURCES = ["hero_api.hip", "rowops.hip", "gemm.hip", "attention.hip"]
+SOURCES = ["hero_api.hip", "rowops.hip", "gemm.hip", "attention.hip", "narrow.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          # packed-fp32 VALU forms are kept out of the generated code on purpose
@@ -32,7 +32,7 @@ def _compile(src: str, extra=()) -> str:
 
 def build(verbose: bool = True, extra=()) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=5) as ex:
         objs = list(ex.map(lambda s: _compile(s, extra), SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)

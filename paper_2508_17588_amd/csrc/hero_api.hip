@@ -170,6 +170,7 @@ struct Layout {
   size_t idx_off, a_off, q_off, o_off, f_off, ktmp_off, vtmp_off, splitk_off, splitk_bytes, ws_bytes;
   size_t seen_off, seen_bytes;   // index check: one bit per token, then one verdict word
   size_t stat_off;               // counters (word 0: attention workgroups that took the running-maximum path)
+  size_t parts_off, parts_bytes, arrivals_off;   // partial sums and arrival counters of the narrow models' kernel (0 bytes: not used)
   // bytes of one layer's slabs: S_cur, then K and V^T if it keeps them, then S_prev if it keeps one
   bool keeps_kv(const hero_config& c, int l) const { return l < c.n_shallow || kv_all; }
   bool keeps_prev(const hero_config& c, int l) const { return l >= c.n_shallow || prev_all; }
@@ -218,6 +219,12 @@ Layout make_layout(const hero_config& c) {
   w += L.seen_bytes;
   L.stat_off = w;
   w += 256;
+  L.parts_off = w;
+  L.parts_bytes = narrow_tail_fits(1, c.hidden, c.ffn_dim)
+                      ? align_up(std::min<size_t>(((size_t)L.n_tokens + 15) / 16 * 4, NARROW_TAIL_BLOCKS) * 16 * c.hidden * 4, 256) : 0;
+  w += L.parts_bytes;
+  L.arrivals_off = w;
+  if (L.parts_bytes) w += NARROW_TAIL_BLOCKS * 4;
   L.ws_bytes = w;
   return L;
 }
@@ -372,6 +379,25 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
   at.split_ws = c->splitk; at.split_ws_bytes = c->lay.splitk_bytes;    // shared with the GEMMs: same stream, never concurrent
   at.fallback_count = c->stats;
   PROF_LAUNCH(c, HERO_PROF_ATTN, 4.0 * rd * n_all, st, launch_attention(at, st));
+
+  if (narrow_tail_fits(n_rows, d, cfg.ffn_dim)) {
+    TailArgs t;
+    memset(&t, 0, sizeof(t));
+    t.o = c->o; t.rows = rows; t.n_rows = n_rows; t.hidden = d; t.ffn = cfg.ffn_dim;
+    t.w_o = (const bf16_t*)w.w_o; t.b_o = (const bf16_t*)w.b_o;
+    t.w1 = (const bf16_t*)w.w_ff1; t.b1 = (const bf16_t*)w.b_ff1;
+    t.w2 = (const bf16_t*)w.w_ff2; t.b2 = (const bf16_t*)w.b_ff2;
+    t.gain = (const bf16_t*)w.ln2_g; t.bias = (const bf16_t*)w.ln2_b; t.eps = cfg.ln_eps; t.mod = m2;
+    if (adaln) {
+      t.gate1_v = mod + 2 * d; t.gate1_t = mod + 5 * d; t.gate2_v = mod + 8 * d; t.gate2_t = mod + 11 * d;
+      t.n_text = cfg.n_text;
+    }
+    t.s = s_dst; t.x = x; t.x_fp32 = x_fp32; t.add_to_x = fuse_resid;
+    t.parts = (float*)(c->ws + c->lay.parts_off); t.parts_bytes = c->lay.parts_bytes;
+    t.arrivals = (uint32_t*)(c->ws + c->lay.arrivals_off);
+    PROF_LAUNCH(c, HERO_PROF_GEMM_FF2, 2.0 * rd * (d + 2.0 * cfg.ffn_dim), st, launch_narrow_tail(t, st));
+    return HERO_OK;
+  }
 
   memset(&g, 0, sizeof(g));
   g.a = c->o; g.w = (const bf16_t*)w.w_o; g.bias = (const bf16_t*)w.b_o;

@@ -135,6 +135,29 @@ struct LnInput {
 // whether one kernel takes LayerNorm and this (QKV or GELU) GEMM faster than two
 bool gemm_takes_ln(const GemmArgs& g);
 hipError_t launch_gemm_ln(const GemmArgs& g, const LnInput& ln, hipStream_t st);
+
+// Out-projection, LayerNorm, FFN and residual of the listed rows in one kernel (narrow models)
+struct TailArgs {
+  const bf16_t* o;            // attention output [n_rows, hidden]
+  const int32_t* rows;        // nullptr: row m
+  int32_t n_rows, hidden, ffn;
+  const bf16_t *w_o, *b_o, *w1, *b1, *w2, *b2;
+  const bf16_t *gain, *bias;  // LayerNorm
+  float eps;
+  LnMod mod;
+  const bf16_t *gate1_v, *gate1_t, *gate2_v, *gate2_t;    // adaLN gates of the two branches (nullptr: none)
+  int32_t n_text;             // rows below it take the _t vectors
+  bf16_t* s;                  // stored feature, row rows[m]
+  void* x;                    // residual stream, read at row rows[m]
+  bool x_fp32, add_to_x;      // add_to_x: += the stored feature
+  float* parts;               // scratch for partial sums (nullptr: the FFN channels are never shared out)
+  size_t parts_bytes;
+  uint32_t* arrivals;         // NARROW_TAIL_BLOCKS counters, zero before and after every launch
+};
+constexpr int NARROW_TAIL_BLOCKS = 256;
+bool narrow_tail_fits(int n_rows, int hidden, int ffn);
+hipError_t launch_narrow_tail(const TailArgs& a, hipStream_t st);
+
 // bytes of scratch launch_gemm would use for this problem if it had all it wanted (0: the problem is not cut along k)
 size_t gemm_wanted_scratch_bytes(const GemmArgs& g);
 
