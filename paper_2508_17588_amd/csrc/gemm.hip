@@ -527,81 +527,115 @@ __device__ __forceinline__ void epilogue256(const GemmArgs& g, floatx16_t (&acc)
 // The tile's fp32 sums lie in LDS as COPIES addends of BM rows of BN + 4 floats (the pad spreads the
 // 16-byte accumulator writes of 16 rows over all banks).  All NT threads add the copies in order, apply
 // the epilogue and store 16-byte pieces, consecutive lanes along a row; V^T pieces run along m.
+// What bounds it is latency: piece after piece, each with its own chain of row number, stored feature and x, took FFN2 of
+// 700 rows of 512 channels from 12.4 to 13.3 us, of 1500 x 768 from 26.3 to 28.4, of 8775 x 1920 from 246.7 to 259.0.
 template <int EPI, int BM, int BN, int NT, int COPIES>
 __device__ __forceinline__ void stream_tile(const GemmArgs& g, const float* tile, int m0, int n0, int tid) {
   constexpr int LDT = BN + 4, PIECES = BN / 8;
   const bool use_rows = EPI != EPI_PLAIN && EPI != EPI_GELU && g.rows != nullptr;
   const int n_rowmajor = EPI == EPI_QKV ? 2 * g.d : g.n;     // columns stored along n
-#pragma unroll 2
-  for (int p = tid; p < BM * PIECES; p += NT) {
-    const int ml = p / PIECES, nl = (p - ml * PIECES) * 8;
-    const int m = m0 + ml, n = n0 + nl;
-    if (m >= g.m || n >= n_rowmajor) continue;
-    float v[8];
-    ResidIO<float>::load8(tile + ml * LDT + nl, v);
+  const bool gated = (EPI == EPI_SCATTER || EPI == EPI_SCATTER_ADD) && g.gate_v != nullptr;
+  const bool add_x = EPI == EPI_SCATTER_ADD && g.x != nullptr;
+  // BATCH pieces of a thread side by side, everything they need from memory asked for before the first is stored: row
+  // numbers, then gates, stored features and x one latency later (addresses past the end are clamped, so that no branch
+  // lies between the loads).
+  constexpr int PER_THREAD = (BM * PIECES + NT - 1) / NT, BATCH = PER_THREAD < 4 ? PER_THREAD : PER_THREAD % 3 == 0 ? 3 : 4;
+  for (int p0 = tid; p0 < BM * PIECES && n0 < n_rowmajor; p0 += BATCH * NT) {
+    int ml[BATCH], nl[BATCH], n[BATCH];
+    bool ok[BATCH];
+    int64_t row[BATCH];
+    u32x4_t bias[BATCH], gate[BATCH], old[BATCH];
+    u32x4_t xraw[BATCH][2];
 #pragma unroll
-    for (int c = 1; c < COPIES; ++c) {
-      float w[8];
-      ResidIO<float>::load8(tile + (c * BM + ml) * LDT + nl, w);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] += w[e];
+    for (int b = 0; b < BATCH; ++b) {
+      const int p = p0 + b * NT;
+      ml[b] = p / PIECES;
+      nl[b] = (p - ml[b] * PIECES) * 8;
+      ok[b] = p < BM * PIECES && m0 + ml[b] < g.m && n0 + nl[b] < n_rowmajor;
+      ml[b] = min(ml[b], BM - 1);
+      n[b] = min(n0 + nl[b], n_rowmajor - 8);
+      const int m = min(m0 + ml[b], g.m - 1);
+      row[b] = use_rows ? g.rows[m] : m;
     }
-    float b[8];
-    ResidIO<bf16_t>::load8(g.bias + n, b);
+    auto at = [](const void* p, int64_t bytes) { return *reinterpret_cast<const u32x4_t*>(static_cast<const char*>(p) + bytes); };
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] += b[e];
-    if (EPI == EPI_QKV) {
-      bf16_t* dst;
-      if (n < g.d) {
+    for (int b = 0; b < BATCH; ++b) {
+      bias[b] = at(g.bias, n[b] * 2);
+      if (EPI == EPI_SCATTER_ADD) old[b] = at(g.c, (row[b] * g.n + n[b]) * 2);
+    }
+    if (gated) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] *= g.q_scale;
-        dst = g.c + (int64_t)m * g.d + n;
-      } else {
-        dst = g.k_out + (int64_t)(use_rows ? g.rows[m] : m) * g.d + (n - g.d);
+      for (int b = 0; b < BATCH; ++b) gate[b] = at(row[b] < g.n_text ? g.gate_t : g.gate_v, n[b] * 2);
+    }
+    if (add_x && g.x_fp32) {
+#pragma unroll
+      for (int b = 0; b < BATCH; ++b) {
+        xraw[b][0] = at(g.x, (row[b] * g.n + n[b]) * 4);
+        xraw[b][1] = at(g.x, (row[b] * g.n + n[b]) * 4 + 16);
+      }
+    } else if (add_x) {
+#pragma unroll
+      for (int b = 0; b < BATCH; ++b) xraw[b][0] = at(g.x, (row[b] * g.n + n[b]) * 2);
+    }
+#pragma unroll
+    for (int b = 0; b < BATCH; ++b) {
+      float v[8];
+      ResidIO<float>::load8(tile + ml[b] * LDT + nl[b], v);
+#pragma unroll
+      for (int c = 1; c < COPIES; ++c) {
+        float w[8];
+        ResidIO<float>::load8(tile + (c * BM + ml[b]) * LDT + nl[b], w);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += w[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { v[2 * e] += unpack_lo(bias[b][e]); v[2 * e + 1] += unpack_hi(bias[b][e]); }
+      if (gated) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { v[2 * e] *= unpack_lo(gate[b][e]); v[2 * e + 1] *= unpack_hi(gate[b][e]); }
+      }
+      bf16_t* dst = g.c + row[b] * g.n + n[b];
+      if (EPI == EPI_QKV) {
+        if (n[b] < g.d) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] *= g.q_scale;
+          dst = g.c + (int64_t)(m0 + ml[b]) * g.d + n[b];
+        } else {
+          dst = g.k_out + row[b] * g.d + (n[b] - g.d);
+        }
+      }
+      if (EPI == EPI_GELU) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = gelu_tanh(v[e]);
+      }
+      if (EPI == EPI_SCATTER_ADD) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { v[2 * e] += unpack_lo(old[b][e]); v[2 * e + 1] += unpack_hi(old[b][e]); }
       }
       u32x4_t out;
 #pragma unroll
       for (int e = 0; e < 4; ++e) out[e] = pack_bf16x2_hw(v[2 * e], v[2 * e + 1]);
-      *reinterpret_cast<u32x4_t*>(dst) = out;
-      continue;
-    }
-    const int64_t row = use_rows ? (int64_t)g.rows[m] : (int64_t)m;
-    if ((EPI == EPI_SCATTER || EPI == EPI_SCATTER_ADD) && g.gate_v != nullptr) {
-      float gate[8];
-      ResidIO<bf16_t>::load8((row < g.n_text ? g.gate_t : g.gate_v) + n, gate);
+      if (ok[b]) *reinterpret_cast<u32x4_t*>(dst) = out;
+      if (add_x) {
+        // residual add with the feature as stored (rounded), so x matches x += S done afterwards
+        u32x4_t lo, hi;
+        if (g.x_fp32) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] *= gate[e];
-    }
-    if (EPI == EPI_GELU) {
+          for (int e = 0; e < 4; ++e) {
+            const float f = (e & 1) ? unpack_hi(out[e >> 1]) : unpack_lo(out[e >> 1]), h = (e & 1) ? unpack_hi(out[2 + (e >> 1)]) : unpack_lo(out[2 + (e >> 1)]);
+            lo[e] = __float_as_uint(__uint_as_float(xraw[b][0][e]) + f);
+            hi[e] = __float_as_uint(__uint_as_float(xraw[b][1][e]) + h);
+          }
+        } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = gelu_tanh(v[e]);
-    }
-    bf16_t* dst = g.c + row * g.n + n;
-    if (EPI == EPI_SCATTER_ADD) {
-      float old[8];
-      ResidIO<bf16_t>::load8(dst, old);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] += old[e];
-    }
-    u32x4_t out;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) out[e] = pack_bf16x2_hw(v[2 * e], v[2 * e + 1]);
-    *reinterpret_cast<u32x4_t*>(dst) = out;
-    if (EPI == EPI_SCATTER_ADD && g.x != nullptr) {
-      // residual add with the feature as stored (rounded), so x matches x += S done afterwards
-      float xv[8];
-      if (g.x_fp32) {
-        float* xp = static_cast<float*>(g.x) + row * g.n + n;
-        ResidIO<float>::load8(xp, xv);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { xv[2 * e] += unpack_lo(out[e]); xv[2 * e + 1] += unpack_hi(out[e]); }
-        ResidIO<float>::store8(xp, xv);
-      } else {
-        bf16_t* xp = static_cast<bf16_t*>(g.x) + row * g.n + n;
-        ResidIO<bf16_t>::load8(xp, xv);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { xv[2 * e] += unpack_lo(out[e]); xv[2 * e + 1] += unpack_hi(out[e]); }
-        ResidIO<bf16_t>::store8(xp, xv);
+          for (int e = 0; e < 4; ++e)
+            lo[e] = pack_bf16x2(unpack_lo(xraw[b][0][e]) + unpack_lo(out[e]), unpack_hi(xraw[b][0][e]) + unpack_hi(out[e]));
+        }
+        if (ok[b]) {
+          char* xp = static_cast<char*>(g.x) + (row[b] * g.n + n[b]) * (g.x_fp32 ? 4 : 2);
+          *reinterpret_cast<u32x4_t*>(xp) = lo;
+          if (g.x_fp32) *reinterpret_cast<u32x4_t*>(xp + 16) = hi;
+        }
       }
     }
   }
