@@ -315,7 +315,8 @@ int hero_attention_scratch(const void* dev_q, const void* dev_k, const void* dev
  * expected time and may change with the library).
  * hero_linear_route: the tile of a GEMM (HERO_ROUTE_*: hero_linear with act 0 and 1, then the four of a layer; QKV:
  * n = 3 * hidden), on listed rows or not, with scratch_bytes of scratch; *k_chunks: the number of chunks along k of
- * the tiles of the last round (1: not cut); *normalises: 1 where a layer's QKV or FFN1 kernel normalises its rows
+ * the tiles of the last round (1: not cut; a layer of a handle, whose workgroups can add up what they share, may also cut
+ * smaller tiles of its out-projection, FFN1 and FFN2, and then prefer another kind); *normalises: 1 where a layer's QKV or FFN1 kernel normalises its rows
  * itself (models of at most 256 channels).
  * hero_attention_route: queries per workgroup (64: the workgroup's waves share the keys, 256: each wave has
  * queries of its own) and *key_ranges, the number of key ranges of the blocks of the last round. */

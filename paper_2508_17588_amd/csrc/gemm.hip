@@ -686,23 +686,41 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& g, const float* tile
 // CUs at work at k = 12288) and, at k = 3072, start-up and epilogue, about 7 of 50 us.  Kernel times of FFN2 after
 // the kernel that writes its rows, against 256 x 256 or the earlier 128 x 128 tiles: 4485 rows at hidden 1920
 // 174 -> 124 us (192 x 192), 1755 rows at hidden 3072 202 -> 153 (128 x 192), 2925 rows 241, fix-up included, -> 194.
+// Tiles of the last round cut along k: slots 0 .. full_items - 1 are whole work items, the `tiles` slots after them are cut
+// in `chunks`, whose sums the workgroup that arrives last adds up (one counter a tile, one block of BM x BN floats a chunk).
+constexpr int MOST_CHUNKS = 8;
+struct Cut {
+  int32_t full_items, tiles, chunks;
+  float* parts;
+  uint32_t* arrivals;
+};
+
 template <int BM, int BN>
 struct HalfK {
   static constexpr int STAGE = (BM + BN) * 128;                          // bytes
   static constexpr int RING = 163840 / STAGE < 4 ? 163840 / STAGE : 4;
-  static constexpr int TILE_BYTES = BM * (BN + 4) * 4;
+  static constexpr int TILE_BYTES = BM * (BN + 4) * 4 + 16;               // and a word for last_to_arrive
   static constexpr int LDS = RING * STAGE > TILE_BYTES ? RING * STAGE : TILE_BYTES;
 };
 
-template <int BM, int BN, int EPI>
-__global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m, int tiles_n, int per_xcd, int group_m) {
+template <int BM, int BN, int EPI, bool CUT>
+__global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m, int tiles_n, int per_xcd, int group_m, Cut cut) {
   using C = HalfK<BM, BN>;
   constexpr int MB = BM / 64, NB = BN / 64;            // 32 x 32 blocks of a wave's BM/2 x BN/2 sub-tile
   constexpr int NF = (BM + BN) / 64;                   // 1 KB fills of a wave per stage
   constexpr int RING = C::RING, STAGE = C::STAGE;
   static_assert(BM % 64 == 0 && BN % 64 == 0 && RING >= 3 && NF <= MB * NB + 2, "tile shape");
+  // workgroup id -> tile slot and k-chunk: all first chunks of the cut tiles, then all second ones, ..., so that the
+  // chunks of a tile stay on the XCD that owns its range of tiles (slots are a multiple of 8)
+  int item = blockIdx.x, chunk = 0, n_chunks = 1;
+  if (CUT && item >= cut.full_items) {
+    const int r = item - cut.full_items;
+    item = cut.full_items + r % cut.tiles;
+    chunk = r / cut.tiles;
+    n_chunks = cut.chunks;
+  }
   int m0, n0;
-  if (!tile_origin(blockIdx.x, BM, BN, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+  if (!tile_origin(item, BM, BN, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
 
   extern __shared__ u32x4_t smem[];
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)smem;
@@ -723,9 +741,10 @@ __global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m
     voff[i] = (uint32_t)(i < BM / 64 ? m0 + row : n0 + row - BM) * row_bytes + chunk * 16;
   }
   const int n_stages = g.k / SBK;
+  const int stage_begin = chunk * n_stages / n_chunks, stage_end = (chunk + 1) * n_stages / n_chunks;
   auto fill = [&](int slot, int stage, int i) {
     lds_fill(i < BM / 64 ? rsA : rsB, lds0 + wave * 1024 + i * 8192 + (uint32_t)slot * STAGE, voff[i],
-             (uint32_t)min(stage, n_stages - 1) * (SBK * 2));            // (past the end: the last stage again, unread)
+             (uint32_t)min(stage, stage_end - 1) * (SBK * 2));           // (past the end: the last stage again, unread)
   };
 
   const char* lbase = reinterpret_cast<const char*>(smem);
@@ -764,9 +783,9 @@ __global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m
 #pragma unroll
   for (int s = 0; s < RING - 1; ++s)
 #pragma unroll
-    for (int i = 0; i < NF; ++i) fill(s, s, i);
+    for (int i = 0; i < NF; ++i) fill(s, stage_begin + s, i);
   int slot = 0;
-  for (int t = 0; t < n_stages; ++t) {
+  for (int t = stage_begin; t < stage_end; ++t) {
     // all but the fills of the RING - 2 newest stages have landed: stage t is in LDS; every wave's
     // fragment reads of stage t-1 are complete, so its slot can be filled again
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((RING - 2) * NF) : "memory");
@@ -819,6 +838,37 @@ __global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m
             }
             *p = v;
           }
+    }
+    __syncthreads();
+  }
+  if (CUT && n_chunks > 1) {
+    // the chunk's sums, 8 KB per store instruction; the last to arrive adds the chunks in their order
+    constexpr int PIECES = BM * BN / 4 / 512, PART = BM * BN * 4;
+    const __amdgpu_buffer_rsrc_t rs = parts_rsrc(cut.parts + (size_t)(item - cut.full_items) * n_chunks * (PART / 4), (uint32_t)n_chunks * PART);
+    auto piece = [&](int i) { const int p = i * 512 + tid; return reinterpret_cast<floatx4_t*>(tile + p / (BN / 4) * LDT + p % (BN / 4) * 4); };
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) store_part(rs, (uint32_t)chunk * PART + (i * 512 + tid) * 16, *piece(i));
+    if (!last_to_arrive(cut.arrivals + (item - cut.full_items), n_chunks, reinterpret_cast<uint32_t*>(tile + BM * LDT))) return;
+    // (two pieces of every chunk on their way at a time: the loads' latency is what this costs)
+    constexpr int N = 2, MOST = MOST_CHUNKS;
+#pragma unroll 2
+    for (int h = 0; h < PIECES; h += N) {
+      floatx4_t v[MOST][N];
+#pragma unroll
+      for (int c = 0; c < MOST; ++c)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+          if (c < n_chunks) v[c][i] = load_part(rs, (uint32_t)c * PART + ((h + i) * 512 + tid) * 16);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        floatx4_t sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < MOST; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (c < n_chunks) sum[e] += v[c][i][e];
+        *piece(h + i) = sum;
+      }
     }
     __syncthreads();
   }
@@ -1100,7 +1150,7 @@ int choose_k_split(const GemmArgs& g, size_t ws_bytes, int* n_rem_out, double* s
   return split;
 }
 
-hipError_t launch_gemm256(const GemmArgs& g, hipStream_t st) {
+hipError_t launch_gemm256(const GemmArgs& g, int split, hipStream_t st) {
   int tiles_m = (g.m + 255) / 256, tiles_n = (g.n + 255) / 256;
   int n_tiles = tiles_m * tiles_n;
   int per_xcd = (n_tiles + 7) / 8;
@@ -1110,12 +1160,7 @@ hipError_t launch_gemm256(const GemmArgs& g, hipStream_t st) {
   // groups (in-session A/B at the 5B shapes: QKV of 4485 rows 4 % faster with 4, the 17776-row
   // problems with k = 3072 0.5 % faster with 8, 16 is 1-7 % slower everywhere).
   const int group_m = (g.k >= 8192 || tiles_m <= 24) ? 4 : 8;
-  SplitK sk;
-  sk.full_items = slots / 256 * 256;
-  sk.ws = g.splitk_ws;
-  int n_rem = 0;
-  sk.split = choose_k_split(g, g.splitk_ws != nullptr ? g.splitk_ws_bytes : 0, &n_rem);
-  if (sk.split == 1) sk.full_items = slots;
+  const SplitK sk = {split > 1 ? slots / 256 * 256 : slots, split, g.splitk_ws};
   const int n_split_tiles = slots - sk.full_items;
   dim3 grid(sk.full_items + n_split_tiles * sk.split), block(512);
 #define HERO_GEMM256_LAUNCH(E)                                                                           \
@@ -1144,38 +1189,49 @@ hipError_t launch_gemm256(const GemmArgs& g, hipStream_t st) {
 
 // A distinct type per kernel, so that each has its own record of the devices it was announced on.
 template <typename Kernel, Kernel KERN>
-hipError_t launch_tiles(const GemmArgs& g, int bm, int bn, int threads, int lds, hipStream_t st) {
+hipError_t launch_tiles(const GemmArgs& g, int bm, int bn, int threads, int lds, int chunks, hipStream_t st) {
   static std::atomic<uint64_t> lds_allowed{0};
   hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(KERN), lds, lds_allowed);
   if (e != hipSuccess) return e;
   const int tiles_m = (g.m + bm - 1) / bm, tiles_n = (g.n + bn - 1) / bn;
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
   const int group_m = (g.k >= 8192 || tiles_m <= 24) ? 4 : 8;      // as for the 256 x 256 tiles
-  hipLaunchKernelGGL(KERN, dim3(per_xcd * 8), dim3(threads), lds, st, g, tiles_m, tiles_n, per_xcd, group_m);
+  if constexpr (std::is_invocable_v<Kernel, GemmArgs, int, int, int, int, Cut>) {
+    const int slots = per_xcd * 8, full = chunks > 1 ? slots / 256 * 256 : slots;
+    const Cut cut = {full, slots - full, chunks, g.parts, g.arrivals};
+    hipLaunchKernelGGL(KERN, dim3(full + (slots - full) * chunks), dim3(threads), lds, st, g, tiles_m, tiles_n, per_xcd, group_m, cut);
+  } else {
+    hipLaunchKernelGGL(KERN, dim3(per_xcd * 8), dim3(threads), lds, st, g, tiles_m, tiles_n, per_xcd, group_m);
+  }
   return hipGetLastError();
 }
 using TileKernel = void (*)(GemmArgs, int, int, int, int);
+using CutTileKernel = void (*)(GemmArgs, int, int, int, int, Cut);
 
-template <int BM, int BN>
-hipError_t launch_halfk(const GemmArgs& g, hipStream_t st) {
+template <int BM, int BN, bool CUT>
+hipError_t launch_halfk(const GemmArgs& g, int split, hipStream_t st) {
   constexpr int LDS = HalfK<BM, BN>::LDS;
   switch (g.epilogue) {
-    case EPI_PLAIN: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_PLAIN>>(g, BM, BN, 512, LDS, st);
-    case EPI_GELU: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_GELU>>(g, BM, BN, 512, LDS, st);
-    case EPI_QKV: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_QKV>>(g, BM, BN, 512, LDS, st);
-    case EPI_SCATTER: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_SCATTER>>(g, BM, BN, 512, LDS, st);
-    case EPI_SCATTER_ADD: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_SCATTER_ADD>>(g, BM, BN, 512, LDS, st);
+    case EPI_PLAIN: return launch_tiles<CutTileKernel, gemm_halfk_kernel<BM, BN, EPI_PLAIN, false>>(g, BM, BN, 512, LDS, 1, st);
+    case EPI_GELU: return launch_tiles<CutTileKernel, gemm_halfk_kernel<BM, BN, EPI_GELU, CUT>>(g, BM, BN, 512, LDS, split, st);
+    case EPI_QKV: return launch_tiles<CutTileKernel, gemm_halfk_kernel<BM, BN, EPI_QKV, false>>(g, BM, BN, 512, LDS, 1, st);
+    case EPI_SCATTER: return launch_tiles<CutTileKernel, gemm_halfk_kernel<BM, BN, EPI_SCATTER, CUT>>(g, BM, BN, 512, LDS, split, st);
+    case EPI_SCATTER_ADD: return launch_tiles<CutTileKernel, gemm_halfk_kernel<BM, BN, EPI_SCATTER_ADD, CUT>>(g, BM, BN, 512, LDS, split, st);
     default: return hipErrorInvalidValue;
   }
+}
+template <int BM, int BN>
+hipError_t launch_halfk(const GemmArgs& g, int split, hipStream_t st) {
+  return split > 1 ? launch_halfk<BM, BN, true>(g, split, st) : launch_halfk<BM, BN, false>(g, 1, st);
 }
 
 hipError_t launch_quarterk(const GemmArgs& g, hipStream_t st) {
   switch (g.epilogue) {
-    case EPI_PLAIN: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_PLAIN>>(g, 64, 64, 256, QK_LDS, st);
-    case EPI_GELU: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_GELU>>(g, 64, 64, 256, QK_LDS, st);
-    case EPI_QKV: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_QKV>>(g, 64, 64, 256, QK_LDS, st);
-    case EPI_SCATTER: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_SCATTER>>(g, 64, 64, 256, QK_LDS, st);
-    case EPI_SCATTER_ADD: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_SCATTER_ADD>>(g, 64, 64, 256, QK_LDS, st);
+    case EPI_PLAIN: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_PLAIN>>(g, 64, 64, 256, QK_LDS, 1, st);
+    case EPI_GELU: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_GELU>>(g, 64, 64, 256, QK_LDS, 1, st);
+    case EPI_QKV: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_QKV>>(g, 64, 64, 256, QK_LDS, 1, st);
+    case EPI_SCATTER: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_SCATTER>>(g, 64, 64, 256, QK_LDS, 1, st);
+    case EPI_SCATTER_ADD: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_SCATTER_ADD>>(g, 64, 64, 256, QK_LDS, 1, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1222,39 +1278,64 @@ constexpr TileCost TILE_COST[] = {{64, 64, 2.2f, 0.17f, 0.18f, 5.f},   {128, 128
                                   {128, 192, 4.5f, 0.43f, 0.70f, 7.f}, {192, 192, 6.f, 0.65f, 0.91f, 10.5f},
                                   {256, 128, 6.f, 0.55f, 0.87f, 9.5f}, {256, 256, 6.f, 0.72f, 1.48f, 7.5f}};
 
+// What it takes workgroups to share tiles cut along k (us): each stores its part, the last to arrive loads them all past
+// the caches, at 35 - 40 GB/s a CU.  part: size in units of 64 KB; fill: work items of the round a CU.  Over 132 problems
+// (out-projection, FFN1 and FFN2 of 330 .. 8775 rows, hidden 512 .. 3072) and every way to cut them, the kind and cut chosen
+// take 0.4 % longer than the best on average, 2.7 % without cuts, and never longer than what is chosen without:
+// FFN2 of 700 x 1536 44.7 -> 29.4 us (128 x 128 in 3), 1500 x 3072 144.8 -> 118.8 (192 x 192 in 2).
+constexpr int MIN_CHUNK = 6;                             // stages of a chunk
+double sharing_cost(double part, int split, double fill) { return 2.0 + part * (split + 4.5 * fill); }
+
+struct TileChoice {
+  TileKind kind;
+  int split;      // chunks along k of the last round's tiles (1: not cut)
+};
+
 // The kind with the least expected time.  Small problems take the smallest tiles that still fit one
 // round (latency along k bounds them), large ones 256 x 256 (least operand traffic a flop), and in between
 // the kind whose tile count fills its last round: e.g. FFN2 of 2925 x 3072 is 144 tiles of 256 x 256 but 256 of
 // 192 x 192 (241 us against 194), of 691 x 1024 (k = 4096) 16.2 us on 64 x 64 tiles against 28.3 on 128 x 128.
 // A problem that has 128 tiles of 256 x 256 keeps them unless another kind is expected to take 1 % less: less than
 // that once took FFN1 of 4485 x 3072 from 296 to 303 us and FFN2 of 17776 x 1920 from 530 to 549, both to 192 x 192.
-TileKind choose_tile(const GemmArgs& g) {
+TileChoice choose_tile(const GemmArgs& g) {
   // (a wave's columns of a 256 x 256 tile must lie inside one of the Q / K / V thirds)
   const bool qkv_split_ok = g.epilogue != EPI_QKV || g.d % 128 == 0;
   const bool scattered = g.epilogue == EPI_QKV && g.rows != nullptr;
   const int stages = g.k / SBK;
-  TileKind best_kind = TILE_128;
+  const size_t ws_bytes = g.splitk_ws != nullptr ? g.splitk_ws_bytes : 0;
+  TileChoice choice = {TILE_128, 1};
   double best = 1e30;
   for (int kind = TILE_64; kind <= TILE_256; ++kind) {
     if (kind == TILE_256 && !qkv_split_ok) continue;
     const TileCost& c = TILE_COST[kind];
     const int64_t tiles = (int64_t)((g.m + c.bm - 1) / c.bm) * ((g.n + c.bn - 1) / c.bn);
-    double rem = (double)(tiles % 256) / 256.0;
     const double full = c.fixed + stages * c.high;
-    double t = (double)(tiles / 256) * full;
+    // `items` work items of `n` stages, at most one a CU at a time
+    auto rounds = [&](int64_t items, double n) {
+      const double rem = (double)(items % 256) / 256.0;
+      return (double)(items / 256) * (c.fixed + n * c.high) + (rem > 0 ? c.fixed + n * (c.low + rem * (c.high - c.low)) : 0.0);
+    };
+    double t = rounds(tiles, stages);
+    int split = 1;
     if (kind == TILE_256) {
       int n_rem = 0;
       double share = 1.0;
-      const int split = choose_k_split(g, g.splitk_ws != nullptr ? g.splitk_ws_bytes : 0, &n_rem, &share);
-      t += split > 1 ? share * full : rem > 0 ? c.fixed + stages * (c.low + rem * (c.high - c.low)) : 0.0;
-    } else if (rem > 0) {
-      t += c.fixed + stages * (c.low + rem * (c.high - c.low));
+      split = choose_k_split(g, ws_bytes, &n_rem, &share);
+      if (split > 1) t = (double)(tiles / 256) * full + share * full;
+    } else if (g.parts != nullptr && g.epilogue != EPI_QKV && kind != TILE_64) {
+      const int64_t n_rem = (tiles + 7) / 8 * 8 % 256;
+      const double uncut = t;
+      for (int s = 2; s <= MOST_CHUNKS && stages / s >= MIN_CHUNK && n_rem > 0 && n_rem * s * c.bm * c.bn * 4 <= (int64_t)g.parts_bytes; ++s) {
+        const double cut = (double)(tiles / 256) * full + rounds(n_rem * s, (double)((stages + s - 1) / s)) +
+                           sharing_cost((double)(c.bm * c.bn) / 16384.0, s, (double)(n_rem * s) / 256.0);
+        if (cut < t && cut < 0.95 * uncut) { t = cut; split = s; }
+      }
     }
     if (scattered) t += c.scatter * std::max(1.0, (double)tiles / 512.0);
     const double margin = kind == TILE_256 && tiles >= 128 ? 1.01 : 1.0;
-    if (t <= best * margin) { best = t; best_kind = (TileKind)kind; }
+    if (t <= best * margin) { best = t; choice = {(TileKind)kind, split}; }
   }
-  return best_kind;
+  return choice;
 }
 
 }  // namespace
@@ -1276,23 +1357,23 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {
   // operands are addressed with 32-bit byte offsets
   if (((int64_t)g.m + 512) * g.k * 2 >= (int64_t)1 << 32 || ((int64_t)g.n + 512) * g.k * 2 >= (int64_t)1 << 32)
     return hipErrorInvalidValue;
-  switch (choose_tile(g)) {
-    case TILE_256: return launch_gemm256(g, st);
+  const auto [kind, split] = choose_tile(g);
+  switch (kind) {
+    case TILE_256: return launch_gemm256(g, split, st);
     case TILE_64: return launch_quarterk(g, st);
-    case TILE_128: return launch_halfk<128, 128>(g, st);
-    case TILE_128x192: return launch_halfk<128, 192>(g, st);
-    case TILE_192: return launch_halfk<192, 192>(g, st);
-    case TILE_256x128: return launch_halfk<256, 128>(g, st);
+    case TILE_128: return launch_halfk<128, 128>(g, split, st);
+    case TILE_128x192: return launch_halfk<128, 192>(g, split, st);
+    case TILE_192: return launch_halfk<192, 192>(g, split, st);
+    case TILE_256x128: return launch_halfk<256, 128>(g, split, st);
   }
   return hipErrorInvalidValue;
 }
 
 void gemm_route(const GemmArgs& g, int* tile_m, int* tile_n, int* k_chunks) {
-  const TileKind kind = choose_tile(g);
+  const auto [kind, split] = choose_tile(g);
   *tile_m = TILE_COST[kind].bm;
   *tile_n = TILE_COST[kind].bn;
-  int n_rem;
-  *k_chunks = kind == TILE_256 ? choose_k_split(g, g.splitk_ws != nullptr ? g.splitk_ws_bytes : 0, &n_rem) : 1;
+  *k_chunks = split;
 }
 
 // Every column tile normalises its rows again, so the line lies where the chip's rounds of tiles cost more in that way

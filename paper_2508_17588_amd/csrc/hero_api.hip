@@ -170,7 +170,8 @@ struct Layout {
   size_t idx_off, a_off, q_off, o_off, f_off, ktmp_off, vtmp_off, splitk_off, splitk_bytes, ws_bytes;
   size_t seen_off, seen_bytes;   // index check: one bit per token, then one verdict word
   size_t stat_off;               // counters (word 0: attention workgroups that took the running-maximum path)
-  size_t parts_off, parts_bytes, arrivals_off;   // partial sums and arrival counters of the narrow models' kernel (0 bytes: not used)
+  size_t parts_off, parts_bytes;   // partial sums of the narrow models' kernel (0 bytes: not used)
+  size_t arrivals_off;             // arrival counters of kernels whose workgroups share a sum
   // bytes of one layer's slabs: S_cur, then K and V^T if it keeps them, then S_prev if it keeps one
   bool keeps_kv(const hero_config& c, int l) const { return l < c.n_shallow || kv_all; }
   bool keeps_prev(const hero_config& c, int l) const { return l >= c.n_shallow || prev_all; }
@@ -210,9 +211,9 @@ Layout make_layout(const hero_config& c) {
     L.vtmp_off = w;
     w += L.vt_bytes;
   }
-  // partial sums of GEMM tiles cut along k: up to 512 blocks of 256 x 256 fp32 (large problems only)
+  // partial sums of GEMM tiles cut along k: up to 512 blocks of 256 x 256 fp32 (few tokens: up to 256 of the smaller tiles)
   L.splitk_off = w;
-  L.splitk_bytes = L.n_tokens >= 2048 ? (size_t)512 * 262144 : 0;
+  L.splitk_bytes = L.n_tokens >= 2048 ? (size_t)512 * 262144 : (size_t)256 * 147456;
   w += L.splitk_bytes;
   L.seen_off = w;
   L.seen_bytes = align_up(((size_t)L.n_tokens + 31) / 32 * 4 + 4, 256);
@@ -224,7 +225,7 @@ Layout make_layout(const hero_config& c) {
                       ? align_up(std::min<size_t>(((size_t)L.n_tokens + 15) / 16 * 4, NARROW_TAIL_BLOCKS) * 16 * c.hidden * 4, 256) : 0;
   w += L.parts_bytes;
   L.arrivals_off = w;
-  if (L.parts_bytes) w += NARROW_TAIL_BLOCKS * 4;
+  w += std::max(NARROW_TAIL_BLOCKS, GEMM_ARRIVALS) * 4;
   L.ws_bytes = w;
   return L;
 }
@@ -271,9 +272,10 @@ struct hero_cache {
   int32_t* ages = nullptr;
   int32_t* idx = nullptr;
   bf16_t *a = nullptr, *q = nullptr, *o = nullptr, *f = nullptr, *ktmp = nullptr, *vtmp = nullptr;
-  float* splitk = nullptr;        // GEMM k-split partial sums (nullptr when the problem is too small to need them)
+  float* splitk = nullptr;        // partial sums of GEMM tiles and attention blocks that are cut
   uint32_t* seen = nullptr;       // index check: token bitmap followed by the verdict word
   uint32_t* stats = nullptr;      // word 0: attention fallback workgroups since create / reset
+  uint32_t* arrivals = nullptr;   // arrival counters, zero between launches
   float2* rope = nullptr;         // rotation table (nullptr without HERO_BLOCK_ROPE)
   std::vector<LayerState> layers;
   // deep-stack sums: slot i holds sum_l S_cur^l taken when the deep layers' fill counts were
@@ -317,6 +319,14 @@ int check_layer(hero_cache_t c, int layer) {
     }                                                                                \
   } while (0)
 
+// Scratch of the GEMMs.  256 x 256 tiles and attention blocks are cut, by kernels that come in pairs, only where there are
+// tokens enough to fill the chip with them.
+bool many_tokens(hero_cache_t c) { return c->lay.n_tokens >= 2048; }
+void use_scratch(hero_cache_t c, GemmArgs& g) {
+  if (many_tokens(c)) { g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes; }
+  g.parts = c->splitk; g.parts_bytes = c->lay.splitk_bytes; g.arrivals = c->arrivals;
+}
+
 // The block of Eq. 2 on the rows listed in `rows` (nullptr = all N rows), writing K/V to
 // (k_dst, vt_dst) and the branch features to s_dst.  It ends before the residual add, unless
 // fuse_resid is set: then the FFN2 kernel adds the stored features of its rows to x itself.
@@ -349,7 +359,7 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
   // (with q/k post-processing the scale is applied there, after the normalisation and rotation)
   const float softmax_scale = 1.4426950408889634f / sqrtf((float)cfg.head_dim);
   g.q_scale = qk_post ? 1.0f : softmax_scale;
-  g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes;
+  use_scratch(c, g);
   if (gemm_takes_ln(g)) {
     const LnInput ln = {x, x_fp32, nullptr, rows, (const bf16_t*)w.ln1_g, (const bf16_t*)w.ln1_b, cfg.ln_eps, m1};
     PROF_LAUNCH(c, HERO_PROF_GEMM_QKV, 6.0 * rd * d, st, launch_gemm_ln(g, ln, st));
@@ -376,7 +386,7 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
   at.q = c->q; at.k = k_dst; at.vt = vt_dst; at.ld_vt = c->lay.n_pad; at.o = c->o;
   at.r = n_rows; at.n_keys = (int)c->lay.n_tokens; at.n_heads = cfg.n_heads; at.head_dim = cfg.head_dim;
   at.q_scale = 1.0f;
-  at.split_ws = c->splitk; at.split_ws_bytes = c->lay.splitk_bytes;    // shared with the GEMMs: same stream, never concurrent
+  if (many_tokens(c)) { at.split_ws = c->splitk; at.split_ws_bytes = c->lay.splitk_bytes; }    // shared with the GEMMs: same stream, never concurrent
   at.fallback_count = c->stats;
   PROF_LAUNCH(c, HERO_PROF_ATTN, 4.0 * rd * n_all, st, launch_attention(at, st));
 
@@ -394,7 +404,7 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
     }
     t.s = s_dst; t.x = x; t.x_fp32 = x_fp32; t.add_to_x = fuse_resid;
     t.parts = (float*)(c->ws + c->lay.parts_off); t.parts_bytes = c->lay.parts_bytes;
-    t.arrivals = (uint32_t*)(c->ws + c->lay.arrivals_off);
+    t.arrivals = c->arrivals;
     PROF_LAUNCH(c, HERO_PROF_GEMM_FF2, 2.0 * rd * (d + 2.0 * cfg.ffn_dim), st, launch_narrow_tail(t, st));
     return HERO_OK;
   }
@@ -403,13 +413,13 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
   g.a = c->o; g.w = (const bf16_t*)w.w_o; g.bias = (const bf16_t*)w.b_o;
   g.m = n_rows; g.n = d; g.k = d; g.epilogue = EPI_SCATTER; g.rows = rows; g.c = s_dst;
   if (adaln) { g.gate_v = mod + 2 * d; g.gate_t = mod + 5 * d; g.n_text = cfg.n_text; }
-  g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes;
+  use_scratch(c, g);
   PROF_LAUNCH(c, HERO_PROF_GEMM_O, 2.0 * rd * d, st, launch_gemm(g, st));
 
   memset(&g, 0, sizeof(g));
   g.a = c->a; g.w = (const bf16_t*)w.w_ff1; g.bias = (const bf16_t*)w.b_ff1;
   g.m = n_rows; g.n = cfg.ffn_dim; g.k = d; g.epilogue = EPI_GELU; g.c = c->f;
-  g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes;
+  use_scratch(c, g);
   if (gemm_takes_ln(g)) {
     const LnInput ln = {x, x_fp32, s_dst, rows, (const bf16_t*)w.ln2_g, (const bf16_t*)w.ln2_b, cfg.ln_eps, m2};
     PROF_LAUNCH(c, HERO_PROF_GEMM_FF1, 2.0 * rd * cfg.ffn_dim, st, launch_gemm_ln(g, ln, st));
@@ -425,7 +435,7 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
   g.m = n_rows; g.n = d; g.k = cfg.ffn_dim; g.epilogue = EPI_SCATTER_ADD; g.rows = rows; g.c = s_dst;
   if (adaln) { g.gate_v = mod + 8 * d; g.gate_t = mod + 11 * d; g.n_text = cfg.n_text; }
   if (fuse_resid) { g.x = x; g.x_fp32 = x_fp32 ? 1 : 0; }
-  g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes;
+  use_scratch(c, g);
   PROF_LAUNCH(c, HERO_PROF_GEMM_FF2, 2.0 * rd * cfg.ffn_dim, st, launch_gemm(g, st));
   return HERO_OK;
 }
@@ -604,6 +614,7 @@ int hero_cache_create(const hero_config* cfg, void* dev_cache, size_t cache_byte
   c->splitk = L.splitk_bytes ? (float*)(c->ws + L.splitk_off) : nullptr;
   c->seen = (uint32_t*)(c->ws + L.seen_off);
   c->stats = (uint32_t*)(c->ws + L.stat_off);
+  c->arrivals = (uint32_t*)(c->ws + L.arrivals_off);
   c->layers.resize(cfg->n_layers);
   if (L.t_bytes) { c->t[0] = (float*)(c->cache + L.t_off[0]); c->t[1] = (float*)(c->cache + L.t_off[1]); }
   if (L.rope_bytes) c->rope = (float2*)(c->cache + L.rope_off);

@@ -100,3 +100,27 @@ __device__ __forceinline__ void lds_fill(u32x4_t rsrc, uint32_t lds_addr, uint32
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                :: "s"(lds_addr), "v"(voffset), "s"(rsrc) : "memory");
 }
+
+// Workgroups that share the sum of one output block: each stores its part, and the one that arrives last adds them up.
+// Parts go past the XCDs' L2s both ways (sc1), and a workgroup's stores are complete before its arrival is counted, so
+// the last one sees all of them; none waits for another.  The count is zero again for the next launch.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t parts_rsrc(float* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ void store_part(__amdgpu_buffer_rsrc_t rs, uint32_t offset, floatx4_t v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), rs, offset, 0, 16);
+}
+__device__ __forceinline__ floatx4_t load_part(__amdgpu_buffer_rsrc_t rs, uint32_t offset) {
+  return __builtin_bit_cast(floatx4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, offset, 0, 16));
+}
+// called by all threads, after store_part; word: an LDS word nothing else uses meanwhile
+__device__ __forceinline__ bool last_to_arrive(uint32_t* count, uint32_t n, uint32_t* word) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) *word = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  const bool last = __builtin_amdgcn_readfirstlane(*word) == n - 1;
+  if (last && threadIdx.x == 0) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  return last;
+}

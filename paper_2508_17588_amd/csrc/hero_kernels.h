@@ -110,6 +110,9 @@ struct GemmArgs {
   float q_scale;        // QKV: the Q third is stored multiplied by this (softmax scale folded into Q)
   float* splitk_ws;     // optional device scratch for k-split partial sums (nullptr: never split)
   size_t splitk_ws_bytes;
+  float* parts;         // scratch for the chunks of smaller tiles cut along k, which need arrivals too (nullptr: never cut)
+  size_t parts_bytes;
+  uint32_t* arrivals;   // GEMM_ARRIVALS counters, zero before and after every launch
   void* x;              // SCATTER_ADD, optional: x[row(m), :] += the stored (rounded) S[row(m), :]  (Alg. 1 residual add)
   int32_t x_fp32;       // x holds fp32 (else bf16)
   const bf16_t* gate_v; // SCATTER*, optional: (acc + bias) is multiplied by gate[n] of the row's stream (adaLN gate)
@@ -117,6 +120,7 @@ struct GemmArgs {
   int32_t n_text;
 };
 
+constexpr int GEMM_ARRIVALS = 256;
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t st);
 // the tile launch_gemm takes for this problem, and the chunks along k of the last round's tiles (1: not cut)
 void gemm_route(const GemmArgs& g, int* tile_m, int* tile_n, int* k_chunks);

@@ -241,26 +241,16 @@ __global__ __launch_bounds__(WAVES * 64) void narrow_tail_kernel(TailArgs a) {
 
   // ---- the workgroup that arrives last adds up the parts, in their order whichever it is ----
   if constexpr (SPLIT > 1) {
-    // Parts go past the XCDs' L2s (sc1) both ways, and the stores are complete before the arrival is counted, so
-    // the last one sees them all; none waits for another.  The count goes back to zero for the next launch.
-    constexpr int PART = WAVES * 64 * TPW * 16, SC1 = 16;            // bytes
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        a.parts + (size_t)row_block * (SPLIT * PART / 4), 0, SPLIT * PART, 0x00020000);
+    constexpr int PART = WAVES * 64 * TPW * 16;        // bytes
+    const __amdgpu_buffer_rsrc_t rs = parts_rsrc(a.parts + (size_t)row_block * (SPLIT * PART / 4), SPLIT * PART);
 #pragma unroll
-    for (int t = 0; t < TPW; ++t)
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[t]), rs, part * PART + (t * WAVES * 64 + tid) * 16, 0, SC1);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) lds.arrived = __hip_atomic_fetch_add(a.arrivals + row_block, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (lds.arrived != SPLIT - 1) return;
-    if (tid == 0) __hip_atomic_store(a.arrivals + row_block, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int t = 0; t < TPW; ++t) store_part(rs, part * PART + (t * WAVES * 64 + tid) * 16, acc[t]);
+    if (!last_to_arrive(a.arrivals + row_block, SPLIT, &lds.arrived)) return;
     floatx4_t p[SPLIT][TPW];
 #pragma unroll
     for (int c = 0; c < SPLIT; ++c)
 #pragma unroll
-      for (int t = 0; t < TPW; ++t)
-        p[c][t] = __builtin_bit_cast(floatx4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, c * PART + (t * WAVES * 64 + tid) * 16, 0, SC1));
+      for (int t = 0; t < TPW; ++t) p[c][t] = load_part(rs, c * PART + (t * WAVES * 64 + tid) * 16);
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
 #pragma unroll
