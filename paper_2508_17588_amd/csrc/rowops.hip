@@ -376,6 +376,24 @@ __device__ __forceinline__ void load8_stream(const bf16_t* p, float* v) {
   for (int i = 0; i < 4; ++i) { v[2 * i] = unpack_lo(a[i]); v[2 * i + 1] = unpack_hi(a[i]); }
 }
 
+// acc += the listed arrays' elements at `at`, in their order; eight arrays are asked for at a time, for with few elements in
+// all the latency of one load after another is what the sum takes (326 x 256: 34 arrays 13 -> 7 us, 8 arrays 6.5 -> 4.5)
+__device__ __forceinline__ void add_features(const FeatureList& fl, int64_t at, float (&acc)[8]) {
+  constexpr int BATCH = 8;
+  for (int l0 = 0; l0 < fl.n; l0 += BATCH) {
+    u32x4_t raw[BATCH];
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i)
+      if (l0 + i < fl.n) raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(fl.p[l0 + i] + at));
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      if (l0 + i >= fl.n) break;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { acc[2 * j] += unpack_lo(raw[i][j]); acc[2 * j + 1] += unpack_hi(raw[i][j]); }
+    }
+  }
+}
+
 template <typename XT, bool HAS_PREV>
 __global__ __launch_bounds__(256) void axpy_features_kernel(
     XT* __restrict__ x, const bf16_t* __restrict__ s_cur, const bf16_t* __restrict__ s_prev,
@@ -430,12 +448,7 @@ __global__ __launch_bounds__(256) void sum_features_kernel(FeatureList fl, float
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
   }
-  for (int l = 0; l < fl.n; ++l) {
-    float v[8];
-    load8_stream(fl.p[l] + c * 8, v);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] += v[j];
-  }
+  add_features(fl, c * 8, acc);
   ResidIO<float>::store8(t + c * 8, acc);
 }
 
@@ -519,14 +532,7 @@ __global__ __launch_bounds__(256) void end_of_cached_step_kernel(
       for (int j = 0; j < 8; ++j) acc[j] += cv[j];
     }
   }
-  if (age != 0) {                       // not refreshed in this step
-    for (int l = 0; l < shallow.n; ++l) {
-      float v[8];
-      load8_stream(shallow.p[l] + c * 8, v);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] += v[j];
-    }
-  }
+  if (age != 0) add_features(shallow, c * 8, acc);       // not refreshed in this step
 #pragma unroll
   for (int j = 0; j < 8; ++j) xv[j] += acc[j];
   ResidIO<XT>::store8(x + c * 8, xv);
