@@ -686,7 +686,8 @@ __device__ __forceinline__ void attention_finish(const AttnArgs& a, int head, in
 }
 
 // ------------------------------------------------------------------------------------------
-// few query blocks, and head_dim 32: 64 queries per workgroup, four waves that share the keys
+// few query blocks, and head_dim 32: 64 queries per workgroup (32 where that leaves most CUs idle), four waves that
+// share the keys
 // ------------------------------------------------------------------------------------------
 // Each wave walks a quarter of the 64-key tiles for the same 64 queries, from K and V^T tiles of its own
 // in LDS (no barrier in the loop); the unnormalised outputs and row sums of the waves add up in LDS at the end,
@@ -698,17 +699,21 @@ __device__ __forceinline__ void attention_finish(const AttnArgs& a, int head, in
 // 14.3 -> 8.7 us, 691 x 2032 x 16 34.1 -> 15.7, 2032 x 2032 x 16 34.7 -> 24.8; head_dim 32, against the running
 // maximum with 256 queries a workgroup: 2032 x 2032 x 8 38.0 -> 13.8, 8000 x 8000 x 16 258 -> 227, 17776 x 17776 x 16
 // 1164 -> 989.  The scale is applied to the fp32 scores.
+// Queries come and outputs leave in whole cache lines, through LDS: in the fragments' order each load of a wave makes 64
+// requests (691 x 2032 x 16 15.5 -> 14.5 us, 2032 x 2032 x 16 26.6 -> 24.7, head_dim 32 2032 x 2032 x 8 13.4 -> 12.1).
 constexpr int SHARE_WAVES = 4;
-template <int HD>
+// QG: groups of 32 queries of a workgroup
+template <int HD, int QG>
 struct ShareKeys {
-  static constexpr int QUADS = HD / 32 * 2 * 4;              // float4 accumulator pieces per lane
+  static constexpr int QUADS = HD / 32 * QG * 4;             // float4 accumulator pieces per lane
   static constexpr int TILE_CHUNKS = BKV * HD / 8;           // 16-byte chunks of a K or V^T tile
-  u32x4_t tiles[SHARE_WAVES][2][TILE_CHUNKS];                         // [wave][K, V^T]; afterwards the partial outputs
-  float sums[SHARE_WAVES][2][64];
-  float refs[SHARE_WAVES][2][64];                            // the waves' reference points (KEYS_RUNNING, KEYS_LAZY)
-  static_assert(QUADS * 64 == 2 * TILE_CHUNKS, "the partial outputs take the place of the tiles");
+  u32x4_t tiles[SHARE_WAVES][2][TILE_CHUNKS];                // [wave][K, V^T]; afterwards the partial outputs
+  u32x4_t rows[QG * 32 * HD / 8];                            // the queries, afterwards their outputs; swizzled like a K tile
+  float sums[SHARE_WAVES][QG][64];
+  float refs[SHARE_WAVES][QG][64];                           // the waves' reference points (KEYS_RUNNING, KEYS_LAZY)
+  static_assert(QUADS * 64 <= 2 * TILE_CHUNKS, "the partial outputs take the place of the tiles");
 };
-template <int HD> using share_keys_lds = __attribute__((address_space(3))) ShareKeys<HD>;
+template <int HD, int QG> using share_keys_lds = __attribute__((address_space(3))) ShareKeys<HD, QG>;
 
 // What the exponentials of a pass refer to:
 //  KEYS_FREE     nothing: exact while every row sum stays within [2^-80, 2^80];
@@ -728,15 +733,15 @@ enum ShareMode { KEYS_FREE, KEYS_RUNNING, KEYS_LAZY, KEYS_SUMS };
 
 // One pass over the keys for queries q0 .. q0+63: leaves the waves' partial outputs in LDS ([wave][quad][lane],
 // quad = (cb*2 + ig)*4 + q) and returns whether another pass is needed (KEYS_FREE, KEYS_SUMS: some row sum is out of range).
-template <int HD, bool SCALED, ShareMode MODE>
-__device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int q0, share_keys_lds<HD>* ldsp, float (&l)[2]) {
-  ShareKeys<HD>& lds = *(ShareKeys<HD>*)ldsp;
+template <int HD, int QG, bool SCALED, ShareMode MODE>
+__device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int q0, share_keys_lds<HD, QG>* ldsp, float (&l)[QG]) {
+  ShareKeys<HD, QG>& lds = *(ShareKeys<HD, QG>*)ldsp;
   constexpr int KCH = HD / 8, VCH = BKV / 8;       // 16-byte chunks per K / V^T tile row
   constexpr int KS = HD / 16, CB = HD / 32;
   constexpr int NF = HD / 8;                       // 1 KB fills per tile, K and V^T each
   constexpr int KROWS = 512 / HD;                  // K rows per fill (V^T: 8)
   constexpr int KPER = 16 / KROWS;                 // fills after which the swizzle repeats (V^T: 2)
-  constexpr int QUADS = ShareKeys<HD>::QUADS;
+  constexpr int QUADS = ShareKeys<HD, QG>::QUADS;
   constexpr bool REFERRED = MODE == KEYS_RUNNING || MODE == KEYS_LAZY;
   const int d = a.n_heads * HD;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -758,7 +763,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
     v_voff[i] = (uint32_t)row * v_row_bytes + ((lane % VCH) ^ ((row >> 1) & (VCH - 1))) * 16;
   }
   const uint32_t lds_k = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr_t)&ldsp->tiles[wave][0][0]);
-  const uint32_t lds_v = lds_k + ShareKeys<HD>::TILE_CHUNKS * 16;
+  const uint32_t lds_v = lds_k + ShareKeys<HD, QG>::TILE_CHUNKS * 16;
   auto fill_k = [&](int tile) {
 #pragma unroll
     for (int i = 0; i < NF; ++i)
@@ -774,29 +779,56 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   const int t_begin = wave * n_tiles / SHARE_WAVES, t_end = (wave + 1) * n_tiles / SHARE_WAVES;
   const int kperm = (lr & ~12) | ((lr & 4) << 1) | ((lr & 8) >> 1);   // K row read as MFMA row lr
 
-  if (t_begin < t_end) fill_k(t_begin);
-  if (MODE != KEYS_SUMS && t_begin < t_end) fill_v(t_begin);
-  bf16x8_t qf[2][KS];
+  // the queries, 16 rows to a wave (rows past the end arrive as zero): whole cache lines, where the fragments' own loads
+  // would make 64 requests each
+  constexpr int QF = QG * 32 / SHARE_WAVES / KROWS > 0 ? QG * 32 / SHARE_WAVES / KROWS : 1;        // fills of a wave
+  const bool fetches = QG * 32 / SHARE_WAVES >= KROWS || wave < QG * 32 / KROWS;
+  {
+    const u32x4_t rsQ = rsrc_words(a.q + (int64_t)q0 * d + head * HD, (uint32_t)(min(QG * 32, a.r - q0) - 1) * k_row_bytes + HD * 2);
+    const uint32_t lds_q = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr_t)&ldsp->rows[0]);
+    if (fetches) {
 #pragma unroll
-  for (int ig = 0; ig < 2; ++ig) {
-    const u32x4_t* qp = reinterpret_cast<const u32x4_t*>(a.q + (int64_t)min(q0 + ig * 32 + lr, a.r - 1) * d + head * HD);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      u32x4_t t = qp[2 * s + lh];
-      qf[ig][s] = *reinterpret_cast<bf16x8_t*>(&t);
+      for (int i = 0; i < QF; ++i) {
+        const int fill = wave * QF + i;
+        lds_fill(rsQ, lds_q + fill * 1024, k_voff[fill % KPER] + (uint32_t)(fill - fill % KPER) * KROWS * k_row_bytes);
+      }
     }
   }
-  floatx16_t o[CB][2];
-  float la[2] = {0.f, 0.f}, lb[2] = {0.f, 0.f};
-  float ref[2] = {0.f, 0.f};
+  if (t_begin < t_end) {
+    fill_k(t_begin);
+    if (MODE != KEYS_SUMS) fill_v(t_begin);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(MODE == KEYS_SUMS ? NF : 2 * NF) : "memory");          // all but these
+  } else {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  asm volatile("s_barrier" ::: "memory");
+  bf16x8_t qf[QG][KS];
+#pragma unroll
+  for (int ig = 0; ig < QG; ++ig) {
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int row = ig * 32 + lr;
+      const u32x4_t t = lds.rows[row * KCH + ((2 * s + lh) ^ ((row >> 1) & (KCH - 1)))];
+      qf[ig][s] = *reinterpret_cast<const bf16x8_t*>(&t);
+    }
+  }
+  floatx16_t o[CB][QG];
+  float la[QG] = {}, lb[QG] = {};
+  float ref[QG] = {};
   bool jumped = false, shifted = false;            // KEYS_LAZY: sums beyond repair (per lane); some reference point is not 0
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-    for (int ig = 0; ig < 2; ++ig)
+    for (int ig = 0; ig < QG; ++ig)
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[cb][ig][e] = 0.f;
 
+  auto total = [&](const float (&x)[QG], const float (&y)[QG]) {     // of a lane's queries
+    float sum = 0.f;
+#pragma unroll
+    for (int ig = 0; ig < QG; ++ig) sum += x[ig] + y[ig];
+    return sum;
+  };
   enum Tile { FIRST_TILE, PLAIN, SHIFTED };                           // PLAIN: no query has a reference point but 0
   auto step = [&](int tile, auto kind) {
     constexpr int KIND = decltype(kind)::value;
@@ -815,31 +847,34 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");               // read: the next K tile may land
     __builtin_amdgcn_sched_barrier(0);
     if (more) fill_k(tile + 1);
-    bf16x8_t pf[2][2][2];          // [jb][ig][t]
+    bf16x8_t pf[2][QG][2];         // [jb][ig][t]
     // scores of 32 keys; accumulators start at -reference where Q carries the scale
-    auto scores = [&](int jb, floatx16_t (&s)[2]) {
+    auto scores = [&](int jb, floatx16_t (&s)[QG]) {
 #pragma unroll
-      for (int ig = 0; ig < 2; ++ig)
+      for (int ig = 0; ig < QG; ++ig)
 #pragma unroll
         for (int e = 0; e < 16; ++e) s[ig][e] = KIND == SHIFTED && !SCALED ? -ref[ig] : 0.f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-        for (int ig = 0; ig < 2; ++ig) s[ig] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[jb][ks], qf[ig][ks], s[ig], 0, 0, 0);
+        for (int ig = 0; ig < QG; ++ig) s[ig] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[jb][ks], qf[ig][ks], s[ig], 0, 0, 0);
       if ((tile + 1) * BKV > a.n_keys) {                             // the ragged last tile
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int j = tile * BKV + jb * 32 + 16 * (g >> 1) + 8 * lh + 4 * (g & 1) + e;
-            if (j >= a.n_keys) { s[0][4 * g + e] = -INFINITY; s[1][4 * g + e] = -INFINITY; }
+            if (j >= a.n_keys) {
+#pragma unroll
+              for (int ig = 0; ig < QG; ++ig) s[ig][4 * g + e] = -INFINITY;
+            }
           }
       }
     };
     // probabilities of 32 keys, packed; their sums are added to sa, sb
-    auto probabilities = [&](int jb, const floatx16_t (&s)[2], float (&sa)[2], float (&sb)[2], auto exponent) {
+    auto probabilities = [&](int jb, const floatx16_t (&s)[QG], float (&sa)[QG], float (&sb)[QG], auto exponent) {
 #pragma unroll
-      for (int ig = 0; ig < 2; ++ig)
+      for (int ig = 0; ig < QG; ++ig)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           uint32_t pk[4];
@@ -858,25 +893,27 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
     if constexpr (!FIRST && MODE != KEYS_RUNNING) {
 #pragma unroll
       for (int jb = 0; jb < 2; ++jb) {
-        floatx16_t s[2];
+        floatx16_t s[QG];
         scores(jb, s);
         probabilities(jb, s, la, lb, [&](float v, int ig) {
           return !SCALED ? v : KIND == SHIFTED ? __builtin_fmaf(v, a.q_scale, -ref[ig]) : v * a.q_scale;
         });
       }
     } else {
-      floatx16_t s[2][2];
-      float na[2] = {la[0], la[1]}, nb[2] = {lb[0], lb[1]};          // the sums with this tile's
+      floatx16_t s[2][QG];
+      float na[QG], nb[QG];                                          // the sums with this tile's
+#pragma unroll
+      for (int ig = 0; ig < QG; ++ig) { na[ig] = la[ig]; nb[ig] = lb[ig]; }
 #pragma unroll
       for (int jb = 0; jb < 2; ++jb) {
         scores(jb, s[jb]);
         if (!FIRST) probabilities(jb, s[jb], na, nb, [&](float v, int ig) { return SCALED ? __builtin_fmaf(v, a.q_scale, -ref[ig]) : v; });
       }
-      const bool beyond = !(na[0] + nb[0] + na[1] + nb[1] <= 0x1p26f);
+      const bool beyond = !(total(na, nb) <= 0x1p26f);
       if (FIRST || __builtin_expect(__builtin_amdgcn_ballot_w64(beyond) != 0, 0)) {
-        float shift[2];                                              // what the scores have yet to lose
+        float shift[QG];                                             // what the scores have yet to lose
 #pragma unroll
-        for (int ig = 0; ig < 2; ++ig) {
+        for (int ig = 0; ig < QG; ++ig) {
           float mx = s[0][ig][0];
 #pragma unroll
           for (int e = 1; e < 32; ++e) mx = fmaxf(mx, s[e >> 4][ig][e & 15]);
@@ -905,7 +942,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
           probabilities(jb, s[jb], na, nb, [&](float v, int ig) { return SCALED ? __builtin_fmaf(v, a.q_scale, -shift[ig]) : v - shift[ig]; });
       }
 #pragma unroll
-      for (int ig = 0; ig < 2; ++ig) { la[ig] = na[ig]; lb[ig] = nb[ig]; }
+      for (int ig = 0; ig < QG; ++ig) { la[ig] = na[ig]; lb[ig] = nb[ig]; }
     }
     if constexpr (MODE == KEYS_SUMS) return;
     if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NF) : "memory");   // all but the next K tile: V^T is in LDS
@@ -927,15 +964,15 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
 #pragma unroll
       for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int ig = 0; ig < 2; ++ig)
+        for (int ig = 0; ig < QG; ++ig)
           o[cb][ig] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[cb][x], pf[x >> 1][ig][x & 1], o[cb][ig], 0, 0, 0);
     if constexpr (MODE == KEYS_LAZY && !FIRST) {
-      const float sum = la[0] + lb[0] + la[1] + lb[1];
+      const float sum = total(la, lb);
       if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(sum <= 0x1p26f)) != 0, 0)) {
         jumped |= !(sum <= 0x1p120f);
         shifted = true;
 #pragma unroll
-        for (int ig = 0; ig < 2; ++ig) {
+        for (int ig = 0; ig < QG; ++ig) {
           const float mine = la[ig] + lb[ig];
           auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mine), __float_as_uint(mine), false, false);
           const float most = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));     // both halves of the query's keys
@@ -960,7 +997,10 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
     if (tile < t_end) step(tile++, First{});
   }
   if constexpr (MODE == KEYS_LAZY) {
-    shifted = __builtin_amdgcn_ballot_w64(ref[0] != 0.f || ref[1] != 0.f) != 0;
+    bool referred = false;
+#pragma unroll
+    for (int ig = 0; ig < QG; ++ig) referred |= ref[ig] != 0.f;
+    shifted = __builtin_amdgcn_ballot_w64(referred) != 0;
     for (; tile < t_end && !shifted; ++tile) step(tile, Plain{});
   }
   if constexpr (REFERRED) {
@@ -974,7 +1014,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-      for (int ig = 0; ig < 2; ++ig)
+      for (int ig = 0; ig < QG; ++ig)
 #pragma unroll
         for (int e = 0; e < 16; ++e) z = __builtin_fmaf(o[cb][ig][e], 0.f, z);
     jumped |= z != 0.f;
@@ -982,12 +1022,12 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   // the four partial results meet in LDS: [wave][quad][lane], quad = (cb*2 + ig)*4 + q
   if constexpr (REFERRED) {
 #pragma unroll
-    for (int ig = 0; ig < 2; ++ig) lds.refs[wave][ig][lane] = t_begin < t_end ? ref[ig] : -INFINITY;
+    for (int ig = 0; ig < QG; ++ig) lds.refs[wave][ig][lane] = t_begin < t_end ? ref[ig] : -INFINITY;
   }
   __syncthreads();
   if constexpr (REFERRED) {
 #pragma unroll
-    for (int ig = 0; ig < 2; ++ig) {
+    for (int ig = 0; ig < QG; ++ig) {
       float top = lds.refs[0][ig][lane];
 #pragma unroll
       for (int w = 1; w < SHARE_WAVES; ++w) top = fmaxf(top, lds.refs[w][ig][lane]);
@@ -1004,17 +1044,17 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
 #pragma unroll
   for (int cb = 0; cb < (MODE == KEYS_SUMS ? 0 : CB); ++cb)
 #pragma unroll
-    for (int ig = 0; ig < 2; ++ig)
+    for (int ig = 0; ig < QG; ++ig)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         floatx4_t v = {o[cb][ig][4 * q], o[cb][ig][4 * q + 1], o[cb][ig][4 * q + 2], o[cb][ig][4 * q + 3]};
-        part[(wave * QUADS + (cb * 2 + ig) * 4 + q) * 64 + lane] = v;
+        part[(wave * QUADS + (cb * QG + ig) * 4 + q) * 64 + lane] = v;
       }
 #pragma unroll
-  for (int ig = 0; ig < 2; ++ig) lds.sums[wave][ig][lane] = la[ig] + lb[ig];
+  for (int ig = 0; ig < QG; ++ig) lds.sums[wave][ig][lane] = la[ig] + lb[ig];
   __syncthreads();
 #pragma unroll
-  for (int ig = 0; ig < 2; ++ig) {
+  for (int ig = 0; ig < QG; ++ig) {
     l[ig] = 0.f;
 #pragma unroll
     for (int w = 0; w < SHARE_WAVES; ++w) l[ig] += lds.sums[w][ig][lane];
@@ -1022,22 +1062,25 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   }
   if (MODE == KEYS_RUNNING) return false;
   if (MODE == KEYS_LAZY) return __syncthreads_or(jumped) != 0;
-  const int bad = !(l[0] >= 0x1p-80f && l[0] <= 0x1p80f) | !(l[1] >= 0x1p-80f && l[1] <= 0x1p80f);
+  int bad = 0;
+#pragma unroll
+  for (int ig = 0; ig < QG; ++ig) bad |= !(l[ig] >= 0x1p-80f && l[ig] <= 0x1p80f);
   return __syncthreads_or(bad) != 0;
 }
 
-// Adds up the waves' partial outputs of queries q0 .. q0+63 and stores them: each wave its share of the quads; lane owns
-// query lr of group ig, channels 8q + 4lh .. +3.
-template <int HD>
-__device__ __forceinline__ void share_keys_store(const AttnArgs& a, int head, int q0, share_keys_lds<HD>* ldsp, float l0, float l1) {
-  constexpr int QUADS = ShareKeys<HD>::QUADS;
+// Adds up the waves' partial outputs of the workgroup's queries and stores them: each wave its share of the quads (lane:
+// query lr of group ig, channels 8q + 4lh .. +3), through LDS, so that the rows leave in whole cache lines.
+template <int HD, int QG>
+__device__ __forceinline__ void share_keys_store(const AttnArgs& a, int head, int q0, share_keys_lds<HD, QG>* ldsp, const float (&l)[QG]) {
+  constexpr int QUADS = ShareKeys<HD, QG>::QUADS, KCH = HD / 8;
+  ShareKeys<HD, QG>& lds = *(ShareKeys<HD, QG>*)ldsp;
   const int d = a.n_heads * HD;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lh = lane >> 5;
-  const floatx4_t* part = reinterpret_cast<const floatx4_t*>(&((ShareKeys<HD>*)ldsp)->tiles[0][0][0]);
+  const floatx4_t* part = reinterpret_cast<const floatx4_t*>(&lds.tiles[0][0][0]);
 #pragma unroll
   for (int i = 0; i < QUADS / SHARE_WAVES; ++i) {
-    const int quad = wave * (QUADS / SHARE_WAVES) + i, q = quad & 3, ig = (quad >> 2) & 1, cb = quad >> 3;
+    const int quad = wave * (QUADS / SHARE_WAVES) + i, q = quad & 3, ig = (quad >> 2) % QG, cb = (quad >> 2) / QG;
     floatx4_t v = part[quad * 64 + lane];
 #pragma unroll
     for (int w = 1; w < SHARE_WAVES; ++w) {
@@ -1045,62 +1088,77 @@ __device__ __forceinline__ void share_keys_store(const AttnArgs& a, int head, in
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] += t[e];
     }
-    const float inv = 1.0f / (ig ? l1 : l0);
-    const int qrow = q0 + ig * 32 + lr;
-    if (qrow < a.r) {
-      u32x2_t pk = {pack_bf16x2_hw(v[0] * inv, v[1] * inv), pack_bf16x2_hw(v[2] * inv, v[3] * inv)};
-      *reinterpret_cast<u32x2_t*>(a.o + (int64_t)qrow * d + head * HD + cb * 32 + 8 * q + 4 * lh) = pk;
-    }
+    const float inv = 1.0f / (ig ? l[QG - 1] : l[0]);
+    const int row = ig * 32 + lr, chunk = cb * 4 + q;
+    char* dst = reinterpret_cast<char*>(&lds.rows[row * KCH + (chunk ^ ((row >> 1) & (KCH - 1)))]) + 8 * lh;
+    *reinterpret_cast<u32x2_t*>(dst) = u32x2_t{pack_bf16x2_hw(v[0] * inv, v[1] * inv), pack_bf16x2_hw(v[2] * inv, v[3] * inv)};
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < (QG * 32 * KCH + SHARE_WAVES * 64 - 1) / (SHARE_WAVES * 64); ++i) {
+    const int p = i * SHARE_WAVES * 64 + tid, row = p / KCH, chunk = p % KCH;
+    if (row < QG * 32 && q0 + row < a.r)
+      *reinterpret_cast<u32x4_t*>(a.o + (int64_t)(q0 + row) * d + head * HD + chunk * 8) = lds.rows[row * KCH + (chunk ^ ((row >> 1) & (KCH - 1)))];
   }
 }
 
-// A pass over the workgroup's 64 queries does not hold: a second one gives them reference points.  The
+// A pass over the workgroup's queries does not hold: a second one gives them reference points.  The
 // fallback counter counts blocks of 256 queries, so the workgroup then looks at the row sums of the block's earlier
-// 64s, as far as one that counts.  Out of line: inlined, it makes the kernel park registers around its loop.
+// workgroups, as far as one that counts.  Out of line: inlined, it makes the kernel park registers around its loop.
 // Kernel times with scores of standard deviation 1.44 / 35 in log2 units (35: every block falls back), one wave of four
 // with queries of its own in the running-maximum form before: 326 x 326 x 4 heads 7.8 / 29.3 -> 20.0 us,
 // 2032 x 2032 x 16 25.4 / 137.9 -> 82.3; with some 64s of most blocks in range (17): 166.7 -> 100.6.
-template <int HD, bool SCALED>
-__device__ __attribute__((noinline)) void share_keys_fallback(AttnArgs a, int head, int qb, share_keys_lds<HD>* lds) {
-  float l[2];
-  share_keys_pass<HD, SCALED, KEYS_RUNNING>(a, head, qb * 64, lds, l);
-  share_keys_store<HD>(a, head, qb * 64, lds, l[0], l[1]);
+template <int HD, int QG, bool SCALED>
+__device__ __attribute__((noinline)) void share_keys_fallback(AttnArgs a, int head, int qb, share_keys_lds<HD, QG>* lds) {
+  constexpr int Q = QG * 32;
+  float l[QG];
+  share_keys_pass<HD, QG, SCALED, KEYS_RUNNING>(a, head, qb * Q, lds, l);
+  share_keys_store<HD, QG>(a, head, qb * Q, lds, l);
   if (HD == 32 || a.fallback_count == nullptr) return;        // (head_dim 32 keeps no count)
-  for (int b = qb & ~3; b < qb; ++b) {
+  for (int b = qb / (256 / Q) * (256 / Q); b < qb; ++b) {
     __syncthreads();
-    if (share_keys_pass<HD, SCALED, KEYS_SUMS>(a, head, b * 64, lds, l)) return;
+    if (share_keys_pass<HD, QG, SCALED, KEYS_SUMS>(a, head, b * Q, lds, l)) return;
   }
   if (threadIdx.x == 0) atomicAdd(a.fallback_count, 1u);
 }
 
-template <int HD, bool SCALED, ShareMode MODE>
+template <int HD, int QG, bool SCALED, ShareMode MODE>
 __global__ __launch_bounds__(SHARE_WAVES * 64, 2) void attention_share_keys_kernel(AttnArgs a, int n_qblocks, int n_blocks, int per_xcd) {
   extern __shared__ u32x4_t smem[];
   const int logical = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (logical >= n_blocks) return;
   const int head = logical / n_qblocks, qb = logical % n_qblocks;
-  auto* lds = (share_keys_lds<HD>*)(lds_ptr_t)smem;
-  float l[2];
-  const bool bad = share_keys_pass<HD, SCALED, MODE>(a, head, qb * 64, lds, l);
+  auto* lds = (share_keys_lds<HD, QG>*)(lds_ptr_t)smem;
+  float l[QG];
+  const bool bad = share_keys_pass<HD, QG, SCALED, MODE>(a, head, qb * QG * 32, lds, l);
   if constexpr (MODE != KEYS_RUNNING) {
     if (bad) {
-      share_keys_fallback<HD, SCALED>(a, head, qb, lds);
+      share_keys_fallback<HD, QG, SCALED>(a, head, qb, lds);
       return;
     }
   }
-  share_keys_store<HD>(a, head, qb * 64, lds, l[0], l[1]);
+  share_keys_store<HD, QG>(a, head, qb * QG * 32, lds, l);
 }
 
-template <int HD, bool SCALED, ShareMode MODE>
+template <int HD, int QG, bool SCALED, ShareMode MODE>
 hipError_t launch_share_keys(const AttnArgs& a, hipStream_t st) {
   static std::atomic<uint64_t> lds_allowed{0};
-  auto kern = attention_share_keys_kernel<HD, SCALED, MODE>;
-  constexpr int LDS = (int)sizeof(ShareKeys<HD>);
+  auto kern = attention_share_keys_kernel<HD, QG, SCALED, MODE>;
+  constexpr int LDS = (int)sizeof(ShareKeys<HD, QG>);
   hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), LDS, lds_allowed);
   if (e != hipSuccess) return e;
-  const int n_q64 = (a.r + 63) / 64, n_blocks = n_q64 * a.n_heads, per_xcd = (n_blocks + 7) / 8;
-  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(SHARE_WAVES * 64), LDS, st, a, n_q64, n_blocks, per_xcd);
+  const int n_qblocks = (a.r + QG * 32 - 1) / (QG * 32), n_blocks = n_qblocks * a.n_heads, per_xcd = (n_blocks + 7) / 8;
+  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(SHARE_WAVES * 64), LDS, st, a, n_qblocks, n_blocks, per_xcd);
   return hipGetLastError();
+}
+
+// 32 queries to a workgroup halve a tile's chain, and pay as long as every workgroup has a CU of its own: 500 x 2000 x 4
+// heads 13.3 -> 10.0 us, 1000 x 2000 x 8 (256 workgroups) 13.9 -> 10.7, but 691 x 2032 x 16 (352) 14.8 -> 16.0 and
+// 1000 x 4000 x 16 (512) 24.5 -> 27.7.
+template <int HD, bool SCALED, ShareMode MODE>
+hipError_t launch_share_keys(const AttnArgs& a, hipStream_t st) {
+  if ((int64_t)((a.r + 31) / 32) * a.n_heads <= 256) return launch_share_keys<HD, 1, SCALED, MODE>(a, st);
+  return launch_share_keys<HD, 2, SCALED, MODE>(a, st);
 }
 
 // The chip runs 512 of the 256-query workgroups at a time (two per CU).  The n_rem blocks of the last

@@ -131,3 +131,10 @@ def test_price_of_spread_scores(hd, heads, passes):
             torch.cuda.synchronize()
             times[size].append(begin.elapsed_time(end))
     assert np.median(times[24]) <= passes * np.median(times[1]), times
+
+
+@pytest.mark.parametrize("scores,v_exp,hd", [("up", 60, 32), ("rise", 0, 32), ("spread", 0, 32), ("spike", 60, 32),
+                                             ("up", 0, 64), ("rise", 0, 64), ("spread", 0, 64), ("spike", 0, 64)])
+def test_attention_of_unusual_scores_with_64_queries_to_a_workgroup(scores, v_exp, hd):
+    assert B.hero_attention_route(300, 520, 27, hd)[0] == 64
+    test_attention_of_unusual_scores(scores, v_exp, hd, 300, 520, 27)          # 270 blocks of 32 queries

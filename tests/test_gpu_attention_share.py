@@ -45,3 +45,19 @@ def test_key_and_query_counts(r, n_keys, heads, hd):
 def test_a_block_of_256_queries_is_counted_once(bad, blocks):
     assert run(300, 700, 3, 64, bad) == 3 * blocks
     assert run(300, 700, 3, 32, bad) == 0            # only head_dim 64 keeps a count
+
+
+# more than 256 blocks of 32 queries: 64 to a workgroup; up to 256: 32
+@pytest.mark.parametrize("hd", [32, 64])
+@pytest.mark.parametrize("r,n_keys,heads", [(1, 65, 256), (1, 65, 257), (33, 63, 128), (33, 64, 129), (65, 65, 90), (200, 255, 40),
+                                            (256, 257, 32), (257, 257, 32), (300, 513, 27)])
+def test_either_number_of_queries_to_a_workgroup(r, n_keys, heads, hd):
+    assert B.hero_attention_route(r, n_keys, heads, hd)[0] == 64
+    assert run(r, n_keys, heads, hd) == 0
+
+
+@pytest.mark.parametrize("bad,blocks", [((77,), 1), ((3, 77, 130, 255), 1), ((70, 290), 2), ((256, 299), 1)])
+def test_a_block_is_counted_once_with_64_queries_to_a_workgroup(bad, blocks):
+    assert B.hero_attention_route(300, 700, 27, 64)[0] == 64
+    assert run(300, 700, 27, 64, bad) == 27 * blocks
+    assert run(300, 700, 27, 32, bad) == 0
