@@ -647,11 +647,33 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& g, const float* tile
       return v;
     };
     if (use_rows) {
-      // scattered columns: lanes along m, whose tokens are neighbours in a V^T row
-      for (int u = tid; u < BM * BN; u += NT) {
-        const int nl = u / BM, ml = u - nl * BM, n = n0 + nl, m = m0 + ml;
-        if (m < g.m && n >= 2 * g.d && n < g.n)
-          g.vt_out[(int64_t)(n - 2 * g.d) * g.ld_vt + g.rows[m]] = f32_to_bf16_hw(value(ml, nl) + bf16_to_f32(g.bias[n]));
+      // scattered columns: lanes along m, whose tokens are neighbours in a V^T row; a thread's row stays the same from
+      // column to column where the threads are a multiple of the rows, and eight columns go side by side
+      constexpr int COLS = 8;
+      constexpr bool SAME_ROW = NT % BM == 0;
+      int64_t token = 0;
+      if (SAME_ROW) token = g.rows[min(m0 + tid % BM, g.m - 1)];
+      for (int u0 = tid; u0 < BM * BN; u0 += COLS * NT) {
+        int nl[COLS], ml[COLS];
+        int64_t at[COLS];
+        float bias[COLS];
+        bool ok[COLS];
+#pragma unroll
+        for (int i = 0; i < COLS; ++i) {
+          const int u = min(u0 + i * NT, BM * BN - 1);
+          nl[i] = u / BM;
+          ml[i] = u - nl[i] * BM;
+          const int n = n0 + nl[i], m = m0 + ml[i];
+          ok[i] = u0 + i * NT < BM * BN && m < g.m && n >= 2 * g.d && n < g.n;
+          bias[i] = bf16_to_f32(g.bias[min(n, g.n - 1)]);
+          at[i] = (int64_t)(n - 2 * g.d) * g.ld_vt + (SAME_ROW ? token : (int64_t)g.rows[min(m, g.m - 1)]);
+        }
+        bf16_t v[COLS];
+#pragma unroll
+        for (int i = 0; i < COLS; ++i) v[i] = f32_to_bf16_hw(value(ml[i], nl[i]) + bias[i]);
+#pragma unroll
+        for (int i = 0; i < COLS; ++i)
+          if (ok[i]) g.vt_out[at[i]] = v[i];
       }
     } else {
       // eight columns x BM/8 pieces of eight rows at a time
