@@ -708,7 +708,7 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& g, const float* tile
 // CUs at work at k = 12288) and, at k = 3072, start-up and epilogue, about 7 of 50 us.  Kernel times of FFN2 after
 // the kernel that writes its rows, against 256 x 256 or the earlier 128 x 128 tiles: 4485 rows at hidden 1920
 // 174 -> 124 us (192 x 192), 1755 rows at hidden 3072 202 -> 153 (128 x 192), 2925 rows 241, fix-up included, -> 194.
-// Tiles of the last round cut along k: slots 0 .. full_items - 1 are whole work items, the `tiles` slots after them are cut
+// Tiles (of less than 256 x 256) of the last round cut along k: slots 0 .. full_items - 1 are whole work items, the `tiles` slots after them are cut
 // in `chunks`, whose sums the workgroup that arrives last adds up (one counter a tile, one block of BM x BN floats a chunk).
 constexpr int MOST_CHUNKS = 8;
 struct Cut {
@@ -716,6 +716,49 @@ struct Cut {
   float* parts;
   uint32_t* arrivals;
 };
+
+// workgroup id -> tile slot and k-chunk: all first chunks of the cut tiles, then all second ones, ..., so that the chunks
+// of a tile stay on the XCD that owns its range of tiles (slots are a multiple of 8)
+struct CutItem { int slot, chunk, n_chunks; };
+__device__ __forceinline__ CutItem cut_item(const Cut& cut) {
+  const int r = (int)blockIdx.x - cut.full_items;
+  if (r < 0) return {(int)blockIdx.x, 0, 1};
+  return {cut.full_items + r % cut.tiles, r / cut.tiles, cut.chunks};
+}
+
+// The workgroup's chunk of a tile, PIECES floatx4 of each of NT threads at piece(i) in LDS, becomes part of the tile's
+// sum; true for the workgroup that arrives last, which then finds the whole sum there, added in the order of the chunks.
+// All chunks' pieces are asked for two at a time: the loads' latency is what this costs.
+template <int PIECES, int NT, typename Piece>
+__device__ __forceinline__ bool share_sum(const Cut& cut, const CutItem& it, Piece piece, int tid, uint32_t* word) {
+  constexpr int PART = PIECES * NT * 16, N = 2;
+  const int tile = it.slot - cut.full_items;
+  const __amdgpu_buffer_rsrc_t rs = parts_rsrc(cut.parts + (size_t)tile * it.n_chunks * (PART / 4), (uint32_t)it.n_chunks * PART);
+#pragma unroll
+  for (int i = 0; i < PIECES; ++i) store_part(rs, (uint32_t)it.chunk * PART + (i * NT + tid) * 16, *piece(i));
+  if (!last_to_arrive(cut.arrivals + tile, it.n_chunks, word)) return false;
+#pragma unroll 2
+  for (int h = 0; h < PIECES; h += N) {
+    floatx4_t v[MOST_CHUNKS][N];
+#pragma unroll
+    for (int c = 0; c < MOST_CHUNKS; ++c)
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        if (c < it.n_chunks) v[c][i] = load_part(rs, (uint32_t)c * PART + ((h + i) * NT + tid) * 16);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      floatx4_t sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < MOST_CHUNKS; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (c < it.n_chunks) sum[e] += v[c][i][e];
+      *piece(h + i) = sum;
+    }
+  }
+  __syncthreads();
+  return true;
+}
 
 template <int BM, int BN>
 struct HalfK {
@@ -732,17 +775,9 @@ __global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m
   constexpr int NF = (BM + BN) / 64;                   // 1 KB fills of a wave per stage
   constexpr int RING = C::RING, STAGE = C::STAGE;
   static_assert(BM % 64 == 0 && BN % 64 == 0 && RING >= 3 && NF <= MB * NB + 2, "tile shape");
-  // workgroup id -> tile slot and k-chunk: all first chunks of the cut tiles, then all second ones, ..., so that the
-  // chunks of a tile stay on the XCD that owns its range of tiles (slots are a multiple of 8)
-  int item = blockIdx.x, chunk = 0, n_chunks = 1;
-  if (CUT && item >= cut.full_items) {
-    const int r = item - cut.full_items;
-    item = cut.full_items + r % cut.tiles;
-    chunk = r / cut.tiles;
-    n_chunks = cut.chunks;
-  }
+  const CutItem it = CUT ? cut_item(cut) : CutItem{(int)blockIdx.x, 0, 1};
   int m0, n0;
-  if (!tile_origin(item, BM, BN, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+  if (!tile_origin(it.slot, BM, BN, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
 
   extern __shared__ u32x4_t smem[];
   const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) void*)smem;
@@ -763,7 +798,7 @@ __global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m
     voff[i] = (uint32_t)(i < BM / 64 ? m0 + row : n0 + row - BM) * row_bytes + chunk * 16;
   }
   const int n_stages = g.k / SBK;
-  const int stage_begin = chunk * n_stages / n_chunks, stage_end = (chunk + 1) * n_stages / n_chunks;
+  const int stage_begin = it.chunk * n_stages / it.n_chunks, stage_end = (it.chunk + 1) * n_stages / it.n_chunks;
   auto fill = [&](int slot, int stage, int i) {
     lds_fill(i < BM / 64 ? rsA : rsB, lds0 + wave * 1024 + i * 8192 + (uint32_t)slot * STAGE, voff[i],
              (uint32_t)min(stage, stage_end - 1) * (SBK * 2));           // (past the end: the last stage again, unread)
@@ -863,36 +898,9 @@ __global__ __launch_bounds__(512) void gemm_halfk_kernel(GemmArgs g, int tiles_m
     }
     __syncthreads();
   }
-  if (CUT && n_chunks > 1) {
-    // the chunk's sums, 8 KB per store instruction; the last to arrive adds the chunks in their order
-    constexpr int PIECES = BM * BN / 4 / 512, PART = BM * BN * 4;
-    const __amdgpu_buffer_rsrc_t rs = parts_rsrc(cut.parts + (size_t)(item - cut.full_items) * n_chunks * (PART / 4), (uint32_t)n_chunks * PART);
+  if constexpr (CUT) {
     auto piece = [&](int i) { const int p = i * 512 + tid; return reinterpret_cast<floatx4_t*>(tile + p / (BN / 4) * LDT + p % (BN / 4) * 4); };
-#pragma unroll
-    for (int i = 0; i < PIECES; ++i) store_part(rs, (uint32_t)chunk * PART + (i * 512 + tid) * 16, *piece(i));
-    if (!last_to_arrive(cut.arrivals + (item - cut.full_items), n_chunks, reinterpret_cast<uint32_t*>(tile + BM * LDT))) return;
-    // (two pieces of every chunk on their way at a time: the loads' latency is what this costs)
-    constexpr int N = 2, MOST = MOST_CHUNKS;
-#pragma unroll 2
-    for (int h = 0; h < PIECES; h += N) {
-      floatx4_t v[MOST][N];
-#pragma unroll
-      for (int c = 0; c < MOST; ++c)
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-          if (c < n_chunks) v[c][i] = load_part(rs, (uint32_t)c * PART + ((h + i) * 512 + tid) * 16);
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        floatx4_t sum = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < MOST; ++c)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (c < n_chunks) sum[e] += v[c][i][e];
-        *piece(h + i) = sum;
-      }
-    }
-    __syncthreads();
+    if (it.n_chunks > 1 && !share_sum<BM * BN / 4 / 512, 512>(cut, it, piece, tid, reinterpret_cast<uint32_t*>(tile + BM * LDT))) return;
   }
   stream_tile<EPI, BM, BN, 512, 1>(g, tile, m0, n0, tid);
 }
@@ -908,10 +916,11 @@ constexpr int QK_RING = 2;
 constexpr int QK_LDS = 4 * QK_RING * QK_STAGE;
 static_assert(4 * 64 * 68 * 4 <= QK_LDS, "the four partial tiles must fit");
 
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tiles_m, int tiles_n, int per_xcd, int group_m) {
+template <int EPI, bool CUT>
+__global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tiles_m, int tiles_n, int per_xcd, int group_m, Cut cut) {
+  const CutItem it = CUT ? cut_item(cut) : CutItem{(int)blockIdx.x, 0, 1};
   int m0, n0;
-  if (!tile_origin(blockIdx.x, 64, 64, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
+  if (!tile_origin(it.slot, 64, 64, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
   extern __shared__ u32x4_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -931,7 +940,8 @@ __global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tile
     voffB[i] = (uint32_t)(n0 + row) * row_bytes + chunk * 16;
   }
   const int n_stages = g.k / SBK;
-  const int begin = wave * n_stages / 4, end = (wave + 1) * n_stages / 4;
+  const int first = it.chunk * n_stages / it.n_chunks, mine = (it.chunk + 1) * n_stages / it.n_chunks - first;
+  const int begin = first + wave * mine / 4, end = first + (wave + 1) * mine / 4;
   auto fill = [&](int slot, int stage) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -983,7 +993,7 @@ __global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tile
   }
   __syncthreads();                       // every wave has read its last stage: no fill is in flight
   float* tile = reinterpret_cast<float*>(smem);
-  float* mine = tile + (wave * 64 + lr) * 68 + 4 * lh;
+  float* sums = tile + (wave * 64 + lr) * 68 + 4 * lh;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -991,9 +1001,29 @@ __global__ __launch_bounds__(256) void gemm_quarterk_kernel(GemmArgs g, int tile
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         floatx4_t v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        *reinterpret_cast<floatx4_t*>(mine + 32 * i * 68 + 32 * j + 8 * q) = v;
+        *reinterpret_cast<floatx4_t*>(sums + 32 * i * 68 + 32 * j + 8 * q) = v;
       }
   __syncthreads();
+  if constexpr (CUT) {
+    if (it.n_chunks > 1) {
+      // (the waves' quarters are added first, into the first one's place)
+      auto piece = [&](int c, int i) { return reinterpret_cast<floatx4_t*>(tile + (c * 64 + i * 16 + tid / 16) * 68 + tid % 16 * 4); };
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        floatx4_t v = *piece(0, i);
+#pragma unroll
+        for (int c = 1; c < 4; ++c) {
+          const floatx4_t w = *piece(c, i);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] += w[e];
+        }
+        *piece(0, i) = v;
+      }
+      if (!share_sum<4, 256>(cut, it, [&](int i) { return piece(0, i); }, tid, reinterpret_cast<uint32_t*>(tile + 4 * 64 * 68))) return;
+      stream_tile<EPI, 64, 64, 256, 1>(g, tile, m0, n0, tid);
+      return;
+    }
+  }
   stream_tile<EPI, 64, 64, 256, 4>(g, tile, m0, n0, tid);
 }
 
@@ -1218,27 +1248,22 @@ hipError_t launch_tiles(const GemmArgs& g, int bm, int bn, int threads, int lds,
   const int tiles_m = (g.m + bm - 1) / bm, tiles_n = (g.n + bn - 1) / bn;
   const int per_xcd = (tiles_m * tiles_n + 7) / 8;
   const int group_m = (g.k >= 8192 || tiles_m <= 24) ? 4 : 8;      // as for the 256 x 256 tiles
-  if constexpr (std::is_invocable_v<Kernel, GemmArgs, int, int, int, int, Cut>) {
-    const int slots = per_xcd * 8, full = chunks > 1 ? slots / 256 * 256 : slots;
-    const Cut cut = {full, slots - full, chunks, g.parts, g.arrivals};
-    hipLaunchKernelGGL(KERN, dim3(full + (slots - full) * chunks), dim3(threads), lds, st, g, tiles_m, tiles_n, per_xcd, group_m, cut);
-  } else {
-    hipLaunchKernelGGL(KERN, dim3(per_xcd * 8), dim3(threads), lds, st, g, tiles_m, tiles_n, per_xcd, group_m);
-  }
+  const int slots = per_xcd * 8, full = chunks > 1 ? slots / 256 * 256 : slots;
+  const Cut cut = {full, slots - full, chunks, g.parts, g.arrivals};
+  hipLaunchKernelGGL(KERN, dim3(full + (slots - full) * chunks), dim3(threads), lds, st, g, tiles_m, tiles_n, per_xcd, group_m, cut);
   return hipGetLastError();
 }
-using TileKernel = void (*)(GemmArgs, int, int, int, int);
-using CutTileKernel = void (*)(GemmArgs, int, int, int, int, Cut);
+using TileKernel = void (*)(GemmArgs, int, int, int, int, Cut);
 
 template <int BM, int BN, bool CUT>
 hipError_t launch_halfk(const GemmArgs& g, int split, hipStream_t st) {
   constexpr int LDS = HalfK<BM, BN>::LDS;
   switch (g.epilogue) {
-    case EPI_PLAIN: return launch_tiles<CutTileKernel, gemm_halfk_kernel<BM, BN, EPI_PLAIN, false>>(g, BM, BN, 512, LDS, 1, st);
-    case EPI_GELU: return launch_tiles<CutTileKernel, gemm_halfk_kernel<BM, BN, EPI_GELU, CUT>>(g, BM, BN, 512, LDS, split, st);
-    case EPI_QKV: return launch_tiles<CutTileKernel, gemm_halfk_kernel<BM, BN, EPI_QKV, false>>(g, BM, BN, 512, LDS, 1, st);
-    case EPI_SCATTER: return launch_tiles<CutTileKernel, gemm_halfk_kernel<BM, BN, EPI_SCATTER, CUT>>(g, BM, BN, 512, LDS, split, st);
-    case EPI_SCATTER_ADD: return launch_tiles<CutTileKernel, gemm_halfk_kernel<BM, BN, EPI_SCATTER_ADD, CUT>>(g, BM, BN, 512, LDS, split, st);
+    case EPI_PLAIN: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_PLAIN, false>>(g, BM, BN, 512, LDS, 1, st);
+    case EPI_GELU: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_GELU, CUT>>(g, BM, BN, 512, LDS, split, st);
+    case EPI_QKV: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_QKV, false>>(g, BM, BN, 512, LDS, 1, st);
+    case EPI_SCATTER: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_SCATTER, CUT>>(g, BM, BN, 512, LDS, split, st);
+    case EPI_SCATTER_ADD: return launch_tiles<TileKernel, gemm_halfk_kernel<BM, BN, EPI_SCATTER_ADD, CUT>>(g, BM, BN, 512, LDS, split, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1247,13 +1272,14 @@ hipError_t launch_halfk(const GemmArgs& g, int split, hipStream_t st) {
   return split > 1 ? launch_halfk<BM, BN, true>(g, split, st) : launch_halfk<BM, BN, false>(g, 1, st);
 }
 
-hipError_t launch_quarterk(const GemmArgs& g, hipStream_t st) {
+template <bool CUT>
+hipError_t launch_quarterk(const GemmArgs& g, int split, hipStream_t st) {
   switch (g.epilogue) {
-    case EPI_PLAIN: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_PLAIN>>(g, 64, 64, 256, QK_LDS, 1, st);
-    case EPI_GELU: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_GELU>>(g, 64, 64, 256, QK_LDS, 1, st);
-    case EPI_QKV: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_QKV>>(g, 64, 64, 256, QK_LDS, 1, st);
-    case EPI_SCATTER: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_SCATTER>>(g, 64, 64, 256, QK_LDS, 1, st);
-    case EPI_SCATTER_ADD: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_SCATTER_ADD>>(g, 64, 64, 256, QK_LDS, 1, st);
+    case EPI_PLAIN: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_PLAIN, false>>(g, 64, 64, 256, QK_LDS, 1, st);
+    case EPI_GELU: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_GELU, CUT>>(g, 64, 64, 256, QK_LDS, split, st);
+    case EPI_QKV: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_QKV, false>>(g, 64, 64, 256, QK_LDS, 1, st);
+    case EPI_SCATTER: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_SCATTER, CUT>>(g, 64, 64, 256, QK_LDS, split, st);
+    case EPI_SCATTER_ADD: return launch_tiles<TileKernel, gemm_quarterk_kernel<EPI_SCATTER_ADD, CUT>>(g, 64, 64, 256, QK_LDS, split, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1301,12 +1327,14 @@ constexpr TileCost TILE_COST[] = {{64, 64, 2.2f, 0.17f, 0.18f, 5.f},   {128, 128
                                   {256, 128, 6.f, 0.55f, 0.87f, 9.5f}, {256, 256, 6.f, 0.72f, 1.48f, 7.5f}};
 
 // What it takes workgroups to share tiles cut along k (us): each stores its part, the last to arrive loads them all past
-// the caches, at 35 - 40 GB/s a CU.  part: size in units of 64 KB; fill: work items of the round a CU.  Over 132 problems
-// (out-projection, FFN1 and FFN2 of 330 .. 8775 rows, hidden 512 .. 3072) and every way to cut them, the kind and cut chosen
-// take 0.4 % longer than the best on average, 2.7 % without cuts, and never longer than what is chosen without:
-// FFN2 of 700 x 1536 44.7 -> 29.4 us (128 x 128 in 3), 1500 x 3072 144.8 -> 118.8 (192 x 192 in 2).
-constexpr int MIN_CHUNK = 6;                             // stages of a chunk
-double sharing_cost(double part, int split, double fill) { return 2.0 + part * (split + 4.5 * fill); }
+// the caches, at 35 - 40 GB/s a CU.  fill: work items of the round a CU.  Over 345 problems (out-projection, FFN1 and FFN2
+// of 45 .. 8775 rows, hidden 320 .. 3072) and every way to cut them, the kind and cut chosen take 0.7 % longer than the best
+// on average, 5.1 % without cuts, and never longer than what is chosen without: FFN2 of 45 x 1536 20.8 -> 14.0 us (64 x 64
+// in 6), 84 x 1920 25.7 -> 16.3 (64 x 64 in 4), 700 x 1536 42.0 -> 29.8 (128 x 128 in 3), 1500 x 3072 143 -> 126 (192 x 192 in 2).
+double sharing_cost(const TileCost& c, int split, double fill) {
+  const double part = (double)(c.bm * c.bn) / 16384.0;          // in units of 64 KB
+  return c.bm == 64 ? 1.0 + 0.8 * split + 1.5 * fill : 2.0 + part * (split + 4.5 * fill);
+}
 
 struct TileChoice {
   TileKind kind;
@@ -1344,12 +1372,13 @@ TileChoice choose_tile(const GemmArgs& g) {
       double share = 1.0;
       split = choose_k_split(g, ws_bytes, &n_rem, &share);
       if (split > 1) t = (double)(tiles / 256) * full + share * full;
-    } else if (g.parts != nullptr && g.epilogue != EPI_QKV && kind != TILE_64) {
+    } else if (g.parts != nullptr && g.epilogue != EPI_QKV) {
       const int64_t n_rem = (tiles + 7) / 8 * 8 % 256;
+      const int least = kind == TILE_64 ? 4 : 6;              // stages of a chunk
       const double uncut = t;
-      for (int s = 2; s <= MOST_CHUNKS && stages / s >= MIN_CHUNK && n_rem > 0 && n_rem * s * c.bm * c.bn * 4 <= (int64_t)g.parts_bytes; ++s) {
+      for (int s = 2; s <= MOST_CHUNKS && stages / s >= least && n_rem > 0 && n_rem * s * c.bm * c.bn * 4 <= (int64_t)g.parts_bytes; ++s) {
         const double cut = (double)(tiles / 256) * full + rounds(n_rem * s, (double)((stages + s - 1) / s)) +
-                           sharing_cost((double)(c.bm * c.bn) / 16384.0, s, (double)(n_rem * s) / 256.0);
+                           sharing_cost(c, s, (double)(n_rem * s) / 256.0);
         if (cut < t && cut < 0.95 * uncut) { t = cut; split = s; }
       }
     }
@@ -1382,7 +1411,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {
   const auto [kind, split] = choose_tile(g);
   switch (kind) {
     case TILE_256: return launch_gemm256(g, split, st);
-    case TILE_64: return launch_quarterk(g, st);
+    case TILE_64: return split > 1 ? launch_quarterk<true>(g, split, st) : launch_quarterk<false>(g, 1, st);
     case TILE_128: return launch_halfk<128, 128>(g, split, st);
     case TILE_128x192: return launch_halfk<128, 192>(g, split, st);
     case TILE_192: return launch_halfk<192, 192>(g, split, st);

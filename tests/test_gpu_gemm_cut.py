@@ -19,6 +19,9 @@ SHAPES = [                     # heads of 64 channels, height, width, text rows
     (45, 20, 35, 1),           # 701: 192 x 192 in 4
     (49, 20, 35, 1),           # 701: 256 x 128 in 3
     (47, 48, 64, 5),           # 3077: 192 x 192, a round of whole tiles, then 16 tiles in 7
+    (24, 6, 7, 3),             # 45: 64 x 64 in 6
+    (31, 8, 10, 4),            # 84: 64 x 64 in 4, columns end inside the last group of eight tiles
+    (17, 12, 12, 6),           # 150: 64 x 64
 ]
 
 
@@ -33,12 +36,12 @@ def test_cut_layers(shape):
     run_block(config(*shape))
 
 
-@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[3]])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[3], SHAPES[9]])
 def test_cut_layers_modulated_bf16_stream(shape):
     run_block(config(*shape, flags=BLOCK_ADALN, fp32=False))
 
 
-@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[5], SHAPES[7]])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[5], SHAPES[7], SHAPES[8]])
 def test_every_call_gives_the_same_bits(shape):
     cfg = config(*shape)
     gen = torch.Generator(device="cuda")
