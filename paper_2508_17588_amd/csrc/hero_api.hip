@@ -382,7 +382,7 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
     PROF_LAUNCH(c, HERO_PROF_QKPOST, rd * 8.0, st, launch_qk_post(qa, st));      // q and k rows, in and out
   }
 
-  AttnArgs at;
+  AttnArgs at = {};
   at.q = c->q; at.k = k_dst; at.vt = vt_dst; at.ld_vt = c->lay.n_pad; at.o = c->o;
   at.r = n_rows; at.n_keys = (int)c->lay.n_tokens; at.n_heads = cfg.n_heads; at.head_dim = cfg.head_dim;
   at.q_scale = 1.0f;
@@ -985,7 +985,7 @@ int hero_attention_route(int32_t r, int32_t n_keys, int32_t n_heads, int32_t hea
   if (head_dim != 32 && head_dim != 64) return fail(HERO_ERR_SHAPE, "head_dim must be 32 or 64");
   if (!attention_offsets_fit(n_keys, (int64_t)n_heads * head_dim, ((int64_t)n_keys + 63) / 64 * 64))
     return fail(HERO_ERR_SHAPE, "beyond the 32-bit operand offsets");
-  AttnArgs a;
+  AttnArgs a = {};
   memset(&a, 0, sizeof(a));
   a.r = r; a.n_keys = n_keys; a.n_heads = n_heads; a.head_dim = head_dim;
   if (scratch_bytes > 0) { a.split_ws = reinterpret_cast<float*>(&a); a.split_ws_bytes = scratch_bytes; }
@@ -1002,7 +1002,7 @@ int hero_attention_counted(const void* dev_q, const void* dev_k, const void* dev
   if (ld_vt % 64 != 0 || ld_vt < n_keys) return fail(HERO_ERR_SHAPE, "ld_vt must be a multiple of 64 and >= n_keys");
   if (!attention_offsets_fit(n_keys, (int64_t)n_heads * head_dim, ld_vt))
     return fail(HERO_ERR_SHAPE, "(n_keys + 256) * hidden * 2 and hidden * ld_vt * 2 must stay below 2^32 (32-bit operand offsets)");
-  AttnArgs a;
+  AttnArgs a = {};
   a.q = (const bf16_t*)dev_q; a.k = (const bf16_t*)dev_k; a.vt = (const bf16_t*)dev_vt; a.ld_vt = ld_vt;
   a.o = (bf16_t*)dev_o; a.r = r; a.n_keys = n_keys; a.n_heads = n_heads; a.head_dim = head_dim;
   a.q_scale = 1.4426950408889634f / sqrtf((float)head_dim);
