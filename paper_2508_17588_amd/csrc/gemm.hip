@@ -107,7 +107,7 @@ __device__ __forceinline__ bool tile_origin(int slot, int bm, int bn, int tiles_
   return true;
 }
 
-template <int EPI>
+template <int EPI, int HALVES>
 __device__ __forceinline__ void epilogue256(const GemmArgs& g, floatx16_t (&acc)[4][2], int m0, int n0, int wave,
                                             int lane, char* region);
 
@@ -276,16 +276,20 @@ __global__ __launch_bounds__(512) void gemm256_kernel(GemmArgs g, int tiles_m, i
     return;
   }
   __syncthreads();                       // every wave is done with the ring
-  epilogue256<EPI>(g, acc, m0, n0, wave, lane, reinterpret_cast<char*>(smem) + wave * STAGE_REGION);
+  epilogue256<EPI, 2>(g, acc, m0, n0, wave, lane, reinterpret_cast<char*>(smem) + wave * STAGE_REGION);
 }
 
 // Adds up the k-chunks of the split tiles and sends the sums through the epilogue.  One
 // single-wave workgroup per 128 x 64 wave sub-tile (8 per tile), so that even a few dozen split
-// tiles spread over the whole chip; the 32 loads of a chunk are independent and in flight together.
+// tiles spread over the whole chip; the loads of a chunk are independent and in flight together.
+// FFN2's epilogue is the longest (S and x are read, added to and written back, row by row) and sets the time: there a wave
+// takes half a sub-tile (FFN2 with its fix-up, 17776 rows x 1920 channels 528 -> 518 us, 33976 x 3072 2086 -> 2071).
+template <int EPI> constexpr int fixup_waves = EPI == EPI_SCATTER_ADD ? 16 : 8;      // to a tile
 template <int EPI>
 __global__ __launch_bounds__(64) void gemm256_fixup_kernel(GemmArgs g, int tiles_m, int tiles_n, int per_xcd,
                                                            int group_m, SplitK sk) {
-  const int tile = blockIdx.x >> 3, wave = blockIdx.x & 7;
+  constexpr int HALVES = fixup_waves<EPI> == 16 ? 1 : 2, LOADS = 16 * HALVES;
+  const int tile = blockIdx.x / fixup_waves<EPI>, wave = (blockIdx.x * HALVES / 2) & 7, half = HALVES == 1 ? blockIdx.x & 1 : 0;
   int m0, n0;
   if (!tile_origin(sk.full_items + tile, 256, 256, tiles_m, tiles_n, per_xcd, group_m, m0, n0)) return;
   extern __shared__ u32x4_t smem[];
@@ -297,20 +301,20 @@ __global__ __launch_bounds__(64) void gemm256_fixup_kernel(GemmArgs g, int tiles
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  const float* part = sk.ws + (size_t)tile * sk.split * 65536 + (wave * 64 + lane) * 4;
+  const float* part = sk.ws + (size_t)tile * sk.split * 65536 + half * 16 * 2048 + (wave * 64 + lane) * 4;
   for (int c = 0; c < sk.split; ++c, part += 65536) {
-    floatx4_t v[32];
+    floatx4_t v[LOADS];
 #pragma unroll
-    for (int x = 0; x < 32; ++x) v[x] = __builtin_nontemporal_load(reinterpret_cast<const floatx4_t*>(part + x * 2048));
+    for (int x = 0; x < LOADS; ++x) v[x] = __builtin_nontemporal_load(reinterpret_cast<const floatx4_t*>(part + x * 2048));
 #pragma unroll
-    for (int x = 0; x < 32; ++x)
+    for (int x = 0; x < LOADS; ++x)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[x >> 3][(x >> 2) & 1][4 * (x & 3) + e] += v[x][e];
   }
-  epilogue256<EPI>(g, acc, m0, n0, wave, lane, reinterpret_cast<char*>(smem));
+  epilogue256<EPI, HALVES>(g, acc, m0 + 64 * half, n0, wave, lane, reinterpret_cast<char*>(smem));
 }
 
-template <int EPI>
+template <int EPI, int HALVES>
 __device__ __forceinline__ void epilogue256(const GemmArgs& g, floatx16_t (&acc)[4][2], int m0, int n0, int wave,
                                             int lane, char* region) {
   const int wm0 = (wave & 1) * 128, wn0 = (wave >> 1) * 64;
@@ -428,9 +432,9 @@ __device__ __forceinline__ void epilogue256(const GemmArgs& g, floatx16_t (&acc)
   };
 
   if (EPI == EPI_SCATTER_ADD) {
-    // two halves of 64 rows staged in fp32; S[row] += . with one rounding
+    // halves of 64 rows staged in fp32; S[row] += . with one rounding
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < HALVES; ++h) {
 #pragma unroll
       for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
@@ -1224,8 +1228,8 @@ hipError_t launch_gemm256(const GemmArgs& g, int split, hipStream_t st) {
     if (e != hipSuccess) return e;                                                                       \
     hipLaunchKernelGGL(kern, grid, block, GEMM256_LDS, st, g, tiles_m, tiles_n, per_xcd, group_m, sk);   \
     if (n_split_tiles > 0)                                                                               \
-      hipLaunchKernelGGL(fix, dim3(n_split_tiles * 8), dim3(64), STAGE_REGION, st, g, tiles_m, tiles_n,  \
-                         per_xcd, group_m, sk);                                                          \
+      hipLaunchKernelGGL(fix, dim3(n_split_tiles * fixup_waves<E>), dim3(64), STAGE_REGION, st, g, tiles_m, \
+                         tiles_n, per_xcd, group_m, sk);                                                         \
   } while (0)
   switch (g.epilogue) {
     case EPI_PLAIN: HERO_GEMM256_LAUNCH(EPI_PLAIN); break;
