@@ -122,8 +122,9 @@ const char* hero_last_error(void);
 int hero_num_selected(const hero_config* cfg, int32_t* n_sel_host);
 
 /* Bytes of device memory the handle needs: cache (persistent features, K/V,
- * token ages) and workspace (per-call temporaries).  HERO_ERR_SHAPE for a configuration
- * the kernels do not support; among the limits, (tokens + 512) * max(hidden, ffn_dim) * 2
+ * token ages, counters) and workspace (per-call temporaries: from one call to the next only the zero
+ * columns that pad V^T have to stay, where some layer keeps no K/V, and what views 5 and 6 of
+ * hero_cache_view show).  HERO_ERR_SHAPE for a configuration the kernels do not support; among the limits, (tokens + 512) * max(hidden, ffn_dim) * 2
  * must stay below 2^32 (32-bit operand offsets in the GEMM and attention kernels), e.g.
  * about 174 000 tokens at ffn_dim 12288. */
 int hero_cache_bytes(const hero_config* cfg, size_t* cache_bytes, size_t* workspace_bytes);

@@ -165,13 +165,13 @@ struct Layout {
   size_t s_bytes, k_bytes, vt_bytes;
   size_t t_off[2], t_bytes;      // fp32 sums of the deep layers' features (two generations); 0 bytes if < 2 deep layers
   size_t rope_off, rope_bytes;   // (cos, sin) of every video token's rotation angles; 0 bytes without HERO_BLOCK_ROPE
+  size_t arrivals_off;           // arrival counters of kernels whose workgroups share a sum
   size_t cache_bytes;
   // workspace
   size_t idx_off, a_off, q_off, o_off, f_off, ktmp_off, vtmp_off, splitk_off, splitk_bytes, ws_bytes;
   size_t seen_off, seen_bytes;   // index check: one bit per token, then one verdict word
   size_t stat_off;               // counters (word 0: attention workgroups that took the running-maximum path)
   size_t parts_off, parts_bytes;   // partial sums of the narrow models' kernel (0 bytes: not used)
-  size_t arrivals_off;             // arrival counters of kernels whose workgroups share a sum
   // bytes of one layer's slabs: S_cur, then K and V^T if it keeps them, then S_prev if it keeps one
   bool keeps_kv(const hero_config& c, int l) const { return l < c.n_shallow || kv_all; }
   bool keeps_prev(const hero_config& c, int l) const { return l >= c.n_shallow || prev_all; }
@@ -179,6 +179,8 @@ struct Layout {
     return s_bytes + (keeps_kv(c, l) ? k_bytes + vt_bytes : 0) + (keeps_prev(c, l) ? s_bytes : 0);
   }
 };
+
+constexpr int ARRIVAL_COUNTERS = std::max(NARROW_TAIL_BLOCKS, GEMM_ARRIVALS);
 
 Layout make_layout(const hero_config& c) {
   Layout L;
@@ -198,6 +200,9 @@ Layout make_layout(const hero_config& c) {
   L.t_off[1] = off; off += L.t_bytes;
   L.rope_bytes = (c.block_flags & HERO_BLOCK_ROPE) ? align_up((size_t)L.n_video * (c.head_dim / 2) * sizeof(float2), 256) : 0;
   L.rope_off = off; off += L.rope_bytes;
+  // (not in the workspace: they have to be zero from one call to the next, and nothing else it holds is needed that long
+  // but the columns that pad a deep layer's V^T)
+  L.arrivals_off = off; off += ARRIVAL_COUNTERS * sizeof(uint32_t);
   L.cache_bytes = off;
   size_t w = 0;
   L.idx_off = w; w += align_up((size_t)L.n_tokens * 4, 256);
@@ -224,8 +229,6 @@ Layout make_layout(const hero_config& c) {
   L.parts_bytes = narrow_tail_fits(1, c.hidden, c.ffn_dim)
                       ? align_up(std::min<size_t>(((size_t)L.n_tokens + 15) / 16 * 4, NARROW_TAIL_BLOCKS) * 16 * c.hidden * 4, 256) : 0;
   w += L.parts_bytes;
-  L.arrivals_off = w;
-  w += std::max(NARROW_TAIL_BLOCKS, GEMM_ARRIVALS) * 4;
   L.ws_bytes = w;
   return L;
 }
@@ -614,7 +617,7 @@ int hero_cache_create(const hero_config* cfg, void* dev_cache, size_t cache_byte
   c->splitk = L.splitk_bytes ? (float*)(c->ws + L.splitk_off) : nullptr;
   c->seen = (uint32_t*)(c->ws + L.seen_off);
   c->stats = (uint32_t*)(c->ws + L.stat_off);
-  c->arrivals = (uint32_t*)(c->ws + L.arrivals_off);
+  c->arrivals = (uint32_t*)(c->cache + L.arrivals_off);
   c->layers.resize(cfg->n_layers);
   if (L.t_bytes) { c->t[0] = (float*)(c->cache + L.t_off[0]); c->t[1] = (float*)(c->cache + L.t_off[1]); }
   if (L.rope_bytes) c->rope = (float2*)(c->cache + L.rope_off);
