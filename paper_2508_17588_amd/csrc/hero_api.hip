@@ -354,7 +354,6 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
     m1.n_text = m2.n_text = cfg.n_text;
   }
   GemmArgs g;
-  memset(&g, 0, sizeof(g));
   g.a = c->a; g.w = (const bf16_t*)w.w_qkv; g.bias = (const bf16_t*)w.b_qkv;
   g.m = n_rows; g.n = 3 * d; g.k = d; g.epilogue = EPI_QKV; g.rows = rows;
   g.c = c->q; g.k_out = k_dst; g.vt_out = vt_dst; g.ld_vt = c->lay.n_pad; g.d = d;
@@ -374,7 +373,6 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
   }
   if (qk_post) {
     QkPostArgs qa;
-    memset(&qa, 0, sizeof(qa));
     qa.q = c->q; qa.k = k_dst; qa.rows = rows; qa.n_rows = n_rows; qa.d = d; qa.head_dim = cfg.head_dim;
     qa.n_text = cfg.n_text; qa.q_scale = softmax_scale;
     if (cfg.block_flags & HERO_BLOCK_QKNORM) {
@@ -385,7 +383,7 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
     PROF_LAUNCH(c, HERO_PROF_QKPOST, rd * 8.0, st, launch_qk_post(qa, st));      // q and k rows, in and out
   }
 
-  AttnArgs at = {};
+  AttnArgs at;
   at.q = c->q; at.k = k_dst; at.vt = vt_dst; at.ld_vt = c->lay.n_pad; at.o = c->o;
   at.r = n_rows; at.n_keys = (int)c->lay.n_tokens; at.n_heads = cfg.n_heads; at.head_dim = cfg.head_dim;
   at.q_scale = 1.0f;
@@ -395,7 +393,6 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
 
   if (narrow_tail_fits(n_rows, d, cfg.ffn_dim)) {
     TailArgs t;
-    memset(&t, 0, sizeof(t));
     t.o = c->o; t.rows = rows; t.n_rows = n_rows; t.hidden = d; t.ffn = cfg.ffn_dim;
     t.w_o = (const bf16_t*)w.w_o; t.b_o = (const bf16_t*)w.b_o;
     t.w1 = (const bf16_t*)w.w_ff1; t.b1 = (const bf16_t*)w.b_ff1;
@@ -412,14 +409,14 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
     return HERO_OK;
   }
 
-  memset(&g, 0, sizeof(g));
+  g = GemmArgs();
   g.a = c->o; g.w = (const bf16_t*)w.w_o; g.bias = (const bf16_t*)w.b_o;
   g.m = n_rows; g.n = d; g.k = d; g.epilogue = EPI_SCATTER; g.rows = rows; g.c = s_dst;
   if (adaln) { g.gate_v = mod + 2 * d; g.gate_t = mod + 5 * d; g.n_text = cfg.n_text; }
   use_scratch(c, g);
   PROF_LAUNCH(c, HERO_PROF_GEMM_O, 2.0 * rd * d, st, launch_gemm(g, st));
 
-  memset(&g, 0, sizeof(g));
+  g = GemmArgs();
   g.a = c->a; g.w = (const bf16_t*)w.w_ff1; g.bias = (const bf16_t*)w.b_ff1;
   g.m = n_rows; g.n = cfg.ffn_dim; g.k = d; g.epilogue = EPI_GELU; g.c = c->f;
   use_scratch(c, g);
@@ -433,7 +430,7 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
     PROF_LAUNCH(c, HERO_PROF_GEMM_FF1, 2.0 * rd * cfg.ffn_dim, st, launch_gemm(g, st));
   }
 
-  memset(&g, 0, sizeof(g));
+  g = GemmArgs();
   g.a = c->f; g.w = (const bf16_t*)w.w_ff2; g.bias = (const bf16_t*)w.b_ff2;
   g.m = n_rows; g.n = d; g.k = cfg.ffn_dim; g.epilogue = EPI_SCATTER_ADD; g.rows = rows; g.c = s_dst;
   if (adaln) { g.gate_v = mod + 8 * d; g.gate_t = mod + 11 * d; g.n_text = cfg.n_text; }
@@ -925,7 +922,6 @@ int hero_linear_scratch(const void* dev_a, const void* dev_w, const void* dev_bi
   if (rc) return rc;
   if (!aligned16({dev_scratch})) return fail(HERO_ERR_INVALID_ARG, "scratch must be 16-byte aligned");
   GemmArgs g;
-  memset(&g, 0, sizeof(g));
   g.a = (const bf16_t*)dev_a; g.w = (const bf16_t*)dev_w; g.bias = (const bf16_t*)dev_bias;
   g.m = m; g.n = n; g.k = k; g.epilogue = act ? EPI_GELU : EPI_PLAIN; g.c = (bf16_t*)dev_c;
   g.splitk_ws = (float*)dev_scratch; g.splitk_ws_bytes = dev_scratch ? scratch_bytes : 0;
@@ -945,7 +941,6 @@ int hero_linear_static(const void* dev_a, const void* dev_w, const void* dev_bia
   if (m == 0) return HERO_OK;
   // what hero_linear_scratch would want for this problem; anything beyond the library's array is refused
   GemmArgs g;
-  memset(&g, 0, sizeof(g));
   g.m = m; g.n = n; g.k = k; g.epilogue = act ? EPI_GELU : EPI_PLAIN;
   const size_t want = gemm_wanted_scratch_bytes(g);
   if (want > STATIC_SCRATCH_BYTES)
@@ -969,7 +964,6 @@ int hero_linear_route(int32_t m, int32_t n, int32_t k, int32_t what, int32_t lis
   if (!gemm_offsets_fit(m, n, k)) return fail(HERO_ERR_SHAPE, "beyond the 32-bit operand offsets");
   static const int32_t any_row = 0;
   GemmArgs g;
-  memset(&g, 0, sizeof(g));
   g.m = m; g.n = n; g.k = k; g.d = n / 3;
   static const int epilogue[] = {EPI_PLAIN, EPI_GELU, EPI_QKV, EPI_SCATTER, EPI_GELU, EPI_SCATTER_ADD};
   g.epilogue = epilogue[what];
@@ -988,8 +982,7 @@ int hero_attention_route(int32_t r, int32_t n_keys, int32_t n_heads, int32_t hea
   if (head_dim != 32 && head_dim != 64) return fail(HERO_ERR_SHAPE, "head_dim must be 32 or 64");
   if (!attention_offsets_fit(n_keys, (int64_t)n_heads * head_dim, ((int64_t)n_keys + 63) / 64 * 64))
     return fail(HERO_ERR_SHAPE, "beyond the 32-bit operand offsets");
-  AttnArgs a = {};
-  memset(&a, 0, sizeof(a));
+  AttnArgs a;
   a.r = r; a.n_keys = n_keys; a.n_heads = n_heads; a.head_dim = head_dim;
   if (scratch_bytes > 0) { a.split_ws = reinterpret_cast<float*>(&a); a.split_ws_bytes = scratch_bytes; }
   attention_route(a, queries, key_ranges);
@@ -1005,7 +998,7 @@ int hero_attention_counted(const void* dev_q, const void* dev_k, const void* dev
   if (ld_vt % 64 != 0 || ld_vt < n_keys) return fail(HERO_ERR_SHAPE, "ld_vt must be a multiple of 64 and >= n_keys");
   if (!attention_offsets_fit(n_keys, (int64_t)n_heads * head_dim, ld_vt))
     return fail(HERO_ERR_SHAPE, "(n_keys + 256) * hidden * 2 and hidden * ld_vt * 2 must stay below 2^32 (32-bit operand offsets)");
-  AttnArgs a = {};
+  AttnArgs a;
   a.q = (const bf16_t*)dev_q; a.k = (const bf16_t*)dev_k; a.vt = (const bf16_t*)dev_vt; a.ld_vt = ld_vt;
   a.o = (bf16_t*)dev_o; a.r = r; a.n_keys = n_keys; a.n_heads = n_heads; a.head_dim = head_dim;
   a.q_scale = 1.4426950408889634f / sqrtf((float)head_dim);

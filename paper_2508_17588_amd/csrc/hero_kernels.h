@@ -20,17 +20,20 @@ inline hipError_t allow_dynamic_lds(const void* kern, int bytes, std::atomic<uin
   return e;
 }
 
+// Every member of the structures below has a value from the start: a launcher that does not know a member yet hands over
+// "none", and not what lay on its stack.
+
 // Patch grid of Eq. 4 and the closed-form output offsets of the selection list.
 // n_take[class]: tokens taken per patch; class = 2*(clipped bottom row) + (clipped right column).
 struct SelectGeom {
-  int32_t frames, height, width, n_text;
-  int32_t patch_h, patch_w;
-  int32_t grid_h, grid_w;        // patches per frame along y / x (ceil)
-  int32_t n_patches;             // frames * grid_h * grid_w
-  int32_t n_take[4];
-  int32_t take_per_full_row;     // picks of one patch-row that is not the last one
-  int32_t take_per_frame;
-  int32_t n_sel;                 // total picks
+  int32_t frames = 0, height = 0, width = 0, n_text = 0;
+  int32_t patch_h = 0, patch_w = 0;
+  int32_t grid_h = 0, grid_w = 0;  // patches per frame along y / x (ceil)
+  int32_t n_patches = 0;           // frames * grid_h * grid_w
+  int32_t n_take[4] = {};
+  int32_t take_per_full_row = 0;   // picks of one patch-row that is not the last one
+  int32_t take_per_frame = 0;
+  int32_t n_sel = 0;               // total picks
 };
 
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st);
@@ -52,13 +55,13 @@ hipError_t launch_gather_ln(const void* x, bool x_fp32, const bf16_t* add, const
 
 // q / k post-processing (per-head LayerNorm, rotary positions on video rows, softmax scale on q), in place
 struct QkPostArgs {
-  bf16_t* q;                 // [n_rows, d]
-  bf16_t* k;                 // [*, d], row rows[i] (or i)
-  const int32_t* rows;
-  int32_t n_rows, d, head_dim, n_text;
-  const bf16_t *qn_g, *qn_b, *kn_g, *kn_b;   // [head_dim]; qn_g == nullptr: no normalisation
-  const float2* rope;        // [n_video, head_dim/2] (cos, sin); nullptr: no rotation
-  float q_scale;
+  bf16_t* q = nullptr;           // [n_rows, d]
+  bf16_t* k = nullptr;           // [*, d], row rows[i] (or i)
+  const int32_t* rows = nullptr;
+  int32_t n_rows = 0, d = 0, head_dim = 0, n_text = 0;
+  const bf16_t *qn_g = nullptr, *qn_b = nullptr, *kn_g = nullptr, *kn_b = nullptr;  // [head_dim]; qn_g == nullptr: no normalisation
+  const float2* rope = nullptr;  // [n_video, head_dim/2] (cos, sin); nullptr: no rotation
+  float q_scale = 0.f;
 };
 hipError_t launch_qk_post(const QkPostArgs& a, hipStream_t st);
 hipError_t launch_rope_table(float2* table, int frames, int height, int width, int head_dim, hipStream_t st);
@@ -69,8 +72,8 @@ hipError_t launch_axpy_features(void* x, bool x_fp32, const bf16_t* s_cur, const
 // Deep-stack collapse: t = (accumulate ? t : 0) + sum of up to 48 bf16 feature arrays (fp32 result),
 // and x += t_cur + (t_cur - t_prev) * alpha (t_prev may be null: x += t_cur).
 struct FeatureList {
-  const bf16_t* p[48];
-  int32_t n;
+  const bf16_t* p[48] = {};
+  int32_t n = 0;
 };
 hipError_t launch_sum_features(const FeatureList& fl, float* t, bool accumulate, int64_t n_elems, hipStream_t st);
 hipError_t launch_apply_sums(void* x, bool x_fp32, const float* t_cur, const float* t_prev, float alpha,
@@ -96,28 +99,28 @@ hipError_t launch_second_diff_stats(const bf16_t* f_prev, const bf16_t* f_cur, c
                                     double* scratch, double* stats, bool accumulate, hipStream_t st);
 
 struct GemmArgs {
-  const bf16_t* a;      // [M, K] row-major
-  const bf16_t* w;      // [N, K] row-major
-  const bf16_t* bias;   // [N]
-  int32_t m, n, k;
-  int32_t epilogue;
-  const int32_t* rows;  // row(m) = rows ? rows[m] : m   (scatter epilogues)
-  bf16_t* c;            // PLAIN/GELU: C; QKV: Q [M, d]; SCATTER*: S [*, n]
-  bf16_t* k_out;        // QKV: K cache [*, d]
-  bf16_t* vt_out;       // QKV: V^T cache [d, ld_vt]
-  int64_t ld_vt;
-  int32_t d;            // QKV: hidden
-  float q_scale;        // QKV: the Q third is stored multiplied by this (softmax scale folded into Q)
-  float* splitk_ws;     // optional device scratch for k-split partial sums (nullptr: never split)
-  size_t splitk_ws_bytes;
-  float* parts;         // scratch for the chunks of smaller tiles cut along k, which need arrivals too (nullptr: never cut)
-  size_t parts_bytes;
-  uint32_t* arrivals;   // GEMM_ARRIVALS counters, zero before and after every launch
-  void* x;              // SCATTER_ADD, optional: x[row(m), :] += the stored (rounded) S[row(m), :]  (Alg. 1 residual add)
-  int32_t x_fp32;       // x holds fp32 (else bf16)
-  const bf16_t* gate_v; // SCATTER*, optional: (acc + bias) is multiplied by gate[n] of the row's stream (adaLN gate)
-  const bf16_t* gate_t; //   rows (after row(m)) below n_text use gate_t, the others gate_v
-  int32_t n_text;
+  const bf16_t* a = nullptr;       // [M, K] row-major
+  const bf16_t* w = nullptr;       // [N, K] row-major
+  const bf16_t* bias = nullptr;    // [N]
+  int32_t m = 0, n = 0, k = 0;
+  int32_t epilogue = 0;
+  const int32_t* rows = nullptr;   // row(m) = rows ? rows[m] : m   (scatter epilogues)
+  bf16_t* c = nullptr;             // PLAIN/GELU: C; QKV: Q [M, d]; SCATTER*: S [*, n]
+  bf16_t* k_out = nullptr;         // QKV: K cache [*, d]
+  bf16_t* vt_out = nullptr;        // QKV: V^T cache [d, ld_vt]
+  int64_t ld_vt = 0;
+  int32_t d = 0;                   // QKV: hidden
+  float q_scale = 0.f;             // QKV: the Q third is stored multiplied by this (softmax scale folded into Q)
+  float* splitk_ws = nullptr;      // optional device scratch for k-split partial sums (nullptr: never split)
+  size_t splitk_ws_bytes = 0;
+  float* parts = nullptr;          // scratch for the chunks of smaller tiles cut along k, which need arrivals too (nullptr: never cut)
+  size_t parts_bytes = 0;
+  uint32_t* arrivals = nullptr;    // GEMM_ARRIVALS counters, zero before and after every launch
+  void* x = nullptr;               // SCATTER_ADD, optional: x[row(m), :] += the stored (rounded) S[row(m), :]  (Alg. 1 residual add)
+  int32_t x_fp32 = 0;              // x holds fp32 (else bf16)
+  const bf16_t* gate_v = nullptr;  // SCATTER*, optional: (acc + bias) is multiplied by gate[n] of the row's stream (adaLN gate)
+  const bf16_t* gate_t = nullptr;  //   rows (after row(m)) below n_text use gate_t, the others gate_v
+  int32_t n_text = 0;
 };
 
 constexpr int GEMM_ARRIVALS = 256;
@@ -128,12 +131,12 @@ void gemm_route(const GemmArgs& g, int* tile_m, int* tile_n, int* k_chunks);
 // The rows a GEMM normalises by itself instead of reading them from `a`: LayerNorm of x[row] (+ add[row]) over
 // the k channels, as launch_gather_ln computes it.
 struct LnInput {
-  const void* x;
-  bool x_fp32;
-  const bf16_t* add;          // nullptr: none
-  const int32_t* rows;        // nullptr: row m
-  const bf16_t *gain, *bias;
-  float eps;
+  const void* x = nullptr;
+  bool x_fp32 = false;
+  const bf16_t* add = nullptr;    // nullptr: none
+  const int32_t* rows = nullptr;  // nullptr: row m
+  const bf16_t *gain = nullptr, *bias = nullptr;
+  float eps = 0.f;
   LnMod mod;
 };
 // whether one kernel takes LayerNorm and this (QKV or GELU) GEMM faster than two
@@ -142,21 +145,21 @@ hipError_t launch_gemm_ln(const GemmArgs& g, const LnInput& ln, hipStream_t st);
 
 // Out-projection, LayerNorm, FFN and residual of the listed rows in one kernel (narrow models)
 struct TailArgs {
-  const bf16_t* o;            // attention output [n_rows, hidden]
-  const int32_t* rows;        // nullptr: row m
-  int32_t n_rows, hidden, ffn;
-  const bf16_t *w_o, *b_o, *w1, *b1, *w2, *b2;
-  const bf16_t *gain, *bias;  // LayerNorm
-  float eps;
+  const bf16_t* o = nullptr;                      // attention output [n_rows, hidden]
+  const int32_t* rows = nullptr;                  // nullptr: row m
+  int32_t n_rows = 0, hidden = 0, ffn = 0;
+  const bf16_t *w_o = nullptr, *b_o = nullptr, *w1 = nullptr, *b1 = nullptr, *w2 = nullptr, *b2 = nullptr;
+  const bf16_t *gain = nullptr, *bias = nullptr;  // LayerNorm
+  float eps = 0.f;
   LnMod mod;
-  const bf16_t *gate1_v, *gate1_t, *gate2_v, *gate2_t;    // adaLN gates of the two branches (nullptr: none)
-  int32_t n_text;             // rows below it take the _t vectors
-  bf16_t* s;                  // stored feature, row rows[m]
-  void* x;                    // residual stream, read at row rows[m]
-  bool x_fp32, add_to_x;      // add_to_x: += the stored feature
-  float* parts;               // scratch for partial sums (nullptr: the FFN channels are never shared out)
-  size_t parts_bytes;
-  uint32_t* arrivals;         // NARROW_TAIL_BLOCKS counters, zero before and after every launch
+  const bf16_t *gate1_v = nullptr, *gate1_t = nullptr, *gate2_v = nullptr, *gate2_t = nullptr;  // adaLN gates of the two branches (nullptr: none)
+  int32_t n_text = 0;                             // rows below it take the _t vectors
+  bf16_t* s = nullptr;                            // stored feature, row rows[m]
+  void* x = nullptr;                              // residual stream, read at row rows[m]
+  bool x_fp32 = false, add_to_x = false;          // add_to_x: += the stored feature
+  float* parts = nullptr;                         // scratch for partial sums (nullptr: the FFN channels are never shared out)
+  size_t parts_bytes = 0;
+  uint32_t* arrivals = nullptr;                   // NARROW_TAIL_BLOCKS counters, zero before and after every launch
 };
 constexpr int NARROW_TAIL_BLOCKS = 256;
 bool narrow_tail_fits(int n_rows, int hidden, int ffn);
@@ -166,17 +169,17 @@ hipError_t launch_narrow_tail(const TailArgs& a, hipStream_t st);
 size_t gemm_wanted_scratch_bytes(const GemmArgs& g);
 
 struct AttnArgs {
-  const bf16_t* q;      // [r, n_heads*head_dim]
-  const bf16_t* k;      // [n_keys, n_heads*head_dim]
-  const bf16_t* vt;     // [n_heads*head_dim, ld_vt]
-  int64_t ld_vt;
-  bf16_t* o;            // [r, n_heads*head_dim]
-  int32_t r, n_keys, n_heads, head_dim;
-  float q_scale;        // scores are exp2(q_scale * q.k): log2(e)/sqrt(head_dim), or 1 if folded into Q
-  float* split_ws;      // optional device scratch for the partial results of key-split query blocks (nullptr: never split)
-  size_t split_ws_bytes;
-  uint32_t* fallback_count;   // optional device counter: += 1 per workgroup (NW * 64 queries of one head) whose row sums
-                              // left the range of the reference-free form and that recomputed with the running maximum
+  const bf16_t* q = nullptr;           // [r, n_heads*head_dim]
+  const bf16_t* k = nullptr;           // [n_keys, n_heads*head_dim]
+  const bf16_t* vt = nullptr;          // [n_heads*head_dim, ld_vt]
+  int64_t ld_vt = 0;
+  bf16_t* o = nullptr;                 // [r, n_heads*head_dim]
+  int32_t r = 0, n_keys = 0, n_heads = 0, head_dim = 0;
+  float q_scale = 0.f;                 // scores are exp2(q_scale * q.k): log2(e)/sqrt(head_dim), or 1 if folded into Q
+  float* split_ws = nullptr;           // optional device scratch for the partial results of key-split query blocks (nullptr: never split)
+  size_t split_ws_bytes = 0;
+  uint32_t* fallback_count = nullptr;  // optional device counter: += 1 per workgroup (NW * 64 queries of one head) whose row sums
+                                       // left the range of the reference-free form and that recomputed with the running maximum
 };
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st);

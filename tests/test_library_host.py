@@ -3,6 +3,7 @@ host logic (sizes, selection counts, argument validation) works without a GPU.""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -12,6 +13,7 @@ from paper_2508_17588_amd import binding as B
 from workloads import CONFIGS, RATIO_SWEEP, get_config
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 @pytest.fixture(scope="module")
@@ -179,3 +181,47 @@ def test_product_path_does_not_import_the_oracle():
             if f.endswith((".py", ".hip", ".h", ".cpp")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in text.replace("no CPU or PyTorch fallback", ""), f
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_argument_structures_start_without_garbage(tmp_path):
+    # a launcher that leaves a member alone passes "none": declared where only garbage lies, every byte of a member is zero
+    header = os.path.join(ROOT, "paper_2508_17588_amd", "csrc", "hero_kernels.h")
+    text = open(header).read()
+    names = re.findall(r"^struct (\w+) \{", text, re.M)
+    assert {"AttnArgs", "GemmArgs", "TailArgs"} <= set(names)
+    checks = []
+    for name in names:
+        body = re.sub(r"//[^\n]*", "", re.search(r"struct %s \{(.*?)\n?\};" % name, text, re.S).group(1))
+        members = [re.match(r"[\s*]*(\w+)", re.sub(r"=.*", "", d).split()[-1]).group(1) for stmt in body.split(";") if stmt.strip()
+                   for d in stmt.split(",")]
+        assert members, name
+        checks += [f"  check(new (place) {name}, &{name}::{m}, \"{name}::{m}\");" for m in members]
+    src = tmp_path / "args.hip"
+    src.write_text(f'''#include "{header}"
+#include <new>
+#include <cstdio>
+#include <cstring>
+#include <type_traits>
+alignas(16) unsigned char place[4096];
+int bad = 0;
+template <typename S, typename M>
+void check(S*, M S::*member, const char* name) {{
+  if (std::is_class<M>::value) return;          // (its own members are looked at by its own name)
+  memset(place, 0xEE, sizeof(place));
+  const S* s = new (place) S;
+  unsigned char bytes[sizeof(M)];
+  memcpy(bytes, &(s->*member), sizeof(M));
+  for (unsigned char b : bytes)
+    if (b) {{ printf("%s\\n", name); bad = 1; return; }}
+}}
+int main() {{
+{chr(10).join(checks)}
+  return bad;
+}}
+''')
+    exe = tmp_path / "args"
+    res = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-O0", str(src), "-o", str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    res = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert res.returncode == 0, res.stdout
