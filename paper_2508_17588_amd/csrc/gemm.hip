@@ -1340,6 +1340,9 @@ double sharing_cost(const TileCost& c, int split, double fill) {
   return c.bm == 64 ? 1.0 + 0.8 * split + 1.5 * fill : 2.0 + part * (split + 4.5 * fill);
 }
 
+// Stages a chunk of a cut tile has at least: fewer do not cover the start of its pipeline.
+constexpr int least_stages(const TileCost& c) { return c.bm == 64 ? 4 : 6; }
+
 struct TileChoice {
   TileKind kind;
   int split;      // chunks along k of the last round's tiles (1: not cut)
@@ -1378,7 +1381,7 @@ TileChoice choose_tile(const GemmArgs& g) {
       if (split > 1) t = (double)(tiles / 256) * full + share * full;
     } else if (g.parts != nullptr && g.epilogue != EPI_QKV) {
       const int64_t n_rem = (tiles + 7) / 8 * 8 % 256;
-      const int least = kind == TILE_64 ? 4 : 6;              // stages of a chunk
+      const int least = least_stages(c);
       const double uncut = t;
       for (int s = 2; s <= MOST_CHUNKS && stages / s >= least && n_rem > 0 && n_rem * s * c.bm * c.bn * 4 <= (int64_t)g.parts_bytes; ++s) {
         const double cut = (double)(tiles / 256) * full + rounds(n_rem * s, (double)((stages + s - 1) / s)) +
@@ -1403,6 +1406,18 @@ size_t gemm_wanted_scratch_bytes(const GemmArgs& g) {
   int n_rem = 0;
   const int split = choose_k_split(g, (size_t)-1, &n_rem);
   return split > 1 ? (size_t)n_rem * split * 262144 : 0;
+}
+
+// (the last round has at most 248 tiles: 256 are a whole one)
+size_t gemm_most_parts_bytes(int m, int n, int k) {
+  size_t most = 0;
+  for (int kind = TILE_64; kind < TILE_256; ++kind) {
+    const TileCost& c = TILE_COST[kind];
+    const int64_t slots = std::min<int64_t>(((int64_t)((m + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn) + 7) / 8 * 8, 248);
+    const int chunks = std::min(k / SBK / least_stages(c), MOST_CHUNKS);
+    if (chunks > 1) most = std::max(most, (size_t)slots * chunks * c.bm * c.bn * 4);
+  }
+  return most;
 }
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {

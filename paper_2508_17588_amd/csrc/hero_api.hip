@@ -171,7 +171,6 @@ struct Layout {
   size_t idx_off, a_off, q_off, o_off, f_off, ktmp_off, vtmp_off, splitk_off, splitk_bytes, ws_bytes;
   size_t seen_off, seen_bytes;   // index check: one bit per token, then one verdict word
   size_t stat_off;               // counters (word 0: attention workgroups that took the running-maximum path)
-  size_t parts_off, parts_bytes;   // partial sums of the narrow models' kernel (0 bytes: not used)
   // bytes of one layer's slabs: S_cur, then K and V^T if it keeps them, then S_prev if it keeps one
   bool keeps_kv(const hero_config& c, int l) const { return l < c.n_shallow || kv_all; }
   bool keeps_prev(const hero_config& c, int l) const { return l >= c.n_shallow || prev_all; }
@@ -180,6 +179,7 @@ struct Layout {
   }
 };
 
+constexpr int MANY_TOKENS = 2048;      // enough to fill the chip with the largest tiles and query blocks
 constexpr int ARRIVAL_COUNTERS = std::max(NARROW_TAIL_BLOCKS, GEMM_ARRIVALS);
 
 Layout make_layout(const hero_config& c) {
@@ -216,19 +216,26 @@ Layout make_layout(const hero_config& c) {
     L.vtmp_off = w;
     w += L.vt_bytes;
   }
-  // partial sums of GEMM tiles cut along k: up to 512 blocks of 256 x 256 fp32 (few tokens: up to 256 of the smaller tiles)
+  // partial sums: up to 512 blocks of 256 x 256 fp32 of GEMM tiles cut along k or attention's key ranges; where tokens are
+  // too few for those, what smaller tiles can be cut into (at most 256 blocks of 192 x 192; hidden 1920, 300 tokens: 36 MiB)
+  // or, where the narrow models' kernel takes their place, its own parts (hidden 128, 272 tokens: 0.5 MiB)
   L.splitk_off = w;
-  L.splitk_bytes = L.n_tokens >= 2048 ? (size_t)512 * 262144 : (size_t)256 * 147456;
+  if (L.n_tokens >= MANY_TOKENS) {
+    L.splitk_bytes = (size_t)512 * 262144;
+  } else if (narrow_tail_fits((int)L.n_tokens, c.hidden, c.ffn_dim)) {
+    L.splitk_bytes = narrow_tail_parts_bytes((int)L.n_tokens, c.hidden);
+  } else {
+    const int n = (int)L.n_tokens, d = c.hidden, f = c.ffn_dim;
+    const size_t most = std::max({gemm_most_parts_bytes(n, d, d), gemm_most_parts_bytes(n, f, d), gemm_most_parts_bytes(n, d, f)});
+    L.splitk_bytes = std::min(most, (size_t)256 * 147456);
+  }
+  L.splitk_bytes = align_up(L.splitk_bytes, 256);
   w += L.splitk_bytes;
   L.seen_off = w;
   L.seen_bytes = align_up(((size_t)L.n_tokens + 31) / 32 * 4 + 4, 256);
   w += L.seen_bytes;
   L.stat_off = w;
   w += 256;
-  L.parts_off = w;
-  L.parts_bytes = narrow_tail_fits(1, c.hidden, c.ffn_dim)
-                      ? align_up(std::min<size_t>(((size_t)L.n_tokens + 15) / 16 * 4, NARROW_TAIL_BLOCKS) * 16 * c.hidden * 4, 256) : 0;
-  w += L.parts_bytes;
   L.ws_bytes = w;
   return L;
 }
@@ -275,7 +282,7 @@ struct hero_cache {
   int32_t* ages = nullptr;
   int32_t* idx = nullptr;
   bf16_t *a = nullptr, *q = nullptr, *o = nullptr, *f = nullptr, *ktmp = nullptr, *vtmp = nullptr;
-  float* splitk = nullptr;        // partial sums of GEMM tiles and attention blocks that are cut
+  float* splitk = nullptr;        // partial sums of GEMM tiles, attention blocks and FFN channels that are shared out
   uint32_t* seen = nullptr;       // index check: token bitmap followed by the verdict word
   uint32_t* stats = nullptr;      // word 0: attention fallback workgroups since create / reset
   uint32_t* arrivals = nullptr;   // arrival counters, zero between launches
@@ -324,7 +331,7 @@ int check_layer(hero_cache_t c, int layer) {
 
 // Scratch of the GEMMs.  256 x 256 tiles and attention blocks are cut, by kernels that come in pairs, only where there are
 // tokens enough to fill the chip with them.
-bool many_tokens(hero_cache_t c) { return c->lay.n_tokens >= 2048; }
+bool many_tokens(hero_cache_t c) { return c->lay.n_tokens >= MANY_TOKENS; }
 void use_scratch(hero_cache_t c, GemmArgs& g) {
   if (many_tokens(c)) { g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes; }
   g.parts = c->splitk; g.parts_bytes = c->lay.splitk_bytes; g.arrivals = c->arrivals;
@@ -403,7 +410,7 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
       t.n_text = cfg.n_text;
     }
     t.s = s_dst; t.x = x; t.x_fp32 = x_fp32; t.add_to_x = fuse_resid;
-    t.parts = (float*)(c->ws + c->lay.parts_off); t.parts_bytes = c->lay.parts_bytes;
+    t.parts = c->splitk; t.parts_bytes = c->lay.splitk_bytes;
     t.arrivals = c->arrivals;
     PROF_LAUNCH(c, HERO_PROF_GEMM_FF2, 2.0 * rd * (d + 2.0 * cfg.ffn_dim), st, launch_narrow_tail(t, st));
     return HERO_OK;

@@ -163,8 +163,12 @@ struct TailArgs {
 };
 constexpr int NARROW_TAIL_BLOCKS = 256;
 bool narrow_tail_fits(int n_rows, int hidden, int ffn);
+// bytes of `parts` it can make use of for up to n_rows rows
+size_t narrow_tail_parts_bytes(int n_rows, int hidden);
 hipError_t launch_narrow_tail(const TailArgs& a, hipStream_t st);
 
+// bytes of `parts` that a layer's GEMM of up to m rows can make use of, however it is cut into smaller tiles
+size_t gemm_most_parts_bytes(int m, int n, int k);
 // bytes of scratch launch_gemm would use for this problem if it had all it wanted (0: the problem is not cut along k)
 size_t gemm_wanted_scratch_bytes(const GemmArgs& g);
 

@@ -326,6 +326,11 @@ bool narrow_tail_fits(int n_rows, int hidden, int ffn) {
   return n_rows <= 512 * ROWS && n_rows > 384 * ROWS;
 }
 
+// (choose_split takes up to four workgroups a block of rows, and no more than NARROW_TAIL_BLOCKS in all)
+size_t narrow_tail_parts_bytes(int n_rows, int hidden) {
+  return (size_t)std::min((n_rows + ROWS - 1) / ROWS * 4, NARROW_TAIL_BLOCKS) * ROWS * hidden * 4;
+}
+
 hipError_t launch_narrow_tail(const TailArgs& a, hipStream_t st) {
   if (a.n_rows <= 0) return hipSuccess;
   if (!narrow_tail_fits(a.n_rows, a.hidden, a.ffn)) return hipErrorInvalidValue;

@@ -84,6 +84,25 @@ def test_cache_bytes(lib):
     assert B.hero_cache_bytes(B.make_config(cfg.with_(block_flags=3)))[0] == cb
 
 
+@pytest.mark.parametrize("heads,ffn,tokens,least,most", [
+    # MiB of partial sums beside the activations
+    (2, 512, 272, 0.4, 0.6),            # narrow models, FFN four times as wide: 17 blocks of 16 rows in four parts
+    (4, 1024, 2047, 3.9, 4.1),          # no more than 256 workgroups share
+    (4, 64, 300, 0, 0),                 # too shallow to be cut
+    (5, 1280, 40, 0.5, 4),
+    (48, 12288, 300, 30, 36),
+    (30, 7680, 2047, 30, 36),
+    (30, 7680, 2048, 128, 128),         # the largest tiles and attention's key ranges too
+    (2, 512, 2048, 128, 128),
+])
+def test_workspace_holds_the_partial_sums_that_its_layers_can_use(lib, heads, ffn, tokens, least, most):
+    cfg = get_config("tiny", n_layers=1, n_shallow=1, hidden=64 * heads, n_heads=heads, head_dim=64, ffn_dim=ffn, frames=1,
+                     height=1, width=tokens, n_text=0)
+    activations = tokens * (3 * 64 * heads + ffn) * 2
+    rest = B.hero_cache_bytes(B.make_config(cfg))[1] - activations - tokens * 4 - tokens / 8
+    assert least * 2 ** 20 <= rest <= most * 2 ** 20 + 8 * 256          # (pieces begin on multiples of 256)
+
+
 def test_invalid_configs_are_rejected(lib):
     def rc_of(**over):
         c = B.make_config(get_config("tiny", **over))
