@@ -270,8 +270,8 @@ int hero_linear_scratch(const void* dev_a, const void* dev_w, const void* dev_bi
  * one head) that took the slower way out.  head_dim 64 evaluates softmax as 2^(q.k log2(e)/sqrt(head_dim))
  * without a running maximum, which is exact while every row sum stays within [2^-80, 2^80]; a workgroup
  * in which some row sum leaves that range recomputes its queries relative to a maximum (the result is the
- * plain definition's either way; the cost of such a block roughly triples).  Where a workgroup has 64
- * queries (hero_attention_route), a block of 256 counts once, however many of its four leave the range.
+ * plain definition's either way; the cost of such a block roughly triples).  Where a workgroup has 32 or 64
+ * queries (hero_attention_route), a block of 256 counts once, however many of its workgroups leave the range.
  * With scores of a few units, as LayerNorm-ed activations give, that never happens; it takes
  * |q.k| / sqrt(head_dim) beyond about 50.  head_dim 32 refers its exponentials to a maximum and has
  * no such way out: the counter stays as it is. */
@@ -319,7 +319,7 @@ int hero_attention_scratch(const void* dev_q, const void* dev_k, const void* dev
  * the tiles of the last round (1: not cut; a layer of a handle, whose workgroups can add up what they share, may also cut
  * smaller tiles of its out-projection, FFN1 and FFN2, and then prefer another kind); *normalises: 1 where a layer's QKV or FFN1 kernel normalises its rows
  * itself (models of at most 256 channels).
- * hero_attention_route: queries per workgroup (64, or 32 of them where few: the workgroup's waves share the keys, 256: each wave has
+ * hero_attention_route: queries per workgroup (32 or 64: the workgroup's waves share the keys, 256: each wave has
  * queries of its own) and *key_ranges, the number of key ranges of the blocks of the last round. */
 enum { HERO_ROUTE_PLAIN = 0, HERO_ROUTE_GELU = 1, HERO_ROUTE_QKV = 2, HERO_ROUTE_OUT = 3, HERO_ROUTE_FFN1 = 4, HERO_ROUTE_FFN2 = 5 };
 int hero_linear_route(int32_t m, int32_t n, int32_t k, int32_t what, int32_t listed, size_t scratch_bytes,

@@ -689,7 +689,7 @@ __device__ __forceinline__ void attention_finish(const AttnArgs& a, int head, in
 // few query blocks, and head_dim 32: 64 queries per workgroup (32 where that leaves most CUs idle), four waves that
 // share the keys
 // ------------------------------------------------------------------------------------------
-// Each wave walks a quarter of the 64-key tiles for the same 64 queries, from K and V^T tiles of its own
+// Each wave walks a quarter of the 64-key tiles for the workgroup's queries, from K and V^T tiles of its own
 // in LDS (no barrier in the loop); the unnormalised outputs and row sums of the waves add up in LDS at the end,
 // as they are or, at head_dim 32, brought to one reference point first.  The next K tile is fetched while
 // the exponentials and PV of this one run, the next V^T tile during the following QK^T.
@@ -731,8 +731,8 @@ template <int HD, int QG> using share_keys_lds = __attribute__((address_space(3)
 // 17776 x 17776 x 16 1006 and 4710) and finite wherever the running maximum is.
 enum ShareMode { KEYS_FREE, KEYS_RUNNING, KEYS_LAZY, KEYS_SUMS };
 
-// One pass over the keys for queries q0 .. q0+63: leaves the waves' partial outputs in LDS ([wave][quad][lane],
-// quad = (cb*2 + ig)*4 + q) and returns whether another pass is needed (KEYS_FREE, KEYS_SUMS: some row sum is out of range).
+// One pass over the keys for queries q0 .. q0 + 32 QG - 1: leaves the waves' partial outputs in LDS ([wave][quad][lane],
+// quad = (cb*QG + ig)*4 + q) and returns whether another pass is needed (KEYS_FREE, KEYS_SUMS: some row sum is out of range).
 template <int HD, int QG, bool SCALED, ShareMode MODE>
 __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int q0, share_keys_lds<HD, QG>* ldsp, float (&l)[QG]) {
   ShareKeys<HD, QG>& lds = *(ShareKeys<HD, QG>*)ldsp;
@@ -779,7 +779,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   const int t_begin = wave * n_tiles / SHARE_WAVES, t_end = (wave + 1) * n_tiles / SHARE_WAVES;
   const int kperm = (lr & ~12) | ((lr & 4) << 1) | ((lr & 8) >> 1);   // K row read as MFMA row lr
 
-  // the queries, 16 rows to a wave (rows past the end arrive as zero): whole cache lines, where the fragments' own loads
+  // the queries, QF KB to a wave, or to the first QG * 32 / KROWS waves (rows past the end arrive as zero): whole cache lines, where the fragments' own loads
   // would make 64 requests each
   constexpr int QF = QG * 32 / SHARE_WAVES / KROWS > 0 ? QG * 32 / SHARE_WAVES / KROWS : 1;        // fills of a wave
   const bool fetches = QG * 32 / SHARE_WAVES >= KROWS || wave < QG * 32 / KROWS;
@@ -1019,7 +1019,7 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
         for (int e = 0; e < 16; ++e) z = __builtin_fmaf(o[cb][ig][e], 0.f, z);
     jumped |= z != 0.f;
   }
-  // the four partial results meet in LDS: [wave][quad][lane], quad = (cb*2 + ig)*4 + q
+  // the four partial results meet in LDS: [wave][quad][lane], quad = (cb*QG + ig)*4 + q
   if constexpr (REFERRED) {
 #pragma unroll
     for (int ig = 0; ig < QG; ++ig) lds.refs[wave][ig][lane] = t_begin < t_end ? ref[ig] : -INFINITY;
@@ -1155,10 +1155,11 @@ hipError_t launch_share_keys(const AttnArgs& a, hipStream_t st) {
 // 32 queries to a workgroup halve a tile's chain, and pay as long as every workgroup has a CU of its own: 500 x 2000 x 4
 // heads 13.3 -> 10.0 us, 1000 x 2000 x 8 (256 workgroups) 13.9 -> 10.7, but 691 x 2032 x 16 (352) 14.8 -> 16.0 and
 // 1000 x 4000 x 16 (512) 24.5 -> 27.7.
+int share_keys_queries(const AttnArgs& a) { return (int64_t)((a.r + 31) / 32) * a.n_heads <= 256 ? 32 : 64; }
+
 template <int HD, bool SCALED, ShareMode MODE>
 hipError_t launch_share_keys(const AttnArgs& a, hipStream_t st) {
-  if ((int64_t)((a.r + 31) / 32) * a.n_heads <= 256) return launch_share_keys<HD, 1, SCALED, MODE>(a, st);
-  return launch_share_keys<HD, 2, SCALED, MODE>(a, st);
+  return share_keys_queries(a) == 32 ? launch_share_keys<HD, 1, SCALED, MODE>(a, st) : launch_share_keys<HD, 2, SCALED, MODE>(a, st);
 }
 
 // The chip runs 512 of the 256-query workgroups at a time (two per CU).  The n_rem blocks of the last
@@ -1228,7 +1229,7 @@ bool sharing_keys_is_faster(const AttnArgs& a) {
 
 void attention_route(const AttnArgs& a, int* queries, int* key_ranges) {
   const bool share = a.head_dim == 32 || sharing_keys_is_faster(a);
-  *queries = share ? 64 : 256;
+  *queries = share ? share_keys_queries(a) : 256;
   *key_ranges = share ? 1 : choose_key_split(a, ((a.r + 255) / 256 * a.n_heads + 7) / 8 * 8).split;
 }
 

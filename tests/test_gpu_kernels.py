@@ -212,7 +212,7 @@ def vt_padded(v, ld):
     (70, 272, 4, 32, "huge"),
 ])
 def test_attention(r, n_keys, heads, hd, case):
-    assert B.hero_attention_route(r, n_keys, heads, hd) == (64, 1)
+    assert B.hero_attention_route(r, n_keys, heads, hd) == (32, 1)
     run_attention(r, n_keys, heads, hd, case, scratch_mib=0)
 
 
@@ -247,7 +247,7 @@ def test_attention_of_cut_query_blocks(r, n_keys, heads, case, scratch_mib, rang
     (600, 4133, 4, 64, "plain", 3), (600, 4133, 4, 64, "plain", 1), (300, 2048, 3, 32, "plain", 64),
 ])
 def test_attention_with_scratch(r, n_keys, heads, hd, case, scratch_mib):
-    assert B.hero_attention_route(r, n_keys, heads, hd, scratch_mib << 20) == (64, 1)
+    assert B.hero_attention_route(r, n_keys, heads, hd, scratch_mib << 20) == (32, 1)
     run_attention(r, n_keys, heads, hd, case, scratch_mib)
 
 

@@ -31,9 +31,10 @@ def test_attention_routes_over_the_range():
     for r in (1, 65, 300, 1755, 4485, 17776):
         for n_keys in (1, 90, 2032, 17776):
             for heads in (1, 4, 16, 48):
-                assert B.hero_attention_route(r, n_keys, heads, 32, 128 * MIB) == (64, 1)
+                few = 32 if (r + 31) // 32 * heads <= 256 else 64          # one workgroup of 32 queries a CU
+                assert B.hero_attention_route(r, n_keys, heads, 32, 128 * MIB) == (few, 1)
                 queries, ranges = B.hero_attention_route(r, n_keys, heads, 64, 128 * MIB)
-                assert queries in (64, 256) and 1 <= ranges <= 16 and (queries == 256 or ranges == 1)
+                assert queries in (few, 256) and 1 <= ranges <= 16 and (queries == 256 or ranges == 1)
                 assert B.hero_attention_route(r, n_keys, heads, 64, 0)[1] == 1
     assert B.hero_attention_route(4485, 17776, 48, 64, 128 * MIB) == (256, 4)
 
@@ -84,7 +85,10 @@ def test_measured_choices_of_narrow_models(m, hidden, ffn, qkv, ffn1):
     (326, 33976, 40, 256),       # 168 us against 217
     (1306, 33976, 12, 256),      # 157 against 174
     (1000, 8218, 30, 256),       # 73 against 76
-    (326, 326, 4, 64),           # 7.8 against 15
+    (326, 326, 4, 32),           # 7.8 (64 queries) against 15
+    (500, 2000, 4, 32),          # 10.0 us; 64 queries 13.3
+    (1000, 2000, 8, 32),         # 10.7; 13.9
+    (691, 2032, 16, 64),         # 14.8; 32 queries 16.0
     (2032, 2032, 16, 64),        # 25 against 37
     (4485, 17776, 48, 256),
 ])
