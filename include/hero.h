@@ -223,7 +223,7 @@ int hero_cache_state(hero_cache_t c, int32_t* n_full, int32_t* last_full_step);
  * the same for the refreshed rows and adds the features of all other rows, of all shallow
  * layers, in its one pass at the end of the step (HERO_PROF_EXTRAP).
  * Where a model of at most 256 channels normalises its rows inside the QKV or FFN1 kernel (see
- * hero_linear_route), there is no HERO_PROF_LN launch for them and the time is part of
+ * hero_layer_route), there is no HERO_PROF_LN launch for them and the time is part of
  * HERO_PROF_GEMM_QKV or HERO_PROF_GEMM_FF1.  Where one kernel takes such a model's rows from the attention output to
  * the residual add, its launch and work (out-projection, FFN1, FFN2) are one HERO_PROF_GEMM_FF2 entry.
  * The three output arrays have 2 * HERO_PROF_KINDS entries (any may be NULL). */
@@ -314,16 +314,25 @@ int hero_attention_scratch(const void* dev_q, const void* dev_k, const void* dev
 
 /* Which kernel a problem goes to (host only, nothing is launched; for tests and tools: the choice is a matter of
  * expected time and may change with the library).
- * hero_linear_route: the tile of a GEMM (HERO_ROUTE_*: hero_linear with act 0 and 1, then the four of a layer; QKV:
- * n = 3 * hidden), on listed rows or not, with scratch_bytes of scratch; *k_chunks: the number of chunks along k of
- * the tiles of the last round (1: not cut; a layer of a handle, whose workgroups can add up what they share, may also cut
- * smaller tiles of its out-projection, FFN1 and FFN2, and then prefer another kind); *normalises: 1 where a layer's QKV or FFN1 kernel normalises its rows
- * itself (models of at most 256 channels).
+ * hero_linear_route: the tile of a GEMM by itself (HERO_ROUTE_*: hero_linear with act 0 and 1, then with the work of a
+ * layer's four on their results; QKV: n = 3 * hidden), on listed rows or not, with scratch_bytes of scratch; *k_chunks: the
+ * number of chunks along k of the tiles of the last round (1: not cut); *normalises: 1 where a QKV or FFN1 kernel that
+ * normalises its rows itself is the faster one (models of at most 256 channels).
+ * hero_layer_route: what the layer entry points of a handle launch for one of a layer's GEMMs (HERO_ROUTE_QKV ..
+ * HERO_ROUTE_FFN2), on n_rows listed rows or the first n_rows.  Its workgroups can also add up what they share, so smaller tiles
+ * may be cut too, and another kind preferred.  *form:
+ *   HERO_FORM_GEMM     a kernel of its own, tiles of tile_m x tile_n, those of the last round cut into *chunks along k;
+ *   HERO_FORM_LN_GEMM  the same, and it normalises its rows itself;
+ *   HERO_FORM_TAIL     part of the kernel that takes rows of narrow models from the attention output to the residual add:
+ *                      *tile_m rows of all *tile_n channels, whose FFN channels *chunks workgroups share.
  * hero_attention_route: queries per workgroup (32 or 64: the workgroup's waves share the keys, 256: each wave has
  * queries of its own) and *key_ranges, the number of key ranges of the blocks of the last round. */
 enum { HERO_ROUTE_PLAIN = 0, HERO_ROUTE_GELU = 1, HERO_ROUTE_QKV = 2, HERO_ROUTE_OUT = 3, HERO_ROUTE_FFN1 = 4, HERO_ROUTE_FFN2 = 5 };
 int hero_linear_route(int32_t m, int32_t n, int32_t k, int32_t what, int32_t listed, size_t scratch_bytes,
                       int32_t* tile_m, int32_t* tile_n, int32_t* k_chunks, int32_t* normalises);
+enum { HERO_FORM_GEMM = 0, HERO_FORM_LN_GEMM = 1, HERO_FORM_TAIL = 2 };
+int hero_layer_route(const hero_config* cfg, int32_t n_rows, int32_t listed, int32_t what, int32_t* form, int32_t* tile_m,
+                     int32_t* tile_n, int32_t* chunks);
 int hero_attention_route(int32_t r, int32_t n_keys, int32_t n_heads, int32_t head_dim, size_t scratch_bytes,
                          int32_t* queries, int32_t* key_ranges);
 

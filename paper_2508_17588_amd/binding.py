@@ -33,6 +33,7 @@ WEIGHT_FIELDS = ("ln1_g", "ln1_b", "w_qkv", "b_qkv", "w_o", "b_o",
                  "ln2_g", "ln2_b", "w_ff1", "b_ff1", "w_ff2", "b_ff2")
 EXTRA_WEIGHT_FIELDS = ("q_norm_g", "q_norm_b", "k_norm_g", "k_norm_b", "mod")
 BLOCK_ADALN, BLOCK_QKNORM, BLOCK_ROPE = 1, 2, 4
+FORM_GEMM, FORM_LN_GEMM, FORM_TAIL = range(3)
 ROUTE_PLAIN, ROUTE_GELU, ROUTE_QKV, ROUTE_OUT, ROUTE_FFN1, ROUTE_FFN2 = range(6)
 CACHE_KV_ALL_LAYERS, CACHE_PREV_ALL_LAYERS = 1, 2
 DEBUG_CHECK_IDX = 1
@@ -44,7 +45,7 @@ EXPORTS = (
     "hero_cache_view", "hero_cache_state", "hero_profile_begin", "hero_profile_begin_kinds", "hero_profile_end", "hero_gather_ln", "hero_linear", "hero_linear_scratch", "hero_linear_static",
     "hero_attention", "hero_attention_scratch", "hero_attention_counted",
     "hero_axpy_features", "hero_second_diff_stats", "hero_stability_scores",
-    "hero_linear_route", "hero_attention_route",
+    "hero_linear_route", "hero_layer_route", "hero_attention_route",
 )
 
 
@@ -112,6 +113,7 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
         "hero_second_diff_stats": [P, P, P, c_int64, P, ctypes.c_size_t, P, I, P],
         "hero_stability_scores": [POINTER(ctypes.c_double), I, POINTER(ctypes.c_double)],
         "hero_linear_route": [I, I, I, I, I, ctypes.c_size_t, POINTER(I), POINTER(I), POINTER(I), POINTER(I)],
+        "hero_layer_route": [POINTER(hero_config), I, I, I, POINTER(I), POINTER(I), POINTER(I), POINTER(I)],
         "hero_attention_route": [I, I, I, I, ctypes.c_size_t, POINTER(I), POINTER(I)],
     }
     for name, argtypes in sig.items():
@@ -385,6 +387,13 @@ def hero_linear_route(m: int, n: int, k: int, what: int = ROUTE_PLAIN, listed: b
     host only."""
     out = [c_int32() for _ in range(4)]
     _check(load_library().hero_linear_route(m, n, k, what, int(listed), scratch_bytes, *(byref(v) for v in out)))
+    return tuple(v.value for v in out)
+
+
+def hero_layer_route(cfg: hero_config, n_rows: int, what: int, listed: bool = False):
+    """(form, tile rows, tile columns, chunks) of one of a layer's GEMMs as a handle of `cfg` launches it; host only."""
+    out = [c_int32() for _ in range(4)]
+    _check(load_library().hero_layer_route(byref(cfg), n_rows, int(listed), what, *(byref(v) for v in out)))
     return tuple(v.value for v in out)
 
 

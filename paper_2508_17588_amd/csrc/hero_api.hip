@@ -329,12 +329,30 @@ int check_layer(hero_cache_t c, int layer) {
     }                                                                                \
   } while (0)
 
-// Scratch of the GEMMs.  256 x 256 tiles and attention blocks are cut, by kernels that come in pairs, only where there are
-// tokens enough to fill the chip with them.
-bool many_tokens(hero_cache_t c) { return c->lay.n_tokens >= MANY_TOKENS; }
-void use_scratch(hero_cache_t c, GemmArgs& g) {
-  if (many_tokens(c)) { g.splitk_ws = c->splitk; g.splitk_ws_bytes = c->lay.splitk_bytes; }
-  g.parts = c->splitk; g.parts_bytes = c->lay.splitk_bytes; g.arrivals = c->arrivals;
+// 256 x 256 tiles and attention blocks are cut, by kernels that come in pairs, only where there are tokens enough to fill
+// the chip with them.
+bool many_tokens(const Layout& L) { return L.n_tokens >= MANY_TOKENS; }
+
+// One of a layer's GEMMs on n_rows rows, all or listed ones, without its operands: what decides the kernel it goes to
+// (layer_form, launch_gemm), so that hero_layer_route and the launches cannot differ.
+GemmArgs layer_gemm(const hero_config& cfg, const Layout& L, float* partial_sums, uint32_t* arrivals, int what, int n_rows, const int32_t* rows) {
+  const int d = cfg.hidden, f = cfg.ffn_dim;
+  GemmArgs g;
+  g.m = n_rows;
+  switch (what) {
+    case HERO_ROUTE_QKV: g.epilogue = EPI_QKV; g.n = 3 * d; g.k = d; g.d = d; g.rows = rows; break;
+    case HERO_ROUTE_OUT: g.epilogue = EPI_SCATTER; g.n = d; g.k = d; g.rows = rows; break;
+    case HERO_ROUTE_FFN1: g.epilogue = EPI_GELU; g.n = f; g.k = d; break;
+    default: g.epilogue = EPI_SCATTER_ADD; g.n = d; g.k = f; g.rows = rows; break;
+  }
+  if (many_tokens(L)) { g.splitk_ws = partial_sums; g.splitk_ws_bytes = L.splitk_bytes; }
+  g.parts = partial_sums; g.parts_bytes = L.splitk_bytes; g.arrivals = arrivals;
+  return g;
+}
+// The form it takes: HERO_FORM_*.  (From the out-projection on, one kernel takes a narrow model's rows to the residual add.)
+int layer_form(const hero_config& cfg, const GemmArgs& g) {
+  if (g.epilogue != EPI_QKV && narrow_tail_fits(g.m, cfg.hidden, cfg.ffn_dim)) return HERO_FORM_TAIL;
+  return gemm_takes_ln(g) ? HERO_FORM_LN_GEMM : HERO_FORM_GEMM;
 }
 
 // The block of Eq. 2 on the rows listed in `rows` (nullptr = all N rows), writing K/V to
@@ -360,16 +378,15 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
     m2.shift_v = mod + 6 * d; m2.scale_v = mod + 7 * d; m2.shift_t = mod + 9 * d; m2.scale_t = mod + 10 * d;
     m1.n_text = m2.n_text = cfg.n_text;
   }
-  GemmArgs g;
+  auto gemm = [&](int what) { return layer_gemm(cfg, c->lay, c->splitk, c->arrivals, what, n_rows, rows); };
+  GemmArgs g = gemm(HERO_ROUTE_QKV);
   g.a = c->a; g.w = (const bf16_t*)w.w_qkv; g.bias = (const bf16_t*)w.b_qkv;
-  g.m = n_rows; g.n = 3 * d; g.k = d; g.epilogue = EPI_QKV; g.rows = rows;
-  g.c = c->q; g.k_out = k_dst; g.vt_out = vt_dst; g.ld_vt = c->lay.n_pad; g.d = d;
+  g.c = c->q; g.k_out = k_dst; g.vt_out = vt_dst; g.ld_vt = c->lay.n_pad;
   // softmax scale and the change to base 2 are folded into Q before its single bf16 rounding
   // (with q/k post-processing the scale is applied there, after the normalisation and rotation)
   const float softmax_scale = 1.4426950408889634f / sqrtf((float)cfg.head_dim);
   g.q_scale = qk_post ? 1.0f : softmax_scale;
-  use_scratch(c, g);
-  if (gemm_takes_ln(g)) {
+  if (layer_form(cfg, g) == HERO_FORM_LN_GEMM) {
     const LnInput ln = {x, x_fp32, nullptr, rows, (const bf16_t*)w.ln1_g, (const bf16_t*)w.ln1_b, cfg.ln_eps, m1};
     PROF_LAUNCH(c, HERO_PROF_GEMM_QKV, 6.0 * rd * d, st, launch_gemm_ln(g, ln, st));
   } else {
@@ -394,11 +411,12 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
   at.q = c->q; at.k = k_dst; at.vt = vt_dst; at.ld_vt = c->lay.n_pad; at.o = c->o;
   at.r = n_rows; at.n_keys = (int)c->lay.n_tokens; at.n_heads = cfg.n_heads; at.head_dim = cfg.head_dim;
   at.q_scale = 1.0f;
-  if (many_tokens(c)) { at.split_ws = c->splitk; at.split_ws_bytes = c->lay.splitk_bytes; }    // shared with the GEMMs: same stream, never concurrent
+  if (many_tokens(c->lay)) { at.split_ws = c->splitk; at.split_ws_bytes = c->lay.splitk_bytes; }    // shared with the GEMMs: same stream, never concurrent
   at.fallback_count = c->stats;
   PROF_LAUNCH(c, HERO_PROF_ATTN, 4.0 * rd * n_all, st, launch_attention(at, st));
 
-  if (narrow_tail_fits(n_rows, d, cfg.ffn_dim)) {
+  g = gemm(HERO_ROUTE_OUT);
+  if (layer_form(cfg, g) == HERO_FORM_TAIL) {
     TailArgs t;
     t.o = c->o; t.rows = rows; t.n_rows = n_rows; t.hidden = d; t.ffn = cfg.ffn_dim;
     t.w_o = (const bf16_t*)w.w_o; t.b_o = (const bf16_t*)w.b_o;
@@ -416,18 +434,13 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
     return HERO_OK;
   }
 
-  g = GemmArgs();
-  g.a = c->o; g.w = (const bf16_t*)w.w_o; g.bias = (const bf16_t*)w.b_o;
-  g.m = n_rows; g.n = d; g.k = d; g.epilogue = EPI_SCATTER; g.rows = rows; g.c = s_dst;
+  g.a = c->o; g.w = (const bf16_t*)w.w_o; g.bias = (const bf16_t*)w.b_o; g.c = s_dst;
   if (adaln) { g.gate_v = mod + 2 * d; g.gate_t = mod + 5 * d; g.n_text = cfg.n_text; }
-  use_scratch(c, g);
   PROF_LAUNCH(c, HERO_PROF_GEMM_O, 2.0 * rd * d, st, launch_gemm(g, st));
 
-  g = GemmArgs();
-  g.a = c->a; g.w = (const bf16_t*)w.w_ff1; g.bias = (const bf16_t*)w.b_ff1;
-  g.m = n_rows; g.n = cfg.ffn_dim; g.k = d; g.epilogue = EPI_GELU; g.c = c->f;
-  use_scratch(c, g);
-  if (gemm_takes_ln(g)) {
+  g = gemm(HERO_ROUTE_FFN1);
+  g.a = c->a; g.w = (const bf16_t*)w.w_ff1; g.bias = (const bf16_t*)w.b_ff1; g.c = c->f;
+  if (layer_form(cfg, g) == HERO_FORM_LN_GEMM) {
     const LnInput ln = {x, x_fp32, s_dst, rows, (const bf16_t*)w.ln2_g, (const bf16_t*)w.ln2_b, cfg.ln_eps, m2};
     PROF_LAUNCH(c, HERO_PROF_GEMM_FF1, 2.0 * rd * cfg.ffn_dim, st, launch_gemm_ln(g, ln, st));
   } else {
@@ -437,12 +450,10 @@ int run_block_rows(hero_cache_t c, LayerState& ls, void* x, const int32_t* rows,
     PROF_LAUNCH(c, HERO_PROF_GEMM_FF1, 2.0 * rd * cfg.ffn_dim, st, launch_gemm(g, st));
   }
 
-  g = GemmArgs();
-  g.a = c->f; g.w = (const bf16_t*)w.w_ff2; g.bias = (const bf16_t*)w.b_ff2;
-  g.m = n_rows; g.n = d; g.k = cfg.ffn_dim; g.epilogue = EPI_SCATTER_ADD; g.rows = rows; g.c = s_dst;
+  g = gemm(HERO_ROUTE_FFN2);
+  g.a = c->f; g.w = (const bf16_t*)w.w_ff2; g.bias = (const bf16_t*)w.b_ff2; g.c = s_dst;
   if (adaln) { g.gate_v = mod + 8 * d; g.gate_t = mod + 11 * d; g.n_text = cfg.n_text; }
   if (fuse_resid) { g.x = x; g.x_fp32 = x_fp32 ? 1 : 0; }
-  use_scratch(c, g);
   PROF_LAUNCH(c, HERO_PROF_GEMM_FF2, 2.0 * rd * cfg.ffn_dim, st, launch_gemm(g, st));
   return HERO_OK;
 }
@@ -979,6 +990,32 @@ int hero_linear_route(int32_t m, int32_t n, int32_t k, int32_t what, int32_t lis
   *normalises = (what == HERO_ROUTE_QKV || what == HERO_ROUTE_FFN1) && gemm_takes_ln(g) ? 1 : 0;
   if (*normalises) { *tile_m = *tile_n = 64; *k_chunks = 1; }
   else gemm_route(g, tile_m, tile_n, k_chunks);
+  return HERO_OK;
+}
+
+int hero_layer_route(const hero_config* cfg, int32_t n_rows, int32_t listed, int32_t what, int32_t* form, int32_t* tile_m,
+                     int32_t* tile_n, int32_t* chunks) {
+  int rc = check_config(cfg);
+  if (rc) return rc;
+  if (!form || !tile_m || !tile_n || !chunks) return fail(HERO_ERR_INVALID_ARG, "output pointer is null");
+  if (what < HERO_ROUTE_QKV || what > HERO_ROUTE_FFN2) return fail(HERO_ERR_INVALID_ARG, "not a GEMM of a layer: %d", what);
+  const Layout L = make_layout(*cfg);
+  if (n_rows < 1 || n_rows > L.n_tokens)
+    return fail(HERO_ERR_INVALID_ARG, "n_rows %d out of range [1, %lld]", n_rows, (long long)L.n_tokens);
+  static const int32_t any_row = 0;
+  static float any_sums[4];
+  static uint32_t any_count;
+  const GemmArgs g = layer_gemm(*cfg, L, L.splitk_bytes ? any_sums : nullptr, &any_count, what, n_rows, listed ? &any_row : nullptr);
+  *form = layer_form(*cfg, g);
+  *tile_m = *tile_n = 64;
+  *chunks = 1;
+  if (*form == HERO_FORM_GEMM) {
+    gemm_route(g, tile_m, tile_n, chunks);
+  } else if (*form == HERO_FORM_TAIL) {
+    *tile_m = NARROW_TAIL_ROWS;
+    *tile_n = cfg->hidden;
+    *chunks = narrow_tail_split(n_rows, cfg->hidden, L.splitk_bytes);
+  }
   return HERO_OK;
 }
 

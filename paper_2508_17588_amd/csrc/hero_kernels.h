@@ -161,8 +161,11 @@ struct TailArgs {
   size_t parts_bytes = 0;
   uint32_t* arrivals = nullptr;                   // NARROW_TAIL_BLOCKS counters, zero before and after every launch
 };
-constexpr int NARROW_TAIL_BLOCKS = 256;
+constexpr int NARROW_TAIL_ROWS = 16;        // rows of a workgroup
+constexpr int NARROW_TAIL_BLOCKS = 256;     // most workgroups that share sums
 bool narrow_tail_fits(int n_rows, int hidden, int ffn);
+// the workgroups that share the FFN channels of a block of rows, with parts_bytes of `parts` (1: not shared)
+int narrow_tail_split(int n_rows, int hidden, size_t parts_bytes);
 // bytes of `parts` it can make use of for up to n_rows rows
 size_t narrow_tail_parts_bytes(int n_rows, int hidden);
 hipError_t launch_narrow_tail(const TailArgs& a, hipStream_t st);

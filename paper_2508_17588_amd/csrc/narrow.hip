@@ -48,7 +48,7 @@ __device__ __forceinline__ void store4(bf16_t* p, const float (&v)[4]) {
 // LDS traffic of this wave is done, then every wave's; loads from global memory stay in flight
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-constexpr int ROWS = 16;      // rows of a workgroup
+constexpr int ROWS = NARROW_TAIL_ROWS;
 constexpr int NB = 4;         // weight batches of a wave on their way
 constexpr int FFN = 4;        // FFN channels for each channel of the stream
 
@@ -294,19 +294,9 @@ hipError_t launch_split(const TailArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// As many parts as keep every workgroup on a CU of its own (at 128 channels and below a CU holds several, but they share
-// what it can stream).  256 channels, 300 rows, a layer: 32.4 us in one part, 27.6 in four.
-int choose_split(const TailArgs& a) {
-  const int blocks = (a.n_rows + ROWS - 1) / ROWS;
-  if (a.parts == nullptr) return 1;
-  for (int split = 4; split > 1; split /= 2)
-    if (blocks * split <= NARROW_TAIL_BLOCKS && (size_t)blocks * split * ROWS * a.hidden * 4 <= a.parts_bytes) return split;
-  return 1;
-}
-
 template <int KD, int WAVES, typename XT>
 hipError_t launch(const TailArgs& a, hipStream_t st) {
-  switch (choose_split(a)) {
+  switch (narrow_tail_split(a.n_rows, a.hidden, a.parts != nullptr ? a.parts_bytes : 0)) {
     case 4: return launch_split<KD, WAVES, 4, XT>(a, st);
     case 2: return launch_split<KD, WAVES, 2, XT>(a, st);
     default: return launch_split<KD, WAVES, 1, XT>(a, st);
@@ -326,7 +316,15 @@ bool narrow_tail_fits(int n_rows, int hidden, int ffn) {
   return n_rows <= 512 * ROWS && n_rows > 384 * ROWS;
 }
 
-// (choose_split takes up to four workgroups a block of rows, and no more than NARROW_TAIL_BLOCKS in all)
+// As many parts as keep every workgroup on a CU of its own (at 128 channels and below a CU holds several, but they share
+// what it can stream).  256 channels, 300 rows, a layer: 32.4 us in one part, 27.6 in four.
+int narrow_tail_split(int n_rows, int hidden, size_t parts_bytes) {
+  const int blocks = (n_rows + ROWS - 1) / ROWS;
+  for (int split = 4; split > 1; split /= 2)
+    if (blocks * split <= NARROW_TAIL_BLOCKS && (size_t)blocks * split * ROWS * hidden * 4 <= parts_bytes) return split;
+  return 1;
+}
+
 size_t narrow_tail_parts_bytes(int n_rows, int hidden) {
   return (size_t)std::min((n_rows + ROWS - 1) / ROWS * 4, NARROW_TAIL_BLOCKS) * ROWS * hidden * 4;
 }

@@ -1,8 +1,13 @@
 """Which kernel a problem goes to (host only)."""
+import random
+
 import pytest
 
+import test_gpu_gemm_cut
+import test_gpu_narrow
 from paper_2508_17588_amd import binding as B
 from torch_block import BLOCKS, block_config
+from workloads import get_config
 
 MIB = 1 << 20
 TILES = {(64, 64), (128, 128), (128, 192), (192, 192), (256, 128), (256, 256)}
@@ -66,7 +71,7 @@ def test_measured_choices(m, n, k, what, listed, tile):
 
 
 @pytest.mark.parametrize("m,hidden,ffn,qkv,ffn1", [
-    # four layers, us, with FFN1 normalising or not as noted
+    # kernels by themselves: four layers, us, with FFN1 normalising or not as noted
     (326, 128, 512, True, True),
     (17576, 64, 4096, True, False),          # 769; normalising 927
     (17576, 128, 512, True, True),           # 771; apart 807
@@ -79,6 +84,55 @@ def test_measured_choices(m, n, k, what, listed, tile):
 def test_measured_choices_of_narrow_models(m, hidden, ffn, qkv, ffn1):
     assert bool(B.hero_linear_route(m, 3 * hidden, hidden, B.ROUTE_QKV)[3]) == qkv
     assert bool(B.hero_linear_route(m, ffn, hidden, B.ROUTE_FFN1)[3]) == ffn1
+
+
+def layer_config(tokens, hidden, ffn):
+    return B.make_config(get_config("tiny", n_layers=1, n_shallow=1, hidden=hidden, n_heads=hidden // 64, head_dim=64, ffn_dim=ffn,
+                                    frames=1, height=1, width=tokens, n_text=0))
+
+
+@pytest.mark.parametrize("m,hidden,ffn,qkv,ffn1", [
+    # what a layer launches: with an FFN four times as wide one kernel takes the rows to the residual add where that is faster
+    (326, 128, 512, B.FORM_LN_GEMM, B.FORM_TAIL),
+    (33000, 64, 256, B.FORM_LN_GEMM, B.FORM_TAIL),           # four layers, us: 1195; three kernels 1287
+    (33000, 128, 512, B.FORM_LN_GEMM, B.FORM_TAIL),          # 2300; 2396
+    (8000, 256, 1024, B.FORM_GEMM, B.FORM_TAIL),          # 507; 522
+    (10000, 256, 1024, B.FORM_GEMM, B.FORM_GEMM),         # 683; one kernel 712
+    (5000, 192, 768, B.FORM_LN_GEMM, B.FORM_GEMM),           # 269; 275
+    (6500, 192, 768, B.FORM_GEMM, B.FORM_TAIL),           # 348; three kernels 384
+    (33000, 192, 768, B.FORM_GEMM, B.FORM_GEMM),          # 3428; one kernel 3531
+    (1306, 256, 1024, B.FORM_LN_GEMM, B.FORM_TAIL),
+    # other widths: as the kernels by themselves
+    (17576, 64, 4096, B.FORM_LN_GEMM, B.FORM_GEMM),
+    (326, 128, 256, B.FORM_LN_GEMM, B.FORM_LN_GEMM),
+    (1306, 256, 4096, B.FORM_LN_GEMM, B.FORM_GEMM),
+    (90, 320, 1280, B.FORM_GEMM, B.FORM_GEMM),
+])
+def test_forms_of_the_layers_of_narrow_models(m, hidden, ffn, qkv, ffn1):
+    c = layer_config(m, hidden, ffn)
+    assert [B.hero_layer_route(c, m, what)[0] for what in (B.ROUTE_QKV, B.ROUTE_FFN1)] == [qkv, ffn1]
+    for what in (B.ROUTE_OUT, B.ROUTE_FFN2):
+        assert B.hero_layer_route(c, m, what)[0] == (B.FORM_TAIL if ffn1 == B.FORM_TAIL else B.FORM_GEMM)
+
+
+@pytest.mark.parametrize("m,hidden,ffn,what,route", [
+    # cut along k, and as fast uncut (us)
+    (45, 1536, 6144, B.ROUTE_FFN2, (64, 64, 4)),          # 14; 20.8
+    (84, 1920, 7680, B.ROUTE_FFN2, (64, 64, 4)),          # 16.3; 25.7
+    (700, 1536, 6144, B.ROUTE_FFN2, (128, 128, 3)),       # 29.8; 42.0
+    (1500, 3072, 12288, B.ROUTE_FFN2, (192, 192, 2)),     # 126; 143
+])
+def test_measured_cuts_of_a_layer(m, hidden, ffn, what, route):
+    assert B.hero_layer_route(layer_config(m, hidden, ffn), m, what) == (B.FORM_GEMM, *route)
+
+
+def test_layer_routes_refuse_what_is_no_gemm_of_a_layer():
+    c = layer_config(100, 128, 512)
+    for n_rows, what in ((0, B.ROUTE_QKV), (101, B.ROUTE_QKV), (100, B.ROUTE_GELU), (100, B.ROUTE_FFN2 + 1)):
+        with pytest.raises(B.HeroError):
+            B.hero_layer_route(c, n_rows, what)
+    with pytest.raises(B.HeroError):
+        B.hero_layer_route(layer_config(100, 128, 100), 100, B.ROUTE_QKV)
 
 
 @pytest.mark.parametrize("r,n_keys,heads,queries", [
@@ -96,21 +150,33 @@ def test_measured_attention_choices(r, n_keys, heads, queries):
     assert B.hero_attention_route(r, n_keys, heads, 64, 128 * MIB)[0] == queries
 
 
-def test_the_blocks_that_the_gemm_tests_run_take_every_kernel():
-    seen = set()
-    for shape in BLOCKS:
-        cfg = block_config(*shape)
-        d, f = cfg.hidden, cfg.ffn_dim
-        scratch = 128 * MIB if cfg.n_tokens >= 2048 else 0            # what a handle has
-        for listed, m in ((False, cfg.n_tokens), (True, B.hero_num_selected(B.make_config(cfg)))):
-            for what, n, k in ((B.ROUTE_QKV, 3 * d, d), (B.ROUTE_OUT, d, d), (B.ROUTE_FFN1, f, d), (B.ROUTE_FFN2, d, f)):
-                tm, tn, chunks, normalises = B.hero_linear_route(m, n, k, what, listed, scratch)
-                seen.add((what, listed, "normalises" if normalises else (tm, tn)))
-                if chunks > 1:
-                    seen.add((what, listed, "cut"))
-    for listed in (False, True):
-        for what in (B.ROUTE_QKV, B.ROUTE_OUT, B.ROUTE_FFN1, B.ROUTE_FFN2):
-            for tile in TILES:
-                assert (what, listed, tile) in seen, (what, listed, tile)
-            assert (what, listed, "normalises") in seen or what in (B.ROUTE_OUT, B.ROUTE_FFN2)
-            assert (what, listed, "cut") in seen or what == B.ROUTE_QKV
+def kernels(c, rows, listed):
+    """The kernels of a layer's four GEMMs: which GEMM, on listed rows or not, form, tile, and whether the tiles are cut (the
+    narrow models' kernel: how many workgroups share)."""
+    for what in (B.ROUTE_QKV, B.ROUTE_OUT, B.ROUTE_FFN1, B.ROUTE_FFN2):
+        form, tm, tn, chunks = B.hero_layer_route(c, rows, what, listed)
+        yield what, listed, form, tm, tn, chunks if form == B.FORM_TAIL else chunks > 1
+
+
+def test_the_blocks_that_the_gpu_tests_run_take_every_kernel():
+    configs = [block_config(*shape) for shape in BLOCKS]
+    configs += [test_gpu_gemm_cut.config(*shape) for shape in test_gpu_gemm_cut.SHAPES]
+    configs += [test_gpu_narrow.config(s[0], widths * 64 * s[0], *s[1:]) for s in test_gpu_narrow.NORMALISING for widths in (3, 4)]
+    configs += [test_gpu_narrow.config(s[0], 256 * s[0], *s[1:5]) for s in test_gpu_narrow.ONE_KERNEL]
+    run = set()
+    for cfg in configs:
+        c = B.make_config(cfg)
+        run.update(kernels(c, cfg.n_tokens, False))
+        run.update(kernels(c, B.hero_num_selected(c), True))
+    reachable, rng = set(), random.Random(1)
+    for heads in (*range(1, 49), 52, 64, 96, 128):
+        for ffn in (64, 320, 1088, 64 * heads, 128 * heads, 256 * heads, 9216):
+            for _ in range(24):
+                tokens = int(2 ** rng.uniform(0, 14.7))
+                if (tokens + 512) * max(64 * heads, ffn) * 2 >= 2 ** 32:
+                    continue
+                c = layer_config(tokens, 64 * heads, ffn)
+                reachable.update(kernels(c, tokens, False))
+                reachable.update(kernels(c, max(1, int(tokens * rng.choice((0.5, 0.25, 0.1)))), True))
+    assert len(reachable) > 80
+    assert reachable <= run, sorted(reachable - run)

@@ -8,10 +8,10 @@ from workloads import BLOCK_ADALN, get_config
 from hero_testlib import assert_close, to_host_f64
 
 
-# Blocks between which each of a layer's four GEMMs, on all rows and on listed ones, takes every kind of tile, both forms
-# of the narrow models, and tiles cut along k where that happens (tests/test_routes.py holds them to it), with
-# remainders of rows and columns and Q / K / V boundaries inside tiles.  Heads of 64 channels, FFN width, frames,
-# height, width, text rows, ratio, patch height and width.
+# Blocks between which each of a layer's four GEMMs, on all rows and on listed ones, takes every kind of tile, with remainders of
+# rows and columns and Q / K / V boundaries inside tiles (tests/test_routes.py holds them to it, together with the shapes of
+# the narrow models and of the cut tiles).  Heads of 64 channels, FFN width, frames, height, width, text rows, ratio,
+# patch height and width.
 BLOCKS = [
     (1, 320, 1, 11, 7, 8, 0.5, 3, 5),            # 85 and 40 rows, one stage along k
     (5, 320, 1, 7, 9, 3, 0.1, 2, 3),             # 66 and 12 rows
