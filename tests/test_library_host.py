@@ -244,3 +244,12 @@ int main() {{
     assert res.returncode == 0, res.stderr[-2000:]
     res = subprocess.run([str(exe)], capture_output=True, text=True)
     assert res.returncode == 0, res.stdout
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    import torch
+    from types import SimpleNamespace
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=0x770))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    assert B._stream().value == 0x770
