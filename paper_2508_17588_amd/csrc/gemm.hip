@@ -25,16 +25,6 @@
 
 namespace {
 
-__device__ __forceinline__ float gelu_tanh(float x) {
-  // x/2 (1 + tanh u) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3);
-  // -2u log2(e) = x (C1 + C2 x^2) with the constants folded: five plain operations and two
-  // transcendentals per element (the epilogue runs while the matrix pipe idles)
-  constexpr float C1 = -2.302208198144325f;     // -2 log2(e) sqrt(2/pi)
-  constexpr float C2 = -0.1029432395800235f;    // C1 * 0.044715
-  float e = __builtin_amdgcn_exp2f(x * __builtin_fmaf(x * x, C2, C1));
-  return x * __builtin_amdgcn_rcpf(1.0f + e);
-}
-
 // ------------------------------------------------------------------------------------------
 // Large problems: 256 x 256 tile, eight waves (two per SIMD) of 128 x 64, K walked in stages of
 // 64 through LDS rings (three slots for A, two for W: all 160 KB of a CU) that are filled by
@@ -704,16 +694,9 @@ __device__ __forceinline__ void stream_tile(const GemmArgs& g, const float* tile
   }
 }
 
-// BM x BN tile, eight waves: 2 x 2 sub-tiles, each computed by two waves that take one half of every
-// 64-wide k stage.  The sub-tile is then large (few LDS reads a flop) with two waves on every SIMD.
-// Stages go global -> LDS into a ring of RING slots, filled RING - 1 stages ahead, one barrier a stage;
-// a slot holds the BM rows of A, then the BN rows of W, in the layout of the 256 x 256 kernel.
-// What bounds it: the fills (48 KB a stage at 192 x 192, two stages on their way; 1.13 PFLOP/s with all
-// CUs at work at k = 12288) and, at k = 3072, start-up and epilogue, about 7 of 50 us.  Kernel times of FFN2 after
-// the kernel that writes its rows, against 256 x 256 or the earlier 128 x 128 tiles: 4485 rows at hidden 1920
-// 174 -> 124 us (192 x 192), 1755 rows at hidden 3072 202 -> 153 (128 x 192), 2925 rows 241, fix-up included, -> 194.
-// Tiles (of less than 256 x 256) of the last round cut along k: slots 0 .. full_items - 1 are whole work items, the `tiles` slots after them are cut
-// in `chunks`, whose sums the workgroup that arrives last adds up (one counter a tile, one block of BM x BN floats a chunk).
+// Tiles (of less than 256 x 256) of the last round cut along k: slots 0 .. full_items - 1 are whole work items, the `tiles`
+// slots after them are cut in `chunks`, whose sums the workgroup that arrives last adds up (one counter a tile, one block
+// of BM x BN floats a chunk).
 constexpr int MOST_CHUNKS = 8;
 struct Cut {
   int32_t full_items, tiles, chunks;
@@ -764,6 +747,14 @@ __device__ __forceinline__ bool share_sum(const Cut& cut, const CutItem& it, Pie
   return true;
 }
 
+// BM x BN tile, eight waves: 2 x 2 sub-tiles, each computed by two waves that take one half of every
+// 64-wide k stage.  The sub-tile is then large (few LDS reads a flop) with two waves on every SIMD.
+// Stages go global -> LDS into a ring of RING slots, filled RING - 1 stages ahead, one barrier a stage;
+// a slot holds the BM rows of A, then the BN rows of W, in the layout of the 256 x 256 kernel.
+// What bounds it: the fills (48 KB a stage at 192 x 192, two stages on their way; 1.13 PFLOP/s with all
+// CUs at work at k = 12288) and, at k = 3072, start-up and epilogue, about 7 of 50 us.  Kernel times of FFN2 after
+// the kernel that writes its rows, against 256 x 256 or the earlier 128 x 128 tiles: 4485 rows at hidden 1920
+// 174 -> 124 us (192 x 192), 1755 rows at hidden 3072 202 -> 153 (128 x 192), 2925 rows 241, fix-up included, -> 194.
 template <int BM, int BN>
 struct HalfK {
   static constexpr int STAGE = (BM + BN) * 128;                          // bytes
@@ -1333,8 +1324,9 @@ constexpr TileCost TILE_COST[] = {{64, 64, 2.2f, 0.17f, 0.18f, 5.f},   {128, 128
 // What it takes workgroups to share tiles cut along k (us): each stores its part, the last to arrive loads them all past
 // the caches, at 35 - 40 GB/s a CU.  fill: work items of the round a CU.  Over 345 problems (out-projection, FFN1 and FFN2
 // of 45 .. 8775 rows, hidden 320 .. 3072) and every way to cut them, the kind and cut chosen take 0.7 % longer than the best
-// on average, 5.1 % without cuts, and never longer than what is chosen without: FFN2 of 45 x 1536 20.8 -> 14.0 us (64 x 64
-// in 6), 84 x 1920 25.7 -> 16.3 (64 x 64 in 4), 700 x 1536 42.0 -> 29.8 (128 x 128 in 3), 1500 x 3072 143 -> 126 (192 x 192 in 2).
+// on average, 5.1 % without cuts, and never longer than what is chosen without.  FFN2, kernel times in a layer, uncut and cut
+// as it is now: 45 x 1536 19.8 -> 12.7 us (64 x 64 in 4), 84 x 1920 24.4 -> 14.4 (64 x 64 in 4), 700 x 1536 41.0 -> 26.7
+// (128 x 128 in 3), 1500 x 3072 148 -> 117 (192 x 192 in 2).
 double sharing_cost(const TileCost& c, int split, double fill) {
   const double part = (double)(c.bm * c.bn) / 16384.0;          // in units of 64 KB
   return c.bm == 64 ? 1.0 + 0.8 * split + 1.5 * fill : 2.0 + part * (split + 4.5 * fill);

@@ -101,6 +101,16 @@ __device__ __forceinline__ void lds_fill(u32x4_t rsrc, uint32_t lds_addr, uint32
                :: "s"(lds_addr), "v"(voffset), "s"(rsrc) : "memory");
 }
 
+__device__ __forceinline__ float gelu_tanh(float x) {
+  // x/2 (1 + tanh u) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3);
+  // -2u log2(e) = x (C1 + C2 x^2) with the constants folded: five plain operations and two
+  // transcendentals per element (the epilogue runs while the matrix pipe idles)
+  constexpr float C1 = -2.302208198144325f;     // -2 log2(e) sqrt(2/pi)
+  constexpr float C2 = -0.1029432395800235f;    // C1 * 0.044715
+  float e = __builtin_amdgcn_exp2f(x * __builtin_fmaf(x * x, C2, C1));
+  return x * __builtin_amdgcn_rcpf(1.0f + e);
+}
+
 // Workgroups that share the sum of one output block: each stores its part, and the one that arrives last adds them up.
 // Parts go past the XCDs' L2s both ways (sc1), and a workgroup's stores are complete before its arrival is counted, so
 // the last one sees all of them; none waits for another.  The count is zero again for the next launch.

@@ -23,12 +23,6 @@
 
 namespace {
 
-__device__ __forceinline__ float gelu_tanh(float x) {
-  constexpr float C1 = -2.302208198144325f, C2 = -0.1029432395800235f;    // x / (1 + exp2(x (C1 + C2 x^2)))
-  const float e = __builtin_amdgcn_exp2f(x * __builtin_fmaf(x * x, C2, C1));
-  return x * __builtin_amdgcn_rcpf(1.0f + e);
-}
-
 __device__ __forceinline__ void load4(const float* p, float (&v)[4]) {
   const floatx4_t t = *reinterpret_cast<const floatx4_t*>(p);
 #pragma unroll

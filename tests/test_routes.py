@@ -116,11 +116,11 @@ def test_forms_of_the_layers_of_narrow_models(m, hidden, ffn, qkv, ffn1):
 
 
 @pytest.mark.parametrize("m,hidden,ffn,what,route", [
-    # cut along k, and as fast uncut (us)
-    (45, 1536, 6144, B.ROUTE_FFN2, (64, 64, 4)),          # 14; 20.8
-    (84, 1920, 7680, B.ROUTE_FFN2, (64, 64, 4)),          # 16.3; 25.7
-    (700, 1536, 6144, B.ROUTE_FFN2, (128, 128, 3)),       # 29.8; 42.0
-    (1500, 3072, 12288, B.ROUTE_FFN2, (192, 192, 2)),     # 126; 143
+    # kernel times in a layer, us, and without the cut
+    (45, 1536, 6144, B.ROUTE_FFN2, (64, 64, 4)),          # 12.7; 19.8
+    (84, 1920, 7680, B.ROUTE_FFN2, (64, 64, 4)),          # 14.4; 24.4
+    (700, 1536, 6144, B.ROUTE_FFN2, (128, 128, 3)),       # 26.7; 41.0
+    (1500, 3072, 12288, B.ROUTE_FFN2, (192, 192, 2)),     # 117; 148 (128 x 192)
 ])
 def test_measured_cuts_of_a_layer(m, hidden, ffn, what, route):
     assert B.hero_layer_route(layer_config(m, hidden, ffn), m, what) == (B.FORM_GEMM, *route)
