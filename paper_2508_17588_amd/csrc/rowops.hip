@@ -187,20 +187,21 @@ __global__ void select_weighted_kernel(SelectGeom g, uint32_t step_salt, int32_t
       if (e < size) ages[tok[e]] = w[e] == 0 ? 0 : age[e] + 1;
     return;
   }
+  // (in row-major order; a division a token, e / ww, is most of what a step of these loops does beside its load)
+  const int end = first_tok + (q.hh - 1) * g.width + q.ww;
+  auto next = [&](int& tok, int& dx) {
+    ++tok;
+    if (++dx == q.ww) { dx = 0; tok += g.width - q.ww; }
+  };
   uint32_t total = 0;
-  for (int e = 0; e < size; ++e) {
-    int dy = e / q.ww, dx = e - dy * q.ww;
-    total += weight(ages[first_tok + dy * g.width + dx]);
-  }
+  for (int tok = first_tok, dx = 0; tok < end; next(tok, dx)) total += weight(ages[tok]);
   for (int j = 0; j < n_p; ++j) {
     const uint32_t r = draw(j, total);
     uint32_t run = 0;
-    for (int e = 0; e < size; ++e) {
-      int dy = e / q.ww, dx = e - dy * q.ww;
-      int tok = first_tok + dy * g.width + dx;
-      int32_t a = ages[tok];
+    for (int tok = first_tok, dx = 0; tok < end; next(tok, dx)) {
+      const int32_t a = ages[tok];
       if (a < 0) continue;
-      uint32_t w = weight(a);
+      const uint32_t w = weight(a);
       run += w;
       if (run > r) {
         idx[out + j] = g.n_text + tok;
@@ -210,10 +211,8 @@ __global__ void select_weighted_kernel(SelectGeom g, uint32_t step_salt, int32_t
       }
     }
   }
-  for (int e = 0; e < size; ++e) {
-    int dy = e / q.ww, dx = e - dy * q.ww;
-    int tok = first_tok + dy * g.width + dx;
-    int32_t a = ages[tok];
+  for (int tok = first_tok, dx = 0; tok < end; next(tok, dx)) {
+    const int32_t a = ages[tok];
     ages[tok] = a < 0 ? 0 : a + 1;
   }
 }
