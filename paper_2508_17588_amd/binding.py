@@ -142,12 +142,12 @@ def make_config(cfg, resid_fp32: Optional[bool] = None) -> hero_config:
 
 def _stream() -> c_void_p:
     # the raw handle: torch.cuda.current_stream() makes a stream object on each call (2.9 us, this 0.5), which a small
-    # model's calls cannot hide behind the GPU (8645 x 384, four extrapolated layers: 51 -> 37 us).  Not every torch has it.
+    # model's calls cannot hide behind the GPU (8645 x 384, four extrapolated layers: 51 -> 37 us)
     import torch
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if raw is None:
+    try:
+        return c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    except AttributeError:          # a torch without it
         return c_void_p(torch.cuda.current_stream().cuda_stream)
-    return c_void_p(raw(torch.cuda.current_device()))
 
 
 def _ptr(t) -> c_void_p:
