@@ -779,8 +779,8 @@ __device__ __forceinline__ bool share_keys_pass(const AttnArgs& a, int head, int
   const int t_begin = wave * n_tiles / SHARE_WAVES, t_end = (wave + 1) * n_tiles / SHARE_WAVES;
   const int kperm = (lr & ~12) | ((lr & 4) << 1) | ((lr & 8) >> 1);   // K row read as MFMA row lr
 
-  // the queries, QF KB to a wave, or to the first QG * 32 / KROWS waves (rows past the end arrive as zero): whole cache lines, where the fragments' own loads
-  // would make 64 requests each
+  // the queries, QF KB to a wave, or to the first QG * 32 / KROWS waves (rows past the end arrive as zero): whole cache
+  // lines, where the fragments' own loads would make 64 requests each
   constexpr int QF = QG * 32 / SHARE_WAVES / KROWS > 0 ? QG * 32 / SHARE_WAVES / KROWS : 1;        // fills of a wave
   const bool fetches = QG * 32 / SHARE_WAVES >= KROWS || wave < QG * 32 / KROWS;
   {

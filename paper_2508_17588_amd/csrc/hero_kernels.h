@@ -185,8 +185,8 @@ struct AttnArgs {
   float q_scale = 0.f;                 // scores are exp2(q_scale * q.k): log2(e)/sqrt(head_dim), or 1 if folded into Q
   float* split_ws = nullptr;           // optional device scratch for the partial results of key-split query blocks (nullptr: never split)
   size_t split_ws_bytes = 0;
-  uint32_t* fallback_count = nullptr;  // optional device counter: += 1 per workgroup (NW * 64 queries of one head) whose row sums
-                                       // left the range of the reference-free form and that recomputed with the running maximum
+  uint32_t* fallback_count = nullptr;  // optional device counter (head_dim 64): += 1 per block of 256 queries of one head, however many
+                                       // workgroups it has, with row sums beyond the reference-free form's range: recomputed with references
 };
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st);
